@@ -105,15 +105,15 @@ int ddqcd_destroy(ddqcd_t ctx);
  * hops (the hop structure of Sec. II-B: project, multiply by the link,
  * reconstruct).  DDQCD_PRODUCT_LANE: one right-hand side per workgroup, one
  * site per thread, products on the vector ALUs.  The tile forms solve one
- * domain for a tile of four right-hand sides of a lattice per workgroup (the
- * link is staged once for the tile): DDQCD_PRODUCT_TILE_VALU with the products
- * on the vector ALUs, DDQCD_PRODUCT_MFMA_F32 on FP32 matrix instructions
+ * domain for a tile of right-hand sides of a lattice per workgroup (two for
+ * DDQCD_PRODUCT_TILE_VALU, four for the others; the link is staged once for
+ * the tile): DDQCD_PRODUCT_TILE_VALU with the products on the vector ALUs, DDQCD_PRODUCT_MFMA_F32 on FP32 matrix instructions
  * (U in real form, 6x6, times the 6x4 block of the four right-hand sides'
  * half-spinors, FP32 inputs and accumulation), DDQCD_PRODUCT_MFMA_BF16 on
  * BF16-input matrix instructions with FP32 accumulation (link and half-spinor
  * rounded to BF16 for the product).  The tile forms need 4x4x4x4 domains and
  * DDQCD_FP16 or DDQCD_BF16 storage; a solve or preconditioner call with nrhs
- * right-hand sides uses ceil(nrhs / 4) tiles. */
+ * right-hand sides uses ceil(nrhs / 2) or ceil(nrhs / 4) tiles. */
 typedef enum {
     DDQCD_PRODUCT_LANE = 0,
     DDQCD_PRODUCT_TILE_VALU = 1,
@@ -302,7 +302,7 @@ int ddqcd_tune_domain(const int lattice[4], double kappa, double c_sw, const dou
  * spinor fields, canonical layout, one after the other) over the pairs (domain
  * shape, product form): for every compiled shape that tiles the lattice and
  * every ddqcd_product its kernels offer for prec (the tile forms only when
- * nrhs >= 2: they take four right-hand sides per workgroup), a context is
+ * nrhs >= 2: they take several right-hand sides per workgroup), a context is
  * created, U loaded and the nrhs systems solved twice, the second solve timed;
  * the fastest pair that converged is written to domain_out and product_out
  * (optional), its time in milliseconds to ms_out (optional; -1 when only one

@@ -101,6 +101,16 @@ template <typename T> __device__ __forceinline__ cx<T> czero() { return {T(0), T
 
 // ---- loads and stores with precision conversion -------------------------
 
+// p, known to the compiler to point to global memory.  A pointer read from
+// memory (the SapArgs fields) is generic otherwise, and generic (flat) loads
+// count as LDS accesses too: every wait for LDS data then also waits for the
+// global loads in flight.
+template <typename P> __device__ __forceinline__ P *global_ptr(P *p)
+{
+    typedef __attribute__((address_space(1))) P *gp;
+    return (P *)(gp)(uintptr_t)p;
+}
+
 template <typename T, typename S> __device__ __forceinline__ cx<T> ld(const v2<S> *p, long idx)
 {
     v2<S> v = p[idx];

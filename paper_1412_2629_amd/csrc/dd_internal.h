@@ -79,12 +79,13 @@ long sap_face_sites(const int b[4]);
 int sap_shape_id(const int b[4]);
 // How a block-solve workgroup forms the SU(3) products of its hops:
 // PRODUCT_LANE, one right-hand side per workgroup and one site per thread
-// (VALU); the TILE forms take a tile of four right-hand sides of one lattice
-// per workgroup (4^4 domains, FP16 storage) with the product on the VALU, on
-// FP32 MFMA, or on BF16-input MFMA with FP32 accumulation.
+// (VALU); the TILE forms take a tile of right-hand sides of one lattice per
+// workgroup (4^4 domains, FP16 or BF16 storage) with the product on the VALU
+// (two right-hand sides), on FP32 MFMA, or on BF16-input MFMA with FP32
+// accumulation (four).
 enum { PRODUCT_LANE = 0, PRODUCT_TILE_VALU = 1, PRODUCT_TILE_MFMA_F32 = 2, PRODUCT_TILE_MFMA_BF16 = 3 };
 bool sap_product_supported(const int b[4], int prec, int product);
-// Right-hand sides one workgroup takes (1, or 4 for the tile forms): the items
+// Right-hand sides one workgroup takes (1, or 2 or 4 for the tile forms): the items
 // of a tile launch are (first system | systems in the tile << 24, domain).
 int sap_rhs_per_workgroup(int product);
 // Domains one block-solve workgroup takes for (shape, precision, product): the

@@ -1223,85 +1223,165 @@ __global__ __launch_bounds__(Sh::VH) void k_sap_sweep(const SapArgs *args, const
 
 // ---- block solves of a tile of right-hand sides ---------------------------------
 //
-// One workgroup solves one domain for a tile of up to RT = 4 right-hand sides
-// of one lattice (systems sys0 .. sys0 + nt - 1), so the domain's links are
-// staged into LDS once for the tile and each link entry read from LDS serves
-// all of them.  Thread t works on the even and the odd site with half index
-// h = t / 4 for right-hand side r = t % 4, so the four threads of a site are
-// four consecutive lanes, and every thread is busy in both parity phases of
-// the MR step.  Spinors in LDS are [component][half index][right-hand side].
+// One workgroup solves one domain for a tile of up to RT right-hand sides of
+// one lattice (systems sys0 .. sys0 + nt - 1), so the domain's links are staged
+// into LDS once for the tile and each link entry read from LDS serves all of
+// them.  Thread t works on the even and the odd site with half index h = t / RT
+// for right-hand side r = t % RT, so the threads of a site are consecutive
+// lanes, and every thread is busy in both parity phases of the MR step.
+// Spinors in LDS are [component pair][half index][right-hand side]; one such
+// array serves both parities, the MR residual r and the solution x stay in the
+// even site's registers.
 //
-// Those four lanes are one 4x4 block of the 16-block MFMA instructions.  In
-// a hop, the SU(3) product U h (U the link or its adjoint, h the projected
-// half-spinor) is, in real form, a 6x6 matrix (rows Re y_a and Im y_a, columns
-// Re h_b and Im h_b) times a 6-vector; for the four right-hand sides and one
-// spin component of h it is a 6x6 times 6x4 product, done as two 4-row blocks
-// of the site's quad: lane r supplies row r of each block of U and column r
-// (its own half-spinor), and receives column r of the result.  PROD selects
-// the product: VALU (per-thread fused multiply-adds, as in k_sap_lds), FP32
-// MFMA (4x4x1, six steps over the inner dimension) or BF16-input MFMA with
-// FP32 accumulation (4x4x4, two steps; the link and half-spinor rounded to
-// BF16).  Lanes of right-hand sides beyond the tile work on zeros and touch no
-// memory.
+// PROD selects the SU(3) product of a hop: VALU (per-thread fused
+// multiply-adds, RT = 2), FP32 MFMA (4x4x1, six steps over the inner
+// dimension) or BF16-input MFMA with FP32 accumulation (4x4x4, two steps; the
+// link and half-spinor rounded to BF16), both RT = 4: the four lanes of a site
+// are one 4x4 block of the 16-block MFMA instructions.  There the product U h
+// (U the link or its adjoint, h the projected half-spinor) is, in real form, a
+// 6x6 matrix (rows Re y_a and Im y_a, columns Re h_b and Im h_b) times a
+// 6-vector; for the four right-hand sides and one spin component of h it is a
+// 6x6 times 6x4 product, done as two 4-row blocks of the site's quad: lane r
+// supplies row r of each block of U and column r (its own half-spinor), and
+// receives column r of the result.  Lanes of right-hand sides beyond the tile
+// work on zeros and touch no memory.
+//
+// Two right-hand sides, not four, for the VALU form: at 80 KB of LDS two
+// workgroups share a CU, and while one moves its domain's data (some 10 bytes a
+// cycle is what one CU gets from beyond its L1) the other one computes.  The
+FP16 launch of one colour for 12 right-hand sides on 32^3x64 (4096 domains of
+4^4) takes 3.11 ms this way.  With tiles of four (157 KB, one workgroup a CU,
+separate arrays for r and C_o^-1 D_oe r) it took 4.73 ms with 8-byte LDS reads,
+mixed-precision multiply-adds and each site's lanes moving its boundary terms
+and accumulator, and 3.89 ms with 16-byte reads, FP32 multiply-adds and whole
+waves moving the boundary terms.
 
 enum { PROD_VALU = 0, PROD_MFMA_F32 = 1, PROD_MFMA_BF16 = 2 };
-constexpr int RT = 4;
-// Link entries in LDS lie LSTR = VD + 16 entries apart: the four lanes of a
-// quad read four different entries of one site (rows or columns of U for the
-// matrix operands), and with a stride of VD (a multiple of the 64 banks) all
-// four would fall in one bank.
-template <class Sh> constexpr int tile_lstr() { return Sh::VD + 16; }
+constexpr int RT_VALU = 2, RT_MFMA = 4;
+template <int PROD> constexpr int tile_rt() { return PROD == PROD_VALU ? RT_VALU : RT_MFMA; }
+// Link entries in LDS lie LSTR entries apart.  For the matrix operands VD + 16:
+// the four lanes of a quad read four different entries of one site (rows or
+// columns of U), and with a stride of VD (a multiple of the 64 banks) all four
+// would fall in one bank.
+template <class Sh, int PROD> constexpr int tile_lstr() { return PROD == PROD_VALU ? Sh::VD : Sh::VD + 16; }
 
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x4_t __attribute__((ext_vector_type(4)));
 
-// sum of v over the threads of this thread's right-hand side (lanes with equal
-// lane % 4), for all NW waves of the workgroup; fixed order, every thread joins
-template <int NW, int N> __device__ __forceinline__ void rhs_sum(float (&v)[N], float *red)
+// A spinor of one site and right-hand side in LDS and in the tile's own global
+// arrays: six 16-byte entries of two complex components, the entries of one
+// component pair contiguous over (site, right-hand side).  16 bytes a lane is
+// what LDS moves at its full rate (measured on gfx950: 131 bytes a cycle and CU
+// against 67 for 8-byte reads).
+typedef f32x4_t c2_t;
+
+template <int STRIDE> __device__ __forceinline__ void ld_c2(const c2_t *p, cx<float> s[12])
 {
 #pragma unroll
-    for (int q = 0; q < N; q++)
-#pragma unroll
-        for (int o = 4; o < 64; o <<= 1) v[q] += __shfl_xor(v[q], o);
-    const int w = threadIdx.x >> 6, r = threadIdx.x & 3;
-    if ((threadIdx.x & 63) < RT)
-#pragma unroll
-        for (int q = 0; q < N; q++) red[(w * RT + r) * N + q] = v[q];
-    __syncthreads();
-#pragma unroll
-    for (int q = 0; q < N; q++) {
-        float s = 0;
-        for (int k = 0; k < NW; k++) s += red[(k * RT + r) * N + q];
-        v[q] = s;
+    for (int j = 0; j < 6; j++) {
+        const c2_t q = p[j * STRIDE];
+        s[2 * j] = {q[0], q[1]};
+        s[2 * j + 1] = {q[2], q[3]};
     }
-    // no closing barrier: the MR step's next two barriers pass before red is
-    // written again (the next step's sums, or the epilogue's maxima)
+}
+template <int STRIDE> __device__ __forceinline__ void st_c2(c2_t *p, const cx<float> s[12])
+{
+#pragma unroll
+    for (int j = 0; j < 6; j++) p[j * STRIDE] = c2_t{s[2 * j].r, s[2 * j].i, s[2 * j + 1].r, s[2 * j + 1].i};
 }
 
-// The maximum of v over the workgroup for this lane's right-hand side, through
-// red[0 .. NW * RT); no closing barrier: the callers (the epilogue) give each
-// maximum its own part of red and write none of it again.
-template <int NW> __device__ __forceinline__ float rhs_max(float v, float *red)
+// A stored pair of 16-bit values as FP32, converted here: hidden from the
+// compiler, so that it does not fold the conversion into mixed-precision
+// multiply-adds, which issue at half the rate of FP32 ones (gfx950, two waves
+// per SIMD: 4.4 against 2.6 cycles each).  The upper half is shifted down first:
+// the conversion that selects it by itself (SDWA) is the slow one.  An SU(3)
+// times half-spinor product with the link's nine pairs read from LDS takes 347
+// cycles this way, 424 with SDWA conversions, 447 with mixed-precision
+// multiply-adds and 299 with FP32 links.
+template <typename G> __device__ __forceinline__ cx<float> widen(v2<G> v)
+{
+    cx<float> c;
+    if constexpr (std::is_same<G, half_t>::value) {
+        unsigned u = __builtin_bit_cast(unsigned, v), h = u >> 16;
+        asm("" : "+v"(h));
+        c = {static_cast<float>(__builtin_bit_cast(half_t, (unsigned short)u)),
+             static_cast<float>(__builtin_bit_cast(half_t, (unsigned short)h))};
+    } else {
+        c = {static_cast<float>(v.x), static_cast<float>(v.y)};
+    }
+    asm("" : "+v"(c.r), "+v"(c.i));
+    return c;
+}
+
+// out = (packed clover block of 36 pairs, load(q) its pair q) in
+template <typename Load> __device__ __forceinline__ void clover_wide(Load load, const cx<float> in[12], cx<float> out[12])
+{
+    clover_block_with<float>(load, in, out);
+    clover_block_with<float>([&](int q) { return load(18 + q); }, in + 6, out + 6);
+}
+
+// Sum over the lanes of a wave with equal lane % RT, returned to all of them.
+template <int RT> __device__ __forceinline__ float rhs_wave_sum(float v)
+{
+    if constexpr (RT == 2)
+        v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x4E, 0xF, 0xF, false));   // quad_perm 2,3,0,1
+    v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x124, 0xF, 0xF, false));   // row_ror:4
+    v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x128, 0xF, 0xF, false));   // row_ror:8
+    v += __shfl_xor(v, 16);
+    v += __shfl_xor(v, 32);
+    return v;
+}
+
+// sum of v over the threads of this thread's right-hand side (lanes with equal
+// lane % RT), for all NW waves of the workgroup; fixed order, every thread joins
+template <int RT, int NW> __device__ __forceinline__ void rhs_sum(float (&v)[3], f32x4_t *red)
 {
 #pragma unroll
-    for (int o = 4; o < 64; o <<= 1) v = fmax(v, __shfl_xor(v, o));
-    const int w = threadIdx.x >> 6, r = threadIdx.x & 3;
-    if ((threadIdx.x & 63) < RT) red[w * RT + r] = v;
+    for (int q = 0; q < 3; q++) v[q] = rhs_wave_sum<RT>(v[q]);
+    const int w = threadIdx.x >> 6, r = threadIdx.x % RT;
+    if ((threadIdx.x & 63) < RT) red[w * RT + r] = f32x4_t{v[0], v[1], v[2], 0.f};
     __syncthreads();
-    float m = red[r];
-    for (int k = 1; k < NW; k++) m = fmax(m, red[k * RT + r]);
-    return m;
+    f32x4_t s = red[r];
+#pragma unroll
+    for (int k = 1; k < NW; k++) s += red[k * RT + r];
+    v[0] = s[0];
+    v[1] = s[1];
+    v[2] = s[2];
+    // no closing barrier: several barriers pass before red is written again
+}
+
+// The maxima of a and b over the workgroup for this lane's right-hand side; no
+// closing barrier: the caller (the epilogue) gives it its own part of red.
+template <int RT, int NW> __device__ __forceinline__ void rhs_max2(float &a, float &b, f32x4_t *red)
+{
+#pragma unroll
+    for (int o = RT; o < 64; o <<= 1) {
+        a = fmax(a, __shfl_xor(a, o));
+        b = fmax(b, __shfl_xor(b, o));
+    }
+    const int w = threadIdx.x >> 6, r = threadIdx.x % RT;
+    if ((threadIdx.x & 63) < RT) red[w * RT + r] = f32x4_t{a, b, 0.f, 0.f};
+    __syncthreads();
+    f32x4_t m = red[r];
+#pragma unroll
+    for (int k = 1; k < NW; k++) {
+        const f32x4_t q = red[k * RT + r];
+        m[0] = fmax(m[0], q[0]);
+        m[1] = fmax(m[1], q[1]);
+    }
+    a = m[0];
+    b = m[1];
 }
 
 // Row `row` of U (forward hop, SIGN < 0) or of U^dagger (backward hop): u[b] =
 // U[row][b], or conj(U[b][row]); links in LDS as three rows [mu][9][VD].
-template <class Sh, int SIGN, typename G>
+template <class Sh, int SIGN, int PROD, typename G>
 __device__ __forceinline__ void link_row(const v2<G> *slink, int mu, int lloc, int row, cx<float> u[3])
 {
 #pragma unroll
     for (int b = 0; b < 3; b++) {
         const int e = SIGN < 0 ? row * 3 + b : b * 3 + row;
-        const v2<G> v = slink[(mu * 9 + e) * tile_lstr<Sh>() + lloc];
+        const v2<G> v = slink[(mu * 9 + e) * tile_lstr<Sh, PROD>() + lloc];
         u[b] = {static_cast<float>(v.x), SIGN < 0 ? static_cast<float>(v.y) : -static_cast<float>(v.y)};
     }
 }
@@ -1314,8 +1394,8 @@ __device__ __forceinline__ void quad_product(const v2<G> *slink, int mu, int llo
 {
     // block 0 rows: Re y_0, Re y_1, Re y_2, Im y_0; block 1: Im y_1, Im y_2, 0, 0
     cx<float> u0[3], u1[3];
-    link_row<Sh, SIGN, G>(slink, mu, lloc, r < 3 ? r : 0, u0);
-    link_row<Sh, SIGN, G>(slink, mu, lloc, r == 0 ? 1 : 2, u1);
+    link_row<Sh, SIGN, PROD, G>(slink, mu, lloc, r < 3 ? r : 0, u0);
+    link_row<Sh, SIGN, PROD, G>(slink, mu, lloc, r == 0 ? 1 : 2, u1);
     const bool re0 = r < 3, use1 = r < 2;
     float a0[6], a1[6];
 #pragma unroll
@@ -1361,26 +1441,32 @@ __device__ __forceinline__ void quad_product(const v2<G> *slink, int mu, int llo
     }
 }
 
-// acc += the in-domain hop into site l (local index loc) along MU; SIGN < 0:
-// from x + mu with (1 - gamma_mu) U_mu(x), SIGN > 0: from x - mu with
-// (1 + gamma_mu) U_mu(x - mu)^dagger.  v holds the other parity's sites.
+// acc += the in-domain hop into a site along MU; SIGN < 0: from x + mu with
+// (1 - gamma_mu) U_mu(x), SIGN > 0: from x - mu with (1 + gamma_mu) U_mu(x -
+// mu)^dagger.  v: this right-hand side's spinor of the other parity's site
+// with this site's half index hi, in LDS; ox: 1 where the site's x is odd (its
+// x neighbours have half indices hi + ox and hi + ox - 1); loc: the site, op:
+// the first site of the other parity.  Neighbour offsets are constants (one
+// address register for x, one for the other directions), so LDS addresses
+// are immediates.
 template <class Sh, int MU, int SIGN, int PROD, typename G>
-__device__ __forceinline__ void tile_hop(const cx<float> (*v)[Sh::VH][RT], const int l[4], int loc, int r,
+__device__ __forceinline__ void tile_hop(const c2_t *v, const int l[4], int loc, int op, int hi, int ox, int r,
                                          const v2<G> *slink, cx<float> acc[12])
 {
-    constexpr int VH = Sh::VH;
+    constexpr int VH = Sh::VH, RT = tile_rt<PROD>(), LS = tile_lstr<Sh, PROD>();
+    constexpr int STEP = MU == 1 ? Sh::B[0] / 2 : MU == 2 ? Sh::B[0] * Sh::B[1] / 2 : Sh::B[0] * Sh::B[1] * Sh::B[2] / 2;
     const bool has = SIGN < 0 ? l[MU] + 1 < Sh::B[MU] : l[MU] > 0;
-    int n[4] = {l[0], l[1], l[2], l[3]};
-    if (has) n[MU] += SIGN < 0 ? 1 : -1;
-    const int nh = Sh::half_index(n);   // without a neighbour: a valid index, its value unused
-    const int lloc = SIGN < 0 ? loc : (1 - (loc >= VH)) * VH + nh;
+    // half index of the neighbour relative to hi
+    const int dn = MU == 0 ? (SIGN < 0 ? ox : ox - 1) : SIGN < 0 ? STEP : -STEP;
     cx<float> s[12], h[6], uh[6];
     if constexpr (PROD == PROD_VALU) {
         if (!has) return;
-#pragma unroll
-        for (int k = 0; k < 12; k++) s[k] = v[k][nh][r];
+        ld_c2<VH * RT>(v + dn * RT, s);
         proj<MU, SIGN>(s, h);
-        const su3<float> U = ld_link<float, G, 9>(slink, (long)MU * 9 * tile_lstr<Sh>() + lloc, tile_lstr<Sh>());
+        const v2<G> *up = slink + MU * 9 * LS + (SIGN < 0 ? loc : op + hi + dn);
+        su3<float> U;
+#pragma unroll
+        for (int e = 0; e < 9; e++) U.m[e] = widen<G>(up[e * LS]);
         if constexpr (SIGN < 0) su3_mul(U, h, uh);
         else su3_dag_mul(U, h, uh);
         recon_acc<MU, SIGN>(acc, uh, 1.0f);
@@ -1388,16 +1474,16 @@ __device__ __forceinline__ void tile_hop(const cx<float> (*v)[Sh::VH][RT], const
         // every lane takes part in the matrix instructions; a site without this
         // neighbour multiplies a finite stand-in (its own index's entry) and
         // adds the product with weight 0
-#pragma unroll
-        for (int k = 0; k < 12; k++) s[k] = v[k][nh][r];
+        const int dv = has ? dn : 0;
+        ld_c2<VH * RT>(v + dv * RT, s);
         proj<MU, SIGN>(s, h);
-        quad_product<Sh, SIGN, PROD, G>(slink, MU, lloc, r, h, uh);
+        quad_product<Sh, SIGN, PROD, G>(slink, MU, SIGN < 0 ? loc : op + hi + dv, r, h, uh);
         recon_acc<MU, SIGN>(acc, uh, has ? 1.0f : 0.0f);
     }
 }
 
 template <class Sh, int PROD, typename G>
-__device__ __forceinline__ void tile_hops(const cx<float> (*v)[Sh::VH][RT], const int l[4], int loc, int r,
+__device__ __forceinline__ void tile_hops(const c2_t *v, const int l[4], int loc, int op, int hi, int ox, int r,
                                           const v2<G> *slink, cx<float> acc[12])
 {
 #pragma unroll
@@ -1407,276 +1493,486 @@ __device__ __forceinline__ void tile_hops(const cx<float> (*v)[Sh::VH][RT], cons
 #pragma unroll 1
         for (int k = 0; k < 8; k++) {
             switch (k) {
-                case 0: tile_hop<Sh, 0, -1, PROD, G>(v, l, loc, r, slink, acc); break;
-                case 1: tile_hop<Sh, 0, +1, PROD, G>(v, l, loc, r, slink, acc); break;
-                case 2: tile_hop<Sh, 1, -1, PROD, G>(v, l, loc, r, slink, acc); break;
-                case 3: tile_hop<Sh, 1, +1, PROD, G>(v, l, loc, r, slink, acc); break;
-                case 4: tile_hop<Sh, 2, -1, PROD, G>(v, l, loc, r, slink, acc); break;
-                case 5: tile_hop<Sh, 2, +1, PROD, G>(v, l, loc, r, slink, acc); break;
-                case 6: tile_hop<Sh, 3, -1, PROD, G>(v, l, loc, r, slink, acc); break;
-                default: tile_hop<Sh, 3, +1, PROD, G>(v, l, loc, r, slink, acc); break;
+                case 0: tile_hop<Sh, 0, -1, PROD, G>(v, l, loc, op, hi, ox, r, slink, acc); break;
+                case 1: tile_hop<Sh, 0, +1, PROD, G>(v, l, loc, op, hi, ox, r, slink, acc); break;
+                case 2: tile_hop<Sh, 1, -1, PROD, G>(v, l, loc, op, hi, ox, r, slink, acc); break;
+                case 3: tile_hop<Sh, 1, +1, PROD, G>(v, l, loc, op, hi, ox, r, slink, acc); break;
+                case 4: tile_hop<Sh, 2, -1, PROD, G>(v, l, loc, op, hi, ox, r, slink, acc); break;
+                case 5: tile_hop<Sh, 2, +1, PROD, G>(v, l, loc, op, hi, ox, r, slink, acc); break;
+                case 6: tile_hop<Sh, 3, -1, PROD, G>(v, l, loc, op, hi, ox, r, slink, acc); break;
+                default: tile_hop<Sh, 3, +1, PROD, G>(v, l, loc, op, hi, ox, r, slink, acc); break;
             }
         }
         return;
     }
-    tile_hop<Sh, 0, -1, PROD, G>(v, l, loc, r, slink, acc);
-    tile_hop<Sh, 0, +1, PROD, G>(v, l, loc, r, slink, acc);
-    tile_hop<Sh, 1, -1, PROD, G>(v, l, loc, r, slink, acc);
-    tile_hop<Sh, 1, +1, PROD, G>(v, l, loc, r, slink, acc);
-    tile_hop<Sh, 2, -1, PROD, G>(v, l, loc, r, slink, acc);
-    tile_hop<Sh, 2, +1, PROD, G>(v, l, loc, r, slink, acc);
-    tile_hop<Sh, 3, -1, PROD, G>(v, l, loc, r, slink, acc);
-    tile_hop<Sh, 3, +1, PROD, G>(v, l, loc, r, slink, acc);
+    tile_hop<Sh, 0, -1, PROD, G>(v, l, loc, op, hi, ox, r, slink, acc);
+    tile_hop<Sh, 0, +1, PROD, G>(v, l, loc, op, hi, ox, r, slink, acc);
+    tile_hop<Sh, 1, -1, PROD, G>(v, l, loc, op, hi, ox, r, slink, acc);
+    tile_hop<Sh, 1, +1, PROD, G>(v, l, loc, op, hi, ox, r, slink, acc);
+    tile_hop<Sh, 2, -1, PROD, G>(v, l, loc, op, hi, ox, r, slink, acc);
+    tile_hop<Sh, 2, +1, PROD, G>(v, l, loc, op, hi, ox, r, slink, acc);
+    tile_hop<Sh, 3, -1, PROD, G>(v, l, loc, op, hi, ox, r, slink, acc);
+    tile_hop<Sh, 3, +1, PROD, G>(v, l, loc, op, hi, ox, r, slink, acc);
+}
+
+// The boundary terms of a face (f = 2 mu + side) for the tile's right-hand
+// sides are moved by whole waves, so that every access to the boundary buffers
+// is a run of cache lines (by the site's own lanes it is 64-byte pieces, and an
+// eighth of the lanes at a time).  A face's places in the buffer are in the
+// order (parity, transverse position / 2) of the sites that write them; no
+// other kernel reads them.
+
+// The site of the domain with parity p at place (p, j) of face f.
+template <class Sh> __device__ __forceinline__ int tile_face_site(int p, int j, int f)
+{
+    static_assert(Sh::B[0] == 4 && Sh::B[1] == 4 && Sh::B[2] == 4 && Sh::B[3] == 4, "4^4 domains: two bits a coordinate");
+    const int sh = f & ~1, l = f & 1 ? 3 : 0;   // 2 mu bits below the face's own coordinate
+    int i = 2 * j;                              // transverse position, its lowest bit fixed by the parity
+    i |= (l ^ i ^ (i >> 2) ^ (i >> 4) ^ p) & 1;
+    const int lex = (i & ((1 << sh) - 1)) | (l << sh) | ((i >> sh) << (sh + 2));
+    return lex >> 1;
+}
+
+// Loads the neighbour's half-spinors of the place of this lane for every
+// right-hand side, and their weights (0 for those that the tile does not hold;
+// their loads repeat the first's).  No branches: the loads of all right-hand
+// sides are in flight together.
+template <class Sh, int RT, typename SS, bool SCALED>
+__device__ __forceinline__ void tile_face_fetch(const SapArgs *args, const Visit &v, int nt, const int D[4], int f,
+                                                v2<SS> (&raw)[RT][6], float (&w)[RT])
+{
+    constexpr int FS = Sh::FS[0];
+    static_assert(FS == 64 && Sh::FS[1] == 64 && Sh::FS[2] == 64 && Sh::FS[3] == 64, "one lane per face site");
+    const Geo &g = args[0].g;
+    const int mu = f >> 1, side = f & 1;
+    int dn = 0;
+    bool wrap = false;
+#pragma unroll
+    for (int m = 3; m >= 0; m--) {
+        int q = D[m];
+        if (m == mu) {
+            wrap = side ? q == g.n[m] - 1 : q == 0;
+            q = side ? (wrap ? 0 : q + 1) : (wrap ? g.n[m] - 1 : q - 1);
+        }
+        dn = dn * g.n[m] + q;
+    }
+    const float wb = wrap ? 0.5f * (float)g.bc[mu] : 0.5f;   // bc is +1 or -1
+    const long fb = face_base<Sh>(dn, f ^ 1) + (threadIdx.x & 63);
+#pragma unroll
+    for (int r = 0; r < RT; r++) {
+        const SapArgs &a = args[r < nt ? r : 0];
+        const bool alt = a.face_alt && !v.flip;
+        const v2<SS> *face = global_ptr((const v2<SS> *)(alt ? a.face_alt : a.face));
+#pragma unroll
+        for (int k = 0; k < 6; k++) raw[r][k] = face[fb + (long)k * FS];
+        w[r] = wb;
+        if constexpr (SCALED) w[r] *= global_ptr(alt ? a.face_scale_alt : a.face_scale)[dn];
+        w[r] = r < nt ? w[r] : 0.f;
+    }
+}
+
+// Their contribution (weight, and the link on the forward side) to stage [3]
+// [FS][RT], by the order of Shape::face_index; the sites of the face add it to
+// their right-hand side.
+template <class Sh, int RT, int PROD, typename SS, typename G>
+__device__ __forceinline__ void tile_face_stage(const v2<SS> (&raw)[RT][6], const float (&w)[RT], int f,
+                                                const v2<G> *slink, c2_t *stage)
+{
+    constexpr int FS = Sh::FS[0], LS = tile_lstr<Sh, PROD>();
+    // place of this lane: the neighbour's site of parity q, this domain's of parity 1 - q
+    const int q = (threadIdx.x & 63) >> 5, j = threadIdx.x & 31;
+    const int h = tile_face_site<Sh>(1 - q, j, f), lex = 2 * h + ((1 - q + (h >> 1) + (h >> 3) + (h >> 5)) & 1);
+    const int sh = f & ~1, i = (lex & ((1 << sh) - 1)) | ((lex >> (sh + 2)) << sh);
+    su3<float> U;
+    if (f & 1) {
+        const v2<G> *up = slink + (f >> 1) * 9 * LS + (1 - q) * Sh::VH + h;
+#pragma unroll
+        for (int e = 0; e < 9; e++) U.m[e] = widen<G>(up[e * LS]);
+    }
+#pragma unroll
+    for (int r = 0; r < RT; r++) {
+        cx<float> hs[6];
+#pragma unroll
+        for (int k = 0; k < 6; k++) hs[k] = scal(w[r], widen<SS>(raw[r][k]));
+        if (f & 1) {
+            cx<float> uh[6];
+            su3_mul(U, hs, uh);
+#pragma unroll
+            for (int k = 0; k < 6; k++) hs[k] = uh[k];
+        }
+#pragma unroll
+        for (int c = 0; c < 3; c++)
+            stage[(c * FS + i) * RT + r] = c2_t{hs[2 * c].r, hs[2 * c].i, hs[2 * c + 1].r, hs[2 * c + 1].i};
+    }
+}
+
+// rho += the staged contribution (stage: both faces of MU) of the site's face
+// along MU, if it has one
+template <class Sh, int RT, int MU>
+__device__ __forceinline__ void tile_face_add(const c2_t *stage, const int l[4], int r, cx<float> rho[12])
+{
+    constexpr int FS = Sh::FS[MU];
+    const bool lo = l[MU] == 0, up = l[MU] == Sh::B[MU] - 1;
+    if (!(lo || up)) return;
+    const c2_t *p = stage + (up ? 3 * RT * FS : 0) + Sh::template face_index<MU>(l) * RT + r;
+    cx<float> h[6];
+#pragma unroll
+    for (int j = 0; j < 3; j++) {
+        const c2_t q = p[j * FS * RT];
+        h[2 * j] = {q[0], q[1]};
+        h[2 * j + 1] = {q[2], q[3]};
+    }
+    if (lo) recon_acc<MU, +1>(rho, h, 1.0f);
+    else recon_acc<MU, -1>(rho, h, 1.0f);
+}
+
+// Writes the domain's own half-spinors of face f at the sites of parity p,
+// places j = (64 / RT) sub + lane / RT, from delta of that parity in LDS; inv: 1
+// / scale of this lane's right-hand side, whose boundary buffer is face (null:
+// nothing to write).
+template <class Sh, int RT, int PROD, typename SS, typename G>
+__device__ __forceinline__ void tile_face_out(v2<SS> *face, int d, int f, int p, int sub, const c2_t *dl, float inv,
+                                              const v2<G> *slink)
+{
+    constexpr int FS = Sh::FS[0], LS = tile_lstr<Sh, PROD>(), VH = Sh::VH;
+    const int lane = threadIdx.x & 63, r = lane % RT, j = sub * (64 / RT) + lane / RT;
+    const int h0 = tile_face_site<Sh>(p, j, f);
+    cx<float> s[12], h[6];
+    ld_c2<VH * RT>(dl + h0 * RT + r, s);
+    switch (f) {
+        case 0: proj<0, -1>(s, h); break;
+        case 1: proj<0, +1>(s, h); break;
+        case 2: proj<1, -1>(s, h); break;
+        case 3: proj<1, +1>(s, h); break;
+        case 4: proj<2, -1>(s, h); break;
+        case 5: proj<2, +1>(s, h); break;
+        case 6: proj<3, -1>(s, h); break;
+        default: proj<3, +1>(s, h); break;
+    }
+    if (f & 1) {
+        su3<float> U;
+        const v2<G> *up = slink + (f >> 1) * 9 * LS + p * VH + h0;
+#pragma unroll
+        for (int e = 0; e < 9; e++) U.m[e] = widen<G>(up[e * LS]);
+        cx<float> uh[6];
+        su3_dag_mul(U, h, uh);
+#pragma unroll
+        for (int k = 0; k < 6; k++) h[k] = uh[k];
+    }
+    if (!face) return;
+    const long fb = face_base<Sh>(d, f) + p * 32 + j;
+#pragma unroll
+    for (int k = 0; k < 6; k++) st<float, SS>(face, fb + (long)k * FS, scal(inv, h[k]));
 }
 
 // Items: x = first system of the tile | (systems in the tile) << 24, y = domain.
 // SS: storage of block residual and boundary terms; G: links and clover (two
-// rows stored, three rows in LDS); arithmetic and accumulator FP32.
+// rows stored, three rows in LDS); arithmetic and accumulator FP32.  The
+// accumulator and the block residual, which no other kernel reads, are laid
+// out for this one: [d][6][VD] and [d][3][VH] 16-byte entries.
 template <class Sh, int PROD, typename SS, typename G, bool SCALED>
-__global__ __launch_bounds__(Sh::VH * RT) void k_sap_tile(const SapArgs *args, const int2 *items, Visit v)
+__global__ __launch_bounds__(Sh::VH * tile_rt<PROD>(), 2) void k_sap_tile(const SapArgs *args, const int2 *items, Visit v)
 {
     using T = float;
-    using PS = float;
-    constexpr int VD = Sh::VD, VH = Sh::VH, NT = VH * RT, NW = NT / 64, NLC = 6, LNLC = 9;
-    static_assert(NT % 64 == 0 && NT <= 1024 && NT == 2 * VD, "whole waves; two threads per site for staging");
-    constexpr int LSTR = tile_lstr<Sh>();
-    __shared__ v2<G> slink[4 * LNLC * LSTR];   // [mu][9][LSTR]
+    constexpr int RT = tile_rt<PROD>();
+    constexpr int VD = Sh::VD, VH = Sh::VH, NT = VH * RT, NW = NT / 64, NLC = 6;
+    constexpr int FPW = 8 / NW;               // faces per wave
+    static_assert(NT % 64 == 0 && NT <= 1024 && (NW == 4 || NW == 8), "one or two faces a wave");
+    constexpr int LSTR = tile_lstr<Sh, PROD>();
+    typedef SS ss8_t __attribute__((ext_vector_type(8)));
+    __shared__ v2<G> slink[4 * 9 * LSTR];     // [mu][9][LSTR]
     __shared__ v2<G> sclo[36][VH];            // C_o^-1 of the odd sites
-    __shared__ cx<T> she[12][VH][RT];
-    __shared__ cx<T> sho[12][VH][RT];
-    __shared__ T red[NW * RT * 3];
+    // [6][VH][RT]: what the next hops read (even sites r, odd sites C_o^-1 D_oe r)
+    __shared__ c2_t sp[6 * VH * RT];
+    __shared__ f32x4_t red[2 * NW * RT];
 
     const int2 it = items[blockIdx.x];
     if (it.x < 0) return;   // padding (XCD lists of unequal length)
     const int sys0 = it.x & 0xffffff, nt = it.x >> 24, d = it.y;
-    const int t = threadIdx.x, hi = t >> 2, r = t & 3;
+    const int t = threadIdx.x, hi = t / RT, r = t % RT;
+    const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
     // this lane's right-hand side; what the tile shares (geometry, links,
     // clover, MR steps) is taken from the first system, so it stays uniform
-    const SapArgs &a0 = args[sys0];
-    SapArgs a = args[sys0 + (r < nt ? r : 0)];
-    a.g = a0.g;
-    a.links = a0.links;
-    a.cs = a0.cs;
-    a.n_mr = a0.n_mr;
-    const bool live = r < nt && a.active;
-    bind_faces(a, v);
+    const SapArgs *const ta = args + sys0;
+    const SapArgs &a0 = ta[0];
+    const SapArgs &a = ta[r < nt ? r : 0];
+    const bool live = (r < nt) & (a.active != 0);
     const int loc_e = hi, loc_o = VH + hi;
     int le[4], lo[4];
     Sh::coords(loc_e, le);
     Sh::coords(loc_o, lo);
+    const int oe = le[0] & 1, oo = lo[0] & 1;
     int D[4];
     {
         int q = d;
-        D[0] = q % a.g.n[0]; q /= a.g.n[0];
-        D[1] = q % a.g.n[1]; q /= a.g.n[1];
-        D[2] = q % a.g.n[2];
-        D[3] = q / a.g.n[2];
+        D[0] = q % a0.g.n[0]; q /= a0.g.n[0];
+        D[1] = q % a0.g.n[1]; q /= a0.g.n[1];
+        D[2] = q % a0.g.n[2];
+        D[3] = q / a0.g.n[2];
     }
-    const v2<G> *glinks = (const v2<G> *)a.links;
-    const v2<G> *cs = (const v2<G> *)a.cs;
+    const v2<G> *glinks = global_ptr((const v2<G> *)a0.links);
+    const v2<G> *cs = global_ptr((const v2<G> *)a0.cs);
+    const int n_mr = a0.n_mr;
+    const long se = (long)d * 12 * VD + loc_e, so = (long)d * 12 * VD + loc_o;
+    c2_t *const pe = global_ptr((c2_t *)a.psi) + (long)d * 6 * VD + loc_e, *const po = pe + VH;
+    ss8_t *const pr = global_ptr((ss8_t *)a.res) + (long)d * 3 * VH + hi;
+    const double2 *const eta = global_ptr(a.eta);
+    double2 *const out = global_ptr(a.out);
+    const bool io32 = a.io32;
+    // this wave's faces: one of each side where it has two
+    int face_of[FPW];
+#pragma unroll
+    for (int q = 0; q < FPW; q++) face_of[q] = FPW == 1 ? wave : q == 0 ? wave : 4 + (wave ^ 1);
 
-    // ---- links and the odd sites' C_o^-1 into LDS (two threads per site, two
-    // link directions each), the even site's C_e into registers; every global
-    // load before the first LDS store
+    // ---- links and the odd sites' C_o^-1 into LDS, the even site's C_e into
+    // registers; every global load before the first LDS store
     v2<G> cle[36];
+    cx<T> Ae[12], Ao[12], P[12], tt[12];
+    v2<SS> fraw[FPW][RT][6];
+    float fw[FPW][RT];
     {
-        const int q = t % VD, m0 = (t / VD) * 2;
-        v2<G> lt[2 * NLC];
+        constexpr int NL = 4 * VD / NT;   // links per thread
+        v2<G> lt[NL][NLC];
 #pragma unroll
-        for (int j = 0; j < 2; j++)
+        for (int j = 0; j < NL; j++) {
+            const int q = t + j * NT;     // = mu VD + site
 #pragma unroll
-            for (int e = 0; e < NLC; e++) lt[j * NLC + e] = glinks[(((long)d * 4 + m0 + j) * NLC + e) * VD + q];
+            for (int e = 0; e < NLC; e++) lt[j][e] = glinks[(((long)d * 4 + q / VD) * NLC + e) * VD + q % VD];
+        }
         const long cb = (long)d * 36 * VD;
-#pragma unroll
-        for (int k = 0; k < 36; k++) cle[k] = cs[cb + (long)k * VD + loc_e];
         constexpr int NCO = 36 * VH / NT;
-        static_assert(36 * VH % NT == 0, "odd clover entries per thread");
+        static_assert(36 * VH % NT == 0 && 4 * VD % NT == 0, "odd clover entries and links per thread");
         v2<G> ct[NCO];
 #pragma unroll
         for (int j = 0; j < NCO; j++) {
             const int i = t + j * NT, k = i / VH;
             ct[j] = cs[cb + (long)k * VD + VH + (i - k * VH)];
         }
+        // the block right-hand side of both sites, without the boundary terms
+        if (!live) {
+#pragma unroll
+            for (int k = 0; k < 12; k++) Ae[k] = Ao[k] = czero<T>();
+        } else if (v.first && io32) {
+#pragma unroll
+            for (int k = 0; k < 12; k++) {
+                Ae[k] = ld<T, float>((const float2 *)eta, se + (long)k * VD);
+                Ao[k] = ld<T, float>((const float2 *)eta, so + (long)k * VD);
+            }
+        } else if (v.first) {
+#pragma unroll
+            for (int k = 0; k < 12; k++) {
+                Ae[k] = ld<T, double>(eta, se + (long)k * VD);
+                Ao[k] = ld<T, double>(eta, so + (long)k * VD);
+            }
+        } else {
+            const T sc = SCALED ? T(global_ptr(a.res_scale)[d]) : T(1);
+#pragma unroll
+            for (int j = 0; j < 3; j++) {
+                const ss8_t q8 = pr[j * VH];
+#pragma unroll
+                for (int e = 0; e < 4; e++)
+                    Ae[4 * j + e] = {sc * static_cast<T>(q8[2 * e]), sc * static_cast<T>(q8[2 * e + 1])};
+            }
+#pragma unroll
+            for (int k = 0; k < 12; k++) Ao[k] = czero<T>();
+        }
+        if (v.faces_in)
+#pragma unroll
+            for (int q = 0; q < FPW; q++) tile_face_fetch<Sh, RT, SS, SCALED>(ta, v, nt, D, face_of[q], fraw[q], fw[q]);
+#pragma unroll
+        for (int k = 0; k < 36; k++) cle[k] = cs[cb + (long)k * VD + loc_e];
 #pragma unroll
         for (int j = 0; j < NCO; j++) {
             const int i = t + j * NT, k = i / VH;
             sclo[k][i - k * VH] = ct[j];
         }
 #pragma unroll
-        for (int j = 0; j < 2; j++) {
-            const su3<T> U = ld_link<T, G, NLC>(lt + j * NLC, 0, 1);
+        for (int j = 0; j < NL; j++) {
+            const int q = t + j * NT;
+            const su3<T> U = ld_link<T, G, NLC>(lt[j], 0, 1);
 #pragma unroll
-            for (int e = 0; e < 9; e++) st<T, G>(slink, (long)((m0 + j) * 9 + e) * LSTR + q, U.m[e]);
-        }
-    }
-
-    // ---- the block right-hand side of both sites
-    cx<T> Ae[12], Ao[12], P[12], tt[12];
-    const long se = (long)d * 12 * VD + loc_e, so = (long)d * 12 * VD + loc_o;
-    if (!live) {
-#pragma unroll
-        for (int k = 0; k < 12; k++) Ae[k] = Ao[k] = czero<T>();
-    } else if (v.first && a.io32) {
-#pragma unroll
-        for (int k = 0; k < 12; k++) {
-            Ae[k] = ld<T, float>((const float2 *)a.eta, se + (long)k * VD);
-            Ao[k] = ld<T, float>((const float2 *)a.eta, so + (long)k * VD);
-        }
-    } else if (v.first) {
-#pragma unroll
-        for (int k = 0; k < 12; k++) {
-            Ae[k] = ld<T, double>(a.eta, se + (long)k * VD);
-            Ao[k] = ld<T, double>(a.eta, so + (long)k * VD);
-        }
-    } else {
-        const T sc = SCALED ? T(a.res_scale[d]) : T(1);
-        const v2<SS> *res = (const v2<SS> *)a.res;
-#pragma unroll
-        for (int k = 0; k < 12; k++) {
-            Ae[k] = scal(sc, ld<T, SS>(res, ((long)d * 12 + k) * VH + hi));
-            Ao[k] = czero<T>();
+            for (int e = 0; e < 9; e++) st<T, G>(slink, (q / VD * 9 + e) * LSTR + q % VD, U.m[e]);
         }
     }
     __syncthreads();   // links staged
-    if (v.faces_in && live) {
+    if (v.faces_in) {
+        // sp holds four faces at a time: along x and y, then along z and t
 #pragma unroll
-        for (int p = 0; p < 2; p++) {
-            const int *l = p ? lo : le;
-            const int loc = p ? loc_o : loc_e;
-            cx<T> *A = p ? Ao : Ae;
-            cx<T> hf[4][6];
-            T wf[4] = {0, 0, 0, 0};
-            int sf[4];
-            face_fetch<Sh, 0, T, SS, SCALED>(a, D, l, hf[0], wf[0], sf[0]);
-            face_fetch<Sh, 1, T, SS, SCALED>(a, D, l, hf[1], wf[1], sf[1]);
-            face_fetch<Sh, 2, T, SS, SCALED>(a, D, l, hf[2], wf[2], sf[2]);
-            face_fetch<Sh, 3, T, SS, SCALED>(a, D, l, hf[3], wf[3], sf[3]);
-            face_apply<Sh, 0, T, G, NLC, LNLC, true, LSTR>(a, d, loc, slink, hf[0], wf[0], sf[0], A);
-            face_apply<Sh, 1, T, G, NLC, LNLC, true, LSTR>(a, d, loc, slink, hf[1], wf[1], sf[1], A);
-            face_apply<Sh, 2, T, G, NLC, LNLC, true, LSTR>(a, d, loc, slink, hf[2], wf[2], sf[2], A);
-            face_apply<Sh, 3, T, G, NLC, LNLC, true, LSTR>(a, d, loc, slink, hf[3], wf[3], sf[3], A);
+        for (int h = 0; h < 2; h++) {
+#pragma unroll
+            for (int q = 0; q < FPW; q++)
+                if (face_of[q] >> 2 == h)
+                    tile_face_stage<Sh, RT, PROD, SS, G>(fraw[q], fw[q], face_of[q], slink, sp + 3 * RT * 64 * (face_of[q] & 3));
+            __syncthreads();
+            if (h == 0) {
+                tile_face_add<Sh, RT, 0>(sp, le, r, Ae);
+                tile_face_add<Sh, RT, 1>(sp + 6 * RT * 64, le, r, Ae);
+                tile_face_add<Sh, RT, 0>(sp, lo, r, Ao);
+                tile_face_add<Sh, RT, 1>(sp + 6 * RT * 64, lo, r, Ao);
+            } else {
+                tile_face_add<Sh, RT, 2>(sp, le, r, Ae);
+                tile_face_add<Sh, RT, 3>(sp + 6 * RT * 64, le, r, Ae);
+                tile_face_add<Sh, RT, 2>(sp, lo, r, Ao);
+                tile_face_add<Sh, RT, 3>(sp + 6 * RT * 64, lo, r, Ao);
+            }
+            __syncthreads();   // sp is written again below
         }
     }
+    c2_t *const vs = sp + hi * RT + r;
+    auto clover_o = [&](const cx<T> in[12], cx<T> o[12]) {
+        clover_wide([&](int q) { return widen<G>(sclo[q][hi]); }, in, o);
+    };
 
     // ---- even-odd preparation: r = rho_e - D_eo C_o^-1 rho_o, x = 0.  With
     // the matrix-instruction products rho_o waits in this right-hand side's
     // global buffer until the reconstruction (their operands leave no room
     // for it in registers); the VALU form keeps it in registers.
     constexpr bool PARK = PROD != PROD_VALU;
-    clover_apply<T, G>(&sclo[0][0], hi, VH, Ao, P);
-    v2<T> *rho_g = (v2<T> *)a.rho_tmp;
+    clover_o(Ao, P);
+    v2<T> *rho_g = global_ptr((v2<T> *)a.rho_tmp);
+    st_c2<VH * RT>(vs, P);
+    if (PARK && live)
 #pragma unroll
-    for (int k = 0; k < 12; k++) {
-        sho[k][hi][r] = P[k];
-        if (PARK && live) st<T, T>(rho_g, ((long)d * 12 + k) * VH + hi, Ao[k]);
-    }
+        for (int k = 0; k < 12; k++) st<T, T>(rho_g, ((long)d * 12 + k) * VH + hi, Ao[k]);
     __syncthreads();
-    tile_hops<Sh, PROD, G>(sho, le, loc_e, r, slink, tt);
+    tile_hops<Sh, PROD, G>(vs, le, loc_e, VH, hi, oe, r, slink, tt);
+    cx<T> rr[12];
 #pragma unroll
     for (int k = 0; k < 12; k++) {
-        she[k][hi][r] = Ae[k] + scal(T(0.5), tt[k]);
+        rr[k] = Ae[k] + scal(T(0.5), tt[k]);
         Ae[k] = czero<T>();
     }
+    // C_e has arrived: without this, a path around the MR loop on which it has
+    // not makes the later waits for its registers wait for younger loads
+#pragma unroll
+    for (int q = 0; q < 36; q++) asm volatile("" : "+v"(cle[q]));
+    __syncthreads();   // sp has been read
+    st_c2<VH * RT>(vs, rr);
 
     // ---- minimal residual on the Schur complement, per right-hand side
 #pragma unroll 1
-    for (int itr = 0; itr < a.n_mr; itr++) {
+    for (int itr = 0; itr < n_mr; itr++) {
         if constexpr (sizeof(v2<G>) == 4) {
             // keep the clover blocks in their 16-bit storage form (see k_sap_lds)
 #pragma unroll
             for (int q = 0; q < 36; q++) asm volatile("" : "+v"(cle[q]));
         }
         __syncthreads();
-        tile_hops<Sh, PROD, G>(she, lo, loc_o, r, slink, tt);
-#pragma unroll
-        for (int k = 0; k < 12; k++) tt[k] = scal(T(-0.5), tt[k]);   // D_oe r
-        clover_apply<T, G>(&sclo[0][0], hi, VH, tt, P);             // C_o^-1 D_oe r
-#pragma unroll
-        for (int k = 0; k < 12; k++) sho[k][hi][r] = P[k];
+        tile_hops<Sh, PROD, G>(vs, lo, loc_o, 0, hi, oo, r, slink, tt);   // -2 D_oe r
+        clover_o(tt, P);                                            // -2 C_o^-1 D_oe r
+        __syncthreads();   // sp has been read
+        st_c2<VH * RT>(vs, P);
         __syncthreads();
-        tile_hops<Sh, PROD, G>(sho, le, loc_e, r, slink, tt);
-        cx<T> rr[12];
-#pragma unroll
-        for (int k = 0; k < 12; k++) rr[k] = she[k][hi][r];
-        clover_reg<T, G>(cle, rr, P);                               // C_e r
+        tile_hops<Sh, PROD, G>(vs, le, loc_e, VH, hi, oe, r, slink, tt);
+        clover_wide([&](int q) { return widen<G>(cle[q]); }, rr, P);   // C_e r
         T dots[3] = {0, 0, 0};
 #pragma unroll
         for (int k = 0; k < 12; k++) {
-            P[k] = P[k] + scal(T(0.5), tt[k]);                      // p = C_e r - D_eo C_o^-1 D_oe r
+            P[k] = P[k] + scal(T(-0.25), tt[k]);                    // p = C_e r - D_eo C_o^-1 D_oe r
             dots[0] = fmad(P[k].i, rr[k].i, fmad(P[k].r, rr[k].r, dots[0]));
             dots[1] = fmad(-P[k].i, rr[k].r, fmad(P[k].r, rr[k].i, dots[1]));
             dots[2] = fmad(P[k].i, P[k].i, fmad(P[k].r, P[k].r, dots[2]));
         }
-        rhs_sum<NW, 3>(dots, red);
+        rhs_sum<RT, NW>(dots, red);   // its barrier: sp has been read
         const cx<T> alpha = dots[2] > T(0) ? cx<T>{dots[0] / dots[2], dots[1] / dots[2]} : czero<T>();
 #pragma unroll
         for (int k = 0; k < 12; k++) {
             Ae[k] = cmac(Ae[k], alpha, rr[k]);
-            she[k][hi][r] = cmac(rr[k], neg(alpha), P[k]);
+            rr[k] = cmac(rr[k], neg(alpha), P[k]);
         }
+        st_c2<VH * RT>(vs, rr);
     }
 
-    // ---- odd sites: delta_o = C_o^-1 (rho_o - D_oe x); x goes through sho
+    // ---- odd sites: delta_o = C_o^-1 (rho_o - D_oe x).  The accumulator is
+    // fetched ahead of it (where registers allow).
+    c2_t pse[6], pso[6];
 #pragma unroll
-    for (int k = 0; k < 12; k++) sho[k][hi][r] = Ae[k];
+    for (int j = 0; j < 6; j++) pse[j] = pso[j] = c2_t{0.f, 0.f, 0.f, 0.f};
+    auto fetch_psi = [&] {
+        if (live && !v.first)
+#pragma unroll
+            for (int j = 0; j < 6; j++) {
+                pse[j] = pe[j * VD];
+                pso[j] = po[j * VD];
+            }
+    };
+    st_c2<VH * RT>(vs, Ae);   // r there was this thread's own entry, not read since
+    if constexpr (!PARK) fetch_psi();
     __syncthreads();
-    tile_hops<Sh, PROD, G>(sho, lo, loc_o, r, slink, tt);
+    tile_hops<Sh, PROD, G>(vs, lo, loc_o, 0, hi, oo, r, slink, tt);
 #pragma unroll
     for (int k = 0; k < 12; k++) {
         const cx<T> ro = !PARK ? Ao[k] : live ? ld<T, T>(rho_g, ((long)d * 12 + k) * VH + hi) : czero<T>();
         tt[k] = ro + scal(T(0.5), tt[k]);
     }
-    clover_apply<T, G>(&sclo[0][0], hi, VH, tt, Ao);                // Ao = delta_o, Ae = delta_e = x
+    clover_o(tt, Ao);                                               // Ao = delta_o, Ae = delta_e = x
+    if constexpr (PARK) fetch_psi();
 
     // ---- epilogue: psi += delta, stored residual, boundary terms
     if (live) {
-        const v2<PS> *psi_in = (const v2<PS> *)a.psi;
-        v2<PS> *psi_out = (v2<PS> *)a.psi;
 #pragma unroll
-        for (int p = 0; p < 2; p++) {
-            const long sb = p ? so : se;
-            const cx<T> *A = p ? Ao : Ae;
+        for (int j = 0; j < 6; j++) {
+            pse[j] += c2_t{Ae[2 * j].r, Ae[2 * j].i, Ae[2 * j + 1].r, Ae[2 * j + 1].i};
+            pso[j] += c2_t{Ao[2 * j].r, Ao[2 * j].i, Ao[2 * j + 1].r, Ao[2 * j + 1].i};
+        }
+        if (v.last) {
 #pragma unroll
             for (int k = 0; k < 12; k++) {
-                const cx<T> ps = v.first ? A[k] : ld<T, PS>(psi_in, sb + (long)k * VD) + A[k];
-                if (v.last && a.io32) st<T, float>((float2 *)a.out, sb + (long)k * VD, ps);
-                else if (v.last) st<T, double>(a.out, sb + (long)k * VD, ps);
-                else st<T, PS>(psi_out, sb + (long)k * VD, ps);
+                const cx<T> ce = {pse[k / 2][2 * (k & 1)], pse[k / 2][2 * (k & 1) + 1]};
+                const cx<T> co = {pso[k / 2][2 * (k & 1)], pso[k / 2][2 * (k & 1) + 1]};
+                if (io32) {
+                    st<T, float>((float2 *)out, se + (long)k * VD, ce);
+                    st<T, float>((float2 *)out, so + (long)k * VD, co);
+                } else {
+                    st<T, double>(out, se + (long)k * VD, ce);
+                    st<T, double>(out, so + (long)k * VD, co);
+                }
+            }
+        } else {
+#pragma unroll
+            for (int j = 0; j < 6; j++) {
+                pe[j * VD] = pse[j];
+                po[j * VD] = pso[j];
             }
         }
     }
-    if (v.res_out) {
-        cx<T> rr[12];
+    if (!v.res_out && !v.faces_out) return;
+    T rsc = T(1), fsc = T(1);
+    if constexpr (SCALED) {
+        T mr = maxabs12(rr), mf = fmax(maxabs12(Ae), maxabs12(Ao));
+        rhs_max2<RT, NW>(mr, mf, red + NW * RT);
+        rsc = pow2_ceil(mr);
+        fsc = T(8) * pow2_ceil(mf);
+    }
+    if (v.res_out && live) {
+        if (SCALED && hi == 0) global_ptr(a.res_scale)[d] = (float)rsc;
+        const T inv = T(1) / rsc;
 #pragma unroll
-        for (int k = 0; k < 12; k++) rr[k] = she[k][hi][r];
-        T sc = T(1);
-        if constexpr (SCALED) {
-            sc = pow2_ceil(rhs_max<NW>(maxabs12(rr), red));
-            if (hi == 0 && live) a.res_scale[d] = (float)sc;
-        }
-        if (live) {
-            v2<SS> *res = (v2<SS> *)a.res;
-            const T inv = T(1) / sc;
+        for (int j = 0; j < 3; j++) {
+            ss8_t q8;
 #pragma unroll
-            for (int k = 0; k < 12; k++) st<T, SS>(res, ((long)d * 12 + k) * VH + hi, scal(inv, rr[k]));
+            for (int e = 0; e < 4; e++) {
+                q8[2 * e] = static_cast<SS>(inv * rr[4 * j + e].r);
+                q8[2 * e + 1] = static_cast<SS>(inv * rr[4 * j + e].i);
+            }
+            pr[j * VH] = q8;
         }
     }
     if (v.faces_out) {
-        T sc = T(1);
-        if constexpr (SCALED) {
-            sc = T(8) * pow2_ceil(rhs_max<NW>(fmax(maxabs12(Ae), maxabs12(Ao)), red + NW * RT));
-            if (hi == 0 && live) a.face_scale[d] = (float)sc;
-        }
-        const T inv = T(1) / sc;
-        if (live) {
-            write_face<Sh, 0, T, SS, G, NLC, LNLC, true, LSTR>(a, d, le, loc_e, Ae, inv, slink);
-            write_face<Sh, 1, T, SS, G, NLC, LNLC, true, LSTR>(a, d, le, loc_e, Ae, inv, slink);
-            write_face<Sh, 2, T, SS, G, NLC, LNLC, true, LSTR>(a, d, le, loc_e, Ae, inv, slink);
-            write_face<Sh, 3, T, SS, G, NLC, LNLC, true, LSTR>(a, d, le, loc_e, Ae, inv, slink);
-            write_face<Sh, 0, T, SS, G, NLC, LNLC, true, LSTR>(a, d, lo, loc_o, Ao, inv, slink);
-            write_face<Sh, 1, T, SS, G, NLC, LNLC, true, LSTR>(a, d, lo, loc_o, Ao, inv, slink);
-            write_face<Sh, 2, T, SS, G, NLC, LNLC, true, LSTR>(a, d, lo, loc_o, Ao, inv, slink);
-            write_face<Sh, 3, T, SS, G, NLC, LNLC, true, LSTR>(a, d, lo, loc_o, Ao, inv, slink);
+        const bool alt = a.face_alt && v.flip;
+        if (SCALED && hi == 0 && live) global_ptr(alt ? a.face_scale_alt : a.face_scale)[d] = (float)fsc;
+        v2<SS> *const face = live ? global_ptr((v2<SS> *)(alt ? a.face_alt : a.face)) : nullptr;
+        const T inv = T(1) / fsc;
+        if (!SCALED) __syncthreads();   // the reconstruction's hops have read sp (SCALED: rhs_max2's barrier)
+        // lane % RT is the right-hand side there too: inv and face are this lane's
+#pragma unroll
+        for (int p = 0; p < 2; p++) {
+            if (p) __syncthreads();     // the even sites' delta has been read
+            st_c2<VH * RT>(vs, p ? Ao : Ae);
+            __syncthreads();
+#pragma unroll 1
+            for (int side = 0; side < 2; side++)
+                tile_face_out<Sh, RT, PROD, SS, G>(face, d, 2 * (wave / (RT / 2)) + side, p, wave % (RT / 2), sp, inv, slink);
         }
     }
 }
@@ -1715,11 +2011,11 @@ static hipError_t launch_batch(const SapArgs *args, const int2 *items, int nitem
     if (product != PRODUCT_LANE) {
         // a tile of right-hand sides per workgroup: 4^4 domains, FP16 storage
         if constexpr (std::is_same<Sh, Shape<4, 4, 4, 4>>::value) {
-            constexpr int NT = Sh::VH * RT;
+            constexpr int NT = Sh::VH * RT_MFMA, NTV = Sh::VH * RT_VALU;
             if (prec == PB16) {
                 switch (product) {
                     case PRODUCT_TILE_VALU:
-                        return launch_bounded(k_sap_tile<Sh, PROD_VALU, bf16_t, bf16_t, false>, nitems, NT, s, args,
+                        return launch_bounded(k_sap_tile<Sh, PROD_VALU, bf16_t, bf16_t, false>, nitems, NTV, s, args,
                                               items, v);
                     case PRODUCT_TILE_MFMA_F32:
                         return launch_bounded(k_sap_tile<Sh, PROD_MFMA_F32, bf16_t, bf16_t, false>, nitems, NT, s, args,
@@ -1733,7 +2029,7 @@ static hipError_t launch_batch(const SapArgs *args, const int2 *items, int nitem
             if (prec != P16) return hipErrorInvalidValue;
             switch (product) {
                 case PRODUCT_TILE_VALU:
-                    return launch_bounded(k_sap_tile<Sh, PROD_VALU, half_t, half_t, true>, nitems, NT, s, args, items, v);
+                    return launch_bounded(k_sap_tile<Sh, PROD_VALU, half_t, half_t, true>, nitems, NTV, s, args, items, v);
                 case PRODUCT_TILE_MFMA_F32:
                     return launch_bounded(k_sap_tile<Sh, PROD_MFMA_F32, half_t, half_t, true>, nitems, NT, s, args, items,
                                           v);
@@ -1776,7 +2072,10 @@ int sap_domains_per_workgroup(int shape, int prec, int product)
     return shape == 0 && prec != P64 && product == PRODUCT_LANE ? 8 : 1;
 }
 
-int sap_rhs_per_workgroup(int product) { return product == PRODUCT_LANE ? 1 : RT; }
+int sap_rhs_per_workgroup(int product)
+{
+    return product == PRODUCT_LANE ? 1 : product == PRODUCT_TILE_VALU ? RT_VALU : RT_MFMA;
+}
 
 bool sap_product_supported(const int b[4], int prec, int product)
 {

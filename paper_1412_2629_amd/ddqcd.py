@@ -150,7 +150,7 @@ class Context:
         self._workspace = ws
 
     def set_sap(self, n_cycles=16, n_mr=5, prec="f32", product="lane"):
-        """product: "lane" (one right-hand side per workgroup), "tile" (four per
+        """product: "lane" (one right-hand side per workgroup), "tile" (two per
         workgroup, VALU products), "mfma_f32" or "mfma_bf16" (four per workgroup,
         link products on matrix instructions)."""
         self._check(lib().ddqcd_set_sap(self._h, n_cycles, n_mr, PREC[prec], PRODUCT[product]), "set_sap")
