@@ -258,43 +258,6 @@ __device__ __forceinline__ void dom_hops(const cx<T> (*v)[Sh::VH], const int l[4
     dom_hop<Sh, 3, T, G, NLC>(v, l, lbase, loc, links, acc);
 }
 
-// The hop sum of every site of parity po, shared by the site's thread pair:
-// the thread of parity po takes directions 0 and 1 of its own site, the thread
-// of the other parity with the same half index takes directions 2 and 3 of
-// that site (partner coordinates lp, index locp) and hands its partial sum over
-// through X ([12][VH] in LDS).  XFREE: nothing reads X during the hops, so the
-// partial is written at once; otherwise after a barrier.  Every thread of the
-// workgroup calls this (it holds barriers); on return the po thread's acc is
-// the whole sum, the other thread's acc is its own partial.
-template <class Sh, typename T, typename G, int NLC, bool XFREE>
-__device__ __forceinline__ void pair_hops(const cx<T> (*v)[Sh::VH], cx<T> (*X)[Sh::VH], int po, int par, int hi,
-                                          const int l[4], int loc, const int lp[4], int locp, long lbase,
-                                          const v2<G> *links, cx<T> acc[12])
-{
-#pragma unroll
-    for (int k = 0; k < 12; k++) acc[k] = czero<T>();
-    if (par == po) {
-        dom_hop<Sh, 0, T, G, NLC>(v, l, lbase, loc, links, acc);
-        dom_hop<Sh, 1, T, G, NLC>(v, l, lbase, loc, links, acc);
-    } else if (par == 1 - po) {
-        dom_hop<Sh, 2, T, G, NLC>(v, lp, lbase, locp, links, acc);
-        dom_hop<Sh, 3, T, G, NLC>(v, lp, lbase, locp, links, acc);
-        if constexpr (XFREE)
-#pragma unroll
-            for (int k = 0; k < 12; k++) X[k][hi] = acc[k];
-    }
-    if constexpr (!XFREE) {
-        __syncthreads();
-        if (par == 1 - po)
-#pragma unroll
-            for (int k = 0; k < 12; k++) X[k][hi] = acc[k];
-    }
-    __syncthreads();
-    if (par == po)
-#pragma unroll
-        for (int k = 0; k < 12; k++) acc[k] = acc[k] + X[k][hi];
-}
-
 // A uniform pointer the compiler must treat as unknown from here on: the
 // addresses derived from it are formed at their use instead of being
 // precomputed and held in registers across loops.
@@ -411,55 +374,12 @@ __device__ __forceinline__ void gather_face(const SapArgs &a, const int D[4], in
     }
 }
 
-// gather_face for all four directions at once, split in two steps so that
-// the boundary loads of every direction are in flight together: face_fetch
-// loads the site's boundary half-spinor along MU (if it has one) and its
-// weight, face_apply adds its contribution.
-template <class Sh, int MU, typename T, typename SS, bool SCALED>
-__device__ __forceinline__ void face_fetch(const SapArgs &a, const int D[4], const int l[4], cx<T> h[6], T &w,
-                                           int &side)
-{
-    const bool bwd = l[MU] == 0, fwd = l[MU] == Sh::B[MU] - 1;
-    side = bwd ? 1 : fwd ? 2 : 0;
-    if (!(bwd || fwd)) return;
-    const v2<SS> *face = (const v2<SS> *)a.face_in;
-    int Dn[4] = {D[0], D[1], D[2], D[3]};
-    const bool wrap = bwd ? D[MU] == 0 : D[MU] == a.g.n[MU] - 1;
-    Dn[MU] = bwd ? (wrap ? a.g.n[MU] - 1 : D[MU] - 1) : (wrap ? 0 : D[MU] + 1);
-    const int dn = Dn[0] + a.g.n[0] * (Dn[1] + a.g.n[1] * (Dn[2] + a.g.n[2] * Dn[3]));
-    // backward hop: the -mu neighbour's +mu face; forward: the +mu neighbour's -mu face
-    const long fb = face_base<Sh>(dn, 2 * MU + (bwd ? 1 : 0));
-    const int fi = Sh::template face_index<MU>(l);
-#pragma unroll
-    for (int k = 0; k < 6; k++) h[k] = ld<T, SS>(face, fb + (long)k * Sh::FS[MU] + fi);
-    const T sc = SCALED ? T(a.face_in_scale[dn]) : T(1);
-    w = sc * T(wrap ? 0.5 * a.g.bc[MU] : 0.5);
-}
-
-template <class Sh, int MU, typename T, typename G, int NLC, int LNLC, bool FROM_LDS, int LSTR = Sh::VD>
-__device__ __forceinline__ void face_apply(const SapArgs &a, int d, int loc, const v2<G> *slink, const cx<T> h[6],
-                                           T w, int side, cx<T> rho[12])
-{
-    constexpr int VD = Sh::VD;
-    if (side == 1) {
-        recon_acc<MU, +1>(rho, h, w);
-    } else if (side == 2) {
-        cx<T> uh[6];
-        su3<T> U;
-        if constexpr (FROM_LDS) U = ld_link<T, G, LNLC>(slink, (long)MU * LNLC * LSTR + loc, LSTR);
-        else U = ld_link<T, G, NLC>((const v2<G> *)a.links, ((long)d * 4 + MU) * NLC * VD + loc, VD);
-        su3_mul(U, h, uh);
-        recon_acc<MU, -1>(rho, uh, w);
-    }
-}
-
-template <class Sh, int MU, typename T, typename SS, typename G, int NLC, int LNLC = NLC, bool FROM_LDS = false,
-          int LSTR = Sh::VD>
+template <class Sh, int MU, typename T, typename SS, typename G, int NLC>
 __device__ __forceinline__ void write_face(const SapArgs &a, int d, const int l[4], int loc, const cx<T> delta[12],
-                                           T inv_sc, const v2<G> *slink = nullptr)
+                                           T inv_sc)
 {
     constexpr int VD = Sh::VD;
-    v2<SS> *face = (v2<SS> *)a.face;
+    v2<SS> *face = global_ptr((v2<SS> *)a.face);
     cx<T> h[6];
     if (l[MU] == 0) {
         proj<MU, -1>(delta, h);
@@ -470,10 +390,7 @@ __device__ __forceinline__ void write_face(const SapArgs &a, int d, const int l[
     } else if (l[MU] == Sh::B[MU] - 1) {
         cx<T> uh[6];
         proj<MU, +1>(delta, h);
-        // FROM_LDS: the domain's links staged in slink ([mu][LNLC][LSTR]), else global
-        su3<T> U;
-        if constexpr (FROM_LDS) U = ld_link<T, G, LNLC>(slink, (long)MU * LNLC * LSTR + loc, LSTR);
-        else U = ld_link<T, G, NLC>((const v2<G> *)a.links, ((long)d * 4 + MU) * NLC * VD + loc, VD);
+        const su3<T> U = ld_link<T, G, NLC>(global_ptr((const v2<G> *)a.links), ((long)d * 4 + MU) * NLC * VD + loc, VD);
         su3_dag_mul(U, h, uh);
         long fb = face_base<Sh>(d, 2 * MU + 1);
         int fi = Sh::template face_index<MU>(l);
@@ -673,70 +590,365 @@ __device__ __forceinline__ void pair_block_solve(const SapArgs &a, const int d)
     write_site<Sh, T, SS, PS, G, NLC>(a, d, le, loc_e, r, T(1) / face_sc);
 }
 
-// ---- the LDS-resident half-sweep kernel (FP32 arithmetic) -----------------
+// ---- the LDS-resident half-sweep kernels (FP32 arithmetic) ----------------
 //
-// One workgroup per domain, one thread per site.  At the start of the block
-// solve the domain's links are staged once into LDS and each thread loads its
-// own site's clover block (C on even sites, C^-1 on odd sites) into
-// registers, so the MR steps read no global memory at all: the hopping terms
-// take the neighbour spinor and the link from LDS, the site terms from
-// registers.  x and r of the even sites and rho/delta of the odd sites stay in
-// the registers of the site's own thread.
+// At the start of the block solve the domain's links are staged once into LDS,
+// so the MR steps read no global memory: the hopping terms take the neighbour
+// spinor and the link from LDS, the site terms from registers (or, the tile's
+// odd sites, from LDS).
 
-template <typename T, typename G>
-__device__ __forceinline__ void clover_block_reg(const v2<G> *c, const cx<T> in[6], cx<T> out[6])
+typedef float f32x4_t __attribute__((ext_vector_type(4)));
+
+// A spinor of one site and right-hand side in LDS and in the accumulator: six 16-byte entries of two complex components, the entries of one
+// component pair contiguous over (site, right-hand side).  16 bytes a lane is
+// what LDS moves at its full rate (measured on gfx950: 131 bytes a cycle and CU
+// against 67 for 8-byte reads).
+typedef f32x4_t c2_t;
+
+template <int STRIDE> __device__ __forceinline__ void ld_c2(const c2_t *p, cx<float> s[12])
 {
-    const T z = opaque_neg_zero<T>();
 #pragma unroll
-    for (int q = 0; q < 3; q++) {
-        const T d0 = static_cast<T>(c[q].x), d1 = static_cast<T>(c[q].y);
-        out[2 * q] = {fmad(d0, in[2 * q].r, z), fmad(d0, in[2 * q].i, z)};
-        out[2 * q + 1] = {fmad(d1, in[2 * q + 1].r, z), fmad(d1, in[2 * q + 1].i, z)};
+    for (int j = 0; j < 6; j++) {
+        const c2_t q = p[j * STRIDE];
+        s[2 * j] = {q[0], q[1]};
+        s[2 * j + 1] = {q[2], q[3]};
     }
-#pragma unroll
-    for (int i = 1; i < 6; i++)
-#pragma unroll
-        for (int j = 0; j < i; j++) {
-            v2<G> mv = c[3 + tri_index(i, j)];
-            cx<T> m = {static_cast<T>(mv.x), static_cast<T>(mv.y)};
-            out[i] = cmac(out[i], m, in[j]);
-            out[j] = cmacc(out[j], m, in[i]);
-        }
 }
-
-template <typename T, typename G>
-__device__ __forceinline__ void clover_reg(const v2<G> cl[36], const cx<T> in[12], cx<T> out[12])
+template <int STRIDE> __device__ __forceinline__ void st_c2(c2_t *p, const cx<float> s[12])
 {
-    clover_block_reg<T, G>(cl, in, out);
-    clover_block_reg<T, G>(cl + 18, in + 6, out + 6);
+#pragma unroll
+    for (int j = 0; j < 6; j++) p[j * STRIDE] = c2_t{s[2 * j].r, s[2 * j].i, s[2 * j + 1].r, s[2 * j + 1].i};
 }
 
-// T: arithmetic; SS: storage of the block residual and faces; PS: storage of
-// the solution accumulator; G: links and clover; NLC: complex numbers stored
-// per link (6: two rows, 9: full).  LINK_LDS stages the domain's links into
-// LDS (else they are read from global memory at each use); CL_REG keeps the
-// site's clover block in registers (else it is read from global memory).
+// A stored pair of 16-bit values as FP32, converted here: hidden from the
+// compiler, so that it does not fold the conversion into mixed-precision
+// multiply-adds, which issue at half the rate of FP32 ones (gfx950, two waves
+// per SIMD: 4.4 against 2.6 cycles each).  The upper half is shifted down first:
+// the conversion that selects it by itself (SDWA) is the slow one.  An SU(3)
+// times half-spinor product with the link's nine pairs read from LDS takes 347
+// cycles this way, 424 with SDWA conversions, 447 with mixed-precision
+// multiply-adds and 299 with FP32 links.
+template <typename G> __device__ __forceinline__ cx<float> widen(v2<G> v)
+{
+    cx<float> c;
+    if constexpr (std::is_same<G, half_t>::value) {
+        unsigned u = __builtin_bit_cast(unsigned, v), h = u >> 16;
+        asm("" : "+v"(h));
+        c = {static_cast<float>(__builtin_bit_cast(half_t, (unsigned short)u)),
+             static_cast<float>(__builtin_bit_cast(half_t, (unsigned short)h))};
+    } else {
+        c = {static_cast<float>(v.x), static_cast<float>(v.y)};
+    }
+    asm("" : "+v"(c.r), "+v"(c.i));
+    return c;
+}
+
+// out = (packed clover block of 36 pairs, load(q) its pair q) in
+template <typename Load> __device__ __forceinline__ void clover_wide(Load load, const cx<float> in[12], cx<float> out[12])
+{
+    clover_block_with<float>(load, in, out);
+    clover_block_with<float>([&](int q) { return load(18 + q); }, in + 6, out + 6);
+}
+
+// The block residual of one site in memory: 16-byte entries, [3][VH] of four
+// 16-bit complex numbers or [6][VH] of two FP32 ones; scale x the stored values.
+template <int VH, typename SS> __device__ __forceinline__ void ld_res(const void *base, long site, float scale, cx<float> s[12])
+{
+    if constexpr (sizeof(SS) == 2) {
+        typedef SS ss8_t __attribute__((ext_vector_type(8)));
+        const ss8_t *p = global_ptr((const ss8_t *)base) + site;
+#pragma unroll
+        for (int j = 0; j < 3; j++) {
+            const ss8_t q = p[j * VH];
+#pragma unroll
+            for (int e = 0; e < 4; e++)
+                s[4 * j + e] = {scale * static_cast<float>(q[2 * e]), scale * static_cast<float>(q[2 * e + 1])};
+        }
+    } else {
+        ld_c2<VH>(global_ptr((const c2_t *)base) + site, s);
+    }
+}
+template <int VH, typename SS> __device__ __forceinline__ void st_res(void *base, long site, float inv, const cx<float> s[12])
+{
+    if constexpr (sizeof(SS) == 2) {
+        typedef SS ss8_t __attribute__((ext_vector_type(8)));
+        ss8_t *p = global_ptr((ss8_t *)base) + site;
+#pragma unroll
+        for (int j = 0; j < 3; j++) {
+            ss8_t q;
+#pragma unroll
+            for (int e = 0; e < 4; e++) {
+                q[2 * e] = static_cast<SS>(inv * s[4 * j + e].r);
+                q[2 * e + 1] = static_cast<SS>(inv * s[4 * j + e].i);
+            }
+            p[j * VH] = q;
+        }
+    } else {
+        st_c2<VH>(global_ptr((c2_t *)base) + site, s);
+    }
+}
+
+// A site's links in registers (one right-hand side per workgroup): 16-bit links
+// widened to three FP32 rows once at staging, FP32 links as the two stored rows,
+// the third rebuilt at each use (its registers go to the FP32 clover block).
+template <typename G> struct RegLink {
+    su3<float> U;
+    __device__ __forceinline__ void put(const v2<G> rows[6])
+    {
+        U = ld_link_with<float, 6>([&](int e) { return widen<G>(rows[e]); });
+        // the third row as the storage type holds it
+#pragma unroll
+        for (int e = 6; e < 9; e++) {
+            v2<G> q;
+            q.x = static_cast<G>(U.m[e].r);
+            q.y = static_cast<G>(U.m[e].i);
+            U.m[e] = widen<G>(q);
+        }
+    }
+    __device__ __forceinline__ su3<float> operator()() const { return U; }
+};
+template <> struct RegLink<float> {
+    float2 m[6];
+    __device__ __forceinline__ void put(const float2 rows[6])
+    {
+#pragma unroll
+        for (int e = 0; e < 6; e++) m[e] = rows[e];
+    }
+    __device__ __forceinline__ su3<float> operator()() const
+    {
+        return ld_link_with<float, 6>([&](int e) { return cx<float>{m[e].x, m[e].y}; });
+    }
+};
+
+// A domain's 16-bit links in LDS (tiles of right-hand sides) as three rows
+// [mu][9][LS], the third rebuilt once at staging; read as FP32 matrices.
+template <typename G, int LS> struct LdsLinks {
+    const v2<G> *p;
+    __device__ __forceinline__ su3<float> operator()(int mu, int site) const
+    {
+        const v2<G> *q = p + mu * 9 * LS + site;
+        su3<float> U;
+#pragma unroll
+        for (int e = 0; e < 9; e++) U.m[e] = widen<G>(q[e * LS]);
+        return U;
+    }
+    // stages one link from its stored rows
+    static __device__ __forceinline__ void put(v2<G> *s, int mu, int site, const v2<G> rows[6])
+    {
+        const su3<float> U = ld_link<float, G, 6>(rows, 0, 1);
+#pragma unroll
+        for (int e = 0; e < 9; e++) st<float, G>(s, (mu * 9 + e) * LS + site, U.m[e]);
+    }
+};
+
+// A site's hop along MU inside the domain; SIGN < 0: from x + mu, SIGN > 0: from
+// x - mu.  hop_exists: the neighbour lies in the domain; hop_step: its half
+// index relative to the site's (ox: 1 where the site's x is odd), a constant
+// except along x.
+template <class Sh, int MU, int SIGN> __device__ __forceinline__ bool hop_exists(const int l[4])
+{
+    return SIGN < 0 ? l[MU] + 1 < Sh::B[MU] : l[MU] > 0;
+}
+template <class Sh, int MU, int SIGN> __device__ __forceinline__ int hop_step(int ox)
+{
+    constexpr int STEP = MU == 1 ? Sh::B[0] / 2 : MU == 2 ? Sh::B[0] * Sh::B[1] / 2 : Sh::B[0] * Sh::B[1] * Sh::B[2] / 2;
+    return MU == 0 ? (SIGN < 0 ? ox : ox - 1) : SIGN < 0 ? STEP : -STEP;
+}
+
+// acc += the hop into a site along MU: (1 - gamma_mu) U_mu(x) v(x + mu) for
+// SIGN < 0, (1 + gamma_mu) U_mu(x - mu)^dagger v(x - mu) for SIGN > 0.  v: this
+// right-hand side's spinor of the other parity's site with this site's half
+// index hi in LDS ([6][VH][RT]); loc: the site, op: the first site of the other
+// parity.  Neighbour offsets are constants (one address register for x, one
+// for the other directions), so LDS addresses are immediates.
+template <class Sh, int MU, int SIGN, int RT, typename Links>
+__device__ __forceinline__ void lds_hop(const c2_t *v, const int l[4], int loc, int op, int hi, int ox, const Links &links,
+                                        cx<float> acc[12])
+{
+    if (!hop_exists<Sh, MU, SIGN>(l)) return;
+    const int dn = hop_step<Sh, MU, SIGN>(ox);
+    cx<float> s[12], h[6], uh[6];
+    ld_c2<Sh::VH * RT>(v + dn * RT, s);
+    proj<MU, SIGN>(s, h);
+    const su3<float> U = links(MU, SIGN < 0 ? loc : op + hi + dn);
+    if constexpr (SIGN < 0) su3_mul(U, h, uh);
+    else su3_dag_mul(U, h, uh);
+    recon_acc<MU, SIGN>(acc, uh, 1.0f);
+}
+
+// ---- one right-hand side per workgroup -------------------------------------
+//
+// One workgroup per domain, one thread per site.  Each thread holds its own
+// site's links and clover block (C on even sites, C^-1 on odd sites) in
+// registers; x of the even sites and rho/delta of the odd sites stay in the
+// registers of the site's own thread, r of the even sites in its LDS entry.
+//
+// A link is used by its own site's thread only.  In the hop sum of the sites of
+// one parity their threads take the forward hops (the neighbour's spinor from
+// LDS, their own link), and the threads of the other parity the backward ones:
+// each multiplies its own spinor by its own link's adjoint and leaves the half-
+// spinor in LDS for the site x + mu.  So both parities' threads work in every
+// phase, links need neither LDS nor a conversion at each use, and the LDS
+// traffic is that of reading eight neighbour spinors.
+// One launch (a colour) with 8x4^3 domains: 45.7 us in FP32 on 16^3x32 (half the
+// CUs have one), 385 us with FP16 storage on 32^3x64.  With a pair of threads
+// reading all eight neighbours and the links from LDS it took 47.8 and 422 us,
+// and 56.4 and 520 us with 8-byte LDS reads, mixed-precision multiply-adds and
+// generic loads.  What is left is mostly the issue of FP32 instructions: 8 of 10
+// cycles a wave can issue in, at two waves per SIMD (256 registers).
 //
 // NDW domains share a workgroup (NDW > 1 for domains of fewer than 64 sites):
 // wave 0 then holds the even sites and wave 1 the odd sites of all of them,
 // so each phase of the even-odd MR step runs one full wave; d is the calling
 // thread's domain.
-//
-// LNLC: complex numbers per link kept in LDS (6, as stored, or 9: the third
-// row rebuilt once at staging instead of at every use).
-template <class Sh, int NDW, typename T, typename SS, typename PS, typename G, int NLC, int LNLC, bool SCALED,
-          bool LINK_LDS, bool CL_REG>
+
+// The forward hop along MU into this site from the other parity's array v
+// (at this half index): acc += (1 - gamma_mu) U_mu(x) v(x + mu).
+template <class Sh, int MU, typename Link>
+__device__ __forceinline__ void lane_fwd(const c2_t *v, const int l[4], int ox, const Link &U, cx<float> acc[12])
+{
+    if (!hop_exists<Sh, MU, -1>(l)) return;
+    cx<float> s[12], h[6], uh[6];
+    ld_c2<Sh::VH>(v + hop_step<Sh, MU, -1>(ox), s);
+    proj<MU, -1>(s, h);
+    su3_mul(U(), h, uh);
+    recon_acc<MU, -1>(acc, uh, 1.0f);
+}
+
+// X (this half index) = U_mu(x)^dagger (1 + gamma_mu) own, for the site x + mu
+template <class Sh, int MU, typename Link>
+__device__ __forceinline__ void lane_push(const cx<float> own[12], const int l[4], const Link &U, c2_t *X)
+{
+    if (!hop_exists<Sh, MU, -1>(l)) return;
+    cx<float> h[6], uh[6];
+    proj<MU, +1>(own, h);
+    su3_dag_mul(U(), h, uh);
+#pragma unroll
+    for (int j = 0; j < 3; j++) X[(MU * 3 + j) * Sh::VH] = c2_t{uh[2 * j].r, uh[2 * j].i, uh[2 * j + 1].r, uh[2 * j + 1].i};
+}
+
+// acc += the half-spinor that x - mu left for this site
+template <class Sh, int MU> __device__ __forceinline__ void lane_pull(const c2_t *X, const int l[4], int ox, cx<float> acc[12])
+{
+    if (!hop_exists<Sh, MU, +1>(l)) return;
+    const c2_t *p = X + MU * 3 * Sh::VH + hop_step<Sh, MU, +1>(ox);
+    cx<float> uh[6];
+#pragma unroll
+    for (int j = 0; j < 3; j++) {
+        const c2_t q = p[j * Sh::VH];
+        uh[2 * j] = {q[0], q[1]};
+        uh[2 * j + 1] = {q[2], q[3]};
+    }
+    recon_acc<MU, +1>(acc, uh, 1.0f);
+}
+
+// The hop sum of every site of parity po, in acc of its thread.  v: the other
+// parity's spinors in LDS at this half index, own: this thread's own spinor
+// (threads of the other parity), X: the half-spinors handed over.  Every thread
+// of the workgroup calls this (it holds a barrier, after which v is free); X is
+// free after the next one.
+template <class Sh, typename Link>
+__device__ __forceinline__ void lane_hops(const c2_t *v, const cx<float> own[12], c2_t *X, int po, int par, const int l[4],
+                                          const Link (&U)[4], cx<float> acc[12])
+{
+    const int ox = l[0] & 1;
+#pragma unroll
+    for (int k = 0; k < 12; k++) acc[k] = czero<float>();
+    if (par == po) {
+        lane_fwd<Sh, 0>(v, l, ox, U[0], acc);
+        lane_fwd<Sh, 1>(v, l, ox, U[1], acc);
+        lane_fwd<Sh, 2>(v, l, ox, U[2], acc);
+        lane_fwd<Sh, 3>(v, l, ox, U[3], acc);
+    } else if (par == 1 - po) {
+        lane_push<Sh, 0>(own, l, U[0], X);
+        lane_push<Sh, 1>(own, l, U[1], X);
+        lane_push<Sh, 2>(own, l, U[2], X);
+        lane_push<Sh, 3>(own, l, U[3], X);
+    }
+    __syncthreads();
+    if (par == po) {
+        lane_pull<Sh, 0>(X, l, ox, acc);
+        lane_pull<Sh, 1>(X, l, ox, acc);
+        lane_pull<Sh, 2>(X, l, ox, acc);
+        lane_pull<Sh, 3>(X, l, ox, acc);
+    }
+}
+
+// The boundary terms of a visit, in two steps so that the loads of every
+// direction are in flight together: face_fetch loads the site's boundary
+// half-spinor along MU (if it has one) and its weight, face_apply adds its
+// contribution.
+template <class Sh, int MU, typename SS, bool SCALED>
+__device__ __forceinline__ void face_fetch(const SapArgs &a, const int D[4], const int l[4], cx<float> h[6], float &w,
+                                           int &side)
+{
+    const bool bwd = l[MU] == 0, fwd = l[MU] == Sh::B[MU] - 1;
+    side = bwd ? 1 : fwd ? 2 : 0;
+    if (!(bwd || fwd)) return;
+    const v2<SS> *face = global_ptr((const v2<SS> *)a.face_in);
+    int Dn[4] = {D[0], D[1], D[2], D[3]};
+    const bool wrap = bwd ? D[MU] == 0 : D[MU] == a.g.n[MU] - 1;
+    Dn[MU] = bwd ? (wrap ? a.g.n[MU] - 1 : D[MU] - 1) : (wrap ? 0 : D[MU] + 1);
+    const int dn = Dn[0] + a.g.n[0] * (Dn[1] + a.g.n[1] * (Dn[2] + a.g.n[2] * Dn[3]));
+    // backward hop: the -mu neighbour's +mu face; forward: the +mu neighbour's -mu face
+    const long fb = face_base<Sh>(dn, 2 * MU + (bwd ? 1 : 0));
+    const int fi = Sh::template face_index<MU>(l);
+#pragma unroll
+    for (int k = 0; k < 6; k++) h[k] = ld<float, SS>(face, fb + (long)k * Sh::FS[MU] + fi);
+    const float sc = SCALED ? global_ptr(a.face_in_scale)[dn] : 1.0f;
+    w = sc * float(wrap ? 0.5 * a.g.bc[MU] : 0.5);
+}
+
+template <class Sh, int MU, typename Link>
+__device__ __forceinline__ void face_apply(const Link &U, const cx<float> h[6], float w, int side, cx<float> rho[12])
+{
+    if (side == 1) {
+        recon_acc<MU, +1>(rho, h, w);
+    } else if (side == 2) {
+        cx<float> uh[6];
+        su3_mul(U(), h, uh);
+        recon_acc<MU, -1>(rho, uh, w);
+    }
+}
+
+template <class Sh, int MU, typename SS, typename Link>
+__device__ __forceinline__ void face_write(const SapArgs &a, int d, const int l[4], const cx<float> delta[12], float inv_sc,
+                                           const Link &U)
+{
+    v2<SS> *face = global_ptr((v2<SS> *)a.face);
+    cx<float> h[6];
+    const bool lo = l[MU] == 0;
+    if (!(lo || l[MU] == Sh::B[MU] - 1)) return;
+    if (lo) {
+        proj<MU, -1>(delta, h);
+    } else {
+        cx<float> g[6];
+        proj<MU, +1>(delta, g);
+        su3_dag_mul(U(), g, h);
+    }
+    const long fb = face_base<Sh>(d, 2 * MU + (lo ? 0 : 1));
+    const int fi = Sh::template face_index<MU>(l);
+#pragma unroll
+    for (int k = 0; k < 6; k++) st<float, SS>(face, fb + (long)k * Sh::FS[MU] + fi, scal(inv_sc, h[k]));
+}
+
+// SS: storage of the block residual and the boundary terms; G: of links (two
+// rows) and clover.  The accumulator ([d][6][VD] 16-byte entries, FP32) and the
+// block residual are laid out for 16-byte accesses.
+template <class Sh, int NDW, typename SS, typename G, bool SCALED>
 __device__ __forceinline__ void lds_block_solve(const SapArgs &a, const int d, const Visit f)
 {
-    constexpr int VD = Sh::VD, VH = Sh::VH;
+    using T = float;
+    constexpr int VD = Sh::VD, VH = Sh::VH, NLC = 6;
     constexpr int NT = NDW > 1 ? NDW * VD : Sh::NT;   // threads of the workgroup
     constexpr int RV = NDW > 1 ? VD : NT;             // reduction width argument
-    constexpr int HNLC = LINK_LDS ? LNLC : NLC;   // link layout the hops read
     static_assert(NDW == 1 || NDW * VH == 64, "packed domains: one wave per parity");
-    static_assert(LNLC == NLC || (LNLC == 9 && NLC == 6), "links in LDS: as stored, or two rows made three");
-    __shared__ v2<G> slink_all[NDW][LINK_LDS ? 4 * LNLC * VD : 1];   // [mu][LNLC][VD] per domain
-    __shared__ cx<T> she_all[NDW][12][VH];
-    __shared__ cx<T> sho_all[NDW][12][VH];
+    __shared__ c2_t she_all[NDW][6 * VH];     // even sites: r
+    __shared__ c2_t sho_all[NDW][6 * VH];     // odd sites: C_o^-1 D_oe r; x in the reconstruction
+    __shared__ c2_t shx_all[NDW][4 * 3 * VH]; // half-spinors handed to x + mu
+    // FP32 clover blocks leave no registers for A through the MR steps: it waits in LDS
+    constexpr bool A_LDS = sizeof(v2<G>) == 8;
+    __shared__ c2_t sa_all[A_LDS ? NDW * 6 * VD : 1];
     __shared__ T red[NDW > 1 ? 6 * NDW : NT >= 64 ? 3 * (NT / 64) : 3 * NT];
 
     const int par = (int)threadIdx.x / (NDW * VH);
@@ -747,16 +959,10 @@ __device__ __forceinline__ void lds_block_solve(const SapArgs &a, const int d, c
     // padding threads (threadIdx >= VD, only when VD is not a multiple of 64)
     // take part in barriers and reductions with zeros and touch no memory
     const bool live = NDW > 1 || NT == VD || (int)threadIdx.x < VD;
-    v2<G> *slink = slink_all[sub];
-    cx<T>(*she)[VH] = she_all[sub];
-    cx<T>(*sho)[VH] = sho_all[sub];
+    // this half index
+    c2_t *const ve = she_all[sub] + hi, *const vo = sho_all[sub] + hi, *const vx = shx_all[sub] + hi;
     int l[4];
     Sh::coords(loc, l);
-    // the site of the other parity with the same half index: its hops in
-    // directions 2 and 3 are this thread's share of its hop sums
-    const int locp = (1 - par) * VH + hi;
-    int lp[4];
-    Sh::coords(par < 2 ? locp : loc, lp);
     int D[4];
     {
         int r = d;
@@ -765,111 +971,95 @@ __device__ __forceinline__ void lds_block_solve(const SapArgs &a, const int d, c
         D[2] = r % a.g.n[2];
         D[3] = r / a.g.n[2];
     }
-    const v2<G> *glinks = (const v2<G> *)a.links;
-    const v2<G> *cs = (const v2<G> *)a.cs;
+    const v2<G> *glinks = global_ptr((const v2<G> *)a.links);
+    const v2<G> *cs = global_ptr((const v2<G> *)a.cs);
     const long sbase = (long)d * 12 * VD + loc;
+    c2_t *const psi = global_ptr((c2_t *)a.psi) + (long)d * 6 * VD + loc;
+    const long rbase = (long)d * (sizeof(SS) == 2 ? 3 : 6) * VH + hi;
 
-    // ---- stage the links into LDS, the site's clover block into registers.
-    // Every global load is issued before the first LDS store: the loads go
-    // through generic pointers, so a load placed after an LDS store must wait
-    // for it, and with loads and stores interleaved each load would wait for
-    // the previous one's data.
-    const v2<G> *links = slink;
-    long lbase = 0;
-    v2<G> lt[LINK_LDS ? 4 * NLC : 1];
-    if constexpr (LINK_LDS) {
-        if (live) {
-            const long lb = (long)d * 4 * NLC * VD + loc;
-#pragma unroll
-            for (int q = 0; q < 4 * NLC; q++) lt[q] = glinks[lb + (long)q * VD];
-        }
-    } else {
-        links = glinks;
-        lbase = (long)d * 4 * NLC * VD;
-    }
-    const long cbase = (long)d * 36 * VD + loc;
-    v2<G> cl[CL_REG ? 36 : 1];
-    if constexpr (CL_REG) {
-#pragma unroll
-        for (int q = 0; q < 36; q++) cl[q] = live ? cs[cbase + (long)q * VD] : v2<G>{};
-    }
-    if (!live) {
-    } else if constexpr (LINK_LDS && LNLC == NLC) {
-#pragma unroll
-        for (int q = 0; q < 4 * NLC; q++) slink[q * VD + loc] = lt[q];
-    } else if constexpr (LINK_LDS) {
-#pragma unroll
-        for (int mu = 0; mu < 4; mu++) {
-            const su3<T> U = ld_link<T, G, NLC>(lt + mu * NLC, 0, 1);
-#pragma unroll
-            for (int e = 0; e < 9; e++) st<T, G>(slink, (long)(mu * 9 + e) * VD + loc, U.m[e]);
-        }
-    }
-    // this site's clover block (C_e on even sites, C_o^-1 on odd sites) times in
-    auto clover = [&](const cx<T> in[12], cx<T> out[12]) {
-        if constexpr (CL_REG) clover_reg<T, G>(cl, in, out);
-        else clover_apply<T, G>(cs, cbase, VD, in, out);
-    };
-
+    // ---- the site's links and clover block and the block right-hand side
     // A: even sites x (MR solution), odd sites rho_o then delta_o
     cx<T> A[12], P[12];
+    v2<G> lt[4][NLC], cl[36];
+    const long lb = (long)d * 4 * NLC * VD + loc;
+#pragma unroll
+    for (int q = 0; q < 4 * NLC; q++) lt[q / NLC][q % NLC] = live ? glinks[lb + (long)q * VD] : v2<G>{};
     if (!live) {
 #pragma unroll
         for (int k = 0; k < 12; k++) A[k] = czero<T>();
     } else if (f.first) {
         if (a.io32) {
 #pragma unroll
-            for (int k = 0; k < 12; k++) A[k] = ld<T, float>((const float2 *)a.eta, sbase + (long)k * VD);
+            for (int k = 0; k < 12; k++) A[k] = ld<T, float>(global_ptr((const float2 *)a.eta), sbase + (long)k * VD);
         } else {
 #pragma unroll
-            for (int k = 0; k < 12; k++) A[k] = ld<T, double>(a.eta, sbase + (long)k * VD);
+            for (int k = 0; k < 12; k++) A[k] = ld<T, double>(global_ptr(a.eta), sbase + (long)k * VD);
         }
     } else if (par == 0) {
-        T sc = SCALED ? T(a.res_scale[d]) : T(1);
-        const v2<SS> *res = (const v2<SS> *)a.res;
-#pragma unroll
-        for (int k = 0; k < 12; k++) A[k] = scal(sc, ld<T, SS>(res, ((long)d * 12 + k) * VH + hi));
+        ld_res<VH, SS>(a.res, rbase, SCALED ? T(global_ptr(a.res_scale)[d]) : T(1), A);
     } else {
 #pragma unroll
         for (int k = 0; k < 12; k++) A[k] = czero<T>();
     }
+    cx<T> hf[4][6];
+    T wf[4] = {0, 0, 0, 0};
+    int sf[4] = {0, 0, 0, 0};
     if (f.faces_in && live) {
-        cx<T> hf[4][6];
-        T wf[4] = {0, 0, 0, 0};
-        int sf[4];
-        face_fetch<Sh, 0, T, SS, SCALED>(a, D, l, hf[0], wf[0], sf[0]);
-        face_fetch<Sh, 1, T, SS, SCALED>(a, D, l, hf[1], wf[1], sf[1]);
-        face_fetch<Sh, 2, T, SS, SCALED>(a, D, l, hf[2], wf[2], sf[2]);
-        face_fetch<Sh, 3, T, SS, SCALED>(a, D, l, hf[3], wf[3], sf[3]);
-        face_apply<Sh, 0, T, G, NLC, LNLC, LINK_LDS>(a, d, loc, slink, hf[0], wf[0], sf[0], A);
-        face_apply<Sh, 1, T, G, NLC, LNLC, LINK_LDS>(a, d, loc, slink, hf[1], wf[1], sf[1], A);
-        face_apply<Sh, 2, T, G, NLC, LNLC, LINK_LDS>(a, d, loc, slink, hf[2], wf[2], sf[2], A);
-        face_apply<Sh, 3, T, G, NLC, LNLC, LINK_LDS>(a, d, loc, slink, hf[3], wf[3], sf[3], A);
+        face_fetch<Sh, 0, SS, SCALED>(a, D, l, hf[0], wf[0], sf[0]);
+        face_fetch<Sh, 1, SS, SCALED>(a, D, l, hf[1], wf[1], sf[1]);
+        face_fetch<Sh, 2, SS, SCALED>(a, D, l, hf[2], wf[2], sf[2]);
+        face_fetch<Sh, 3, SS, SCALED>(a, D, l, hf[3], wf[3], sf[3]);
+    }
+    const long cbase = (long)d * 36 * VD + loc;
+#pragma unroll
+    for (int q = 0; q < 36; q++) cl[q] = live ? cs[cbase + (long)q * VD] : v2<G>{};
+    RegLink<G> U[4];
+#pragma unroll
+    for (int mu = 0; mu < 4; mu++) U[mu].put(lt[mu]);
+    // this site's clover block (C_e on even sites, C_o^-1 on odd sites) times in
+    auto clover = [&](const cx<T> in[12], cx<T> out[12]) {
+        if constexpr (sizeof(v2<G>) == 4) clover_wide([&](int q) { return widen<G>(cl[q]); }, in, out);
+        else clover_wide([&](int q) { return cx<T>{(T)cl[q].x, (T)cl[q].y}; }, in, out);
+    };
+    if (f.faces_in && live) {
+        face_apply<Sh, 0>(U[0], hf[0], wf[0], sf[0], A);
+        face_apply<Sh, 1>(U[1], hf[1], wf[1], sf[1], A);
+        face_apply<Sh, 2>(U[2], hf[2], wf[2], sf[2], A);
+        face_apply<Sh, 3>(U[3], hf[3], wf[3], sf[3], A);
     }
 
     // ---- even-odd preparation: r = rho_e - D_eo C_o^-1 rho_o, x = 0
     if (par == 1) {
         clover(A, P);
-#pragma unroll
-        for (int k = 0; k < 12; k++) sho[k][hi] = P[k];
+        st_c2<VH>(vo, P);
     }
-    __syncthreads();   // also publishes slink
+    __syncthreads();
     // the even-site MR residual r lives in its own slot of she for the whole
-    // solve (fewer live registers); x stays in the registers of A.  she is
-    // free until r is written, so it carries the odd threads' partial sums.
-    pair_hops<Sh, T, G, HNLC, true>(sho, she, 0, par, hi, l, loc, lp, locp, lbase, links, P);
+    // solve (fewer live registers); x stays in the registers of A
+    cx<T> t[12];
+    lane_hops<Sh>(vo, P, vx, 0, par, l, U, t);
     if (par == 0) {
 #pragma unroll
         for (int k = 0; k < 12; k++) {
-            she[k][hi] = A[k] + scal(T(0.5), P[k]);
+            P[k] = A[k] + scal(T(0.5), t[k]);
             A[k] = czero<T>();
         }
+        st_c2<VH>(ve, P);
+    }
+    c2_t *const va = sa_all + (A_LDS ? sub * 6 * VD + loc : 0);
+    if (A_LDS && live) st_c2<VD>(va, A);
+    // C has arrived: without this, a path around the MR loop on which it has
+    // not makes the later waits for its registers wait for younger loads
+#pragma unroll
+    for (int q = 0; q < 36; q++) {
+        if constexpr (sizeof(v2<G>) == 4) asm volatile("" : "+v"(cl[q]));
+        else asm volatile("" : "+v"(cl[q].x), "+v"(cl[q].y));
     }
 
     // ---- minimal residual on the Schur complement
 #pragma unroll 1
     for (int it = 0; it < a.n_mr; it++) {
-        if constexpr (CL_REG && sizeof(v2<G>) == 4) {
+        if constexpr (sizeof(v2<G>) == 4) {
             // keep the clover block in its 16-bit storage form: stops the
             // compiler from hoisting its widening out of the loop, which would
             // double the registers it occupies
@@ -877,104 +1067,103 @@ __device__ __forceinline__ void lds_block_solve(const SapArgs &a, const int d, c
             for (int q = 0; q < 36; q++) asm volatile("" : "+v"(cl[q]));
         }
         __syncthreads();
-        // sho is dead here (its last readers passed the reduction's barriers),
-        // so it carries the even threads' partial sums
-        cx<T> t[12];
-        pair_hops<Sh, T, G, HNLC, true>(she, sho, 1, par, hi, l, loc, lp, locp, lbase, links, t);
+        if (par == 0) ld_c2<VH>(ve, P);
+        lane_hops<Sh>(ve, P, vx, 1, par, l, U, t);       // -2 D_oe r
         if (par == 1) {
-#pragma unroll
-            for (int k = 0; k < 12; k++) t[k] = scal(T(-0.5), t[k]);   // D_oe r
-            clover(t, P);                                // C_o^-1 D_oe r
-#pragma unroll
-            for (int k = 0; k < 12; k++) sho[k][hi] = P[k];
+            clover(t, P);                                // -2 C_o^-1 D_oe r
+            st_c2<VH>(vo, P);
         } else if (par == 0) {
             // meanwhile the even sites form C_e r, which needs only r
-            cx<T> rr[12];
-#pragma unroll
-            for (int k = 0; k < 12; k++) rr[k] = she[k][hi];
-            clover(rr, P);
+            ld_c2<VH>(ve, t);
+            clover(t, P);
         }
         __syncthreads();
         T dots[3] = {0, 0, 0};
-        pair_hops<Sh, T, G, HNLC, false>(sho, sho, 0, par, hi, l, loc, lp, locp, lbase, links, t);
+        lane_hops<Sh>(vo, P, vx, 0, par, l, U, t);
+        cx<T> rr[12];
         if (par == 0) {
+            ld_c2<VH>(ve, rr);
 #pragma unroll
             for (int k = 0; k < 12; k++) {
-                const cx<T> rk = she[k][hi];
-                P[k] = P[k] + scal(T(0.5), t[k]);
-                dots[0] = fmad(P[k].i, rk.i, fmad(P[k].r, rk.r, dots[0]));
-                dots[1] = fmad(-P[k].i, rk.r, fmad(P[k].r, rk.i, dots[1]));
+                P[k] = P[k] + scal(T(-0.25), t[k]);      // p = C_e r - D_eo C_o^-1 D_oe r
+                dots[0] = fmad(P[k].i, rr[k].i, fmad(P[k].r, rr[k].r, dots[0]));
+                dots[1] = fmad(-P[k].i, rr[k].r, fmad(P[k].r, rr[k].i, dots[1]));
                 dots[2] = fmad(P[k].i, P[k].i, fmad(P[k].r, P[k].r, dots[2]));
             }
         }
         slot_sum<RV, NDW, T, 3>(dots, red);
         if (par == 0) {
             cx<T> alpha = dots[2] > T(0) ? cx<T>{dots[0] / dots[2], dots[1] / dots[2]} : czero<T>();
+            if (A_LDS) ld_c2<VD>(va, A);
 #pragma unroll
             for (int k = 0; k < 12; k++) {
-                cx<T> rk = she[k][hi];
-                A[k] = cmac(A[k], alpha, rk);
-                she[k][hi] = cmac(rk, neg(alpha), P[k]);
+                A[k] = cmac(A[k], alpha, rr[k]);
+                P[k] = cmac(rr[k], neg(alpha), P[k]);
             }
+            if (A_LDS) st_c2<VD>(va, A);
+            st_c2<VH>(ve, P);
         }
     }
 
     // ---- odd sites: delta_o = C_o^-1 (rho_o - D_oe x); x goes through sho
-    // (free since the last reduction), she keeps r for the epilogue
-    if (par == 0)
+    // (free since the last reduction), she keeps r for the epilogue.  The
+    // accumulator is fetched ahead of it.
+    c2_t ps[6];
 #pragma unroll
-        for (int k = 0; k < 12; k++) sho[k][hi] = A[k];
+    for (int j = 0; j < 6; j++) ps[j] = c2_t{0.f, 0.f, 0.f, 0.f};
+    if (A_LDS && live) ld_c2<VD>(va, A);
+    if (par == 0) st_c2<VH>(vo, A);
+    if (live && !f.first)
+#pragma unroll
+        for (int j = 0; j < 6; j++) ps[j] = psi[j * VD];
     __syncthreads();
-    {
-        cx<T> t[12];
-        pair_hops<Sh, T, G, HNLC, false>(sho, sho, 1, par, hi, l, loc, lp, locp, lbase, links, t);
-        if (par == 1) {
+    lane_hops<Sh>(vo, A, vx, 1, par, l, U, t);
+    if (par == 1) {
 #pragma unroll
-            for (int k = 0; k < 12; k++) t[k] = A[k] + scal(T(0.5), t[k]);
-            clover(t, A);
-        }
+        for (int k = 0; k < 12; k++) t[k] = A[k] + scal(T(0.5), t[k]);
+        clover(t, A);
     }
 
     // ---- epilogue
     if (live) {
-        const v2<PS> *psi_in = (const v2<PS> *)a.psi;
-        v2<PS> *psi_out = (v2<PS> *)a.psi;
 #pragma unroll
-        for (int k = 0; k < 12; k++) {
-            cx<T> ps = f.first ? A[k] : ld<T, PS>(psi_in, sbase + (long)k * VD) + A[k];
-            if (f.last && a.io32) st<T, float>((float2 *)a.out, sbase + (long)k * VD, ps);
-            else if (f.last) st<T, double>(a.out, sbase + (long)k * VD, ps);
-            else st<T, PS>(psi_out, sbase + (long)k * VD, ps);
+        for (int j = 0; j < 6; j++) ps[j] += c2_t{A[2 * j].r, A[2 * j].i, A[2 * j + 1].r, A[2 * j + 1].i};
+        if (f.last) {
+#pragma unroll
+            for (int k = 0; k < 12; k++) {
+                const cx<T> c = {ps[k / 2][2 * (k & 1)], ps[k / 2][2 * (k & 1) + 1]};
+                if (a.io32) st<T, float>(global_ptr((float2 *)a.out), sbase + (long)k * VD, c);
+                else st<T, double>(global_ptr(a.out), sbase + (long)k * VD, c);
+            }
+        } else {
+#pragma unroll
+            for (int j = 0; j < 6; j++) psi[j * VD] = ps[j];
         }
     }
     if (f.res_out) {
         cx<T> rr[12];
 #pragma unroll
-        for (int k = 0; k < 12; k++) rr[k] = par == 0 ? she[k][hi] : czero<T>();
+        for (int k = 0; k < 12; k++) rr[k] = czero<T>();
+        if (par == 0) ld_c2<VH>(ve, rr);
         T sc = T(1);
         if constexpr (SCALED) {
             sc = pow2_ceil(slot_max<RV, NDW, T>(maxabs12(rr), red));
-            if (loc == 0) a.res_scale[d] = (float)sc;
+            if (loc == 0) global_ptr(a.res_scale)[d] = (float)sc;
         }
-        if (par == 0) {
-            v2<SS> *res = (v2<SS> *)a.res;
-            T inv = T(1) / sc;
-#pragma unroll
-            for (int k = 0; k < 12; k++) st<T, SS>(res, ((long)d * 12 + k) * VH + hi, scal(inv, rr[k]));
-        }
+        if (par == 0) st_res<VH, SS>(a.res, rbase, T(1) / sc, rr);
     }
     if (f.faces_out) {
         T sc = T(1);
         if constexpr (SCALED) {
             sc = T(8) * pow2_ceil(slot_max<RV, NDW, T>(maxabs12(A), red));
-            if (loc == 0) a.face_scale[d] = (float)sc;
+            if (loc == 0) global_ptr(a.face_scale)[d] = (float)sc;
         }
         T inv = T(1) / sc;
         if (live) {
-            write_face<Sh, 0, T, SS, G, NLC, LNLC, LINK_LDS>(a, d, l, loc, A, inv, slink);
-            write_face<Sh, 1, T, SS, G, NLC, LNLC, LINK_LDS>(a, d, l, loc, A, inv, slink);
-            write_face<Sh, 2, T, SS, G, NLC, LNLC, LINK_LDS>(a, d, l, loc, A, inv, slink);
-            write_face<Sh, 3, T, SS, G, NLC, LNLC, LINK_LDS>(a, d, l, loc, A, inv, slink);
+            face_write<Sh, 0, SS>(a, d, l, A, inv, U[0]);
+            face_write<Sh, 1, SS>(a, d, l, A, inv, U[1]);
+            face_write<Sh, 2, SS>(a, d, l, A, inv, U[2]);
+            face_write<Sh, 3, SS>(a, d, l, A, inv, U[3]);
         }
     }
 }
@@ -1177,9 +1366,8 @@ __device__ __forceinline__ void bind_faces(SapArgs &a, const Visit &v)
 
 // With NDW > 1, items come in runs of NDW domains of one system (the plan
 // never splits or pads a run), and workgroup i takes run i.
-template <class Sh, int NDW, typename T, typename SS, typename PS, typename G, int NLC, int LNLC, bool SCALED,
-          bool LINK_LDS, bool CL_REG>
-__global__ __launch_bounds__(NDW > 1 ? Sh::VD * NDW : Sh::NT) void k_sap_lds(const SapArgs *args, const int2 *items,
+template <class Sh, int NDW, typename SS, typename G, bool SCALED>
+__global__ __launch_bounds__(NDW > 1 ? Sh::VD * NDW : Sh::NT, 2) void k_sap_lds(const SapArgs *args, const int2 *items,
                                                                              Visit v)
 {
     const int2 it = items[(long)blockIdx.x * NDW];
@@ -1189,7 +1377,7 @@ __global__ __launch_bounds__(NDW > 1 ? Sh::VD * NDW : Sh::NT) void k_sap_lds(con
     bind_faces(a, v);
     int d = it.y;
     if constexpr (NDW > 1) d = items[(long)blockIdx.x * NDW + ((int)threadIdx.x & 63) / Sh::VH].y;
-    lds_block_solve<Sh, NDW, T, SS, PS, G, NLC, LNLC, SCALED, LINK_LDS, CL_REG>(a, d, v);
+    lds_block_solve<Sh, NDW, SS, G, SCALED>(a, d, v);
 }
 
 template <class Sh>
@@ -1265,60 +1453,7 @@ template <int PROD> constexpr int tile_rt() { return PROD == PROD_VALU ? RT_VALU
 // would fall in one bank.
 template <class Sh, int PROD> constexpr int tile_lstr() { return PROD == PROD_VALU ? Sh::VD : Sh::VD + 16; }
 
-typedef float f32x4_t __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x4_t __attribute__((ext_vector_type(4)));
-
-// A spinor of one site and right-hand side in LDS and in the tile's own global
-// arrays: six 16-byte entries of two complex components, the entries of one
-// component pair contiguous over (site, right-hand side).  16 bytes a lane is
-// what LDS moves at its full rate (measured on gfx950: 131 bytes a cycle and CU
-// against 67 for 8-byte reads).
-typedef f32x4_t c2_t;
-
-template <int STRIDE> __device__ __forceinline__ void ld_c2(const c2_t *p, cx<float> s[12])
-{
-#pragma unroll
-    for (int j = 0; j < 6; j++) {
-        const c2_t q = p[j * STRIDE];
-        s[2 * j] = {q[0], q[1]};
-        s[2 * j + 1] = {q[2], q[3]};
-    }
-}
-template <int STRIDE> __device__ __forceinline__ void st_c2(c2_t *p, const cx<float> s[12])
-{
-#pragma unroll
-    for (int j = 0; j < 6; j++) p[j * STRIDE] = c2_t{s[2 * j].r, s[2 * j].i, s[2 * j + 1].r, s[2 * j + 1].i};
-}
-
-// A stored pair of 16-bit values as FP32, converted here: hidden from the
-// compiler, so that it does not fold the conversion into mixed-precision
-// multiply-adds, which issue at half the rate of FP32 ones (gfx950, two waves
-// per SIMD: 4.4 against 2.6 cycles each).  The upper half is shifted down first:
-// the conversion that selects it by itself (SDWA) is the slow one.  An SU(3)
-// times half-spinor product with the link's nine pairs read from LDS takes 347
-// cycles this way, 424 with SDWA conversions, 447 with mixed-precision
-// multiply-adds and 299 with FP32 links.
-template <typename G> __device__ __forceinline__ cx<float> widen(v2<G> v)
-{
-    cx<float> c;
-    if constexpr (std::is_same<G, half_t>::value) {
-        unsigned u = __builtin_bit_cast(unsigned, v), h = u >> 16;
-        asm("" : "+v"(h));
-        c = {static_cast<float>(__builtin_bit_cast(half_t, (unsigned short)u)),
-             static_cast<float>(__builtin_bit_cast(half_t, (unsigned short)h))};
-    } else {
-        c = {static_cast<float>(v.x), static_cast<float>(v.y)};
-    }
-    asm("" : "+v"(c.r), "+v"(c.i));
-    return c;
-}
-
-// out = (packed clover block of 36 pairs, load(q) its pair q) in
-template <typename Load> __device__ __forceinline__ void clover_wide(Load load, const cx<float> in[12], cx<float> out[12])
-{
-    clover_block_with<float>(load, in, out);
-    clover_block_with<float>([&](int q) { return load(18 + q); }, in + 6, out + 6);
-}
 
 // Sum over the lanes of a wave with equal lane % RT, returned to all of them.
 template <int RT> __device__ __forceinline__ float rhs_wave_sum(float v)
@@ -1441,43 +1576,24 @@ __device__ __forceinline__ void quad_product(const v2<G> *slink, int mu, int llo
     }
 }
 
-// acc += the in-domain hop into a site along MU; SIGN < 0: from x + mu with
-// (1 - gamma_mu) U_mu(x), SIGN > 0: from x - mu with (1 + gamma_mu) U_mu(x -
-// mu)^dagger.  v: this right-hand side's spinor of the other parity's site
-// with this site's half index hi, in LDS; ox: 1 where the site's x is odd (its
-// x neighbours have half indices hi + ox and hi + ox - 1); loc: the site, op:
-// the first site of the other parity.  Neighbour offsets are constants (one
-// address register for x, one for the other directions), so LDS addresses
-// are immediates.
+// lds_hop with the product form PROD
 template <class Sh, int MU, int SIGN, int PROD, typename G>
 __device__ __forceinline__ void tile_hop(const c2_t *v, const int l[4], int loc, int op, int hi, int ox, int r,
                                          const v2<G> *slink, cx<float> acc[12])
 {
-    constexpr int VH = Sh::VH, RT = tile_rt<PROD>(), LS = tile_lstr<Sh, PROD>();
-    constexpr int STEP = MU == 1 ? Sh::B[0] / 2 : MU == 2 ? Sh::B[0] * Sh::B[1] / 2 : Sh::B[0] * Sh::B[1] * Sh::B[2] / 2;
-    const bool has = SIGN < 0 ? l[MU] + 1 < Sh::B[MU] : l[MU] > 0;
-    // half index of the neighbour relative to hi
-    const int dn = MU == 0 ? (SIGN < 0 ? ox : ox - 1) : SIGN < 0 ? STEP : -STEP;
-    cx<float> s[12], h[6], uh[6];
+    constexpr int RT = tile_rt<PROD>(), LS = tile_lstr<Sh, PROD>();
     if constexpr (PROD == PROD_VALU) {
-        if (!has) return;
-        ld_c2<VH * RT>(v + dn * RT, s);
-        proj<MU, SIGN>(s, h);
-        const v2<G> *up = slink + MU * 9 * LS + (SIGN < 0 ? loc : op + hi + dn);
-        su3<float> U;
-#pragma unroll
-        for (int e = 0; e < 9; e++) U.m[e] = widen<G>(up[e * LS]);
-        if constexpr (SIGN < 0) su3_mul(U, h, uh);
-        else su3_dag_mul(U, h, uh);
-        recon_acc<MU, SIGN>(acc, uh, 1.0f);
+        lds_hop<Sh, MU, SIGN, RT>(v, l, loc, op, hi, ox, LdsLinks<G, LS>{slink}, acc);
     } else {
         // every lane takes part in the matrix instructions; a site without this
         // neighbour multiplies a finite stand-in (its own index's entry) and
         // adds the product with weight 0
-        const int dv = has ? dn : 0;
-        ld_c2<VH * RT>(v + dv * RT, s);
+        const bool has = hop_exists<Sh, MU, SIGN>(l);
+        const int dn = has ? hop_step<Sh, MU, SIGN>(ox) : 0;
+        cx<float> s[12], h[6], uh[6];
+        ld_c2<Sh::VH * RT>(v + dn * RT, s);
         proj<MU, SIGN>(s, h);
-        quad_product<Sh, SIGN, PROD, G>(slink, MU, SIGN < 0 ? loc : op + hi + dv, r, h, uh);
+        quad_product<Sh, SIGN, PROD, G>(slink, MU, SIGN < 0 ? loc : op + hi + dn, r, h, uh);
         recon_acc<MU, SIGN>(acc, uh, has ? 1.0f : 0.0f);
     }
 }
@@ -1584,11 +1700,7 @@ __device__ __forceinline__ void tile_face_stage(const v2<SS> (&raw)[RT][6], cons
     const int h = tile_face_site<Sh>(1 - q, j, f), lex = 2 * h + ((1 - q + (h >> 1) + (h >> 3) + (h >> 5)) & 1);
     const int sh = f & ~1, i = (lex & ((1 << sh) - 1)) | ((lex >> (sh + 2)) << sh);
     su3<float> U;
-    if (f & 1) {
-        const v2<G> *up = slink + (f >> 1) * 9 * LS + (1 - q) * Sh::VH + h;
-#pragma unroll
-        for (int e = 0; e < 9; e++) U.m[e] = widen<G>(up[e * LS]);
-    }
+    if (f & 1) U = LdsLinks<G, LS>{slink}(f >> 1, (1 - q) * Sh::VH + h);
 #pragma unroll
     for (int r = 0; r < RT; r++) {
         cx<float> hs[6];
@@ -1650,12 +1762,8 @@ __device__ __forceinline__ void tile_face_out(v2<SS> *face, int d, int f, int p,
         default: proj<3, +1>(s, h); break;
     }
     if (f & 1) {
-        su3<float> U;
-        const v2<G> *up = slink + (f >> 1) * 9 * LS + p * VH + h0;
-#pragma unroll
-        for (int e = 0; e < 9; e++) U.m[e] = widen<G>(up[e * LS]);
         cx<float> uh[6];
-        su3_dag_mul(U, h, uh);
+        su3_dag_mul(LdsLinks<G, LS>{slink}(f >> 1, p * VH + h0), h, uh);
 #pragma unroll
         for (int k = 0; k < 6; k++) h[k] = uh[k];
     }
@@ -1679,7 +1787,6 @@ __global__ __launch_bounds__(Sh::VH * tile_rt<PROD>(), 2) void k_sap_tile(const 
     constexpr int FPW = 8 / NW;               // faces per wave
     static_assert(NT % 64 == 0 && NT <= 1024 && (NW == 4 || NW == 8), "one or two faces a wave");
     constexpr int LSTR = tile_lstr<Sh, PROD>();
-    typedef SS ss8_t __attribute__((ext_vector_type(8)));
     __shared__ v2<G> slink[4 * 9 * LSTR];     // [mu][9][LSTR]
     __shared__ v2<G> sclo[36][VH];            // C_o^-1 of the odd sites
     // [6][VH][RT]: what the next hops read (even sites r, odd sites C_o^-1 D_oe r)
@@ -1715,7 +1822,7 @@ __global__ __launch_bounds__(Sh::VH * tile_rt<PROD>(), 2) void k_sap_tile(const 
     const int n_mr = a0.n_mr;
     const long se = (long)d * 12 * VD + loc_e, so = (long)d * 12 * VD + loc_o;
     c2_t *const pe = global_ptr((c2_t *)a.psi) + (long)d * 6 * VD + loc_e, *const po = pe + VH;
-    ss8_t *const pr = global_ptr((ss8_t *)a.res) + (long)d * 3 * VH + hi;
+    const long rbase = (long)d * 3 * VH + hi;
     const double2 *const eta = global_ptr(a.eta);
     double2 *const out = global_ptr(a.out);
     const bool io32 = a.io32;
@@ -1765,14 +1872,7 @@ __global__ __launch_bounds__(Sh::VH * tile_rt<PROD>(), 2) void k_sap_tile(const 
                 Ao[k] = ld<T, double>(eta, so + (long)k * VD);
             }
         } else {
-            const T sc = SCALED ? T(global_ptr(a.res_scale)[d]) : T(1);
-#pragma unroll
-            for (int j = 0; j < 3; j++) {
-                const ss8_t q8 = pr[j * VH];
-#pragma unroll
-                for (int e = 0; e < 4; e++)
-                    Ae[4 * j + e] = {sc * static_cast<T>(q8[2 * e]), sc * static_cast<T>(q8[2 * e + 1])};
-            }
+            ld_res<VH, SS>(a.res, rbase, SCALED ? T(global_ptr(a.res_scale)[d]) : T(1), Ae);
 #pragma unroll
             for (int k = 0; k < 12; k++) Ao[k] = czero<T>();
         }
@@ -1789,9 +1889,7 @@ __global__ __launch_bounds__(Sh::VH * tile_rt<PROD>(), 2) void k_sap_tile(const 
 #pragma unroll
         for (int j = 0; j < NL; j++) {
             const int q = t + j * NT;
-            const su3<T> U = ld_link<T, G, NLC>(lt[j], 0, 1);
-#pragma unroll
-            for (int e = 0; e < 9; e++) st<T, G>(slink, (q / VD * 9 + e) * LSTR + q % VD, U.m[e]);
+            LdsLinks<G, LSTR>::put(slink, q / VD, q % VD, lt[j]);
         }
     }
     __syncthreads();   // links staged
@@ -1946,17 +2044,7 @@ __global__ __launch_bounds__(Sh::VH * tile_rt<PROD>(), 2) void k_sap_tile(const 
     }
     if (v.res_out && live) {
         if (SCALED && hi == 0) global_ptr(a.res_scale)[d] = (float)rsc;
-        const T inv = T(1) / rsc;
-#pragma unroll
-        for (int j = 0; j < 3; j++) {
-            ss8_t q8;
-#pragma unroll
-            for (int e = 0; e < 4; e++) {
-                q8[2 * e] = static_cast<SS>(inv * rr[4 * j + e].r);
-                q8[2 * e + 1] = static_cast<SS>(inv * rr[4 * j + e].i);
-            }
-            pr[j * VH] = q8;
-        }
+        st_res<VH, SS>(a.res, rbase, T(1) / rsc, rr);
     }
     if (v.faces_out) {
         const bool alt = a.face_alt && v.flip;
@@ -2056,13 +2144,13 @@ static hipError_t launch_batch(const SapArgs *args, const int2 *items, int nitem
         constexpr int NT = NDW > 1 ? Sh::VD * NDW : Sh::NT;
         if (nitems % NDW) return hipErrorInvalidValue;
         if (prec == P32)
-            return launch_bounded(k_sap_lds<Sh, NDW, float, float, float, float, 6, 6, false, true, true>, nitems / NDW,
+            return launch_bounded(k_sap_lds<Sh, NDW, float, float, false>, nitems / NDW,
                                   NT, s, args, items, v);
         else if (prec == P16)
-            return launch_bounded(k_sap_lds<Sh, NDW, float, half_t, float, half_t, 6, 9, true, true, true>,
+            return launch_bounded(k_sap_lds<Sh, NDW, half_t, half_t, true>,
                                   nitems / NDW, NT, s, args, items, v);
         else
-            return launch_bounded(k_sap_lds<Sh, NDW, float, bf16_t, float, bf16_t, 6, 9, false, true, true>,
+            return launch_bounded(k_sap_lds<Sh, NDW, bf16_t, bf16_t, false>,
                                   nitems / NDW, NT, s, args, items, v);
     }
 }
