@@ -349,7 +349,8 @@ int build_plan_once(const std::vector<Sys> &sys, const std::string &key, Plan *&
     std::vector<std::array<int, 3>> gk;
     std::vector<std::vector<int>> members;
     for (size_t i = 0; i < sys.size(); i++) {
-        const std::array<int, 3> k{sap_shape_id(sys[i].c->g.b), sys[i].c->sap_prec, sys[i].c->product};
+        const std::array<int, 3> k{sap_shape_id(sys[i].c->g.b), sys[i].c->sap_prec,
+                                   sap_kernel_form(sys[i].c->g, sys[i].c->sap_prec, sys[i].c->product)};
         size_t gi = std::find(gk.begin(), gk.end(), k) - gk.begin();
         if (gi == gk.size()) {
             gk.push_back(k);
@@ -2042,8 +2043,9 @@ int ddqcd_sap_noalloc(ddqcd_t c, double *out, const double *in, void *stream)
     a.active = 1;
     HIPCHK(c, import_spinor(g, in, eta, P64, s));
     HIPCHK(c, sap_put_args(a, d_args, s));
-    HIPCHK(c, sap_schedule_items(g, sap_rhs_per_workgroup(c->product) > 1 ? 1 << 24 : 0, items, s));
     const int shape = sap_shape_id(g.b), prec = c->sap_prec, half_nd = g.nd / 2;
+    const int form = sap_kernel_form(g, prec, c->product);
+    HIPCHK(c, sap_schedule_items(g, sap_rhs_per_workgroup(form) > 1 ? 1 << 24 : 0, items, s));
     for (int cyc = 0; cyc < c->n_cycles; cyc++) {
         Visit v{};
         v.first = cyc == 0;
@@ -2053,13 +2055,13 @@ int ddqcd_sap_noalloc(ddqcd_t c, double *out, const double *in, void *stream)
             v.faces_in = cyc > 0;
             v.faces_out = !v.last;
             v.flip = cyc & 1;
-            HIPCHK(c, sap_sweep_batch(d_args, items, g.nd, shape, prec, c->product, v, s));
+            HIPCHK(c, sap_sweep_batch(d_args, items, g.nd, shape, prec, form, v, s));
             continue;
         }
         for (int col = 0; col < 2; col++) {
             v.faces_in = !(cyc == 0 && col == 0);
             v.faces_out = !(v.last && col == 1);
-            HIPCHK(c, sap_sweep_batch(d_args, items + col * half_nd, half_nd, shape, prec, c->product, v, s));
+            HIPCHK(c, sap_sweep_batch(d_args, items + col * half_nd, half_nd, shape, prec, form, v, s));
         }
     }
     HIPCHK(c, export_spinor(g, res_out, P64, out, s));

@@ -83,7 +83,12 @@ int sap_shape_id(const int b[4]);
 // workgroup (4^4 domains, FP16 or BF16 storage) with the product on the VALU
 // (two right-hand sides), on FP32 MFMA, or on BF16-input MFMA with FP32
 // accumulation (four).
-enum { PRODUCT_LANE = 0, PRODUCT_TILE_VALU = 1, PRODUCT_TILE_MFMA_F32 = 2, PRODUCT_TILE_MFMA_BF16 = 3 };
+// PRODUCT_LANE_SPLIT, two threads per site, is not selected by the caller:
+// sap_kernel_form names it for PRODUCT_LANE where it is the better kernel.
+enum { PRODUCT_LANE = 0, PRODUCT_TILE_VALU = 1, PRODUCT_TILE_MFMA_F32 = 2, PRODUCT_TILE_MFMA_BF16 = 3, PRODUCT_LANE_SPLIT = 4 };
+// The kernel form that solves this lattice's blocks, given the caller's product;
+// the functions below take it as their product.
+int sap_kernel_form(const Geo &g, int prec, int product);
 bool sap_product_supported(const int b[4], int prec, int product);
 // Right-hand sides one workgroup takes (1, or 2 or 4 for the tile forms): the items
 // of a tile launch are (first system | systems in the tile << 24, domain).

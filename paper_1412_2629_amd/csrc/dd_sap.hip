@@ -246,52 +246,25 @@ __device__ __forceinline__ void dom_hop(const cx<T> (*v)[Sh::VH], const int l[4]
     }
 }
 
-template <class Sh, typename T, typename G, int NLC>
-__device__ __forceinline__ void dom_hops(const cx<T> (*v)[Sh::VH], const int l[4], long lbase, int loc,
-                                         const v2<G> *links, cx<T> acc[12])
-{
-#pragma unroll
-    for (int k = 0; k < 12; k++) acc[k] = czero<T>();
-    dom_hop<Sh, 0, T, G, NLC>(v, l, lbase, loc, links, acc);
-    dom_hop<Sh, 1, T, G, NLC>(v, l, lbase, loc, links, acc);
-    dom_hop<Sh, 2, T, G, NLC>(v, l, lbase, loc, links, acc);
-    dom_hop<Sh, 3, T, G, NLC>(v, l, lbase, loc, links, acc);
-}
-
-// A uniform pointer the compiler must treat as unknown from here on: the
+// A uniform global pointer the compiler must treat as unknown from here on: the
 // addresses derived from it are formed at their use instead of being
 // precomputed and held in registers across loops.
 template <typename P> __device__ __forceinline__ P opaque(P p)
 {
     asm volatile("" : "+s"(p));
-    return p;
+    return global_ptr(p);
 }
 
-// acc (= 0 first if ZERO) += scale * (in-domain hops), directions visited in
-// a loop that is not unrolled: one direction's temporaries live at a time
-// (fewer registers)
-template <class Sh, typename T, typename G, int NLC, bool ZERO>
-__device__ __forceinline__ void dom_hops_rolled(const cx<T> (*v)[Sh::VH], const int l[4], long lbase, int loc,
-                                                const v2<G> *links, cx<T> acc[12], T scale)
-{
-    if constexpr (ZERO)
-#pragma unroll
-        for (int k = 0; k < 12; k++) acc[k] = czero<T>();
-#pragma unroll 1
-    for (int mu = 0; mu < 4; mu++) {
-        const v2<G> *lk = opaque(links);
-        switch (mu) {
-            case 0: dom_hop<Sh, 0, T, G, NLC>(v, l, lbase, loc, lk, acc, scale); break;
-            case 1: dom_hop<Sh, 1, T, G, NLC>(v, l, lbase, loc, lk, acc, scale); break;
-            case 2: dom_hop<Sh, 2, T, G, NLC>(v, l, lbase, loc, lk, acc, scale); break;
-            default: dom_hop<Sh, 3, T, G, NLC>(v, l, lbase, loc, lk, acc, scale); break;
-        }
-    }
-}
-
-// pair_hops with the directions visited in a loop that is not unrolled and a
-// scale: the po thread's acc (zeroed first if ZERO) gains scale x its share
-// and then the helper's; the helper's acc is zeroed and takes its share.
+// The hop sum of every site of parity po, shared by the site's thread pair:
+// the thread of parity po takes directions 0 and 1 of its own site, the thread
+// of the other parity with the same half index takes directions 2 and 3 of
+// that site (partner coordinates lp, index locp) and hands its partial sum over
+// through X ([12][VH] in LDS).  XFREE: nothing reads X during the hops, so the
+// partial is written at once; otherwise after a barrier.  Every thread of the
+// workgroup calls this (it holds barriers).  The directions are visited in a
+// loop that is not unrolled (one direction's temporaries live at a time); the po
+// thread's acc (zeroed first if ZERO) gains scale x its share and then the
+// helper's; the helper's acc is zeroed and takes its share.
 template <class Sh, typename T, typename G, int NLC, bool XFREE, bool ZERO>
 __device__ __forceinline__ void pair_hops_rolled(const cx<T> (*v)[Sh::VH], cx<T> (*X)[Sh::VH], int po, int par,
                                                  int hi, const int l[4], int loc, const int lp[4], int locp,
@@ -343,7 +316,7 @@ __device__ __forceinline__ void gather_face(const SapArgs &a, const int D[4], in
                                             cx<T> rho[12])
 {
     constexpr int VD = Sh::VD;
-    const v2<SS> *face = (const v2<SS> *)a.face_in;
+    const v2<SS> *face = global_ptr((const v2<SS> *)a.face_in);
     int Dn[4] = {D[0], D[1], D[2], D[3]};
     cx<T> h[6];
     if (l[MU] == 0) {
@@ -351,7 +324,7 @@ __device__ __forceinline__ void gather_face(const SapArgs &a, const int D[4], in
         bool wrap = D[MU] == 0;
         Dn[MU] = wrap ? a.g.n[MU] - 1 : D[MU] - 1;
         int dn = Dn[0] + a.g.n[0] * (Dn[1] + a.g.n[1] * (Dn[2] + a.g.n[2] * Dn[3]));
-        T sc = SCALED ? T(a.face_in_scale[dn]) : T(1);
+        T sc = SCALED ? T(global_ptr(a.face_in_scale)[dn]) : T(1);
         long fb = face_base<Sh>(dn, 2 * MU + 1);
         int fi = Sh::template face_index<MU>(l);
 #pragma unroll
@@ -362,13 +335,13 @@ __device__ __forceinline__ void gather_face(const SapArgs &a, const int D[4], in
         bool wrap = D[MU] == a.g.n[MU] - 1;
         Dn[MU] = wrap ? 0 : D[MU] + 1;
         int dn = Dn[0] + a.g.n[0] * (Dn[1] + a.g.n[1] * (Dn[2] + a.g.n[2] * Dn[3]));
-        T sc = SCALED ? T(a.face_in_scale[dn]) : T(1);
+        T sc = SCALED ? T(global_ptr(a.face_in_scale)[dn]) : T(1);
         long fb = face_base<Sh>(dn, 2 * MU);
         int fi = Sh::template face_index<MU>(l);
 #pragma unroll
         for (int k = 0; k < 6; k++) h[k] = scal(sc, ld<T, SS>(face, fb + (long)k * Sh::FS[MU] + fi));
         cx<T> uh[6];
-        su3<T> U = ld_link<T, G, NLC>((const v2<G> *)a.links, ((long)d * 4 + MU) * NLC * VD + loc, VD);
+        su3<T> U = ld_link<T, G, NLC>(global_ptr((const v2<G> *)a.links), ((long)d * 4 + MU) * NLC * VD + loc, VD);
         su3_mul(U, h, uh);
         recon_acc<MU, -1>(rho, uh, T(wrap ? 0.5 * a.g.bc[MU] : 0.5));
     }
@@ -397,197 +370,6 @@ __device__ __forceinline__ void write_face(const SapArgs &a, int d, const int l[
 #pragma unroll
         for (int k = 0; k < 6; k++) st<T, SS>(face, fb + (long)k * Sh::FS[MU] + fi, scal(inv_sc, uh[k]));
     }
-}
-
-// ---- the half-sweep kernel --------------------------------------------------
-//
-// One workgroup per domain, one thread per (even site, odd site) pair: thread
-// t owns the even site with half-lattice index t and the odd site with
-// half-lattice index t, so in every phase of the block solve (which works on
-// one parity at a time) all threads are busy.  The MR residual r of the even
-// site stays in registers; the MR solution x, the odd-site right-hand side
-// rho_o and the exchanged half-lattice spinors live in LDS.
-//
-// T: arithmetic; SS: storage of the block residual and the boundary terms;
-// PS: storage of the solution accumulator; G: storage of links and clover;
-// RHO_LDS: keep rho_o in LDS (else in a per-domain global buffer, used when
-// four FP64 half-lattice spinors would not fit in LDS).
-
-template <class Sh, typename T, typename SS, typename G, int NLC, bool SCALED>
-__device__ __forceinline__ void stage_site(const SapArgs &a, const int D[4], int d, const int l[4], int loc,
-                                           cx<T> rho[12])
-{
-    constexpr int VD = Sh::VD, VH = Sh::VH;
-    const long sidx = (long)d * 12 * VD + loc;
-    if (a.first) {
-#pragma unroll
-        for (int k = 0; k < 12; k++) rho[k] = ld<T, double>(a.eta, sidx + (long)k * VD);
-    } else if (loc < VH) {
-        T sc = SCALED ? T(a.res_scale[d]) : T(1);
-        const v2<SS> *res = (const v2<SS> *)a.res;
-#pragma unroll
-        for (int k = 0; k < 12; k++) rho[k] = scal(sc, ld<T, SS>(res, ((long)d * 12 + k) * VH + loc));
-    } else {
-#pragma unroll
-        for (int k = 0; k < 12; k++) rho[k] = czero<T>();
-    }
-    if (a.faces_in) {
-        gather_face<Sh, 0, T, SS, G, NLC, SCALED>(a, D, d, l, loc, rho);
-        gather_face<Sh, 1, T, SS, G, NLC, SCALED>(a, D, d, l, loc, rho);
-        gather_face<Sh, 2, T, SS, G, NLC, SCALED>(a, D, d, l, loc, rho);
-        gather_face<Sh, 3, T, SS, G, NLC, SCALED>(a, D, d, l, loc, rho);
-    }
-}
-
-template <class Sh, typename T, typename SS, typename PS, typename G, int NLC>
-__device__ __forceinline__ void write_site(const SapArgs &a, int d, const int l[4], int loc, const cx<T> delta[12],
-                                           T inv_face_sc)
-{
-    constexpr int VD = Sh::VD;
-    const long sidx = (long)d * 12 * VD + loc;
-    const v2<PS> *psi_in = (const v2<PS> *)a.psi;
-    v2<PS> *psi_out = (v2<PS> *)a.psi;
-#pragma unroll
-    for (int k = 0; k < 12; k++) {
-        cx<T> ps = a.first ? delta[k] : ld<T, PS>(psi_in, sidx + (long)k * VD) + delta[k];
-        if (a.last) st<T, double>(a.out, sidx + (long)k * VD, ps);
-        else st<T, PS>(psi_out, sidx + (long)k * VD, ps);
-    }
-    if (a.faces_out) {
-        write_face<Sh, 0, T, SS, G, NLC>(a, d, l, loc, delta, inv_face_sc);
-        write_face<Sh, 1, T, SS, G, NLC>(a, d, l, loc, delta, inv_face_sc);
-        write_face<Sh, 2, T, SS, G, NLC>(a, d, l, loc, delta, inv_face_sc);
-        write_face<Sh, 3, T, SS, G, NLC>(a, d, l, loc, delta, inv_face_sc);
-    }
-}
-
-template <class Sh, typename T, typename SS, typename PS, typename G, int NLC, bool SCALED, bool RHO_LDS>
-__device__ __forceinline__ void pair_block_solve(const SapArgs &a, const int d)
-{
-    constexpr int VD = Sh::VD, VH = Sh::VH;
-    __shared__ cx<T> she[12][VH];                                  // even-site spinor being hopped
-    __shared__ cx<T> sho[12][VH];                                  // odd-site spinor being hopped
-    __shared__ cx<T> shx[12][VH];                                  // MR solution on the even sites
-    __shared__ cx<T> shr[RHO_LDS ? 12 : 1][RHO_LDS ? VH : 1];      // rho on the odd sites
-    __shared__ T red[VH >= 64 ? 3 * (VH / 64) : 3 * VH];
-
-    const int t = threadIdx.x;
-    const int loc_e = t, loc_o = VH + t;
-    int le[4], lo[4];
-    Sh::coords(loc_e, le);
-    Sh::coords(loc_o, lo);
-    int D[4];
-    {
-        int r = d;
-        D[0] = r % a.g.n[0]; r /= a.g.n[0];
-        D[1] = r % a.g.n[1]; r /= a.g.n[1];
-        D[2] = r % a.g.n[2];
-        D[3] = r / a.g.n[2];
-    }
-    const v2<G> *links = (const v2<G> *)a.links;
-    const v2<G> *cs = (const v2<G> *)a.cs;
-    const long lbase = (long)d * 4 * NLC * VD;
-    const long cbase = (long)d * 36 * VD;
-    v2<T> *rho_g = (v2<T> *)a.rho_tmp;
-
-    cx<T> r[12], P[12];
-
-    // ---- staging (Sec. II-D: the residual restricted to the domain)
-    {
-        cx<T> ro[12];
-        stage_site<Sh, T, SS, G, NLC, SCALED>(a, D, d, lo, loc_o, ro);
-        // odd part of the preparation: C_o^-1 rho_o
-        clover_apply<T, G>(cs, cbase + loc_o, VD, ro, P);
-#pragma unroll
-        for (int k = 0; k < 12; k++) {
-            sho[k][t] = P[k];
-            if constexpr (RHO_LDS) shr[k][t] = ro[k];
-            else st<T, T>(rho_g, ((long)d * 12 + k) * VH + t, ro[k]);
-            shx[k][t] = czero<T>();
-        }
-    }
-    stage_site<Sh, T, SS, G, NLC, SCALED>(a, D, d, le, loc_e, r);
-    __syncthreads();
-    // r = rho_e - D_eo C_o^-1 rho_o  (D_eo = -1/2 hops)
-    dom_hops<Sh, T, G, NLC>(sho, le, lbase, loc_e, links, P);
-#pragma unroll
-    for (int k = 0; k < 12; k++) r[k] = r[k] + scal(T(0.5), P[k]);
-
-    // ---- minimal residual on the Schur complement C_e - D_eo C_o^-1 D_oe
-    for (int it = 0; it < a.n_mr; it++) {
-#pragma unroll
-        for (int k = 0; k < 12; k++) she[k][t] = r[k];
-        __syncthreads();
-        {
-            cx<T> q[12];
-            dom_hops<Sh, T, G, NLC>(she, lo, lbase, loc_o, links, q);
-#pragma unroll
-            for (int k = 0; k < 12; k++) q[k] = scal(T(-0.5), q[k]);   // D_oe r
-            clover_apply<T, G>(cs, cbase + loc_o, VD, q, P);           // C_o^-1 D_oe r
-#pragma unroll
-            for (int k = 0; k < 12; k++) sho[k][t] = P[k];
-        }
-        __syncthreads();
-        T dots[3] = {0, 0, 0};
-        {
-            cx<T> q[12];
-            dom_hops<Sh, T, G, NLC>(sho, le, lbase, loc_e, links, q);
-            clover_apply<T, G>(cs, cbase + loc_e, VD, r, P);           // C_e r
-#pragma unroll
-            for (int k = 0; k < 12; k++) {
-                P[k] = P[k] + scal(T(0.5), q[k]);                      // p = C_e r - D_eo C_o^-1 D_oe r
-                dots[0] = fmad(P[k].i, r[k].i, fmad(P[k].r, r[k].r, dots[0]));
-                dots[1] = fmad(-P[k].i, r[k].r, fmad(P[k].r, r[k].i, dots[1]));
-                dots[2] = fmad(P[k].i, P[k].i, fmad(P[k].r, P[k].r, dots[2]));
-            }
-        }
-        block_sum<VH, T, 3>(dots, red);
-        const cx<T> alpha = dots[2] > T(0) ? cx<T>{dots[0] / dots[2], dots[1] / dots[2]} : czero<T>();
-#pragma unroll
-        for (int k = 0; k < 12; k++) {
-            shx[k][t] = cmac(shx[k][t], alpha, r[k]);
-            r[k] = cmac(r[k], neg(alpha), P[k]);
-        }
-    }
-    __syncthreads();
-
-    // ---- odd sites: delta_o = C_o^-1 (rho_o - D_oe x)
-    {
-        cx<T> q[12];
-        dom_hops<Sh, T, G, NLC>(shx, lo, lbase, loc_o, links, q);
-#pragma unroll
-        for (int k = 0; k < 12; k++) {
-            cx<T> ro;
-            if constexpr (RHO_LDS) ro = shr[k][t];
-            else ro = ld<T, T>(rho_g, ((long)d * 12 + k) * VH + t);
-            q[k] = ro + scal(T(0.5), q[k]);
-        }
-        clover_apply<T, G>(cs, cbase + loc_o, VD, q, P);               // P = delta_o
-    }
-
-    // ---- epilogue: psi += delta, stored residual, boundary terms
-    T face_sc = T(1);
-    if (a.res_out) {
-        T sc = T(1);
-        if constexpr (SCALED) {
-            sc = pow2_ceil(block_max<VH, T>(maxabs12(r), red));
-            if (t == 0) a.res_scale[d] = (float)sc;
-        }
-        v2<SS> *res = (v2<SS> *)a.res;
-        T inv = T(1) / sc;
-#pragma unroll
-        for (int k = 0; k < 12; k++) st<T, SS>(res, ((long)d * 12 + k) * VH + t, scal(inv, r[k]));
-    }
-#pragma unroll
-    for (int k = 0; k < 12; k++) r[k] = shx[k][t];                    // r <- delta_e
-    if (a.faces_out) {
-        if constexpr (SCALED) {
-            face_sc = T(8) * pow2_ceil(block_max<VH, T>(fmax(maxabs12(r), maxabs12(P)), red));
-            if (t == 0) a.face_scale[d] = (float)face_sc;
-        }
-    }
-    write_site<Sh, T, SS, PS, G, NLC>(a, d, lo, loc_o, P, T(1) / face_sc);
-    write_site<Sh, T, SS, PS, G, NLC>(a, d, le, loc_e, r, T(1) / face_sc);
 }
 
 // ---- the LDS-resident half-sweep kernels (FP32 arithmetic) ----------------
@@ -718,6 +500,16 @@ template <> struct RegLink<float> {
     {
         return ld_link_with<float, 6>([&](int e) { return cx<float>{m[e].x, m[e].y}; });
     }
+};
+
+template <> struct RegLink<double> {
+    su3<double> U;
+    __device__ __forceinline__ void put(const double2 rows[9])
+    {
+#pragma unroll
+        for (int e = 0; e < 9; e++) U.m[e] = {rows[e].x, rows[e].y};
+    }
+    __device__ __forceinline__ const su3<double> &operator()() const { return U; }
 };
 
 // A domain's 16-bit links in LDS (tiles of right-hand sides) as three rows
@@ -878,9 +670,8 @@ __device__ __forceinline__ void lane_hops(const c2_t *v, const cx<float> own[12]
 // direction are in flight together: face_fetch loads the site's boundary
 // half-spinor along MU (if it has one) and its weight, face_apply adds its
 // contribution.
-template <class Sh, int MU, typename SS, bool SCALED>
-__device__ __forceinline__ void face_fetch(const SapArgs &a, const int D[4], const int l[4], cx<float> h[6], float &w,
-                                           int &side)
+template <class Sh, int MU, typename T, typename SS, bool SCALED>
+__device__ __forceinline__ void face_fetch(const SapArgs &a, const int D[4], const int l[4], cx<T> h[6], T &w, int &side)
 {
     const bool bwd = l[MU] == 0, fwd = l[MU] == Sh::B[MU] - 1;
     side = bwd ? 1 : fwd ? 2 : 0;
@@ -894,42 +685,42 @@ __device__ __forceinline__ void face_fetch(const SapArgs &a, const int D[4], con
     const long fb = face_base<Sh>(dn, 2 * MU + (bwd ? 1 : 0));
     const int fi = Sh::template face_index<MU>(l);
 #pragma unroll
-    for (int k = 0; k < 6; k++) h[k] = ld<float, SS>(face, fb + (long)k * Sh::FS[MU] + fi);
-    const float sc = SCALED ? global_ptr(a.face_in_scale)[dn] : 1.0f;
-    w = sc * float(wrap ? 0.5 * a.g.bc[MU] : 0.5);
+    for (int k = 0; k < 6; k++) h[k] = ld<T, SS>(face, fb + (long)k * Sh::FS[MU] + fi);
+    const T sc = SCALED ? T(global_ptr(a.face_in_scale)[dn]) : T(1);
+    w = sc * T(wrap ? 0.5 * a.g.bc[MU] : 0.5);
 }
 
-template <class Sh, int MU, typename Link>
-__device__ __forceinline__ void face_apply(const Link &U, const cx<float> h[6], float w, int side, cx<float> rho[12])
+template <class Sh, int MU, typename T, typename Link>
+__device__ __forceinline__ void face_apply(const Link &U, const cx<T> h[6], T w, int side, cx<T> rho[12])
 {
     if (side == 1) {
         recon_acc<MU, +1>(rho, h, w);
     } else if (side == 2) {
-        cx<float> uh[6];
+        cx<T> uh[6];
         su3_mul(U(), h, uh);
         recon_acc<MU, -1>(rho, uh, w);
     }
 }
 
-template <class Sh, int MU, typename SS, typename Link>
-__device__ __forceinline__ void face_write(const SapArgs &a, int d, const int l[4], const cx<float> delta[12], float inv_sc,
+template <class Sh, int MU, typename T, typename SS, typename Link>
+__device__ __forceinline__ void face_write(const SapArgs &a, int d, const int l[4], const cx<T> delta[12], T inv_sc,
                                            const Link &U)
 {
     v2<SS> *face = global_ptr((v2<SS> *)a.face);
-    cx<float> h[6];
+    cx<T> h[6];
     const bool lo = l[MU] == 0;
     if (!(lo || l[MU] == Sh::B[MU] - 1)) return;
     if (lo) {
         proj<MU, -1>(delta, h);
     } else {
-        cx<float> g[6];
+        cx<T> g[6];
         proj<MU, +1>(delta, g);
         su3_dag_mul(U(), g, h);
     }
     const long fb = face_base<Sh>(d, 2 * MU + (lo ? 0 : 1));
     const int fi = Sh::template face_index<MU>(l);
 #pragma unroll
-    for (int k = 0; k < 6; k++) st<float, SS>(face, fb + (long)k * Sh::FS[MU] + fi, scal(inv_sc, h[k]));
+    for (int k = 0; k < 6; k++) st<T, SS>(face, fb + (long)k * Sh::FS[MU] + fi, scal(inv_sc, h[k]));
 }
 
 // SS: storage of the block residual and the boundary terms; G: of links (two
@@ -1005,10 +796,10 @@ __device__ __forceinline__ void lds_block_solve(const SapArgs &a, const int d, c
     T wf[4] = {0, 0, 0, 0};
     int sf[4] = {0, 0, 0, 0};
     if (f.faces_in && live) {
-        face_fetch<Sh, 0, SS, SCALED>(a, D, l, hf[0], wf[0], sf[0]);
-        face_fetch<Sh, 1, SS, SCALED>(a, D, l, hf[1], wf[1], sf[1]);
-        face_fetch<Sh, 2, SS, SCALED>(a, D, l, hf[2], wf[2], sf[2]);
-        face_fetch<Sh, 3, SS, SCALED>(a, D, l, hf[3], wf[3], sf[3]);
+        face_fetch<Sh, 0, T, SS, SCALED>(a, D, l, hf[0], wf[0], sf[0]);
+        face_fetch<Sh, 1, T, SS, SCALED>(a, D, l, hf[1], wf[1], sf[1]);
+        face_fetch<Sh, 2, T, SS, SCALED>(a, D, l, hf[2], wf[2], sf[2]);
+        face_fetch<Sh, 3, T, SS, SCALED>(a, D, l, hf[3], wf[3], sf[3]);
     }
     const long cbase = (long)d * 36 * VD + loc;
 #pragma unroll
@@ -1022,10 +813,10 @@ __device__ __forceinline__ void lds_block_solve(const SapArgs &a, const int d, c
         else clover_wide([&](int q) { return cx<T>{(T)cl[q].x, (T)cl[q].y}; }, in, out);
     };
     if (f.faces_in && live) {
-        face_apply<Sh, 0>(U[0], hf[0], wf[0], sf[0], A);
-        face_apply<Sh, 1>(U[1], hf[1], wf[1], sf[1], A);
-        face_apply<Sh, 2>(U[2], hf[2], wf[2], sf[2], A);
-        face_apply<Sh, 3>(U[3], hf[3], wf[3], sf[3], A);
+        face_apply<Sh, 0, T>(U[0], hf[0], wf[0], sf[0], A);
+        face_apply<Sh, 1, T>(U[1], hf[1], wf[1], sf[1], A);
+        face_apply<Sh, 2, T>(U[2], hf[2], wf[2], sf[2], A);
+        face_apply<Sh, 3, T>(U[3], hf[3], wf[3], sf[3], A);
     }
 
     // ---- even-odd preparation: r = rho_e - D_eo C_o^-1 rho_o, x = 0
@@ -1160,10 +951,469 @@ __device__ __forceinline__ void lds_block_solve(const SapArgs &a, const int d, c
         }
         T inv = T(1) / sc;
         if (live) {
-            face_write<Sh, 0, SS>(a, d, l, A, inv, U[0]);
-            face_write<Sh, 1, SS>(a, d, l, A, inv, U[1]);
-            face_write<Sh, 2, SS>(a, d, l, A, inv, U[2]);
-            face_write<Sh, 3, SS>(a, d, l, A, inv, U[3]);
+            face_write<Sh, 0, T, SS>(a, d, l, A, inv, U[0]);
+            face_write<Sh, 1, T, SS>(a, d, l, A, inv, U[1]);
+            face_write<Sh, 2, T, SS>(a, d, l, A, inv, U[2]);
+            face_write<Sh, 3, T, SS>(a, d, l, A, inv, U[3]);
+        }
+    }
+}
+
+
+// ---- one right-hand side per workgroup, two threads per site --------------------
+//
+// The schedule of lds_block_solve for lattices whose colour does not fill the
+// device with one thread per site (a launch then lasts as long as one block
+// solve), and for FP64 on 2^4 domains.  Thread (parity, q, half index) holds the
+// site's links of directions 2q and 2q + 1 and its clover block q (the spinor's
+// components 6q .. 6q + 5, on which C is block diagonal), and owns that half of
+// x, r, rho and delta: it takes the forward or backward hops of its directions,
+// hands the other half of its partial sum to its twin through LDS, and gathers
+// its half of the backward hops of all four directions.  The four groups of
+// threads are whole waves, so no wave diverges.
+// A block solve is then half as long a chain of instructions per thread, and
+// a CU with one workgroup has two waves per SIMD instead of one (one wave
+// issues an FP32 instruction every 5.2 cycles, two every 2.6).  Launches of one
+// colour: 33.7 us against 40.5 (FP16, 4^4 domains, 16^3x32), about 37 against 58
+// (FP32, 6x6x2x4 domains, 12^3x24: 72 workgroups), and in FP64 on 2^4 domains
+// 78.6 us against 681 on 16^3x32 (eight threads per domain, links and clover
+// blocks read from memory at each use).
+// Spinors of precision T in LDS and memory: 16-byte entries of two FP32 or one
+// FP64 complex number.
+template <typename T> struct SpEntry {
+    typedef c2_t type;
+    static constexpr int N = 2;   // complex numbers per entry
+    static __device__ __forceinline__ c2_t make(const cx<float> *s) { return c2_t{s[0].r, s[0].i, s[1].r, s[1].i}; }
+    static __device__ __forceinline__ void split(const c2_t &e, cx<float> *s)
+    {
+        s[0] = {e[0], e[1]};
+        s[1] = {e[2], e[3]};
+    }
+};
+template <> struct SpEntry<double> {
+    typedef double2 type;
+    static constexpr int N = 1;
+    static __device__ __forceinline__ double2 make(const cx<double> *s) { return make_double2(s[0].r, s[0].i); }
+    static __device__ __forceinline__ void split(const double2 &e, cx<double> *s) { s[0] = {e.x, e.y}; }
+};
+// components 0 .. NC - 1 from entries p[0], p[STRIDE], ...
+template <int STRIDE, int NC, typename T> __device__ __forceinline__ void ld_sp(const typename SpEntry<T>::type *p, cx<T> *s)
+{
+#pragma unroll
+    for (int j = 0; j < NC / SpEntry<T>::N; j++) SpEntry<T>::split(p[j * STRIDE], s + j * SpEntry<T>::N);
+}
+template <int STRIDE, int NC, typename T> __device__ __forceinline__ void st_sp(typename SpEntry<T>::type *p, const cx<T> *s)
+{
+#pragma unroll
+    for (int j = 0; j < NC / SpEntry<T>::N; j++) p[j * STRIDE] = SpEntry<T>::make(s + j * SpEntry<T>::N);
+}
+
+// the spin halves of recon_acc: out (components 6q .. 6q + 5) += the half q of
+// the spinor whose projection is h
+template <int Q, int MU, int SG, typename T> __device__ __forceinline__ void recon_half(cx<T> out[6], const cx<T> h[6])
+{
+#pragma unroll
+    for (int c = 0; c < 3; c++) {
+        if constexpr (Q == 0) {
+            out[c] = out[c] + h[c];
+            out[3 + c] = out[3 + c] + h[3 + c];
+        } else if constexpr (MU == 0) {
+            out[c] = out[c] + (SG < 0 ? times_mi(h[3 + c]) : times_i(h[3 + c]));
+            out[3 + c] = out[3 + c] + (SG < 0 ? times_mi(h[c]) : times_i(h[c]));
+        } else if constexpr (MU == 1) {
+            out[c] = SG < 0 ? out[c] - h[3 + c] : out[c] + h[3 + c];
+            out[3 + c] = SG < 0 ? out[3 + c] + h[c] : out[3 + c] - h[c];
+        } else if constexpr (MU == 2) {
+            out[c] = out[c] + (SG < 0 ? times_mi(h[c]) : times_i(h[c]));
+            out[3 + c] = out[3 + c] + (SG < 0 ? times_i(h[3 + c]) : times_mi(h[3 + c]));
+        } else {
+            out[c] = SG < 0 ? out[c] + h[c] : out[c] - h[c];
+            out[3 + c] = SG < 0 ? out[3 + c] + h[3 + c] : out[3 + c] - h[3 + c];
+        }
+    }
+}
+
+// One direction's forward hop, push and pull, as lane_fwd, lane_push, lane_pull.
+template <class Sh, int MU, typename T, typename Link>
+__device__ __forceinline__ void split_fwd(const typename SpEntry<T>::type *v, const int l[4], int ox, const Link &U, cx<T> acc[12])
+{
+    if (!hop_exists<Sh, MU, -1>(l)) return;
+    cx<T> s[12], h[6], uh[6];
+    ld_sp<Sh::VH, 12, T>(v + hop_step<Sh, MU, -1>(ox), s);
+    proj<MU, -1>(s, h);
+    su3_mul(U(), h, uh);
+    recon_acc<MU, -1>(acc, uh, T(1));
+}
+template <class Sh, int MU, typename T, typename Link>
+__device__ __forceinline__ void split_push(const cx<T> own[12], const int l[4], const Link &U, typename SpEntry<T>::type *X)
+{
+    if (!hop_exists<Sh, MU, -1>(l)) return;
+    cx<T> h[6], uh[6];
+    proj<MU, +1>(own, h);
+    su3_dag_mul(U(), h, uh);
+    st_sp<Sh::VH, 6, T>(X + MU * (6 / SpEntry<T>::N) * Sh::VH, uh);
+}
+template <class Sh, int Q, int MU, typename T>
+__device__ __forceinline__ void split_pull(const typename SpEntry<T>::type *X, const int l[4], int ox, cx<T> half[6])
+{
+    if (!hop_exists<Sh, MU, +1>(l)) return;
+    cx<T> uh[6];
+    ld_sp<Sh::VH, 6, T>(X + MU * (6 / SpEntry<T>::N) * Sh::VH + hop_step<Sh, MU, +1>(ox), uh);
+    recon_half<Q, MU, +1>(half, uh);
+}
+template <class Sh, int Q, typename T>
+__device__ __forceinline__ void split_pulls(const typename SpEntry<T>::type *X, const int l[4], int ox, cx<T> half[6])
+{
+    split_pull<Sh, Q, 0, T>(X, l, ox, half);
+    split_pull<Sh, Q, 1, T>(X, l, ox, half);
+    split_pull<Sh, Q, 2, T>(X, l, ox, half);
+    split_pull<Sh, Q, 3, T>(X, l, ox, half);
+}
+
+// The hop sum of the sites of parity po: this thread's half of it where par ==
+// po.  v, own: the other parity's spinors in LDS at this half index and at this
+// thread's own site (the same pointer); X, E: handed-over half-spinors and
+// twin's halves.  Holds one barrier, after which v is free; X and E are free
+// after the next one.
+template <class Sh, typename T, typename Link>
+__device__ __forceinline__ void split_hops(const typename SpEntry<T>::type *v, typename SpEntry<T>::type *X,
+                                           typename SpEntry<T>::type *E, int po, int par, int q, bool live, const int l[4],
+                                           const Link (&U)[2], cx<T> half[6])
+{
+    constexpr int VH = Sh::VH, HE = 6 / SpEntry<T>::N * VH;   // entries of a half
+    const int ox = l[0] & 1;
+#pragma unroll
+    for (int k = 0; k < 6; k++) half[k] = czero<T>();
+    if (live && par == po) {
+        cx<T> acc[12];
+#pragma unroll
+        for (int k = 0; k < 12; k++) acc[k] = czero<T>();
+        if (q == 0) {
+            split_fwd<Sh, 0, T>(v, l, ox, U[0], acc);
+            split_fwd<Sh, 1, T>(v, l, ox, U[1], acc);
+            st_sp<VH, 6, T>(E + HE, acc + 6);
+#pragma unroll
+            for (int k = 0; k < 6; k++) half[k] = acc[k];
+        } else {
+            split_fwd<Sh, 2, T>(v, l, ox, U[0], acc);
+            split_fwd<Sh, 3, T>(v, l, ox, U[1], acc);
+            st_sp<VH, 6, T>(E, acc);
+#pragma unroll
+            for (int k = 0; k < 6; k++) half[k] = acc[6 + k];
+        }
+    } else if (live) {
+        cx<T> own[12];
+        ld_sp<VH, 12, T>(v, own);
+        if (q == 0) {
+            split_push<Sh, 0, T>(own, l, U[0], X);
+            split_push<Sh, 1, T>(own, l, U[1], X);
+        } else {
+            split_push<Sh, 2, T>(own, l, U[0], X);
+            split_push<Sh, 3, T>(own, l, U[1], X);
+        }
+    }
+    __syncthreads();
+    if (live && par == po) {
+        cx<T> o[6];
+        ld_sp<VH, 6, T>(E + q * HE, o);
+#pragma unroll
+        for (int k = 0; k < 6; k++) half[k] = half[k] + o[k];
+        if (q == 0) split_pulls<Sh, 0, T>(X, l, ox, half);
+        else split_pulls<Sh, 1, T>(X, l, ox, half);
+    }
+}
+
+// Sums (or, MAX, maxima) over the threads of each domain; every thread joins.
+// Waves hold VH consecutive lanes of one domain each (NDW > 1) or one domain's
+// sites; NWD waves (all of the workgroup's) contribute.  No closing barrier:
+// each call site has its own part of red.
+template <int VH, int NDW, int NW, bool MAX, typename T, int N>
+__device__ __forceinline__ void split_reduce(T (&v)[N], T *red, int sub)
+{
+    const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    constexpr int SEG = NDW > 1 ? VH : 64;
+#pragma unroll
+    for (int k = 0; k < N; k++) {
+        if constexpr (!MAX && NDW == 1) {
+            v[k] = wave_sum(v[k]);
+        } else {
+#pragma unroll
+            for (int o = SEG / 2; o > 0; o >>= 1) {
+                const T x = __shfl_xor(v[k], o);
+                v[k] = MAX ? fmax(v[k], x) : v[k] + x;
+            }
+        }
+        if (lane % SEG == 0) red[(k * NW + w) * NDW + (NDW > 1 ? lane / SEG : 0)] = v[k];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < N; k++) {
+        T s = red[k * NW * NDW + sub];
+#pragma unroll
+        for (int j = 1; j < NW; j++) {
+            const T x = red[(k * NW + j) * NDW + sub];
+            s = MAX ? fmax(s, x) : s + x;
+        }
+        v[k] = s;
+    }
+}
+
+template <class Sh, int NDW> struct SplitShape {
+    static constexpr int GP = (NDW * Sh::VH + 63) / 64 * 64;   // threads of one (parity, q)
+    static constexpr int NT = 4 * GP;
+    // waves per SIMD the registers are divided among (FP64: all for one)
+    template <typename T> static constexpr int waves() { return NT / 64 >= 12 ? 3 : sizeof(T) == 8 ? 1 : 2; }
+};
+
+// T: arithmetic; SS: storage of the block residual and boundary terms; G: of
+// links and clover.  The accumulator has precision T.
+template <class Sh, int NDW, typename T, typename SS, typename G, bool SCALED>
+__device__ __forceinline__ void split_block_solve(const SapArgs &a, const int d, const int sub, const Visit f)
+{
+    constexpr int VD = Sh::VD, VH = Sh::VH, GP = SplitShape<Sh, NDW>::GP, NW = SplitShape<Sh, NDW>::NT / 64;
+    constexpr int NLC = sizeof(G) == 8 ? 9 : 6;   // FP64 links are stored whole
+    typedef SpEntry<T> E;
+    typedef typename E::type e_t;
+    constexpr int HE = 6 / E::N * VH, FE = 2 * HE;   // entries of half a spinor array, of a whole one
+    // FP64 clover blocks: LDS, read at each use (FP32 and 16-bit ones: registers)
+    constexpr bool CL_LDS = sizeof(G) == 8;
+    __shared__ e_t se_all[NDW][FE], so_all[NDW][FE], sx_all[NDW][2 * FE], sE_all[NDW][FE];
+    __shared__ v2<G> scl_all[CL_LDS ? 4 * 18 * GP : 1];
+    __shared__ T red[3][3 * NW * NDW];
+
+    const int grp = __builtin_amdgcn_readfirstlane((int)threadIdx.x / GP);   // whole waves
+    const int par = grp >> 1, q = grp & 1, idx = (int)threadIdx.x - grp * GP;
+    const bool live = idx < NDW * VH;
+    const int hi = live ? idx % VH : 0, loc = par * VH + hi;
+    e_t *const ve = se_all[sub] + hi, *const vo = so_all[sub] + hi, *const vx = sx_all[sub] + hi, *const vE = sE_all[sub] + hi;
+    int l[4];
+    Sh::coords(loc, l);
+    int D[4];
+    {
+        int r = d;
+        D[0] = r % a.g.n[0]; r /= a.g.n[0];
+        D[1] = r % a.g.n[1]; r /= a.g.n[1];
+        D[2] = r % a.g.n[2];
+        D[3] = r / a.g.n[2];
+    }
+    const long sbase = ((long)d * 12 + 6 * q) * VD + loc;
+
+    // ---- this thread's links, clover block and half of the right-hand side
+    cx<T> A[6], P[6];   // A: even sites x, odd sites rho_o then delta_o
+    v2<G> lt[2][NLC], cl[18];
+    {
+        const v2<G> *gl = global_ptr((const v2<G> *)a.links) + ((long)d * 4 + 2 * q) * NLC * VD + loc;
+        const v2<G> *cs = global_ptr((const v2<G> *)a.cs) + ((long)d * 36 + 18 * q) * VD + loc;
+#pragma unroll
+        for (int k = 0; k < 2 * NLC; k++) lt[k / NLC][k % NLC] = gl[(long)k * VD];
+#pragma unroll
+        for (int k = 0; k < 18; k++) cl[k] = cs[(long)k * VD];
+    }
+    const e_t *const psi_in = global_ptr((const e_t *)a.psi) + ((long)d * (12 / E::N) + q * (6 / E::N)) * VD + loc;
+    e_t *const psi_out = const_cast<e_t *>(psi_in);
+    v2<SS> *const res = global_ptr((v2<SS> *)a.res) + (long)d * 12 * VH + hi * E::N + q * 6 * VH;   // see below
+#pragma unroll
+    for (int k = 0; k < 6; k++) A[k] = czero<T>();
+    if (f.first) {
+        if (a.io32) {
+#pragma unroll
+            for (int k = 0; k < 6; k++) A[k] = ld<T, float>(global_ptr((const float2 *)a.eta), sbase + (long)k * VD);
+        } else {
+#pragma unroll
+            for (int k = 0; k < 6; k++) A[k] = ld<T, double>(global_ptr(a.eta), sbase + (long)k * VD);
+        }
+    } else if (par == 0) {
+        // stored as the LDS entries are: E::N consecutive components at a time
+        const T sc = SCALED ? T(global_ptr(a.res_scale)[d]) : T(1);
+#pragma unroll
+        for (int k = 0; k < 6; k++) A[k] = scal(sc, ld<T, SS>(res, (long)(k / E::N) * E::N * VH + k % E::N));
+    }
+    RegLink<G> U[2];
+    U[0].put(lt[0]);
+    U[1].put(lt[1]);
+    if constexpr (CL_LDS) {
+#pragma unroll
+        for (int k = 0; k < 18; k++) scl_all[k * 4 * GP + threadIdx.x] = cl[k];
+    }
+    auto clover = [&](const cx<T> in[6], cx<T> out[6]) {
+        if constexpr (CL_LDS) clover_block_with<T>([&](int k) { return ld<T, G>(scl_all, k * 4 * GP + (int)threadIdx.x); }, in, out);
+        else if constexpr (sizeof(v2<G>) == 4) clover_block_with<T>([&](int k) { return widen<G>(cl[k]); }, in, out);
+        else clover_block_with<T>([&](int k) { return cx<T>{(T)cl[k].x, (T)cl[k].y}; }, in, out);
+    };
+    // the boundary terms of directions 2q and 2q + 1; the twin's half goes
+    // through vx, which holds a whole spinor for each parity
+    if (f.faces_in) {
+        cx<T> rho[12];
+#pragma unroll
+        for (int k = 0; k < 12; k++) rho[k] = czero<T>();
+        if (live) {
+            cx<T> hf[2][6];
+            T wf[2] = {0, 0};
+            int sf[2] = {0, 0};
+            if (q == 0) {
+                face_fetch<Sh, 0, T, SS, SCALED>(a, D, l, hf[0], wf[0], sf[0]);
+                face_fetch<Sh, 1, T, SS, SCALED>(a, D, l, hf[1], wf[1], sf[1]);
+                face_apply<Sh, 0, T>(U[0], hf[0], wf[0], sf[0], rho);
+                face_apply<Sh, 1, T>(U[1], hf[1], wf[1], sf[1], rho);
+                st_sp<VH, 6, T>(vx + par * FE + HE, rho + 6);
+            } else {
+                face_fetch<Sh, 2, T, SS, SCALED>(a, D, l, hf[0], wf[0], sf[0]);
+                face_fetch<Sh, 3, T, SS, SCALED>(a, D, l, hf[1], wf[1], sf[1]);
+                face_apply<Sh, 2, T>(U[0], hf[0], wf[0], sf[0], rho);
+                face_apply<Sh, 3, T>(U[1], hf[1], wf[1], sf[1], rho);
+                st_sp<VH, 6, T>(vx + par * FE, rho);
+            }
+        }
+        __syncthreads();
+        if (live) {
+            cx<T> o[6];
+            ld_sp<VH, 6, T>(vx + par * FE + q * HE, o);
+#pragma unroll
+            for (int k = 0; k < 6; k++) A[k] = A[k] + ((q == 0 ? rho[k] : rho[6 + k]) + o[k]);
+        }
+    }
+
+    // ---- even-odd preparation: r = rho_e - D_eo C_o^-1 rho_o, x = 0
+    if (par == 1) {
+        clover(A, P);
+        if (live) st_sp<VH, 6, T>(vo + q * HE, P);
+    }
+    __syncthreads();
+    cx<T> t[6];
+    split_hops<Sh, T>(vo, vx, vE, 0, par, q, live, l, U, t);
+    if (par == 0) {
+#pragma unroll
+        for (int k = 0; k < 6; k++) {
+            P[k] = A[k] + scal(T(0.5), t[k]);
+            A[k] = czero<T>();
+        }
+        if (live) st_sp<VH, 6, T>(ve + q * HE, P);
+    }
+
+    // ---- minimal residual on the Schur complement
+#pragma unroll 1
+    for (int it = 0; it < a.n_mr; it++) {
+        if constexpr (sizeof(v2<G>) == 4) {
+            // keep the clover block in its 16-bit storage form (see lds_block_solve)
+#pragma unroll
+            for (int k = 0; k < 18; k++) asm volatile("" : "+v"(cl[k]));
+        }
+        __syncthreads();
+        split_hops<Sh, T>(ve, vx, vE, 1, par, q, live, l, U, t);   // -2 D_oe r
+        cx<T> rr[6];
+        if (par == 1) {
+            clover(t, P);                                // -2 C_o^-1 D_oe r
+            if (live) st_sp<VH, 6, T>(vo + q * HE, P);
+        } else {
+            // meanwhile the even sites form C_e r, which needs only r
+            ld_sp<VH, 6, T>(ve + q * HE, rr);
+            clover(rr, P);
+        }
+        __syncthreads();
+        T dots[3] = {0, 0, 0};
+        split_hops<Sh, T>(vo, vx, vE, 0, par, q, live, l, U, t);
+        if (par == 0 && live) {
+#pragma unroll
+            for (int k = 0; k < 6; k++) {
+                P[k] = P[k] + scal(T(-0.25), t[k]);      // p = C_e r - D_eo C_o^-1 D_oe r
+                dots[0] = fmad(P[k].i, rr[k].i, fmad(P[k].r, rr[k].r, dots[0]));
+                dots[1] = fmad(-P[k].i, rr[k].r, fmad(P[k].r, rr[k].i, dots[1]));
+                dots[2] = fmad(P[k].i, P[k].i, fmad(P[k].r, P[k].r, dots[2]));
+            }
+        }
+        split_reduce<VH, NDW, NW, false>(dots, red[0], sub);
+        if (par == 0) {
+            const cx<T> alpha = dots[2] > T(0) ? cx<T>{dots[0] / dots[2], dots[1] / dots[2]} : czero<T>();
+#pragma unroll
+            for (int k = 0; k < 6; k++) {
+                A[k] = cmac(A[k], alpha, rr[k]);
+                P[k] = cmac(rr[k], neg(alpha), P[k]);
+            }
+            if (live) st_sp<VH, 6, T>(ve + q * HE, P);
+        }
+    }
+
+    // ---- odd sites: delta_o = C_o^-1 (rho_o - D_oe x); x goes through so, se
+    // keeps r for the epilogue.  The accumulator is fetched ahead of it.
+    e_t ps[6 / E::N];
+    {
+        const cx<T> z[2] = {czero<T>(), czero<T>()};
+#pragma unroll
+        for (int j = 0; j < 6 / E::N; j++) ps[j] = E::make(z);
+    }
+    if (par == 0 && live) st_sp<VH, 6, T>(vo + q * HE, A);
+    if (!f.first)
+#pragma unroll
+        for (int j = 0; j < 6 / E::N; j++) ps[j] = psi_in[(long)j * VD];
+    __syncthreads();
+    split_hops<Sh, T>(vo, vx, vE, 1, par, q, live, l, U, t);
+    if (par == 1) {
+#pragma unroll
+        for (int k = 0; k < 6; k++) t[k] = A[k] + scal(T(0.5), t[k]);
+        clover(t, A);
+    }
+
+    // ---- epilogue: psi += delta, stored residual, boundary terms
+    if (live) {
+        cx<T> c[6];
+#pragma unroll
+        for (int j = 0; j < 6 / E::N; j++) E::split(ps[j], c + j * E::N);
+#pragma unroll
+        for (int k = 0; k < 6; k++) c[k] = c[k] + A[k];
+        if (f.last) {
+#pragma unroll
+            for (int k = 0; k < 6; k++) {
+                if (a.io32) st<T, float>(global_ptr((float2 *)a.out), sbase + (long)k * VD, c[k]);
+                else st<T, double>(global_ptr(a.out), sbase + (long)k * VD, c[k]);
+            }
+        } else {
+#pragma unroll
+            for (int j = 0; j < 6 / E::N; j++) psi_out[(long)j * VD] = E::make(c + j * E::N);
+        }
+    }
+    if (!f.res_out && !f.faces_out) return;
+    cx<T> rr[6];
+#pragma unroll
+    for (int k = 0; k < 6; k++) rr[k] = czero<T>();
+    if (par == 0 && live) ld_sp<VH, 6, T>(ve + q * HE, rr);
+    T mx[2] = {0, 0};
+    if constexpr (SCALED) {
+#pragma unroll
+        for (int k = 0; k < 6; k++) {
+            mx[0] = fmax(mx[0], fmax(fabs(rr[k].r), fabs(rr[k].i)));
+            mx[1] = fmax(mx[1], fmax(fabs(A[k].r), fabs(A[k].i)));
+        }
+        if (!live) mx[1] = 0;
+        T m[2] = {mx[0], mx[1]};
+        split_reduce<VH, NDW, NW, true>(m, red[1], sub);
+        mx[0] = pow2_ceil(m[0]);
+        mx[1] = T(8) * pow2_ceil(m[1]);
+    } else {
+        mx[0] = mx[1] = T(1);
+        __syncthreads();   // the reconstruction's hops have read so
+    }
+    if (f.res_out && par == 0 && live) {
+        if (SCALED && hi == 0 && q == 0) global_ptr(a.res_scale)[d] = (float)mx[0];
+        const T inv = T(1) / mx[0];
+#pragma unroll
+        for (int k = 0; k < 6; k++) st<T, SS>(res, (long)(k / E::N) * E::N * VH + k % E::N, scal(inv, rr[k]));
+    }
+    if (f.faces_out) {
+        if (SCALED && loc == 0 && q == 0 && live) global_ptr(a.face_scale)[d] = (float)mx[1];
+        const T inv = T(1) / mx[1];
+        e_t *const vd = par == 0 ? ve : vo;
+        if (live) st_sp<VH, 6, T>(vd + q * HE, A);
+        __syncthreads();
+        if (live) {
+            cx<T> delta[12];
+            ld_sp<VH, 12, T>(vd, delta);
+            if (q == 0) {
+                face_write<Sh, 0, T, SS>(a, d, l, delta, inv, U[0]);
+                face_write<Sh, 1, T, SS>(a, d, l, delta, inv, U[1]);
+            } else {
+                face_write<Sh, 2, T, SS>(a, d, l, delta, inv, U[0]);
+                face_write<Sh, 3, T, SS>(a, d, l, delta, inv, U[1]);
+            }
         }
     }
 }
@@ -1212,16 +1462,16 @@ __device__ __forceinline__ void f64_block_solve(const SapArgs &a, const int d, c
     const long lbase = (long)d * 4 * NLC * VD;
     const v2<G> *cs = (const v2<G> *)a.cs;
     const long cbase = (long)d * 36 * VD + loc;
-    v2<T> *rho_g = (v2<T> *)a.rho_tmp;
+    v2<T> *rho_g = global_ptr((v2<T> *)a.rho_tmp);
     const long sbase = (long)d * 12 * VD + loc;
 
     // ---- the block right-hand side rho
     cx<T> A[12], P[12];
     if (f.first) {
 #pragma unroll
-        for (int k = 0; k < 12; k++) A[k] = ld<T, double>(a.eta, sbase + (long)k * VD);
+        for (int k = 0; k < 12; k++) A[k] = ld<T, double>(global_ptr(a.eta), sbase + (long)k * VD);
     } else if (par == 0) {
-        const v2<T> *res = (const v2<T> *)a.res;
+        const v2<T> *res = global_ptr((const v2<T> *)a.res);
 #pragma unroll
         for (int k = 0; k < 12; k++) A[k] = ld<T, T>(res, ((long)d * 12 + k) * VH + hi);
     } else {
@@ -1313,17 +1563,17 @@ __device__ __forceinline__ void f64_block_solve(const SapArgs &a, const int d, c
 
     // ---- epilogue: psi += delta, stored residual, boundary terms
     {
-        const v2<T> *psi_in = (const v2<T> *)a.psi;
-        v2<T> *psi_out = (v2<T> *)a.psi;
+        const v2<T> *psi_in = global_ptr((const v2<T> *)a.psi);
+        v2<T> *psi_out = global_ptr((v2<T> *)a.psi);
 #pragma unroll
         for (int k = 0; k < 12; k++) {
             const cx<T> ps = f.first ? A[k] : ld<T, T>(psi_in, sbase + (long)k * VD) + A[k];
-            if (f.last) st<T, double>(a.out, sbase + (long)k * VD, ps);
+            if (f.last) st<T, double>(global_ptr(a.out), sbase + (long)k * VD, ps);
             else st<T, T>(psi_out, sbase + (long)k * VD, ps);
         }
     }
     if (f.res_out && par == 0) {
-        v2<T> *res = (v2<T> *)a.res;
+        v2<T> *res = global_ptr((v2<T> *)a.res);
 #pragma unroll
         for (int k = 0; k < 12; k++) st<T, T>(res, ((long)d * 12 + k) * VH + hi, she[k][hi]);
     }
@@ -1391,20 +1641,21 @@ __global__ __launch_bounds__(Sh::VD) void k_sap_f64(const SapArgs *args, const i
     f64_block_solve<Sh>(a, it.y, v);
 }
 
-template <class Sh, typename T, typename SS, typename PS, typename G, int NLC, bool SCALED, bool RHO_LDS>
-__global__ __launch_bounds__(Sh::VH) void k_sap_sweep(const SapArgs *args, const int2 *items, Visit v)
+template <class Sh, int NDW, typename T, typename SS, typename G, bool SCALED>
+__global__ __launch_bounds__((SplitShape<Sh, NDW>::NT), (SplitShape<Sh, NDW>::template waves<T>())) void k_sap_split(
+    const SapArgs *args, const int2 *items, Visit v)
 {
-    const int2 it = items[blockIdx.x];
+    const int2 it = items[(long)blockIdx.x * NDW];
     if (it.x < 0) return;
     SapArgs a = args[it.x];
     if (!a.active) return;
     bind_faces(a, v);
-    a.first = v.first;
-    a.faces_in = v.faces_in;
-    a.last = v.last;
-    a.faces_out = v.faces_out;
-    a.res_out = v.res_out;
-    pair_block_solve<Sh, T, SS, PS, G, NLC, SCALED, RHO_LDS>(a, it.y);
+    int d = it.y, sub = 0;
+    if constexpr (NDW > 1) {
+        sub = ((int)threadIdx.x % SplitShape<Sh, NDW>::GP) / Sh::VH;
+        d = items[(long)blockIdx.x * NDW + sub].y;
+    }
+    split_block_solve<Sh, NDW, T, SS, G, SCALED>(a, d, sub, v);
 }
 
 // ---- dispatch ---------------------------------------------------------------
@@ -2096,7 +2347,7 @@ template <class Sh>
 static hipError_t launch_batch(const SapArgs *args, const int2 *items, int nitems, int prec, int product, Visit v,
                                hipStream_t s)
 {
-    if (product != PRODUCT_LANE) {
+    if (product != PRODUCT_LANE && product != PRODUCT_LANE_SPLIT) {
         // a tile of right-hand sides per workgroup: 4^4 domains, FP16 storage
         if constexpr (std::is_same<Sh, Shape<4, 4, 4, 4>>::value) {
             constexpr int NT = Sh::VH * RT_MFMA, NTV = Sh::VH * RT_VALU;
@@ -2129,40 +2380,48 @@ static hipError_t launch_batch(const SapArgs *args, const int2 *items, int nitem
         }
         return hipErrorInvalidValue;
     }
+    constexpr int NDW = Sh::VD < 64 ? 128 / Sh::VD : 1;
+    if (nitems % NDW) return hipErrorInvalidValue;
+    if (product == PRODUCT_LANE_SPLIT) {
+        if constexpr (Sh::VD < 512) {
+            constexpr int NT = SplitShape<Sh, NDW>::NT;
+            if constexpr (Sh::VD == 16)
+                if (prec == P64)
+                    return launch_bounded(k_sap_split<Sh, NDW, double, double, double, false>, nitems / NDW, NT, s, args, items, v);
+            if (prec == P32)
+                return launch_bounded(k_sap_split<Sh, NDW, float, float, float, false>, nitems / NDW, NT, s, args, items, v);
+            if (prec == P16)
+                return launch_bounded(k_sap_split<Sh, NDW, float, half_t, half_t, true>, nitems / NDW, NT, s, args, items, v);
+            if (prec == PB16)
+                return launch_bounded(k_sap_split<Sh, NDW, float, bf16_t, bf16_t, false>, nitems / NDW, NT, s, args, items, v);
+        }
+        return hipErrorInvalidValue;
+    }
     if (prec == P64) {
-        // FP64: one thread per even/odd site pair on 2^4 domains, else the LDS
-        // layout (whole waves only: no FP64 kernel for padded workgroups)
-        if constexpr (Sh::VD == 16)
-            return launch_bounded(k_sap_sweep<Sh, double, double, double, double, 9, false, false>, nitems, Sh::VH, s,
-                                  args, items, v);
-        else if constexpr (Sh::VD % 64 == 0)
+        // whole waves only: no FP64 kernel for padded workgroups
+        if constexpr (Sh::VD >= 64 && Sh::VD % 64 == 0)
             return launch_bounded(k_sap_f64<Sh>, nitems, Sh::VD, s, args, items, v);
         else
             return hipErrorInvalidValue;
     } else {
-        constexpr int NDW = Sh::VD < 64 ? 128 / Sh::VD : 1;
         constexpr int NT = NDW > 1 ? Sh::VD * NDW : Sh::NT;
-        if (nitems % NDW) return hipErrorInvalidValue;
         if (prec == P32)
-            return launch_bounded(k_sap_lds<Sh, NDW, float, float, false>, nitems / NDW,
-                                  NT, s, args, items, v);
+            return launch_bounded(k_sap_lds<Sh, NDW, float, float, false>, nitems / NDW, NT, s, args, items, v);
         else if (prec == P16)
-            return launch_bounded(k_sap_lds<Sh, NDW, half_t, half_t, true>,
-                                  nitems / NDW, NT, s, args, items, v);
+            return launch_bounded(k_sap_lds<Sh, NDW, half_t, half_t, true>, nitems / NDW, NT, s, args, items, v);
         else
-            return launch_bounded(k_sap_lds<Sh, NDW, bf16_t, bf16_t, false>,
-                                  nitems / NDW, NT, s, args, items, v);
+            return launch_bounded(k_sap_lds<Sh, NDW, bf16_t, bf16_t, false>, nitems / NDW, NT, s, args, items, v);
     }
 }
 
 int sap_domains_per_workgroup(int shape, int prec, int product)
 {
-    return shape == 0 && prec != P64 && product == PRODUCT_LANE ? 8 : 1;
+    return shape == 0 ? 8 : 1;   // only one-right-hand-side kernels take 2^4 domains
 }
 
 int sap_rhs_per_workgroup(int product)
 {
-    return product == PRODUCT_LANE ? 1 : product == PRODUCT_TILE_VALU ? RT_VALU : RT_MFMA;
+    return product == PRODUCT_LANE || product == PRODUCT_LANE_SPLIT ? 1 : product == PRODUCT_TILE_VALU ? RT_VALU : RT_MFMA;
 }
 
 bool sap_product_supported(const int b[4], int prec, int product)
@@ -2170,6 +2429,22 @@ bool sap_product_supported(const int b[4], int prec, int product)
     if (product == PRODUCT_LANE) return sap_prec_supported(b, prec);
     if (product < PRODUCT_TILE_VALU || product > PRODUCT_TILE_MFMA_BF16) return false;
     return sap_shape_id(b) == 1 && (prec == P16 || prec == PB16);
+}
+
+// Two threads per site where one thread per site would leave the device idle:
+// a colour of at most SPLIT_MAX workgroups (one per CU).  The rule looks at the
+// lattice, not at the launch, so that a system is solved with the same bits
+// alone and in a batch.  At 256 workgroups of 4^4 domains two threads per site
+// take 33.7 us and one takes 40.5; beyond, a second round of workgroups begins,
+// while with one thread per site two workgroups share a CU in 344 us for 4096
+// (21.5 us per 256).  512-site domains have two waves per SIMD as they are.
+constexpr int SPLIT_MAX = 256;
+int sap_kernel_form(const Geo &g, int prec, int product)
+{
+    if (product != PRODUCT_LANE) return product;
+    if (prec == P64) return g.Vd == 16 ? PRODUCT_LANE_SPLIT : product;
+    const int shape = sap_shape_id(g.b);
+    return g.Vd < 512 && g.nd / 2 / sap_domains_per_workgroup(shape, prec, product) <= SPLIT_MAX ? PRODUCT_LANE_SPLIT : product;
 }
 
 int sap_shape_id(const int b[4])
