@@ -133,6 +133,11 @@ struct ddqcd_ctx {
     void *Cs32 = nullptr, *Cs16 = nullptr, *CsB16 = nullptr;
     void *t_lo_in = nullptr, *t_lo_out = nullptr;   // FP32/FP16 operands of apply_D
     hipStream_t capture = nullptr;   // private stream on which launch graphs are captured
+    // streams and events of the groups of a plan led by this context (group g
+    // > 0 runs on side[g - 1]); fork: recorded on the caller's stream
+    std::vector<hipStream_t> side;
+    std::vector<hipEvent_t> side_done;
+    hipEvent_t fork = nullptr;
     // reduction results of the systems of a solve led by this context, side by
     // side (32 pairs each) on the device and in pinned host memory
     double2 *res_dev = nullptr, *res_host = nullptr;
@@ -426,43 +431,69 @@ int build_plan_once(const std::vector<Sys> &sys, const std::string &key, Plan *&
 }
 
 // the launches of one preconditioner call: black domains first (colour 0),
-// then white, n_cycles times, one launch per (shape, precision) group
-hipError_t enqueue_sweeps(const Plan &plan, int n_cycles, hipStream_t s)
+// then white, n_cycles times, one launch per (shape, precision) group.  Group g
+// goes to streams[g].
+hipError_t enqueue_sweeps(const Plan &plan, int n_cycles, const std::vector<hipStream_t> &streams)
 {
-    if (plan.additive) {
-        // one launch per cycle over all domains; the boundary buffers alternate
-        for (int cyc = 0; cyc < n_cycles; cyc++) {
-            Visit v;
-            v.first = cyc == 0;
-            v.faces_in = cyc > 0;
-            v.last = cyc == n_cycles - 1;
-            v.faces_out = !v.last;
-            v.res_out = !v.last;
-            v.flip = cyc & 1;
-            for (const Plan::Group &G : plan.groups) {
-                hipError_t e =
-                    sap_sweep_batch(plan.d_args, G.items[2], G.nitems[2], G.shape, G.prec, G.product, v, s);
-                if (e != hipSuccess) return e;
-            }
-        }
-        return hipSuccess;
-    }
+    // additive: one launch per cycle over all domains, alternating boundary buffers
+    const int ncol = plan.additive ? 1 : 2;
     for (int cyc = 0; cyc < n_cycles; cyc++)
-        for (int col = 0; col < 2; col++) {
+        for (int col = 0; col < ncol; col++) {
             Visit v;
             v.first = cyc == 0;
             v.faces_in = !(cyc == 0 && col == 0);
             v.last = cyc == n_cycles - 1;
-            v.faces_out = !(v.last && col == 1);
+            v.faces_out = !(v.last && col == ncol - 1);
             v.res_out = !v.last;
-            v.flip = 0;
-            for (const Plan::Group &G : plan.groups) {
-                hipError_t e =
-                    sap_sweep_batch(plan.d_args, G.items[col], G.nitems[col], G.shape, G.prec, G.product, v, s);
+            v.flip = plan.additive ? cyc & 1 : 0;
+            const int list = plan.additive ? 2 : col;
+            for (size_t g = 0; g < plan.groups.size(); g++) {
+                const Plan::Group &G = plan.groups[g];
+                const hipError_t e = sap_sweep_batch(plan.d_args, G.items[list], G.nitems[list], G.shape, G.prec, G.product,
+                                                     v, streams[g]);
                 if (e != hipSuccess) return e;
             }
         }
     return hipSuccess;
+}
+
+// The groups of a plan share no data within a preconditioner call, so each
+// runs its whole chain of launches on a stream of its own: small groups, whose
+// launches do not fill the device, run beside the others instead of after them
+// at every half-sweep.  All are joined to s before this returns, also after an
+// error.
+int run_sweeps(ddqcd_t lead, const Plan &plan, int n_cycles, hipStream_t s)
+{
+    const size_t ng = plan.groups.size();
+    if (ng == 1) {
+        HIPCHK(lead, enqueue_sweeps(plan, n_cycles, {s}));
+        return DDQCD_OK;
+    }
+    if (!lead->fork) HIPCHK(lead, hipEventCreateWithFlags(&lead->fork, hipEventDisableTiming));
+    while (lead->side.size() + 1 < ng) {
+        hipStream_t st = nullptr;
+        hipEvent_t ev = nullptr;
+        HIPCHK(lead, hipEventCreateWithFlags(&ev, hipEventDisableTiming));
+        const hipError_t e = hipStreamCreateWithFlags(&st, hipStreamNonBlocking);
+        if (e != hipSuccess) (void)hipEventDestroy(ev);
+        HIPCHK(lead, e);
+        lead->side.push_back(st);
+        lead->side_done.push_back(ev);
+    }
+    std::vector<hipStream_t> streams{s};
+    HIPCHK(lead, hipEventRecord(lead->fork, s));
+    for (size_t g = 1; g < ng; g++) {
+        HIPCHK(lead, hipStreamWaitEvent(lead->side[g - 1], lead->fork, 0));
+        streams.push_back(lead->side[g - 1]);
+    }
+    hipError_t e = enqueue_sweeps(plan, n_cycles, streams);
+    for (size_t g = 1; g < ng; g++) {
+        const hipError_t e1 = hipEventRecord(lead->side_done[g - 1], lead->side[g - 1]);
+        const hipError_t e2 = hipStreamWaitEvent(s, lead->side_done[g - 1], 0);
+        if (e == hipSuccess) e = e1 != hipSuccess ? e1 : e2;
+    }
+    HIPCHK(lead, e);
+    return DDQCD_OK;
 }
 
 int capture_graph(ddqcd_t lead, Plan &plan, int n_cycles)
@@ -473,7 +504,7 @@ int capture_graph(ddqcd_t lead, Plan &plan, int n_cycles)
     }
     if (!lead->capture) HIPCHK(lead, hipStreamCreateWithFlags(&lead->capture, hipStreamNonBlocking));
     HIPCHK(lead, hipStreamBeginCapture(lead->capture, hipStreamCaptureModeThreadLocal));
-    const hipError_t e = enqueue_sweeps(plan, n_cycles, lead->capture);
+    const hipError_t e = enqueue_sweeps(plan, n_cycles, std::vector<hipStream_t>(plan.groups.size(), lead->capture));
     hipGraph_t g = nullptr;
     const hipError_t e2 = hipStreamEndCapture(lead->capture, &g);   // always ends the capture
     if (e != hipSuccess || e2 != hipSuccess) {
@@ -546,8 +577,7 @@ int run_sap(const std::vector<Sys> &all, const std::vector<const double2 *> &eta
         HIPCHK(lead, hipGraphLaunch(plan->graph, s));
         return DDQCD_OK;
     }
-    HIPCHK(lead, enqueue_sweeps(*plan, n_cycles, s));
-    return DDQCD_OK;
+    return run_sweeps(lead, *plan, n_cycles, s);
 }
 
 int apply_A64(ddqcd_t c, const double2 *in, double2 *out, hipStream_t s)
@@ -1785,6 +1815,9 @@ int ddqcd_destroy(ddqcd_t c)
     if (!c) return DDQCD_OK;
     c->plans.clear();
     if (c->capture) (void)hipStreamDestroy(c->capture);
+    for (hipStream_t s : c->side) (void)hipStreamDestroy(s);
+    for (hipEvent_t e : c->side_done) (void)hipEventDestroy(e);
+    if (c->fork) (void)hipEventDestroy(c->fork);
     if (c->res_host) (void)hipHostFree(c->res_host);
     for (void *p : c->owned) (void)hipFree(p);
     delete c;
