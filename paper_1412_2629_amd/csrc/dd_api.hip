@@ -586,24 +586,23 @@ int apply_A64(ddqcd_t c, const double2 *in, double2 *out, hipStream_t s)
     return DDQCD_OK;
 }
 
-// out_i = A in_i (FP64) for the listed systems; two consecutive systems of one
-// context share a launch where the kernel allows it (each link and clover
-// load then serves both), with the bits of two single calls
+// out_i = A in_i (FP64) for the listed systems; consecutive systems of one
+// context share a launch (each link and clover load then serves them all), with
+// the bits of single calls
 template <typename In, typename Out>
 int apply_A64_list(const std::vector<Sys> &sys, const std::vector<int> &list, In in_of, Out out_of, hipStream_t s)
 {
+    std::vector<const void *> in;
+    std::vector<void *> out;
     for (size_t q = 0; q < list.size();) {
-        const int i = list[q];
-        ddqcd_t c = sys[i].c;
-        if (q + 1 < list.size() && sys[list[q + 1]].c == c && apply_A_pairs(c->g, P64)) {
-            const int j = list[q + 1];
-            HIPCHK(c, apply_A_pair(c->g, in_of(i), out_of(i), in_of(j), out_of(j), c->U64, c->C64, P64, s));
-            q += 2;
-        } else {
-            const int e = apply_A64(c, in_of(i), out_of(i), s);
-            if (e) return e;
-            q += 1;
+        ddqcd_t c = sys[list[q]].c;
+        in.clear();
+        out.clear();
+        for (; q < list.size() && sys[list[q]].c == c; q++) {
+            in.push_back(in_of(list[q]));
+            out.push_back(out_of(list[q]));
         }
+        HIPCHK(c, apply_A_multi(c->g, in.data(), out.data(), (int)in.size(), c->U64, c->C64, P64, s));
     }
     return DDQCD_OK;
 }
@@ -1988,6 +1987,10 @@ int ddqcd_apply_D(ddqcd_t c, double *out, const double *in, int nrhs, int prec, 
     if (e || (e = ensure_slots(c, 1))) return e;
     hipStream_t s = (hipStream_t)stream;
     const Geo &g = c->g;
+    if (apply_A_canonical_fits(g, prec)) {
+        HIPCHK(c, apply_A_canonical(g, in, out, nrhs, links_for(c, prec), clover_for(c, prec), prec, s));
+        return DDQCD_OK;
+    }
     const long n = ncomplex(g);
     if (prec != DDQCD_FP64 && !c->t_lo_in) {
         if ((e = dev_alloc(c, &c->t_lo_in, (size_t)n * 8))) return e;

@@ -2,6 +2,8 @@
 // linear algebra of the outer solver.
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "dd_device.h"
 #include "dd_internal.h"
 
@@ -420,10 +422,53 @@ hipError_t clover_schur(const Geo &g, const double2 *C64, double2 *Cs64, int *ba
 // global operator A (Sec. II-B, Eqs. 1-2): one thread per site
 // ===========================================================================
 
-// one hop: DIR = +1 forward, -1 backward
-template <int MU, int DIR, typename T, typename SI, typename G, int NLC>
-__device__ __forceinline__ void a_hop(const Geo &g, const int x[4], int d, int loc, const v2<SI> *in,
-                                      const v2<G> *links, cx<T> acc[12])
+// The spinor of site y (internal position (dj, lj)) from the input field
+template <typename T, typename SI, bool CANON>
+__device__ __forceinline__ void a_load(const Geo &g, const v2<std::conditional_t<CANON, double, SI>> *in, const int y[4],
+                                       unsigned dj, unsigned lj, cx<T> v[12])
+{
+    if constexpr (CANON) {
+        const unsigned b = (unsigned)canon_index(g, y) * 12;
+#pragma unroll
+        for (int k = 0; k < 12; k++) {
+            const cx<double> c = ld32<double, double>(in, b + k);
+            v[k] = {static_cast<T>(static_cast<SI>(c.r)), static_cast<T>(static_cast<SI>(c.i))};
+        }
+    } else {
+#pragma unroll
+        for (int k = 0; k < 12; k++) v[k] = ld32<T, SI>(in, (dj * 12 + k) * (unsigned)g.Vd + lj);
+    }
+}
+
+// The right-hand sides of a launch.
+struct RhsFields {
+    const void *in[A_MAX_RHS];
+    void *out[A_MAX_RHS];
+    int n;
+};
+// Block and right-hand side of this workgroup.  Workgroup w runs on XCD w mod 8.
+// Each XCD sweeps one contiguous eighth of the domain-blocked site order: most
+// neighbour spinors and links a workgroup reads were brought into the same
+// XCD's L2 by its neighbours (a plain order spreads neighbouring blocks over
+// all eight L2s).  The right-hand sides of a block follow one another there, so
+// its links and clover blocks come from memory once for all of them.
+__device__ __forceinline__ void rhs_block(int n, unsigned &blk, unsigned &rhs)
+{
+    const unsigned nr = (unsigned)n, nbk = gridDim.x / nr, w = blockIdx.x;
+    if (nbk % 8 == 0) {
+        const unsigned q = w / 8;
+        rhs = q % nr;
+        blk = (w % 8) * (nbk / 8) + q / nr;
+    } else {
+        rhs = w % nr;
+        blk = w / nr;
+    }
+}
+
+// one hop: DIR = +1 forward, -1 backward (CANON: in is the canonical FP64 field)
+template <int MU, int DIR, typename T, typename SI, typename G, int NLC, bool CANON>
+__device__ __forceinline__ void a_hop(const Geo &g, const int x[4], int d, int loc,
+                                      const v2<std::conditional_t<CANON, double, SI>> *in, const v2<G> *links, cx<T> acc[12])
 {
     const long Vd = g.Vd;
     int y[4] = {x[0], x[1], x[2], x[3]};
@@ -438,8 +483,10 @@ __device__ __forceinline__ void a_hop(const Geo &g, const int x[4], int d, int l
     const long J = encode(g, y);
     const int dj = (int)(J / Vd), lj = (int)(J - (long)dj * Vd);
     cx<T> v[12], h[6], uh[6];
+    if constexpr (CANON) a_load<T, SI, CANON>(g, in, y, dj, lj, v);
+    else
 #pragma unroll
-    for (int k = 0; k < 12; k++) v[k] = ld<T, SI>(in, ((long)dj * 12 + k) * Vd + lj);
+        for (int k = 0; k < 12; k++) v[k] = ld<T, SI>(in, ((long)dj * 12 + k) * Vd + lj);
     if constexpr (DIR > 0) {
         // -1/2 (1 - gamma_mu) U_mu(x) psi(x + mu)
         proj<MU, -1>(v, h);
@@ -455,27 +502,28 @@ __device__ __forceinline__ void a_hop(const Geo &g, const int x[4], int d, int l
     }
 }
 
-template <typename T, typename SI, typename SO, typename G, int NLC>
-__global__ __launch_bounds__(256) void k_apply_A(Geo g, const v2<SI> *in, v2<SO> *out, const v2<G> *links,
-                                                 const v2<G> *clov)
+// One thread per site; CANON: in the canonical FP64 fields of the interface.
+template <typename T, typename SI, typename SO, typename G, int NLC, bool CANON>
+__global__ __launch_bounds__(256) void k_apply_A(Geo g, RhsFields io, const v2<G> *links, const v2<G> *clov)
 {
-    // Workgroup w runs on XCD w mod 8.  Blocks are handed out so that each
-    // XCD sweeps one contiguous eighth of the domain-blocked site order: most
-    // neighbour spinors and links a workgroup reads were brought into the
-    // same XCD's L2 by its neighbours (a plain order spreads neighbouring
-    // blocks over all eight L2s).
-    const unsigned nbk = gridDim.x, w = blockIdx.x;
-    const unsigned blk = nbk % 8 == 0 ? (w % 8) * (nbk / 8) + w / 8 : w;
+    typedef std::conditional_t<CANON, double, SI> FI;
+    typedef std::conditional_t<CANON, double, SO> FO;
+    unsigned blk, rhs;
+    rhs_block(io.n, blk, rhs);
     long I = (long)blk * blockDim.x + threadIdx.x;
     if (I >= g.V) return;
+    const v2<FI> *in = global_ptr((const v2<FI> *)io.in[rhs]);
+    v2<FO> *out = global_ptr((v2<FO> *)io.out[rhs]);
     int x[4], d, loc;
     decode(g, I, x, d, loc);
     const long Vd = g.Vd;
     cx<T> acc[12];
     {
         cx<T> s[12];
+        if constexpr (CANON) a_load<T, SI, CANON>(g, in, x, d, loc, s);
+        else
 #pragma unroll
-        for (int k = 0; k < 12; k++) s[k] = ld<T, SI>(in, ((long)d * 12 + k) * Vd + loc);
+            for (int k = 0; k < 12; k++) s[k] = ld<T, SI>(in, ((long)d * 12 + k) * Vd + loc);
         clover_apply<T, G>(clov, (long)d * 36 * Vd + loc, Vd, s, acc);
     }
     // The eight hops one after another (a loop the compiler keeps rolled): only
@@ -485,46 +533,62 @@ __global__ __launch_bounds__(256) void k_apply_A(Geo g, const v2<SI> *in, v2<SO>
 #pragma unroll 1
     for (int k = 0; k < 8; k++) {
         switch (k) {
-            case 0: a_hop<0, +1, T, SI, G, NLC>(g, x, d, loc, in, links, acc); break;
-            case 1: a_hop<0, -1, T, SI, G, NLC>(g, x, d, loc, in, links, acc); break;
-            case 2: a_hop<1, +1, T, SI, G, NLC>(g, x, d, loc, in, links, acc); break;
-            case 3: a_hop<1, -1, T, SI, G, NLC>(g, x, d, loc, in, links, acc); break;
-            case 4: a_hop<2, +1, T, SI, G, NLC>(g, x, d, loc, in, links, acc); break;
-            case 5: a_hop<2, -1, T, SI, G, NLC>(g, x, d, loc, in, links, acc); break;
-            case 6: a_hop<3, +1, T, SI, G, NLC>(g, x, d, loc, in, links, acc); break;
-            default: a_hop<3, -1, T, SI, G, NLC>(g, x, d, loc, in, links, acc); break;
+            case 0: a_hop<0, +1, T, SI, G, NLC, CANON>(g, x, d, loc, in, links, acc); break;
+            case 1: a_hop<0, -1, T, SI, G, NLC, CANON>(g, x, d, loc, in, links, acc); break;
+            case 2: a_hop<1, +1, T, SI, G, NLC, CANON>(g, x, d, loc, in, links, acc); break;
+            case 3: a_hop<1, -1, T, SI, G, NLC, CANON>(g, x, d, loc, in, links, acc); break;
+            case 4: a_hop<2, +1, T, SI, G, NLC, CANON>(g, x, d, loc, in, links, acc); break;
+            case 5: a_hop<2, -1, T, SI, G, NLC, CANON>(g, x, d, loc, in, links, acc); break;
+            case 6: a_hop<3, +1, T, SI, G, NLC, CANON>(g, x, d, loc, in, links, acc); break;
+            default: a_hop<3, -1, T, SI, G, NLC, CANON>(g, x, d, loc, in, links, acc); break;
         }
     }
+    if constexpr (CANON) {
+        const unsigned b = (unsigned)canon_index(g, x) * 12;
 #pragma unroll
-    for (int k = 0; k < 12; k++) st<T, SO>(out, ((long)d * 12 + k) * Vd + loc, acc[k]);
+        for (int k = 0; k < 12; k++)
+            st32<double, double>(out, b + k, cx<double>{static_cast<double>(static_cast<SO>(acc[k].r)),
+                                                        static_cast<double>(static_cast<SO>(acc[k].i))});
+    } else {
+#pragma unroll
+        for (int k = 0; k < 12; k++) st<T, SO>(out, ((long)d * 12 + k) * Vd + loc, acc[k]);
+    }
 }
 
 // A on whole domains: a workgroup takes NT consecutive sites of the
-// domain-blocked order (NT / Vd whole domains) for R right-hand sides, one
-// thread per (site, right-hand side) with the R threads of a site adjacent,
-// so their link and clover loads are one request.  The workgroup's input
-// spinors are staged in LDS, and each site pushes its backward term
-// U_mu(x)^+ (1 + gamma_mu) psi(x) to the site x + mu through LDS, so inside a
-// domain every link and spinor is read from memory once (by its own site);
-// only hops that leave the domain read a neighbour domain's spinor (and,
-// backwards, its link).  The hops are summed in the order of k_apply_A (per
-// direction: forward, then backward) with the same products, so both kernels
-// give the same bits, for any R.  Field offsets are 32-bit byte offsets (the
-// host checks that every field is under 4 GiB), which keeps an address in
-// one VGPR.
-template <int R, typename SI, typename SO> struct RhsPtrs {
-    const v2<SI> *in[R];
-    v2<SO> *out[R];
-};
+// domain-blocked order (NT / Vd whole domains), one thread per site.  The
+// workgroup's input spinors are staged in LDS, and each site pushes its
+// backward term U_mu(x)^+ (1 + gamma_mu) psi(x) to the site x + mu through LDS,
+// so inside a domain every link and spinor is read from memory once (by its
+// own site); only hops that leave the domain read a neighbour domain's spinor
+// (and, backwards, its link).  The hops are summed in the order of k_apply_A
+// (per direction: forward, then backward) with the same products, so both
+// kernels give the same bits.  Field offsets are 32-bit byte offsets (the host
+// checks that every field is under 4 GiB), which keeps an address in one VGPR.
+//
+// CANON: in and out are the canonical FP64 fields of the interface (SI, SO the
+// precision in which the operator takes and returns its values): the domain's
+// spinors go from and to memory through LDS as its x-runs (contiguous there),
+// a neighbour domain's spinor is 192 contiguous bytes, and no separate layout
+// conversions are needed.
+//
+// Bound by memory.  FP64 on 32^3x64 with 4^4 domains, per right-hand side: in
+// canonical fields 802 us alone, 616 us when three share a launch (their
+// workgroups follow one another on one XCD, and the links and clover blocks
+// come from its L2: 960 + 192 bytes a site instead of 1536); a layout conversion
+// each way and one launch per right-hand side took 1065 us, two right-hand
+// sides in the lanes of one workgroup 728 us in canonical fields.
 
-template <int MU, int NT, int R, typename T, typename SI, typename G, int NLC>
-__device__ __forceinline__ void a_dom_dir(const Geo &g, const int x[4], int d, int loc, int ts, int r,
-                                          const v2<SI> *in, const v2<G> *links, cx<T> (*sp)[NT * R],
-                                          cx<T> (*ex)[NT * R], cx<T> acc[12])
+// Spinors in LDS: [12][NT + 1]; the odd stride keeps the twelve components of
+// one site, which consecutive lanes move to and from canonical memory, in
+// different banks.
+template <int MU, int NT, typename T, typename SI, typename G, int NLC, bool CANON>
+__device__ __forceinline__ void a_dom_dir(const Geo &g, const int x[4], int d, int loc, int ts,
+                                          const v2<std::conditional_t<CANON, double, SI>> *in, const v2<G> *links,
+                                          cx<T> (*sp)[NT + 1], cx<T> (*ex)[NT], cx<T> acc[12])
 {
     const unsigned Vd = (unsigned)g.Vd;
     const int base = ts - loc;                // first site of this site's domain in the workgroup
-    const int me = ts * R + r;                // this thread's LDS slot
     const int lx = x[MU] % g.b[MU];           // coordinate inside the domain
     cx<T> h[6], uh[6];
     {
@@ -539,13 +603,12 @@ __device__ __forceinline__ void a_dom_dir(const Geo &g, const int x[4], int d, i
             if (lx + 1 < g.b[MU]) {
                 const int lj = (int)(encode(g, y) - (long)d * Vd);
 #pragma unroll
-                for (int k = 0; k < 12; k++) v[k] = sp[k][(base + lj) * R + r];
+                for (int k = 0; k < 12; k++) v[k] = sp[k][base + lj];
             } else {
                 if (y[MU] == g.L[MU]) { y[MU] = 0; wrap = true; }
                 const long J = encode(g, y);
                 const unsigned dj = (unsigned)(J / Vd), lj = (unsigned)(J - (long)dj * Vd);
-#pragma unroll
-                for (int k = 0; k < 12; k++) v[k] = ld32<T, SI>(in, (dj * 12 + k) * Vd + lj);
+                a_load<T, SI, CANON>(g, in, y, dj, lj, v);
             }
             proj<MU, -1>(v, h);
             su3_mul(U, h, uh);
@@ -555,12 +618,12 @@ __device__ __forceinline__ void a_dom_dir(const Geo &g, const int x[4], int d, i
         {
             cx<T> v[12];
 #pragma unroll
-            for (int k = 0; k < 12; k++) v[k] = sp[k][me];
+            for (int k = 0; k < 12; k++) v[k] = sp[k][ts];
             proj<MU, +1>(v, h);
         }
         su3_dag_mul(U, h, uh);
 #pragma unroll
-        for (int k = 0; k < 6; k++) ex[k][me] = uh[k];
+        for (int k = 0; k < 6; k++) ex[k][ts] = uh[k];
     }
     __syncthreads();   // every push of this direction is in LDS
     // backward: -1/2 (1 + gamma_mu) U_mu(x - mu)^+ psi(x - mu)
@@ -569,7 +632,7 @@ __device__ __forceinline__ void a_dom_dir(const Geo &g, const int x[4], int d, i
         y[MU] = x[MU] - 1;
         const int lj = (int)(encode(g, y) - (long)d * Vd);
 #pragma unroll
-        for (int k = 0; k < 6; k++) uh[k] = ex[k][(base + lj) * R + r];
+        for (int k = 0; k < 6; k++) uh[k] = ex[k][base + lj];
         recon_acc<MU, +1>(acc, uh, T(-0.5));
     } else {
         int y[4] = {x[0], x[1], x[2], x[3]};
@@ -579,8 +642,7 @@ __device__ __forceinline__ void a_dom_dir(const Geo &g, const int x[4], int d, i
         const long J = encode(g, y);
         const unsigned dj = (unsigned)(J / Vd), lj = (unsigned)(J - (long)dj * Vd);
         cx<T> v[12];
-#pragma unroll
-        for (int k = 0; k < 12; k++) v[k] = ld32<T, SI>(in, (dj * 12 + k) * Vd + lj);
+        a_load<T, SI, CANON>(g, in, y, dj, lj, v);
         proj<MU, +1>(v, h);
         const unsigned lb = (dj * 4 + MU) * NLC * Vd + lj;
         const su3<T> W = ld_link_with<T, NLC>([&](int e) { return ld32<T, G>(links, lb + e * Vd); });
@@ -590,55 +652,80 @@ __device__ __forceinline__ void a_dom_dir(const Geo &g, const int x[4], int d, i
     __syncthreads();   // the pushes are consumed before the next direction's
 }
 
-template <int NT, int R, typename T, typename SI, typename SO, typename G, int NLC>
-__global__ __launch_bounds__(NT * R, 2) void k_apply_A_dom(Geo g, RhsPtrs<R, SI, SO> io, const v2<G> *links,
-                                                           const v2<G> *clov)
+template <int NT, typename T, typename SI, typename SO, typename G, int NLC, bool CANON>
+__global__ __launch_bounds__(NT, 2) void k_apply_A_dom(Geo g, RhsFields io, const v2<G> *links, const v2<G> *clov)
 {
-    __shared__ cx<T> sp[12][NT * R];   // the workgroup's input spinors
-    __shared__ cx<T> ex[6][NT * R];    // backward terms pushed to x + mu
-    // XCD-aware order as in k_apply_A: each XCD sweeps one contiguous eighth
-    const unsigned nbk = gridDim.x, w = blockIdx.x;
-    const unsigned blk = nbk % 8 == 0 ? (w % 8) * (nbk / 8) + w / 8 : w;
-    const int t = threadIdx.x, ts = t / R, r = t - ts * R;
-    const long I = (long)blk * NT + ts;   // V is a multiple of NT: every thread has a site
-    const v2<SI> *in = io.in[0];
-    v2<SO> *out = io.out[0];
-#pragma unroll
-    for (int q = 1; q < R; q++)
-        if (r == q) {
-            in = io.in[q];
-            out = io.out[q];
-        }
+    typedef std::conditional_t<CANON, double, SI> FI;
+    typedef std::conditional_t<CANON, double, SO> FO;
+    __shared__ cx<T> sp[12][NT + 1];           // the workgroup's input spinors
+    __shared__ cx<T> ex[6][NT];                // backward terms pushed to x + mu
+    __shared__ int2 site_of[CANON ? NT : 1];   // lexicographic sites: (canonical index, place in the workgroup)
+    unsigned blk, rhs;
+    rhs_block(io.n, blk, rhs);
+    const int t = threadIdx.x;
+    const long I = (long)blk * NT + t;         // V is a multiple of NT: every thread has a site
+    const v2<FI> *in = global_ptr((const v2<FI> *)io.in[rhs]);
+    v2<FO> *out = global_ptr((v2<FO> *)io.out[rhs]);
     int x[4], d, loc;
     decode(g, I, x, d, loc);
     const unsigned Vd = (unsigned)g.Vd;
     cx<T> acc[12];
+    if constexpr (CANON) {
+        site_of[t - loc + local_lex(g, x)] = make_int2((int)canon_index(g, x), t);
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < 12; i++) {
+            const int e = t + i * NT, sl = e / 12, k = e - sl * 12;
+            const int2 p = site_of[sl];
+            const cx<double> c = ld32<double, double>(in, (unsigned)p.x * 12 + k);
+            sp[k][p.y] = {static_cast<T>(static_cast<SI>(c.r)), static_cast<T>(static_cast<SI>(c.i))};
+        }
+        __syncthreads();
+    }
     {
         cx<T> s[12];
+        if constexpr (CANON) {
 #pragma unroll
-        for (int k = 0; k < 12; k++) s[k] = ld32<T, SI>(in, ((unsigned)d * 12 + k) * Vd + loc);
+            for (int k = 0; k < 12; k++) s[k] = sp[k][t];
+        } else {
 #pragma unroll
-        for (int k = 0; k < 12; k++) sp[k][t] = s[k];
+            for (int k = 0; k < 12; k++) s[k] = ld32<T, SI>(in, ((unsigned)d * 12 + k) * Vd + loc);
+#pragma unroll
+            for (int k = 0; k < 12; k++) sp[k][t] = s[k];
+        }
         const unsigned cb = (unsigned)d * 36 * Vd + loc;
         clover_block_with<T>([&](int q) { return ld32<T, G>(clov, cb + q * Vd); }, s, acc);
         clover_block_with<T>([&](int q) { return ld32<T, G>(clov, cb + (18 + q) * Vd); }, s + 6, acc + 6);
     }
-    __syncthreads();
+    if constexpr (!CANON) __syncthreads();
 #pragma unroll 1
     for (int mu = 0; mu < 4; mu++) {
         // the site's indices made opaque per direction: what is formed from
         // them (neighbour indices, offsets) is formed here, not hoisted out of
         // the loop and held in registers through it
-        int xs[4] = {x[0], x[1], x[2], x[3]}, ds = d, ls = loc, tss = ts;
+        int xs[4] = {x[0], x[1], x[2], x[3]}, ds = d, ls = loc, tss = t;
         asm volatile("" : "+v"(xs[0]), "+v"(xs[1]), "+v"(xs[2]), "+v"(xs[3]), "+v"(ds), "+v"(ls), "+v"(tss));
         switch (mu) {
-            case 0: a_dom_dir<0, NT, R, T, SI, G, NLC>(g, xs, ds, ls, tss, r, in, links, sp, ex, acc); break;
-            case 1: a_dom_dir<1, NT, R, T, SI, G, NLC>(g, xs, ds, ls, tss, r, in, links, sp, ex, acc); break;
-            case 2: a_dom_dir<2, NT, R, T, SI, G, NLC>(g, xs, ds, ls, tss, r, in, links, sp, ex, acc); break;
-            default: a_dom_dir<3, NT, R, T, SI, G, NLC>(g, xs, ds, ls, tss, r, in, links, sp, ex, acc); break;
+            case 0: a_dom_dir<0, NT, T, SI, G, NLC, CANON>(g, xs, ds, ls, tss, in, links, sp, ex, acc); break;
+            case 1: a_dom_dir<1, NT, T, SI, G, NLC, CANON>(g, xs, ds, ls, tss, in, links, sp, ex, acc); break;
+            case 2: a_dom_dir<2, NT, T, SI, G, NLC, CANON>(g, xs, ds, ls, tss, in, links, sp, ex, acc); break;
+            default: a_dom_dir<3, NT, T, SI, G, NLC, CANON>(g, xs, ds, ls, tss, in, links, sp, ex, acc); break;
         }
     }
-    {
+    if constexpr (CANON) {
+        // (the last direction's closing barrier: sp has been read)
+#pragma unroll
+        for (int k = 0; k < 12; k++) sp[k][t] = acc[k];
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < 12; i++) {
+            const int e = t + i * NT, sl = e / 12, k = e - sl * 12;
+            const int2 p = site_of[sl];
+            const cx<T> c = sp[k][p.y];
+            st32<double, double>(out, (unsigned)p.x * 12 + k,
+                                 cx<double>{static_cast<double>(static_cast<SO>(c.r)), static_cast<double>(static_cast<SO>(c.i))});
+        }
+    } else {
         int ds = d, ls = loc;   // output offsets formed here, not held through the hops
         asm volatile("" : "+v"(ds), "+v"(ls));
 #pragma unroll
@@ -646,27 +733,27 @@ __global__ __launch_bounds__(NT * R, 2) void k_apply_A_dom(Geo g, RhsPtrs<R, SI,
     }
 }
 
-template <int NT, int R, typename T, typename S, int NLC>
-static void launch_A_dom(const Geo &g, const void *const *in, void *const *out, const void *links, const void *clov,
-                         hipStream_t s)
+template <bool DOM, int NT, typename T, typename S, int NLC, bool CANON>
+static void launch_A(const Geo &g, const RhsFields &io, const void *links, const void *clov, hipStream_t s)
 {
-    RhsPtrs<R, S, S> io;
-    for (int q = 0; q < R; q++) {
-        io.in[q] = (const v2<S> *)in[q];
-        io.out[q] = (v2<S> *)out[q];
-    }
-    hipLaunchKernelGGL((k_apply_A_dom<NT, R, T, S, S, S, NLC>), (unsigned)(g.V / NT), NT * R, 0, s, g, io,
-                       (const v2<S> *)links, (const v2<S> *)clov);
+    if constexpr (DOM)
+        hipLaunchKernelGGL((k_apply_A_dom<NT, T, S, S, S, NLC, CANON>), (unsigned)(g.V / NT) * io.n, NT, 0, s, g, io,
+                           (const v2<S> *)links, (const v2<S> *)clov);
+    else
+        hipLaunchKernelGGL((k_apply_A<T, S, S, S, NLC, CANON>), nblocks(g.V, NT) * io.n, NT, 0, s, g, io,
+                           (const v2<S> *)links, (const v2<S> *)clov);
 }
 
-template <int NT, int R>
-static void launch_apply_A_dom(const Geo &g, const void *const *in, void *const *out, const void *links,
-                               const void *clov, int prec, hipStream_t s)
+template <bool DOM, int NT>
+static void launch_apply_A(const Geo &g, const RhsFields &io, const void *links, const void *clov, int prec, bool canon,
+                           hipStream_t s)
 {
-    if (prec == P64) launch_A_dom<NT, R, double, double, 9>(g, in, out, links, clov, s);
-    else if (prec == P32) launch_A_dom<NT, R, float, float, 6>(g, in, out, links, clov, s);
-    else if (prec == P16) launch_A_dom<NT, R, float, half_t, 6>(g, in, out, links, clov, s);
-    else launch_A_dom<NT, R, float, bf16_t, 6>(g, in, out, links, clov, s);
+    if (canon && prec == P64) launch_A<DOM, NT, double, double, 9, true>(g, io, links, clov, s);
+    else if (canon) launch_A<DOM, NT, float, float, 6, true>(g, io, links, clov, s);
+    else if (prec == P64) launch_A<DOM, NT, double, double, 9, false>(g, io, links, clov, s);
+    else if (prec == P32) launch_A<DOM, NT, float, float, 6, false>(g, io, links, clov, s);
+    else if (prec == P16) launch_A<DOM, NT, float, half_t, 6, false>(g, io, links, clov, s);
+    else launch_A<DOM, NT, float, bf16_t, 6, false>(g, io, links, clov, s);
 }
 
 // whole domains per workgroup where the domain size divides the workgroup's
@@ -681,43 +768,72 @@ static int dom_sites(const Geo &g, int prec)
     return 0;
 }
 
-bool apply_A_pairs(const Geo &g, int prec) { return dom_sites(g, prec) == 256; }
-
-hipError_t apply_A_pair(const Geo &g, const void *in0, void *out0, const void *in1, void *out1, const void *links,
-                        const void *clov, int prec, hipStream_t s)
+// Whole domains per workgroup, or one thread per site: the latter for domains
+// without such a kernel (288 sites), and where the launch has at most one
+// workgroup per CU, which then lasts as long as one workgroup: without LDS and
+// barriers it waits for memory less often (8^4 in canonical fields: FP64 18.7
+// against 21.3 us, FP32 15.9 against 20.9; 16^3x32 with three right-hand sides,
+// 1536 workgroups: FP64 162 against 116 us for all).  Not in FP16, where the two
+// kernels' third link rows are not contracted alike and the bits would depend
+// on the number of right-hand sides.
+static hipError_t apply_A_rhs(const Geo &g, const void *const *in, void *const *out, int n, const void *links,
+                              const void *clov, int prec, bool canon, hipStream_t s)
 {
-    if (!apply_A_pairs(g, prec)) return hipErrorInvalidValue;
-    const void *in[2] = {in0, in1};
-    void *out[2] = {out0, out1};
-    launch_apply_A_dom<256, 2>(g, in, out, links, clov, prec, s);
-    return hipGetLastError();
+    const int nt = dom_sites(g, prec);
+    for (int k = 0; k < n; k += A_MAX_RHS) {
+        RhsFields io{};
+        io.n = n - k < A_MAX_RHS ? n - k : A_MAX_RHS;
+        for (int q = 0; q < io.n; q++) {
+            io.in[q] = in[k + q];
+            io.out[q] = out[k + q];
+        }
+        const bool few = g.V / 256 * io.n <= 256 && prec != P16;
+        if (!nt || few) launch_apply_A<false, 256>(g, io, links, clov, prec, canon, s);
+        else if (nt == 256) launch_apply_A<true, 256>(g, io, links, clov, prec, canon, s);
+        else launch_apply_A<true, 512>(g, io, links, clov, prec, canon, s);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+
+// FP64 and FP32 only: with 16-bit storage the neighbours' FP64 spinors cost more
+// than the conversions save (BF16 on 32^3x64: 551 against 521 us); the field
+// under 4 GiB (32-bit byte offsets)
+bool apply_A_canonical_fits(const Geo &g, int prec)
+{
+    return (prec == P64 || prec == P32) && (size_t)g.V * 12 * 16 < ((size_t)1 << 32);
+}
+
+hipError_t apply_A_canonical(const Geo &g, const double *in, double *out, int nrhs, const void *links, const void *clov,
+                             int prec, hipStream_t s)
+{
+    if (!apply_A_canonical_fits(g, prec)) return hipErrorInvalidValue;
+    const size_t n = (size_t)g.V * 24;
+    const void *ins[A_MAX_RHS];
+    void *outs[A_MAX_RHS];
+    for (int k = 0; k < nrhs; k += A_MAX_RHS) {
+        const int take = nrhs - k < A_MAX_RHS ? nrhs - k : A_MAX_RHS;
+        for (int q = 0; q < take; q++) {
+            ins[q] = in + (size_t)(k + q) * n;
+            outs[q] = out + (size_t)(k + q) * n;
+        }
+        const hipError_t e = apply_A_rhs(g, ins, outs, take, links, clov, prec, true, s);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+
+hipError_t apply_A_multi(const Geo &g, const void *const *in, void *const *out, int n, const void *links, const void *clov,
+                         int prec, hipStream_t s)
+{
+    return apply_A_rhs(g, in, out, n, links, clov, prec, false, s);
 }
 
 hipError_t apply_A(const Geo &g, const void *in, void *out, const void *links, const void *clov, int prec,
                    hipStream_t s)
 {
-    unsigned nb = nblocks(g.V, 256);
-    const int nt = dom_sites(g, prec);
-    if (nt) {
-        const void *ins[1] = {in};
-        void *outs[1] = {out};
-        if (nt == 256) launch_apply_A_dom<256, 1>(g, ins, outs, links, clov, prec, s);
-        else launch_apply_A_dom<512, 1>(g, ins, outs, links, clov, prec, s);
-        return hipGetLastError();
-    }
-    if (prec == P64)
-        hipLaunchKernelGGL((k_apply_A<double, double, double, double, 9>), nb, 256, 0, s, g, (const double2 *)in,
-                           (double2 *)out, (const double2 *)links, (const double2 *)clov);
-    else if (prec == P32)
-        hipLaunchKernelGGL((k_apply_A<float, float, float, float, 6>), nb, 256, 0, s, g, (const float2 *)in,
-                           (float2 *)out, (const float2 *)links, (const float2 *)clov);
-    else if (prec == P16)
-        hipLaunchKernelGGL((k_apply_A<float, half_t, half_t, half_t, 6>), nb, 256, 0, s, g, (const half2_t *)in,
-                           (half2_t *)out, (const half2_t *)links, (const half2_t *)clov);
-    else
-        hipLaunchKernelGGL((k_apply_A<float, bf16_t, bf16_t, bf16_t, 6>), nb, 256, 0, s, g, (const bf162_t *)in,
-                           (bf162_t *)out, (const bf162_t *)links, (const bf162_t *)clov);
-    return hipGetLastError();
+    return apply_A_multi(g, &in, &out, 1, links, clov, prec, s);
 }
 
 // ===========================================================================
