@@ -16,6 +16,7 @@
 #include <complex>
 #include <cstdio>
 #include <cstring>
+#include <functional>
 #include <map>
 #include <memory>
 #include <mutex>
@@ -1987,7 +1988,12 @@ int ddqcd_apply_D(ddqcd_t c, double *out, const double *in, int nrhs, int prec, 
     if (e || (e = ensure_slots(c, 1))) return e;
     hipStream_t s = (hipStream_t)stream;
     const Geo &g = c->g;
-    if (apply_A_canonical_fits(g, prec)) {
+    // (overlapping buffers, such as an output shifted by one right-hand side:
+    // one right-hand side after the other through the internal layout, below)
+    const double *const in_end = in + (size_t)nrhs * ncomplex(g) * 2;
+    const double *const out_end = out + (size_t)nrhs * ncomplex(g) * 2;
+    const bool apart = std::less_equal<const double *>()(in_end, out) || std::less_equal<const double *>()(out_end, in);
+    if (apart && apply_A_canonical_fits(g, prec)) {
         HIPCHK(c, apply_A_canonical(g, in, out, nrhs, links_for(c, prec), clover_for(c, prec), prec, s));
         return DDQCD_OK;
     }
