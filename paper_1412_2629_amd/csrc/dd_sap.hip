@@ -547,27 +547,6 @@ template <class Sh, int MU, int SIGN> __device__ __forceinline__ int hop_step(in
     return MU == 0 ? (SIGN < 0 ? ox : ox - 1) : SIGN < 0 ? STEP : -STEP;
 }
 
-// acc += the hop into a site along MU: (1 - gamma_mu) U_mu(x) v(x + mu) for
-// SIGN < 0, (1 + gamma_mu) U_mu(x - mu)^dagger v(x - mu) for SIGN > 0.  v: this
-// right-hand side's spinor of the other parity's site with this site's half
-// index hi in LDS ([6][VH][RT]); loc: the site, op: the first site of the other
-// parity.  Neighbour offsets are constants (one address register for x, one
-// for the other directions), so LDS addresses are immediates.
-template <class Sh, int MU, int SIGN, int RT, typename Links>
-__device__ __forceinline__ void lds_hop(const c2_t *v, const int l[4], int loc, int op, int hi, int ox, const Links &links,
-                                        cx<float> acc[12])
-{
-    if (!hop_exists<Sh, MU, SIGN>(l)) return;
-    const int dn = hop_step<Sh, MU, SIGN>(ox);
-    cx<float> s[12], h[6], uh[6];
-    ld_c2<Sh::VH * RT>(v + dn * RT, s);
-    proj<MU, SIGN>(s, h);
-    const su3<float> U = links(MU, SIGN < 0 ? loc : op + hi + dn);
-    if constexpr (SIGN < 0) su3_mul(U, h, uh);
-    else su3_dag_mul(U, h, uh);
-    recon_acc<MU, SIGN>(acc, uh, 1.0f);
-}
-
 // ---- one right-hand side per workgroup -------------------------------------
 //
 // One workgroup per domain, one thread per site.  Each thread holds its own
