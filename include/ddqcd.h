@@ -160,7 +160,7 @@ int ddqcd_set_schwarz(ddqcd_t ctx, int kind);
  * clover term and C_e / C_o^-1 in every precision; per right-hand side the
  * work slot (solution accumulator, block residual, boundary terms of both
  * Schwarz variants, FP64 vectors, reduction buffers, the FGCR basis of 2 x
- * max(restart, 5) vectors); the apply_D operands; the reduction area; and a
+ * max(restart, 5) vectors); the apply_D operands; and a
  * region for launch plans.  ddqcd_set_workspace hands the context dev_ptr
  * (device memory of the device ddqcd_load_gauge will run on, 256-byte
  * aligned, at least ddqcd_workspace_size(ctx, 1) bytes), before

@@ -140,8 +140,8 @@ struct ddqcd_ctx {
     std::vector<hipEvent_t> side_done;
     hipEvent_t fork = nullptr;
     // reduction results of the systems of a solve led by this context, side by
-    // side (32 pairs each) on the device and in pinned host memory
-    double2 *res_dev = nullptr, *res_host = nullptr;
+    // side (32 pairs each) in pinned host memory, written by the reductions
+    double2 *res_host = nullptr;
     int res_cap = 0;
     std::vector<std::unique_ptr<Slot>> slots;
     std::map<std::string, std::unique_ptr<Plan>> plans;   // batch plans led by this context
@@ -264,7 +264,6 @@ int ensure_slots(ddqcd_t c, int n)
         if ((e = alloc(c, &sl->r, nc * 16))) return e;
         if ((e = alloc(c, &sl->b, nc * 16))) return e;
         if ((e = alloc(c, &sl->blas.partial, sizeof(double2) * BLAS_NBLK * 32))) return e;
-        if ((e = alloc(c, &sl->blas.result, sizeof(double2) * 32))) return e;
         if ((e = alloc(c, &sl->blas.coef, sizeof(double2) * 32))) return e;
         if ((e = alloc(c, &sl->rcoef, sizeof(double2) * RCOEF))) return e;
         c->slots.push_back(std::move(sl));
@@ -674,15 +673,14 @@ struct FgcrState {
     int status = DDQCD_ERR_NOT_CONVERGED;
     std::vector<C> a, cc, alpha;
     std::vector<double> bb;
-    double2 h[32];          // results of the last reduction
+    double2 h[32];          // results of the last reductions
 };
 
-// During a solve every system's reduction results live side by side in the
-// lead context's result area (system i at pairs [32 i, 32 i + 32)), so one
-// copy into pinned memory and one wait read all of them back.
+// During a solve the reductions write every system's results into the lead
+// context's pinned host area (system i at pairs [32 i, 32 i + 32)): one wait
+// makes them all readable.
 struct ResultArea {
     const std::vector<Sys> &sys;
-    std::vector<double2 *> saved;
     ddqcd_t lead;
     explicit ResultArea(const std::vector<Sys> &s) : sys(s), lead(s[0].c) {}
     int bind()
@@ -691,53 +689,38 @@ struct ResultArea {
         if (lead->res_cap < ns && lead->ws)
             return fail(lead, DDQCD_ERR_NOMEM, "more systems than the workspace's reduction area holds (" +
                                                    std::to_string(lead->res_cap) + ")");
-        if (!lead->res_host && lead->res_cap > 0)   // pinned host copy of a workspace's reduction area
-            HIPCHK(lead, hipHostMalloc((void **)&lead->res_host, sizeof(double2) * 32 * lead->res_cap,
-                                       hipHostMallocDefault));
-        if (lead->res_cap < ns) {
-            int e;
-            if ((e = alloc(lead, &lead->res_dev, sizeof(double2) * 32 * ns))) return e;
+        if (!lead->res_host || lead->res_cap < ns) {
+            const int cap = std::max(lead->res_cap, ns);
             if (lead->res_host) (void)hipHostFree(lead->res_host);
             lead->res_host = nullptr;
-            lead->res_cap = 0;
-            HIPCHK(lead, hipHostMalloc((void **)&lead->res_host, sizeof(double2) * 32 * ns, hipHostMallocDefault));
-            lead->res_cap = ns;
+            HIPCHK(lead, hipHostMalloc((void **)&lead->res_host, sizeof(double2) * 32 * cap, hipHostMallocDefault));
+            lead->res_cap = cap;
         }
-        for (int i = 0; i < ns; i++) {
-            saved.push_back(sys[i].sl->blas.result);
-            sys[i].sl->blas.result = lead->res_dev + 32L * i;
-        }
+        for (int i = 0; i < ns; i++) sys[i].sl->blas.result = lead->res_host + 32L * i;
         return DDQCD_OK;
     }
     ~ResultArea()
     {
-        for (size_t i = 0; i < saved.size(); i++) sys[i].sl->blas.result = saved[i];
+        for (const Sys &y : sys) y.sl->blas.result = nullptr;
     }
 };
 
-// read back result[0..m-1] of every listed system with one copy and one wait
-int fetch_all(const std::vector<Sys> &sys, std::vector<FgcrState> &st, const std::vector<int> &which, int m,
-              hipStream_t s)
+// wait for the reductions launched so far; h: their results
+int fetch(const Sys &y, double2 h[32], hipStream_t s)
+{
+    HIPCHK(y.c, hipStreamSynchronize(s));
+    std::copy(y.sl->blas.result, y.sl->blas.result + 32, h);
+    return DDQCD_OK;
+}
+int fetch_all(const std::vector<Sys> &sys, std::vector<FgcrState> &st, const std::vector<int> &which, hipStream_t s)
 {
     if (which.empty()) return DDQCD_OK;
-    ddqcd_t lead = sys[0].c;
-    const int lo = *std::min_element(which.begin(), which.end());
-    const int hi = *std::max_element(which.begin(), which.end());
-    const size_t off = 32L * lo, len = 32L * (hi - lo) + m;
-    HIPCHK(lead, hipMemcpyAsync(lead->res_host + off, lead->res_dev + off, sizeof(double2) * len,
-                                hipMemcpyDeviceToHost, s));
-    HIPCHK(lead, hipStreamSynchronize(s));
-    for (int i : which) std::copy(lead->res_host + 32L * i, lead->res_host + 32L * i + m, st[i].h);
+    HIPCHK(sys[0].c, hipStreamSynchronize(s));
+    for (int i : which) std::copy(sys[i].sl->blas.result, sys[i].sl->blas.result + 32, st[i].h);
     return DDQCD_OK;
 }
-
-int put_coef(const Sys &y, const std::vector<C> &v, hipStream_t s)
-{
-    static_assert(sizeof(C) == sizeof(double2), "layout");
-    if (v.empty()) return DDQCD_OK;
-    HIPCHK(y.c, hipMemcpyAsync(y.sl->blas.coef, v.data(), sizeof(double2) * v.size(), hipMemcpyHostToDevice, s));
-    return DDQCD_OK;
-}
+static_assert(sizeof(C) == sizeof(double2), "layout");
+const double2 *pairs(const std::vector<C> &v) { return (const double2 *)v.data(); }
 
 // Solves A x = b for every system (x, b: the slot's internal FP64 vectors; x
 // holds a guess where guess[i]).  The timings are those of the whole batch.
@@ -764,15 +747,27 @@ int fgcr(const std::vector<Sys> &sys, const std::vector<int> &guess, std::vector
     auto nc = [&](int i) { return ncomplex(sys[i].c->g); };
     auto Zk = [&](int i, int k) { return sys[i].sl->Z + (long)k * nc(i); };
     auto Wk = [&](int i, int k) { return sys[i].sl->W + (long)k * nc(i); };
+    // the listed systems' operands: w from w_of, the columns W and r the slot's own
+    auto ops = [&](const std::vector<int> &which, auto w_of) {
+        std::vector<BlasOp> v;
+        for (int i : which) {
+            v.push_back(blas_op(sys[i].sl->blas, nc(i)));
+            v.back().W = sys[i].sl->W;
+            v.back().w = w_of(i);
+            v.back().r = sys[i].sl->r;
+        }
+        return v;
+    };
+    auto b_of = [&](int i) { return sys[i].sl->b; };
 
     // |b| and the initial residual
     std::vector<int> all(ns), live;
     for (int i = 0; i < ns; i++) {
         all[i] = i;
         if (!guess[i]) HIPCHK(sys[i].c, zero(sys[i].sl->x, nc(i), s));
-        HIPCHK(sys[i].c, norm2(sys[i].sl->blas, sys[i].sl->b, nc(i), s));
     }
-    if ((e = fetch_all(sys, st, all, 1, s))) return e;
+    HIPCHK(lead, norm2(ops(all, b_of), s));
+    if ((e = fetch_all(sys, st, all, s))) return e;
     for (int i = 0; i < ns; i++) {
         st[i].bn = std::sqrt(st[i].h[0].x);
         if (!std::isfinite(st[i].bn)) return fail(sys[i].c, DDQCD_ERR_NONFINITE, "non-finite right-hand side");
@@ -801,8 +796,8 @@ int fgcr(const std::vector<Sys> &sys, const std::vector<int> &guess, std::vector
     }
     {
         Timer t(clk, &tother);
-        for (int i : guessed) HIPCHK(sys[i].c, residual(sys[i].sl->blas, sys[i].sl->b, sys[i].sl->r, nc(i), s));
-        if (!guessed.empty() && (e = fetch_all(sys, st, guessed, 1, s))) return e;
+        HIPCHK(lead, residual(ops(guessed, b_of), s));
+        if ((e = fetch_all(sys, st, guessed, s))) return e;
     }
     for (int i : live) {
         st[i].rel = guess[i] ? std::sqrt(st[i].h[0].x) / st[i].bn : 1.0;
@@ -850,66 +845,43 @@ int fgcr(const std::vector<Sys> &sys, const std::vector<int> &guess, std::vector
             {
                 Timer t(clk, &tgs);
                 // classical Gram-Schmidt against the earlier w-hat, repeated
-                // once for a system whose new vector lost more than half its norm
-                std::vector<double> before(ns, 0), wn2(ns, 0);
-                std::vector<C> wr(ns);
+                // once for a system whose new vector lost more than half its norm.
+                // The columns of W are kept unnormalised, W_j = b_j w-hat_j:
+                // <w-hat_j, w> = <W_j, w> / b_j, and w -= sum <w-hat_j, w> w-hat_j
+                // takes the coefficients <W_j, w> / b_j^2 on the columns.  The step
+                // is launched as a whole (fgcr_step); the host reads what it did.
                 std::vector<int> todo = act;
                 for (int pass = 0; pass < 2 && !todo.empty(); pass++) {
                     // the first pass also takes <w, w> (column k of W is w itself),
                     // which only the repeat test reads: not for the first vector
                     const int nd = pass == 0 && k > 0 ? k + 1 : k;
-                    if (nd > 0) {
-                        for (int i : todo)
-                            HIPCHK(sys[i].c, multidot(sys[i].sl->blas, sys[i].sl->W, nc(i), nd, Wk(i, k), nc(i), s));
-                        if ((e = fetch_all(sys, st, todo, nd, s))) return e;
-                        for (int i : todo) {
-                            if (pass == 0) before[i] = st[i].h[k].x;
-                            if (k == 0) continue;
-                            // the columns of W are kept unnormalised, W_j = b_j w-hat_j:
-                            // <w-hat_j, w> = <W_j, w> / b_j, and w -= sum <w-hat_j, w> w-hat_j
-                            // takes the coefficients <W_j, w> / b_j^2 on the columns
-                            std::vector<C> coef(k);
-                            for (int j = 0; j < k; j++) {
-                                const C cj = C(st[i].h[j].x, st[i].h[j].y) / st[i].bb[j];
-                                st[i].a[(size_t)j * m + k] += cj;
-                                coef[j] = cj / st[i].bb[j];
-                            }
-                            if ((e = put_coef(sys[i], coef, s))) return e;
-                        }
-                    }
-                    for (int i : todo)
-                        HIPCHK(sys[i].c, cgs_update(sys[i].sl->blas, Wk(i, k), sys[i].sl->W, nc(i), k, sys[i].sl->r,
-                                                    nc(i), s));
-                    if ((e = fetch_all(sys, st, todo, 2, s))) return e;
+                    const bool may_repeat = pass == 0 && k > 0;
+                    HIPCHK(lead, fgcr_step(ops(todo, [&](int i) { return Wk(i, k); }), k, nd, may_repeat, s));
+                    if ((e = fetch_all(sys, st, todo, s))) return e;
                     std::vector<int> again;
                     for (int i : todo) {
-                        wn2[i] = st[i].h[0].x;
-                        wr[i] = C(st[i].h[1].x, st[i].h[1].y);
-                        if (k > 0 && !(wn2[i] > 0.25 * before[i])) {
-                            before[i] = wn2[i];
+                        FgcrState &f = st[i];
+                        const double2 *h = f.h + STEP_DOTS;
+                        for (int j = 0; j < k; j++) f.a[(size_t)j * m + k] += C(h[j].x, h[j].y) / f.bb[j];
+                        const double wn2 = f.h[STEP_W].x;
+                        if (may_repeat && !(wn2 > 0.25 * h[k].x)) {
                             again.push_back(i);
+                            continue;
                         }
+                        f.bb[k] = std::sqrt(wn2);
+                        if (!(f.bb[k] > 0) || !std::isfinite(f.bb[k]))
+                            return fail(sys[i].c, DDQCD_ERR_NONFINITE, "breakdown: A M r vanished or is non-finite");
+                        // r -= <w-hat, r> w-hat = (<w, r> / b^2) w; w stays unnormalised
+                        f.cc[k] = C(f.h[STEP_W + 1].x, f.h[STEP_W + 1].y) / f.bb[k];
                     }
                     todo = again;
                 }
-                for (int i : act) {
-                    FgcrState &f = st[i];
-                    f.bb[k] = std::sqrt(wn2[i]);
-                    if (!(f.bb[k] > 0) || !std::isfinite(f.bb[k]))
-                        return fail(sys[i].c, DDQCD_ERR_NONFINITE, "breakdown: A M r vanished or is non-finite");
-                    f.cc[k] = wr[i] / f.bb[k];
-                    // r -= <w-hat, r> w-hat = (<w, r> / b^2) w; w stays unnormalised
-                    const C al = f.cc[k] / f.bb[k];
-                    HIPCHK(sys[i].c, residual_update(sys[i].sl->blas, Wk(i, k), sys[i].sl->r,
-                                                     make_double2(al.real(), al.imag()), nc(i), s));
-                }
-                if ((e = fetch_all(sys, st, act, 1, s))) return e;
             }
             for (int i : act) {
                 FgcrState &f = st[i];
                 f.steps++;
                 f.kend = k + 1;
-                f.rel = std::sqrt(f.h[0].x) / f.bn;
+                f.rel = std::sqrt(f.h[STEP_R].x) / f.bn;
                 if (!std::isfinite(f.rel)) return fail(sys[i].c, DDQCD_ERR_NONFINITE, "non-finite residual");
                 if (f.rel <= tol) f.in_cycle = false;
             }
@@ -924,9 +896,7 @@ int fgcr(const std::vector<Sys> &sys, const std::vector<int> &guess, std::vector
                     for (int j = k + 1; j < f.kend; j++) sum -= f.a[(size_t)k * m + j] * f.alpha[j];
                     f.alpha[k] = sum / f.bb[k];
                 }
-                std::vector<C> al(f.alpha.begin(), f.alpha.begin() + f.kend);
-                if ((e = put_coef(sys[i], al, s))) return e;
-                HIPCHK(sys[i].c, axpy_multi(sys[i].sl->blas, sys[i].sl->x, sys[i].sl->Z, nc(i), f.kend, nc(i), s));
+                HIPCHK(sys[i].c, axpy_multi(sys[i].sl->x, sys[i].sl->Z, pairs(f.alpha), f.kend, nc(i), s));
                 std::fill(f.a.begin(), f.a.end(), C(0));
             }
         }
@@ -939,8 +909,8 @@ int fgcr(const std::vector<Sys> &sys, const std::vector<int> &guess, std::vector
         }
         {
             Timer t(clk, &tother);
-            for (int i : cur) HIPCHK(sys[i].c, residual(sys[i].sl->blas, sys[i].sl->b, sys[i].sl->r, nc(i), s));
-            if ((e = fetch_all(sys, st, cur, 1, s))) return e;
+            HIPCHK(lead, residual(ops(cur, b_of), s));
+            if ((e = fetch_all(sys, st, cur, s))) return e;
         }
         for (int i : cur) {
             FgcrState &f = st[i];
@@ -1164,11 +1134,9 @@ int fgmres_dr(const Sys &y, bool guess, ddqcd_info &info, hipStream_t s)
     double tsap = 0, tA = 0, tgs = 0, tother = 0;
     Clock clk(s);
     double2 h[32];
-    auto fetch = [&](int cnt) -> int {
-        HIPCHK(c, hipMemcpyAsync(h, sl.blas.result, sizeof(double2) * cnt, hipMemcpyDeviceToHost, s));
-        HIPCHK(c, hipStreamSynchronize(s));
-        return DDQCD_OK;
-    };
+    const std::vector<Sys> self{y};
+    ResultArea area(self);
+    if ((e = area.bind())) return e;
     auto put = [&](const std::vector<C> &v, double2 *dst) -> int {
         HIPCHK(c, hipMemcpyAsync(dst, v.data(), sizeof(double2) * v.size(), hipMemcpyHostToDevice, s));
         return DDQCD_OK;
@@ -1176,7 +1144,7 @@ int fgmres_dr(const Sys &y, bool guess, ddqcd_info &info, hipStream_t s)
     info = ddqcd_info{};
     if (!guess) HIPCHK(c, zero(sl.x, n, s));
     HIPCHK(c, norm2(sl.blas, sl.b, n, s));
-    if ((e = fetch(1))) return e;
+    if ((e = fetch(y, h, s))) return e;
     const double bn = std::sqrt(h[0].x);
     if (!std::isfinite(bn)) return fail(c, DDQCD_ERR_NONFINITE, "non-finite right-hand side");
     if (bn == 0) {
@@ -1190,7 +1158,7 @@ int fgmres_dr(const Sys &y, bool guess, ddqcd_info &info, hipStream_t s)
         if ((e = apply_A64(c, sl.x, sl.r, s))) return e;
     }
     HIPCHK(c, residual(sl.blas, sl.b, sl.r, n, s));
-    if ((e = fetch(1))) return e;
+    if ((e = fetch(y, h, s))) return e;
     rn = std::sqrt(h[0].x);
     double rel = rn / bn;
     if (!std::isfinite(rel)) return fail(c, DDQCD_ERR_NONFINITE, "non-finite residual");
@@ -1222,26 +1190,26 @@ int fgmres_dr(const Sys &y, bool guess, ddqcd_info &info, hipStream_t s)
                 std::vector<C> hsum(j + 1, 0.0);
                 // first pass; <w, w> in the same multi-dot where the column fits
                 const bool joint = j + 2 <= BLAS_MAXK;
-                HIPCHK(c, multidot(sl.blas, Vb, n, joint ? j + 2 : j + 1, w, n, s));
-                if ((e = fetch(joint ? j + 2 : j + 1))) return e;
+                HIPCHK(c, multidot(sl.blas, Vb, joint ? j + 2 : j + 1, w, n, s));
+                if ((e = fetch(y, h, s))) return e;
                 std::vector<C> coef(j + 1);
                 for (int i = 0; i <= j; i++) coef[i] = C(h[i].x, h[i].y);
                 if (joint) before = h[j + 1].x;
                 else {
                     HIPCHK(c, norm2(sl.blas, w, n, s));
-                    if ((e = fetch(1))) return e;
+                    if ((e = fetch(y, h, s))) return e;
                     before = h[0].x;
                 }
                 for (int pass = 0; pass < 2; pass++) {
                     for (int i = 0; i <= j; i++) hsum[i] += coef[i];
                     if ((e = put(coef, sl.blas.coef))) return e;
-                    HIPCHK(c, cgs_update(sl.blas, w, Vb, n, j + 1, w, n, s));
-                    if ((e = fetch(1))) return e;
+                    HIPCHK(c, cgs_update(sl.blas, w, Vb, j + 1, w, n, s));
+                    if ((e = fetch(y, h, s))) return e;
                     wn2 = h[0].x;
                     if (pass == 1 || wn2 > 0.25 * before) break;
                     before = wn2;
-                    HIPCHK(c, multidot(sl.blas, Vb, n, j + 1, w, n, s));
-                    if ((e = fetch(j + 1))) return e;
+                    HIPCHK(c, multidot(sl.blas, Vb, j + 1, w, n, s));
+                    if ((e = fetch(y, h, s))) return e;
                     for (int i = 0; i <= j; i++) coef[i] = C(h[i].x, h[i].y);
                 }
                 const double hn = std::sqrt(wn2);
@@ -1262,15 +1230,14 @@ int fgmres_dr(const Sys &y, bool guess, ddqcd_info &info, hipStream_t s)
         }
         {
             Timer t(clk, &tother);
-            if ((e = put(std::vector<C>(yv.begin(), yv.begin() + jend), sl.blas.coef))) return e;
-            HIPCHK(c, axpy_multi(sl.blas, sl.x, Zb, n, jend, n, s));
+            HIPCHK(c, axpy_multi(sl.x, Zb, pairs(yv), jend, n, s));
         }
         {
             Timer t(clk, &tA);
             if ((e = apply_A64(c, sl.x, sl.r, s))) return e;
         }
         HIPCHK(c, residual(sl.blas, sl.b, sl.r, n, s));
-        if ((e = fetch(1))) return e;
+        if ((e = fetch(y, h, s))) return e;
         rn = std::sqrt(h[0].x);
         rel = rn / bn;
         cycles++;
@@ -1376,11 +1343,9 @@ int fgcr_mixed(const Sys &y, bool guess, ddqcd_info &info, hipStream_t s)
     double tsap = 0, tA = 0, tgs = 0, tother = 0;
     Clock clk(s);
     double2 h[32];
-    auto fetch = [&](int cnt) -> int {
-        HIPCHK(c, hipMemcpyAsync(h, sl.blas.result, sizeof(double2) * cnt, hipMemcpyDeviceToHost, s));
-        HIPCHK(c, hipStreamSynchronize(s));
-        return DDQCD_OK;
-    };
+    const std::vector<Sys> self{y};
+    ResultArea area(self);
+    if ((e = area.bind())) return e;
     auto put = [&](const std::vector<C> &v) -> int {
         HIPCHK(c, hipMemcpyAsync(sl.blas.coef, v.data(), sizeof(double2) * v.size(), hipMemcpyHostToDevice, s));
         return DDQCD_OK;
@@ -1388,7 +1353,7 @@ int fgcr_mixed(const Sys &y, bool guess, ddqcd_info &info, hipStream_t s)
     info = ddqcd_info{};
     if (!guess) HIPCHK(c, zero(sl.x, n, s));
     HIPCHK(c, norm2(sl.blas, sl.b, n, s));
-    if ((e = fetch(1))) return e;
+    if ((e = fetch(y, h, s))) return e;
     const double bn = std::sqrt(h[0].x);
     if (!std::isfinite(bn)) return fail(c, DDQCD_ERR_NONFINITE, "non-finite right-hand side");
     if (bn == 0) {
@@ -1407,7 +1372,7 @@ int fgcr_mixed(const Sys &y, bool guess, ddqcd_info &info, hipStream_t s)
             if ((e = apply_A64(c, sl.x, sl.r, s))) return e;
         }
         HIPCHK(c, residual(sl.blas, sl.b, sl.r, n, s));
-        if ((e = fetch(1))) return e;
+        if ((e = fetch(y, h, s))) return e;
         const double rn = std::sqrt(h[0].x);
         rel = rn / bn;
         if (!std::isfinite(rel)) return fail(c, DDQCD_ERR_NONFINITE, "non-finite residual");
@@ -1435,7 +1400,7 @@ int fgcr_mixed(const Sys &y, bool guess, ddqcd_info &info, hipStream_t s)
             double before = 0, wn2 = 0;
             if (k > 0) {
                 HIPCHK(c, multidot32(sl.blas, W32, n, k + 1, wk, n, s));   // column k is w itself
-                if ((e = fetch(k + 1))) return e;
+                if ((e = fetch(y, h, s))) return e;
                 before = h[k].x;
                 for (int pass = 0; pass < 2; pass++) {
                     std::vector<C> coef(k);
@@ -1445,26 +1410,26 @@ int fgcr_mixed(const Sys &y, bool guess, ddqcd_info &info, hipStream_t s)
                     }
                     if ((e = put(coef))) return e;
                     HIPCHK(c, cgs_update32(sl.blas, wk, W32, n, k, n, s));
-                    if ((e = fetch(1))) return e;
+                    if ((e = fetch(y, h, s))) return e;
                     wn2 = h[0].x;
                     if (pass == 1 || wn2 > 0.25 * before) break;
                     before = wn2;
                     HIPCHK(c, multidot32(sl.blas, W32, n, k, wk, n, s));
-                    if ((e = fetch(k))) return e;
+                    if ((e = fetch(y, h, s))) return e;
                 }
             } else {
                 HIPCHK(c, multidot32(sl.blas, wk, n, 1, wk, n, s));
-                if ((e = fetch(1))) return e;
+                if ((e = fetch(y, h, s))) return e;
                 wn2 = h[0].x;
             }
             bb[k] = std::sqrt(wn2);
             if (!(bb[k] > 0) || !std::isfinite(bb[k]))
                 return fail(c, DDQCD_ERR_NONFINITE, "breakdown: A M r vanished or is non-finite");
             HIPCHK(c, scale_dot32(sl.blas, wk, 1.0 / bb[k], r32, n, s));
-            if ((e = fetch(1))) return e;
+            if ((e = fetch(y, h, s))) return e;
             cc[k] = C(h[0].x, h[0].y);
             HIPCHK(c, axpy32(sl.blas, r32, make_double2(cc[k].real(), cc[k].imag()), wk, n, s));
-            if ((e = fetch(1))) return e;
+            if ((e = fetch(y, h, s))) return e;
             steps++;
             kend = k + 1;
             if (std::sqrt(h[0].x) <= target) break;
@@ -1530,30 +1495,22 @@ int solve_systems(const std::vector<Sys> &sys, double *const *x, const double *c
 // BiCGstab (van der Vorst 1992) on A in FP64, no preconditioner: the solver
 // without domain decomposition that the paper compares against (Sec. IV-C).
 // x and b are the slot's internal vectors; work vectors are basis columns.
-int bicgstab(ddqcd_t c, Slot &sl, bool guess, int max_iter, ddqcd_info &info, hipStream_t s)
+int bicgstab(const Sys &y, bool guess, int max_iter, ddqcd_info &info, hipStream_t s)
 {
+    ddqcd_t c = y.c;
+    Slot &sl = *y.sl;
     const long n = ncomplex(c->g);
     int e;
     if ((e = ensure_basis(c, sl, 5))) return e;
-    double2 *r0 = sl.Z, *p = sl.Z + n, *v = sl.Z + 2 * n, *sv = sl.Z + 3 * n, *t = sl.Z + 4 * n;
+    const BicgVectors V{sl.x, sl.r, sl.Z, sl.Z + n, sl.Z + 2 * n, sl.Z + 3 * n, sl.Z + 4 * n};
     double2 *x = sl.x, *r = sl.r, *b = sl.b;
-    double2 h[2];
-    auto fetch = [&](int m) -> int {
-        HIPCHK(c, hipMemcpyAsync(h, sl.blas.result, sizeof(double2) * m, hipMemcpyDeviceToHost, s));
-        HIPCHK(c, hipStreamSynchronize(s));
-        return DDQCD_OK;
-    };
-    auto dot = [&](const double2 *a, const double2 *bb, C &out) -> int {   // <a, bb>
-        HIPCHK(c, multidot(sl.blas, a, n, 1, bb, n, s));
-        int e2 = fetch(1);
-        out = C(h[0].x, h[0].y);
-        return e2;
-    };
-    const double2 one = make_double2(1, 0), zero2 = make_double2(0, 0);
-    auto cd = [](C z) { return make_double2(z.real(), z.imag()); };
+    double2 h[32];
+    const std::vector<Sys> self{y};
+    ResultArea area(self);
+    if ((e = area.bind())) return e;
     if (!guess) HIPCHK(c, zero(x, n, s));
     HIPCHK(c, norm2(sl.blas, b, n, s));
-    if ((e = fetch(1))) return e;
+    if ((e = fetch(y, h, s))) return e;
     const double bn = std::sqrt(h[0].x);
     info = ddqcd_info{};
     if (!std::isfinite(bn)) return fail(c, DDQCD_ERR_NONFINITE, "non-finite right-hand side");
@@ -1562,78 +1519,72 @@ int bicgstab(ddqcd_t c, Slot &sl, bool guess, int max_iter, ddqcd_info &info, hi
         info.converged = 1;
         return DDQCD_OK;
     }
-    // r = b - A x, r0 = r, p = v = 0
-    if ((e = apply_A64(c, x, r, s))) return e;
-    HIPCHK(c, residual(sl.blas, b, r, n, s));
-    if ((e = fetch(1))) return e;
-    double rel = std::sqrt(h[0].x) / bn;
-    HIPCHK(c, lincomb(r0, r, one, r, zero2, nullptr, zero2, n, s));
-    HIPCHK(c, zero(p, n, s));
-    HIPCHK(c, zero(v, n, s));
-    C rho_old = 1, alpha = 1, omega = 1;
-    int it = 0, restarts = 0, breakdowns = 0;
-    // restart from the current x: r = b - A x (unless r already is), r0 = r,
-    // p = v = 0
-    auto restart = [&](bool have_r) -> int {
+    double rel = 0;
+    auto true_residual = [&]() -> int {   // r = b - A x
         int e2;
-        if (!have_r) {
-            if ((e2 = apply_A64(c, x, r, s))) return e2;
-            HIPCHK(c, residual(sl.blas, b, r, n, s));
-            if ((e2 = fetch(1))) return e2;
-            rel = std::sqrt(h[0].x) / bn;
-        }
-        HIPCHK(c, lincomb(r0, r, one, r, zero2, nullptr, zero2, n, s));
-        HIPCHK(c, zero(p, n, s));
-        HIPCHK(c, zero(v, n, s));
-        rho_old = alpha = omega = 1;
+        if ((e2 = apply_A64(c, x, r, s))) return e2;
+        HIPCHK(c, residual(sl.blas, b, r, n, s));
+        if ((e2 = fetch(y, h, s))) return e2;
+        rel = std::sqrt(h[0].x) / bn;
+        return DDQCD_OK;
+    };
+    // r0 = r, p = v = 0, and the first direction's v = A p
+    auto direction = [&]() -> int {
+        HIPCHK(c, bicg_direction(sl.blas, V, n, s));
+        return apply_A64(c, V.p, V.v, s);
+    };
+    auto begin = [&]() -> int {
+        HIPCHK(c, hipMemcpyAsync(V.r0, r, sizeof(double2) * n, hipMemcpyDeviceToDevice, s));
+        HIPCHK(c, zero(V.p, n, s));
+        HIPCHK(c, zero(V.v, n, s));
+        HIPCHK(c, bicg_start(sl.blas, V, n, s));
+        return direction();
+    };
+    int it = 0, restarts = 0, breakdowns = 0;
+    // A breakdown (rho, omega or <r0, A p> vanished): restart from the current
+    // iterate with the true residual as the new shadow vector
+    auto broken = [&]() -> int {
+        if (++breakdowns > 100) return fail(c, DDQCD_ERR_NONFINITE, "BiCGstab breakdown");
+        int e2;
+        if ((e2 = true_residual()) || (e2 = begin())) return e2;
         restarts++;
         return DDQCD_OK;
     };
+    if ((e = true_residual())) return e;
+    hipEvent_t done;
+    HIPCHK(c, hipEventCreateWithFlags(&done, hipEventDisableTiming));
+    struct EventGuard {
+        hipEvent_t ev;
+        ~EventGuard() { (void)hipEventDestroy(ev); }
+    } guard{done};
+    if (rel > c->tol && it < max_iter && (e = begin())) return e;
     while (rel > c->tol && it < max_iter) {
-        C rho;
-        if ((e = dot(r0, r, rho))) return e;
-        if (std::abs(rho) == 0 || std::abs(omega) == 0) {
-            // breakdown (rho or omega vanished): restart from the current
-            // iterate with the true residual as the new shadow vector
-            if (++breakdowns > 100) return fail(c, DDQCD_ERR_NONFINITE, "BiCGstab breakdown");
-            if ((e = restart(false))) return e;
+        // p and v = A p stand: the rest of the iteration, and the next p and v
+        // after it while the host waits for this one's residual
+        HIPCHK(c, bicg_half(sl.blas, V, n, s));
+        if ((e = apply_A64(c, V.s, V.t, s))) return e;
+        HIPCHK(c, bicg_update(sl.blas, V, n, s));
+        HIPCHK(c, hipEventRecord(done, s));
+        if ((e = direction())) return e;
+        HIPCHK(c, hipEventSynchronize(done));
+        std::copy(sl.blas.result, sl.blas.result + 32, h);
+        if (h[BICG_STOP].x != 0) {   // before x took the step
+            if ((e = broken())) return e;
             continue;
         }
-        const C beta = (rho / rho_old) * (alpha / omega);
-        // p = r + beta (p - omega v)
-        HIPCHK(c, lincomb(p, r, one, p, cd(beta), v, cd(-beta * omega), n, s));
-        if ((e = apply_A64(c, p, v, s))) return e;
-        C r0v;
-        if ((e = dot(r0, v, r0v))) return e;
-        alpha = rho / r0v;
-        if (!std::isfinite(alpha.real()) || !std::isfinite(alpha.imag())) {
-            // <r0, A p> vanished: restart before x takes the step
-            if (++breakdowns > 100) return fail(c, DDQCD_ERR_NONFINITE, "BiCGstab breakdown");
-            if ((e = restart(false))) return e;
-            continue;
-        }
-        // s = r - alpha v, t = A s, omega = <t, s> / <t, t>
-        HIPCHK(c, lincomb(sv, r, one, v, cd(-alpha), nullptr, zero2, n, s));
-        if ((e = apply_A64(c, sv, t, s))) return e;
-        HIPCHK(c, dot2(sl.blas, t, sv, n, s));
-        if ((e = fetch(2))) return e;
-        omega = h[1].x > 0 && std::isfinite(h[0].x) && std::isfinite(h[0].y) ? C(h[0].x, h[0].y) / h[1].x : C(0);
-        // x += alpha p + omega s, r = s - omega t
-        HIPCHK(c, lincomb(x, x, one, p, cd(alpha), sv, cd(omega), n, s));
-        HIPCHK(c, lincomb(r, sv, one, t, cd(-omega), nullptr, zero2, n, s));
-        HIPCHK(c, norm2(sl.blas, r, n, s));
-        if ((e = fetch(1))) return e;
-        rel = std::sqrt(h[0].x) / bn;
-        rho_old = rho;
+        rel = std::sqrt(h[BICG_RR].x) / bn;
         it++;
         if (!std::isfinite(rel)) return fail(c, DDQCD_ERR_NONFINITE, "non-finite residual");
         if (rel <= c->tol) {
             // confirm with the true residual; restart from it if the recursion drifted
-            if ((e = apply_A64(c, x, r, s))) return e;
-            HIPCHK(c, residual(sl.blas, b, r, n, s));
-            if ((e = fetch(1))) return e;
-            rel = std::sqrt(h[0].x) / bn;
-            if (rel > c->tol && (e = restart(true))) return e;
+            if ((e = true_residual())) return e;
+            if (rel > c->tol) {
+                if ((e = begin())) return e;
+                restarts++;
+            }
+        } else if (it < max_iter && ((h[BICG_RHO].x == 0 && h[BICG_RHO].y == 0) ||
+                                     (h[BICG_OMEGA].x == 0 && h[BICG_OMEGA].y == 0))) {
+            if ((e = broken())) return e;
         }
     }
     info.converged = rel <= c->tol;
@@ -1651,11 +1602,8 @@ bool is_pm1(double v) { return v == 1.0 || v == -1.0; }
 
 // ---- workspace layout ---------------------------------------------------------
 // The sum of every device array the context allocates for nrhs right-hand
-// sides (each rounded up to 256 bytes), in three parts: the reduction area at
-// the bottom, the arrays of load_gauge, the work slots and the apply_D
-// temporaries above it, and the plan region at the top.
-size_t ws_result_bytes(int nrhs) { return aligned(sizeof(double2) * 32 * std::max(nrhs, 64)); }
-
+// sides (each rounded up to 256 bytes), in two parts: the arrays of load_gauge,
+// the work slots and the apply_D temporaries, and the plan region at the top.
 size_t ws_plan_bytes(const Geo &g, int nrhs)
 {
     const size_t per_plan =
@@ -1671,7 +1619,7 @@ size_t ws_main_bytes(ddqcd_t c, int nrhs)
     size_t gauge = aligned(sizeof(int)) + aligned(V * 4 * 9 * 16) + aligned(V * 4 * 6 * 8) + 2 * aligned(V * 4 * 6 * 4);
     gauge += 2 * (aligned(V * 36 * 16) + aligned(V * 36 * 8) + 2 * aligned(V * 36 * 4));   // clover, C_e / C_o^-1
     size_t slot = 4 * aligned(nc * 16) + 2 * aligned(half * 16) + aligned(faces * 16) + 2 * aligned((size_t)g.nd * 4);
-    slot += aligned(sizeof(double2) * BLAS_NBLK * 32) + 2 * aligned(sizeof(double2) * 32);
+    slot += aligned(sizeof(double2) * BLAS_NBLK * 32) + aligned(sizeof(double2) * 32);
     slot += aligned(sizeof(double2) * RCOEF);
     slot += 2 * aligned(nc * 16 * basis_columns(c));                        // outer solver basis
     slot += aligned(faces * 16) + aligned((size_t)g.nd * 4);                 // additive Schwarz
@@ -1680,7 +1628,7 @@ size_t ws_main_bytes(ddqcd_t c, int nrhs)
 
 size_t ws_total_bytes(ddqcd_t c, int nrhs)
 {
-    return ws_result_bytes(nrhs) + ws_main_bytes(c, nrhs) + ws_plan_bytes(c->g, nrhs);
+    return ws_main_bytes(c, nrhs) + ws_plan_bytes(c->g, nrhs);
 }
 
 }  // namespace
@@ -1890,9 +1838,7 @@ int ddqcd_set_workspace(ddqcd_t c, void *dev_ptr, size_t bytes)
     c->ws_plan = c->ws + (bytes - c->ws_plan_bytes) / 256 * 256;
     c->ws_plan_bytes = bytes - (size_t)(c->ws_plan - c->ws);
     c->ws_nrhs = nrhs;
-    // the reduction area of the solves this context leads, at the bottom
-    c->res_dev = (double2 *)c->ws;
-    c->ws_used = ws_result_bytes(nrhs);
+    // systems of the solves this context leads
     c->res_cap = std::max(nrhs, 64);
     return DDQCD_OK;
 }
@@ -2169,7 +2115,7 @@ int ddqcd_solve_bicgstab(ddqcd_t c, double *x, const double *b, int x_is_guess, 
     HIPCHK(c, import_spinor(c->g, b, sl.b, P64, s));
     if (x_is_guess) HIPCHK(c, import_spinor(c->g, x, sl.x, P64, s));
     ddqcd_info inf{};
-    const int st = bicgstab(c, sl, x_is_guess != 0, max_iter, inf, s);
+    const int st = bicgstab(Sys{c, &sl}, x_is_guess != 0, max_iter, inf, s);
     if (st != DDQCD_OK && st != DDQCD_ERR_NOT_CONVERGED) return st;
     HIPCHK(c, export_spinor(c->g, sl.x, P64, x, s));
     HIPCHK(c, hipStreamSynchronize(s));

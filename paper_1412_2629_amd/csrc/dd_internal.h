@@ -2,6 +2,8 @@
 #pragma once
 #include <hip/hip_runtime.h>
 
+#include <vector>
+
 #include "dd_device.h"
 
 namespace dd {
@@ -120,25 +122,42 @@ hipError_t sap_sweep_batch(const SapArgs *args, const int2 *items, int nitems, i
 // ---- FP64 linear algebra on flat complex vectors (double2) ---------------
 struct Blas {
     double2 *partial = nullptr;   // [NBLK][32]
-    double2 *result = nullptr;    // [32] device
-    double2 *coef = nullptr;      // [32] device coefficients
-    hipError_t init();
-    void release();
+    double2 *result = nullptr;    // [32] pinned host memory, set while a solve runs
+    double2 *coef = nullptr;      // [32] device: coefficients and scalars between kernels
 };
-enum { BLAS_NBLK = 1024, BLAS_MAXK = 16 };
-// result[j] = <W_j, v>, j < k (k <= 16); W_j = W + j*ldw
-hipError_t multidot(Blas &B, const double2 *W, long ldw, int k, const double2 *v, long n, hipStream_t s);
+enum { BLAS_NBLK = 1024, BLAS_MAXK = 16, BLAS_LIST = 16 };
+// One system's operands of a launch over several: columns W (W_j = W + j*n),
+// vectors w and r
+struct BlasOp {
+    const double2 *W;
+    double2 *w, *r, *partial, *result, *coef;
+    long n;
+    int nblk;
+};
+struct BlasList {
+    BlasOp op[BLAS_LIST];
+};
+BlasOp blas_op(const Blas &B, long n);   // W, w, r left empty
+// result[j] = <W_j, v>, j < k (1 <= k <= 16); W_j = W + j*n
+hipError_t multidot(Blas &B, const double2 *W, int k, double2 *v, long n, hipStream_t s);
 // w -= sum_j coef[j] W_j (coef on device, k <= 16); result[0] = (|w|^2, 0), result[1] = <w, r>
-hipError_t cgs_update(Blas &B, double2 *w, const double2 *W, long ldw, int k, const double2 *r, long n,
-                      hipStream_t s);
-// r -= c w; result[0] = (|r|^2, 0)
-hipError_t residual_update(Blas &B, const double2 *w, double2 *r, double2 c, long n, hipStream_t s);
-// x += sum_j coef[j] Z_j (coef on device, k <= 16)
-hipError_t axpy_multi(Blas &B, double2 *x, const double2 *Z, long ldz, int k, long n, hipStream_t s);
-// r = b - r; result[0] = (|r|^2, 0)
-hipError_t residual(Blas &B, const double2 *b, double2 *r, long n, hipStream_t s);
-// result[0] = (|v|^2, 0)
-hipError_t norm2(Blas &B, const double2 *v, long n, hipStream_t s);
+hipError_t cgs_update(Blas &B, double2 *w, const double2 *W, int k, double2 *r, long n, hipStream_t s);
+// A Gram-Schmidt pass of FGCR step k for each system (w: the new vector, W: the
+// k before it, unnormalised, the norms of which earlier steps left in coef):
+// result[STEP_DOTS + j] = <W_j, w>, j < nd (nd = k, or k + 1 with w itself last);
+// w -= sum_j <W_j, w> / |W_j|^2 W_j; result[STEP_W] = (|w|^2, 0), result[STEP_W + 1]
+// = <w, r>; then r -= <w, r> / |w|^2 w, result[STEP_R] = (|r|^2, 0), left out where
+// may_repeat and |w|^2 is not more than a quarter of what it was, or w vanished.
+enum { STEP_DOTS = 0, STEP_W = 16, STEP_R = 18 };
+hipError_t fgcr_step(const std::vector<BlasOp> &ops, int k, int nd, bool may_repeat, hipStream_t s);
+// x += sum_j coef[j] Z_j (coef on the host, 1 <= k <= 16)
+hipError_t axpy_multi(double2 *x, const double2 *Z, const double2 *coef, int k, long n, hipStream_t s);
+// r = b - r; result[0] = (|r|^2, 0); in a list, b is the operand w
+hipError_t residual(Blas &B, double2 *b, double2 *r, long n, hipStream_t s);
+hipError_t residual(const std::vector<BlasOp> &ops, hipStream_t s);
+// result[0] = (|v|^2, 0); in a list, v is the operand w
+hipError_t norm2(Blas &B, double2 *v, long n, hipStream_t s);
+hipError_t norm2(const std::vector<BlasOp> &ops, hipStream_t s);
 hipError_t zero(double2 *v, long n, hipStream_t s);
 // FP32 vectors, FP64 accumulation: result[j] = <W_j, v> (k <= 16);
 // w -= sum_j coef[j] W_j with result[0] = |w|^2; w *= inv_b with result[0] =
@@ -154,8 +173,19 @@ hipError_t to_f32(const double2 *in, double sc, float2 *out, long n, hipStream_t
 // device; out must not overlap W)
 hipError_t recombine(const double2 *W, long ldw, int nin, const double2 *P, int nq, double2 *out, long ldo, long n,
                      hipStream_t s);
-// result[0] = <t, s>, result[1] = (|t|^2, 0)
-hipError_t dot2(Blas &B, const double2 *t, const double2 *s_vec, long n, hipStream_t s);
+// BiCGstab on the device's own scalars: rho = <r0, r> at a (re)start, where p and
+// v are zero (result[BICG_RHO]); p = r + beta (p - omega v); with v = A p, alpha =
+// rho / <r0, v> (result[BICG_STOP].x not 0: not finite) and s = r - alpha v; with t
+// = A s, omega (result[BICG_OMEGA]), x += alpha p + omega s and r = s - omega t
+// unless stopped, |r|^2 (result[BICG_RR]) and the next rho
+struct BicgVectors {
+    double2 *x, *r, *r0, *p, *v, *s, *t;
+};
+enum { BICG_R0V = 0, BICG_STOP = 1, BICG_TS = 2, BICG_OMEGA = 4, BICG_RR = 5, BICG_RHO = 6 };
+hipError_t bicg_start(Blas &B, const BicgVectors &V, long n, hipStream_t s);
+hipError_t bicg_direction(Blas &B, const BicgVectors &V, long n, hipStream_t s);
+hipError_t bicg_half(Blas &B, const BicgVectors &V, long n, hipStream_t s);
+hipError_t bicg_update(Blas &B, const BicgVectors &V, long n, hipStream_t s);
 // out = ca a + cb b + cc c; c may be null; out may alias an input
 hipError_t lincomb(double2 *out, const double2 *a, double2 ca, const double2 *b, double2 cb, const double2 *c,
                    double2 cc, long n, hipStream_t s);

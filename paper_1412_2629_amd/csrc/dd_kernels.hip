@@ -874,150 +874,292 @@ static int blas_blocks(long n)
     return (int)(b < 1 ? 1 : b > BLAS_NBLK ? BLAS_NBLK : b);
 }
 
-// stage 2: result[j] = sum over blocks of partial[b][j], j < m pairs
-__global__ void k_finish(const double2 *partial, int nblk, int m, double2 *result)
+// Stage 2 of a reduction, for every system of a list (blockIdx.y): the sum over
+// the system's blocks of partial[b][j], j < m, to result[at + j] (pinned host
+// memory, read after the stream is waited for), then what the next kernel needs
+// of it, formed here so that the host does not have to be asked in between.
+enum Finish {
+    FIN_STORE,     // nothing more
+    FIN_DOTS,      // coef[j] = <W_j, w> / b_j^2 for the first k; the last of m > k is |w|^2
+    FIN_CGS,       // b = |w|, the step's coefficient <w, r> / b^2, whether to repeat
+    FIN_BICG_RHO, FIN_BICG_ALPHA, FIN_BICG_OMEGA, FIN_BICG_NEXT
+};
+// A system's scalars on the device, in Blas::coef: 0..15 coefficients of the
+// Gram-Schmidt pass, then
+enum { CO_STEP = 16, CO_SKIP = 17, CO_BEFORE = 18, CO_NORMS = 19 };   // norms b_j: two a pair, 8 pairs
+// and, during BiCGstab,
+enum { CO_RHO = 0, CO_ALPHA = 1, CO_OMEGA = 2, CO_BETA = 3, CO_BETA_OMEGA = 4, CO_STOP = 5 };
+
+__device__ __forceinline__ double2 cdiv(double2 a, double2 b)
 {
-    __shared__ double2 red[BS];
+    // scaled by the power of two of the larger part of b, so that |b|^2 neither
+    // overflows nor vanishes
+    const int e = -ilogb(fmax(fabs(b.x), fabs(b.y)));
+    const double c = ldexp(b.x, e), d = ldexp(b.y, e), q = c * c + d * d;
+    return make_double2(ldexp((a.x * c + a.y * d) / q, e), ldexp((a.y * c - a.x * d) / q, e));
+}
+__device__ __forceinline__ double2 cmul2(double2 a, double2 b)
+{
+    return make_double2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x);
+}
+
+template <int FIN> __device__ void finish_scalars(const BlasOp &o, const double2 *sum, int m, int k, bool may_repeat, int at)
+{
+    double2 *co = o.coef;
+    double *norms = (double *)(co + CO_NORMS);
+    if constexpr (FIN == FIN_DOTS) {
+        for (int j = 0; j < k; j++) {
+            const double b = norms[j];
+            co[j] = make_double2(sum[j].x / b / b, sum[j].y / b / b);
+        }
+        if (m > k) co[CO_BEFORE] = sum[k];
+    } else if constexpr (FIN == FIN_CGS) {
+        const double b = sqrt(sum[0].x);
+        const bool repeat = may_repeat && !(sum[0].x > 0.25 * co[CO_BEFORE].x);
+        norms[k] = b;
+        co[CO_STEP] = make_double2(sum[1].x / b / b, sum[1].y / b / b);
+        co[CO_SKIP] = make_double2(repeat || !(b > 0) || !isfinite(b), 0);
+        if (repeat) co[CO_BEFORE] = sum[0];
+    } else if constexpr (FIN == FIN_BICG_RHO) {
+        co[CO_RHO] = co[CO_BETA] = sum[0];   // rho, alpha and omega of the step before are 1
+        co[CO_BETA_OMEGA] = make_double2(-sum[0].x, -sum[0].y);
+    } else if constexpr (FIN == FIN_BICG_ALPHA) {
+        const double2 a = cdiv(co[CO_RHO], sum[0]);
+        co[CO_ALPHA] = a;
+        co[CO_STOP] = o.result[at + 1] = make_double2(!isfinite(a.x) || !isfinite(a.y), 0);
+    } else if constexpr (FIN == FIN_BICG_OMEGA) {
+        const bool ok = sum[1].x > 0 && isfinite(sum[0].x) && isfinite(sum[0].y);
+        co[CO_OMEGA] = o.result[at + 2] = ok ? make_double2(sum[0].x / sum[1].x, sum[0].y / sum[1].x) : make_double2(0, 0);
+    } else if constexpr (FIN == FIN_BICG_NEXT) {
+        const double2 beta = cmul2(cdiv(sum[1], co[CO_RHO]), cdiv(co[CO_ALPHA], co[CO_OMEGA]));
+        const double2 bo = cmul2(beta, co[CO_OMEGA]);
+        co[CO_RHO] = sum[1];
+        co[CO_BETA] = beta;
+        co[CO_BETA_OMEGA] = make_double2(-bo.x, -bo.y);
+    }
+}
+
+template <int FIN> __global__ __launch_bounds__(BS) void k_finish(BlasList L, int m, int k, bool may_repeat, int at)
+{
+    __shared__ double2 red[BS], sum[BLAS_MAXK];
+    const BlasOp o = L.op[blockIdx.y];
     for (int j = 0; j < m; j++) {
         double2 s = make_double2(0, 0);
-        for (int b = threadIdx.x; b < nblk; b += BS) {
-            double2 v = partial[(long)b * 32 + j];
+        for (int b = threadIdx.x; b < o.nblk; b += BS) {
+            double2 v = o.partial[(long)b * 32 + j];
             s.x += v.x;
             s.y += v.y;
         }
         red[threadIdx.x] = s;
         __syncthreads();
-        for (int o = BS / 2; o > 0; o >>= 1) {
-            if ((int)threadIdx.x < o) {
-                red[threadIdx.x].x += red[threadIdx.x + o].x;
-                red[threadIdx.x].y += red[threadIdx.x + o].y;
+        for (int q = BS / 2; q > 0; q >>= 1) {
+            if ((int)threadIdx.x < q) {
+                red[threadIdx.x].x += red[threadIdx.x + q].x;
+                red[threadIdx.x].y += red[threadIdx.x + q].y;
             }
             __syncthreads();
         }
-        if (threadIdx.x == 0) result[j] = red[0];
+        if (threadIdx.x == 0) sum[j] = o.result[at + j] = red[0];
         __syncthreads();
     }
+    if (threadIdx.x == 0) finish_scalars<FIN>(o, sum, m, k, may_repeat, at);
 }
 
-template <int K> __global__ __launch_bounds__(BS) void k_multidot(const double2 *W, long ldw, const double2 *v, long n, double2 *partial)
+template <int FIN> static void launch_finish(const BlasList &L, int ns, int m, int at, hipStream_t s, int k = 0, bool may_repeat = false)
 {
+    hipLaunchKernelGGL(k_finish<FIN>, dim3(1, ns), BS, 0, s, L, m, k, may_repeat, at);
+}
+
+// ---- several systems in one launch: blockIdx.y is the system -----------------
+// Every system keeps the blocks, and with them the order of its sums, that it
+// has alone; a launch has those of the largest.
+
+BlasOp blas_op(const Blas &B, long n)
+{
+    BlasOp o{};
+    o.partial = B.partial;
+    o.result = B.result;
+    o.coef = B.coef;
+    o.n = n;
+    o.nblk = blas_blocks(n);
+    return o;
+}
+
+static hipError_t finish_one(const Blas &B, long n, int m, hipStream_t s)
+{
+    BlasList L{};
+    L.op[0] = blas_op(B, n);
+    launch_finish<FIN_STORE>(L, 1, m, 0, s);
+    return hipGetLastError();
+}
+
+// f(list, systems, grid) for BLAS_LIST systems at a time
+template <typename F> static hipError_t for_lists(const std::vector<BlasOp> &ops, F f)
+{
+    for (size_t i = 0; i < ops.size(); i += BLAS_LIST) {
+        BlasList L{};
+        const int ns = (int)(ops.size() - i < BLAS_LIST ? ops.size() - i : BLAS_LIST);
+        int nb = 1;
+        for (int q = 0; q < ns; q++) {
+            L.op[q] = ops[i + q];
+            if (L.op[q].nblk > nb) nb = L.op[q].nblk;
+        }
+        f(L, ns, dim3(nb, ns));
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+
+// this block's system and its elements: first, past the last, step
+#define DD_BLAS_OP(o, i)                                                   \
+    const BlasOp o = L.op[blockIdx.y];                                     \
+    if ((int)blockIdx.x >= o.nblk) return;                                 \
+    const long step = (long)o.nblk * BS;                                   \
+    long i = (long)blockIdx.x * BS + threadIdx.x
+
+// <W_j, w>, j < K
+template <int K> __global__ __launch_bounds__(BS) void k_multidot(BlasList L)
+{
+    DD_BLAS_OP(o, i);
     double acc[2 * K];
 #pragma unroll
     for (int q = 0; q < 2 * K; q++) acc[q] = 0;
-    for (long i = (long)blockIdx.x * BS + threadIdx.x; i < n; i += (long)gridDim.x * BS) {
-        double2 b = v[i];
+    for (; i < o.n; i += step) {
+        double2 b = o.w[i];
 #pragma unroll
         for (int j = 0; j < K; j++) {
-            double2 a = W[j * ldw + i];
+            double2 a = o.W[j * o.n + i];
             acc[2 * j] += a.x * b.x + a.y * b.y;
             acc[2 * j + 1] += a.x * b.y - a.y * b.x;
         }
     }
-    block_reduce_store<2 * K>(acc, partial + (long)blockIdx.x * 32);
+    block_reduce_store<2 * K>(acc, o.partial + (long)blockIdx.x * 32);
 }
 
-template <int K> static void launch_multidot(const double2 *W, long ldw, const double2 *v, long n, double2 *partial, hipStream_t s)
-{
-    hipLaunchKernelGGL(k_multidot<K>, blas_blocks(n), BS, 0, s, W, ldw, v, n, partial);
-}
-
-hipError_t Blas::init()
-{
-    hipError_t e = hipMalloc(&partial, sizeof(double2) * BLAS_NBLK * 32);
-    if (e == hipSuccess) e = hipMalloc(&result, sizeof(double2) * 32);
-    if (e == hipSuccess) e = hipMalloc(&coef, sizeof(double2) * 32);
-    return e;
-}
-
-void Blas::release()
-{
-    if (partial) (void)hipFree(partial);
-    if (result) (void)hipFree(result);
-    if (coef) (void)hipFree(coef);
-    partial = result = coef = nullptr;
-}
-
-hipError_t multidot(Blas &B, const double2 *W, long ldw, int k, const double2 *v, long n, hipStream_t s)
+static hipError_t launch_multidot(const BlasList &L, dim3 grid, int k, hipStream_t s)
 {
     switch (k) {
-#define MD(K) case K: launch_multidot<K>(W, ldw, v, n, B.partial, s); break;
+#define MD(K) case K: hipLaunchKernelGGL(k_multidot<K>, grid, BS, 0, s, L); break;
         MD(1) MD(2) MD(3) MD(4) MD(5) MD(6) MD(7) MD(8) MD(9) MD(10) MD(11) MD(12) MD(13) MD(14) MD(15) MD(16)
 #undef MD
         default: return hipErrorInvalidValue;
     }
-    hipLaunchKernelGGL(k_finish, 1, BS, 0, s, B.partial, blas_blocks(n), k, B.result);
-    return hipGetLastError();
+    return hipSuccess;
 }
 
-template <int K>
-__global__ __launch_bounds__(BS) void k_cgs_update(double2 *w, const double2 *W, long ldw, const double2 *coef, const double2 *r,
-                                                   long n, double2 *partial)
+hipError_t multidot(Blas &B, const double2 *W, int k, double2 *v, long n, hipStream_t s)
 {
+    if (k < 1 || k > BLAS_MAXK) return hipErrorInvalidValue;
+    BlasOp o = blas_op(B, n);
+    o.W = W;
+    o.w = v;
+    return for_lists({o}, [&](const BlasList &L, int ns, dim3 grid) {
+        (void)launch_multidot(L, grid, k, s);
+        launch_finish<FIN_STORE>(L, ns, k, 0, s);
+    });
+}
+
+// w -= sum_j coef[j] W_j; |w|^2 and <w, r>
+template <int K> __global__ __launch_bounds__(BS) void k_cgs_update(BlasList L)
+{
+    DD_BLAS_OP(o, i);
     double2 c[K > 0 ? K : 1];
 #pragma unroll
-    for (int j = 0; j < K; j++) c[j] = coef[j];
+    for (int j = 0; j < K; j++) c[j] = o.coef[j];
     double acc[4] = {0, 0, 0, 0};
-    for (long i = (long)blockIdx.x * BS + threadIdx.x; i < n; i += (long)gridDim.x * BS) {
-        double2 x = w[i];
+    for (; i < o.n; i += step) {
+        double2 x = o.w[i];
 #pragma unroll
         for (int j = 0; j < K; j++) {
-            double2 a = W[j * ldw + i];
+            double2 a = o.W[j * o.n + i];
             x.x -= c[j].x * a.x - c[j].y * a.y;
             x.y -= c[j].x * a.y + c[j].y * a.x;
         }
-        w[i] = x;
-        double2 b = r[i];
+        if (K > 0) o.w[i] = x;
+        double2 b = o.r[i];
         acc[0] += x.x * x.x + x.y * x.y;
         acc[2] += x.x * b.x + x.y * b.y;
         acc[3] += x.x * b.y - x.y * b.x;
     }
-    block_reduce_store<4>(acc, partial + (long)blockIdx.x * 32);
+    block_reduce_store<4>(acc, o.partial + (long)blockIdx.x * 32);
 }
 
-hipError_t cgs_update(Blas &B, double2 *w, const double2 *W, long ldw, int k, const double2 *r, long n, hipStream_t s)
+static hipError_t launch_cgs_update(const BlasList &L, dim3 grid, int k, hipStream_t s)
 {
     switch (k) {
-#define CU(K) case K: hipLaunchKernelGGL(k_cgs_update<K>, blas_blocks(n), BS, 0, s, w, W, ldw, B.coef, r, n, B.partial); break;
+#define CU(K) case K: hipLaunchKernelGGL(k_cgs_update<K>, grid, BS, 0, s, L); break;
         CU(0) CU(1) CU(2) CU(3) CU(4) CU(5) CU(6) CU(7) CU(8) CU(9) CU(10) CU(11) CU(12) CU(13) CU(14) CU(15) CU(16)
 #undef CU
         default: return hipErrorInvalidValue;
     }
-    hipLaunchKernelGGL(k_finish, 1, BS, 0, s, B.partial, blas_blocks(n), 2, B.result);
-    return hipGetLastError();
+    return hipSuccess;
 }
 
-__global__ __launch_bounds__(BS) void k_residual_update(const double2 *w, double2 *r, double2 c, long n,
-                                                        double2 *partial)
+hipError_t cgs_update(Blas &B, double2 *w, const double2 *W, int k, double2 *r, long n, hipStream_t s)
 {
+    if (k < 0 || k > BLAS_MAXK) return hipErrorInvalidValue;
+    BlasOp o = blas_op(B, n);
+    o.W = W;
+    o.w = w;
+    o.r = r;
+    return for_lists({o}, [&](const BlasList &L, int ns, dim3 grid) {
+        (void)launch_cgs_update(L, grid, k, s);
+        launch_finish<FIN_STORE>(L, ns, 2, 0, s);
+    });
+}
+
+// r -= <w, r> / |w|^2 w unless the pass is to be repeated (or w vanished); |r|^2
+__global__ __launch_bounds__(BS) void k_residual_update(BlasList L)
+{
+    DD_BLAS_OP(o, i);
+    if (o.coef[CO_SKIP].x != 0) return;
+    const double2 c = o.coef[CO_STEP];
     double acc[2] = {0, 0};
-    for (long i = (long)blockIdx.x * BS + threadIdx.x; i < n; i += (long)gridDim.x * BS) {
-        const double2 x = w[i];
-        double2 y = r[i];
+    for (; i < o.n; i += step) {
+        const double2 x = o.w[i];
+        double2 y = o.r[i];
         y.x -= c.x * x.x - c.y * x.y;
         y.y -= c.x * x.y + c.y * x.x;
-        r[i] = y;
+        o.r[i] = y;
         acc[0] += y.x * y.x + y.y * y.y;
     }
-    block_reduce_store<2>(acc, partial + (long)blockIdx.x * 32);
+    block_reduce_store<2>(acc, o.partial + (long)blockIdx.x * 32);
 }
 
-hipError_t residual_update(Blas &B, const double2 *w, double2 *r, double2 c, long n, hipStream_t s)
+// One pass of the Gram-Schmidt step of every system and, unless it has to be
+// repeated, the residual's update: three reductions whose results are used on
+// the device and read by the host together.  With a copy and a wait after each
+// reduction and a launch per system, five steps on 8x4^3 took 180 us more (2810
+// us, now 2630) and those of 12 systems on 16^3x32 1.7 ms more (42.6, now 40.9).
+hipError_t fgcr_step(const std::vector<BlasOp> &ops, int k, int nd, bool may_repeat, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_residual_update, blas_blocks(n), BS, 0, s, w, r, c, n, B.partial);
-    hipLaunchKernelGGL(k_finish, 1, BS, 0, s, B.partial, blas_blocks(n), 1, B.result);
-    return hipGetLastError();
+    if (k < 0 || k > BLAS_MAXK || nd < k || nd > BLAS_MAXK) return hipErrorInvalidValue;
+    return for_lists(ops, [&](const BlasList &L, int ns, dim3 grid) {
+        if (nd > 0) {
+            (void)launch_multidot(L, grid, nd, s);
+            launch_finish<FIN_DOTS>(L, ns, nd, STEP_DOTS, s, k);
+        }
+        (void)launch_cgs_update(L, grid, k, s);
+        launch_finish<FIN_CGS>(L, ns, 2, STEP_W, s, k, may_repeat);
+        hipLaunchKernelGGL(k_residual_update, grid, BS, 0, s, L);
+        launch_finish<FIN_STORE>(L, ns, 1, STEP_R, s);
+    });
 }
 
-template <int K> __global__ __launch_bounds__(BS) void k_axpy_multi(double2 *x, const double2 *Z, long ldz, const double2 *coef, long n)
+struct Coefs {
+    double2 c[BLAS_MAXK];
+};
+template <int K> __global__ __launch_bounds__(BS) void k_axpy_multi(double2 *x, const double2 *Z, Coefs co, long n)
 {
     double2 c[K];
 #pragma unroll
-    for (int j = 0; j < K; j++) c[j] = coef[j];
+    for (int j = 0; j < K; j++) c[j] = co.c[j];
     for (long i = (long)blockIdx.x * BS + threadIdx.x; i < n; i += (long)gridDim.x * BS) {
         double2 y = x[i];
 #pragma unroll
         for (int j = 0; j < K; j++) {
-            double2 a = Z[j * ldz + i];
+            double2 a = Z[j * n + i];
             y.x += c[j].x * a.x - c[j].y * a.y;
             y.y += c[j].x * a.y + c[j].y * a.x;
         }
@@ -1025,60 +1167,111 @@ template <int K> __global__ __launch_bounds__(BS) void k_axpy_multi(double2 *x, 
     }
 }
 
-hipError_t axpy_multi(Blas &B, double2 *x, const double2 *Z, long ldz, int k, long n, hipStream_t s)
+hipError_t axpy_multi(double2 *x, const double2 *Z, const double2 *coef, int k, long n, hipStream_t s)
 {
+    if (k < 1 || k > BLAS_MAXK) return hipErrorInvalidValue;
+    Coefs co{};
+    for (int j = 0; j < k; j++) co.c[j] = coef[j];
     switch (k) {
-#define AX(K) case K: hipLaunchKernelGGL(k_axpy_multi<K>, blas_blocks(n), BS, 0, s, x, Z, ldz, B.coef, n); break;
+#define AX(K) case K: hipLaunchKernelGGL(k_axpy_multi<K>, blas_blocks(n), BS, 0, s, x, Z, co, n); break;
         AX(1) AX(2) AX(3) AX(4) AX(5) AX(6) AX(7) AX(8) AX(9) AX(10) AX(11) AX(12) AX(13) AX(14) AX(15) AX(16)
 #undef AX
-        default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
 }
 
-__global__ __launch_bounds__(BS) void k_residual(const double2 *b, double2 *r, long n, double2 *partial)
+// r = b - r (b: the operand w); |r|^2
+__global__ __launch_bounds__(BS) void k_residual(BlasList L)
 {
+    DD_BLAS_OP(o, i);
     double acc[2] = {0, 0};
-    for (long i = (long)blockIdx.x * BS + threadIdx.x; i < n; i += (long)gridDim.x * BS) {
-        double2 y = b[i], a = r[i];
+    for (; i < o.n; i += step) {
+        double2 y = o.w[i], a = o.r[i];
         y.x -= a.x;
         y.y -= a.y;
-        r[i] = y;
+        o.r[i] = y;
         acc[0] += y.x * y.x + y.y * y.y;
     }
-    block_reduce_store<2>(acc, partial + (long)blockIdx.x * 32);
+    block_reduce_store<2>(acc, o.partial + (long)blockIdx.x * 32);
 }
 
-hipError_t residual(Blas &B, const double2 *b, double2 *r, long n, hipStream_t s)
+hipError_t residual(const std::vector<BlasOp> &ops, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_residual, blas_blocks(n), BS, 0, s, b, r, n, B.partial);
-    hipLaunchKernelGGL(k_finish, 1, BS, 0, s, B.partial, blas_blocks(n), 1, B.result);
-    return hipGetLastError();
+    return for_lists(ops, [&](const BlasList &L, int ns, dim3 grid) {
+        hipLaunchKernelGGL(k_residual, grid, BS, 0, s, L);
+        launch_finish<FIN_STORE>(L, ns, 1, 0, s);
+    });
 }
 
-__global__ __launch_bounds__(BS) void k_norm2(const double2 *v, long n, double2 *partial)
+hipError_t residual(Blas &B, double2 *b, double2 *r, long n, hipStream_t s)
 {
+    BlasOp o = blas_op(B, n);
+    o.w = b;
+    o.r = r;
+    return residual({o}, s);
+}
+
+__global__ __launch_bounds__(BS) void k_norm2(BlasList L)
+{
+    DD_BLAS_OP(o, i);
     double acc[2] = {0, 0};
-    for (long i = (long)blockIdx.x * BS + threadIdx.x; i < n; i += (long)gridDim.x * BS) {
-        double2 y = v[i];
+    for (; i < o.n; i += step) {
+        double2 y = o.w[i];
         acc[0] += y.x * y.x + y.y * y.y;
     }
-    block_reduce_store<2>(acc, partial + (long)blockIdx.x * 32);
+    block_reduce_store<2>(acc, o.partial + (long)blockIdx.x * 32);
 }
 
-hipError_t norm2(Blas &B, const double2 *v, long n, hipStream_t s)
+hipError_t norm2(const std::vector<BlasOp> &ops, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_norm2, blas_blocks(n), BS, 0, s, v, n, B.partial);
-    hipLaunchKernelGGL(k_finish, 1, BS, 0, s, B.partial, blas_blocks(n), 1, B.result);
-    return hipGetLastError();
+    return for_lists(ops, [&](const BlasList &L, int ns, dim3 grid) {
+        hipLaunchKernelGGL(k_norm2, grid, BS, 0, s, L);
+        launch_finish<FIN_STORE>(L, ns, 1, 0, s);
+    });
 }
 
-// result[0] = <t, s>, result[1] = (|t|^2, 0)
-__global__ __launch_bounds__(BS) void k_dot2(const double2 *t, const double2 *sv, long n, double2 *partial)
+hipError_t norm2(Blas &B, double2 *v, long n, hipStream_t s)
+{
+    BlasOp o = blas_op(B, n);
+    o.w = v;
+    return norm2({o}, s);
+}
+
+// ---- BiCGstab: vector updates whose coefficients earlier reductions left on
+// the device (coef of the system), so that an iteration is launched as a whole.
+// Each is bound by memory; what shares operands shares a pass: 21 vectors are
+// moved an iteration besides the operator's.  16^3x32: 196 us an iteration, 285
+// with a wait for the host after each of four reductions and 24 vectors moved.
+
+__device__ __forceinline__ double2 axpy2(double2 y, double2 c, double2 x)
+{
+    y.x += c.x * x.x - c.y * x.y;
+    y.y += c.x * x.y + c.y * x.x;
+    return y;
+}
+
+// p = r + beta (p - omega v)
+__global__ __launch_bounds__(BS) void k_bicg_p(BicgVectors V, const double2 *co, long n)
+{
+    const double2 b = co[CO_BETA], bo = co[CO_BETA_OMEGA];
+    for (long i = (long)blockIdx.x * BS + threadIdx.x; i < n; i += (long)gridDim.x * BS)
+        V.p[i] = axpy2(axpy2(V.r[i], b, V.p[i]), bo, V.v[i]);
+}
+
+// s = r - alpha v
+__global__ __launch_bounds__(BS) void k_bicg_s(BicgVectors V, const double2 *co, long n)
+{
+    const double2 a = co[CO_ALPHA], ma = make_double2(-a.x, -a.y);
+    for (long i = (long)blockIdx.x * BS + threadIdx.x; i < n; i += (long)gridDim.x * BS)
+        V.s[i] = axpy2(V.r[i], ma, V.v[i]);
+}
+
+// <t, s>, |t|^2
+__global__ __launch_bounds__(BS) void k_bicg_ts(BicgVectors V, long n, double2 *partial)
 {
     double acc[4] = {0, 0, 0, 0};
     for (long i = (long)blockIdx.x * BS + threadIdx.x; i < n; i += (long)gridDim.x * BS) {
-        const double2 a = t[i], b = sv[i];
+        const double2 a = V.t[i], b = V.s[i];
         acc[0] += a.x * b.x + a.y * b.y;
         acc[1] += a.x * b.y - a.y * b.x;
         acc[2] += a.x * a.x + a.y * a.y;
@@ -1086,10 +1279,71 @@ __global__ __launch_bounds__(BS) void k_dot2(const double2 *t, const double2 *sv
     block_reduce_store<4>(acc, partial + (long)blockIdx.x * 32);
 }
 
-hipError_t dot2(Blas &B, const double2 *t, const double2 *sv, long n, hipStream_t s)
+// x += alpha p + omega s, r = s - omega t, |r|^2, <r0, r>; nothing where alpha
+// is not finite
+__global__ __launch_bounds__(BS) void k_bicg_xr(BicgVectors V, const double2 *co, long n, double2 *partial)
 {
-    hipLaunchKernelGGL(k_dot2, blas_blocks(n), BS, 0, s, t, sv, n, B.partial);
-    hipLaunchKernelGGL(k_finish, 1, BS, 0, s, B.partial, blas_blocks(n), 2, B.result);
+    if (co[CO_STOP].x != 0) return;
+    const double2 a = co[CO_ALPHA], w = co[CO_OMEGA], mw = make_double2(-w.x, -w.y);
+    double acc[4] = {0, 0, 0, 0};
+    for (long i = (long)blockIdx.x * BS + threadIdx.x; i < n; i += (long)gridDim.x * BS) {
+        const double2 sv = V.s[i], y = axpy2(sv, mw, V.t[i]), r0 = V.r0[i];
+        V.x[i] = axpy2(axpy2(V.x[i], a, V.p[i]), w, sv);
+        V.r[i] = y;
+        acc[0] += y.x * y.x + y.y * y.y;
+        acc[2] += r0.x * y.x + r0.y * y.y;
+        acc[3] += r0.x * y.y - r0.y * y.x;
+    }
+    block_reduce_store<4>(acc, partial + (long)blockIdx.x * 32);
+}
+
+static void bicg_finish(const Blas &B, long n, int fin, int m, int at, hipStream_t s)
+{
+    BlasList L{};
+    L.op[0] = blas_op(B, n);
+    switch (fin) {
+        case FIN_BICG_RHO: launch_finish<FIN_BICG_RHO>(L, 1, m, at, s); break;
+        case FIN_BICG_ALPHA: launch_finish<FIN_BICG_ALPHA>(L, 1, m, at, s); break;
+        case FIN_BICG_OMEGA: launch_finish<FIN_BICG_OMEGA>(L, 1, m, at, s); break;
+        default: launch_finish<FIN_BICG_NEXT>(L, 1, m, at, s); break;
+    }
+}
+
+static void bicg_dot(const Blas &B, const double2 *a, double2 *b, long n, int fin, int at, hipStream_t s)
+{
+    BlasList L{};
+    L.op[0] = blas_op(B, n);
+    L.op[0].W = a;
+    L.op[0].w = b;
+    hipLaunchKernelGGL(k_multidot<1>, blas_blocks(n), BS, 0, s, L);
+    bicg_finish(B, n, fin, 1, at, s);
+}
+
+hipError_t bicg_start(Blas &B, const BicgVectors &V, long n, hipStream_t s)
+{
+    bicg_dot(B, V.r0, V.r, n, FIN_BICG_RHO, BICG_RHO, s);
+    return hipGetLastError();
+}
+
+hipError_t bicg_direction(Blas &B, const BicgVectors &V, long n, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_bicg_p, blas_blocks(n), BS, 0, s, V, B.coef, n);
+    return hipGetLastError();
+}
+
+hipError_t bicg_half(Blas &B, const BicgVectors &V, long n, hipStream_t s)
+{
+    bicg_dot(B, V.r0, V.v, n, FIN_BICG_ALPHA, BICG_R0V, s);
+    hipLaunchKernelGGL(k_bicg_s, blas_blocks(n), BS, 0, s, V, B.coef, n);
+    return hipGetLastError();
+}
+
+hipError_t bicg_update(Blas &B, const BicgVectors &V, long n, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_bicg_ts, blas_blocks(n), BS, 0, s, V, n, B.partial);
+    bicg_finish(B, n, FIN_BICG_OMEGA, 2, BICG_TS, s);
+    hipLaunchKernelGGL(k_bicg_xr, blas_blocks(n), BS, 0, s, V, B.coef, n, B.partial);
+    bicg_finish(B, n, FIN_BICG_NEXT, 2, BICG_RR, s);
     return hipGetLastError();
 }
 
@@ -1147,8 +1401,7 @@ hipError_t multidot32(Blas &B, const float2 *W, long ldw, int k, const float2 *v
 #undef MD
         default: return hipErrorInvalidValue;
     }
-    hipLaunchKernelGGL(k_finish, 1, BS, 0, s, B.partial, blas_blocks(n), k, B.result);
-    return hipGetLastError();
+    return finish_one(B, n, k, s);
 }
 
 template <int K>
@@ -1183,8 +1436,7 @@ hipError_t cgs_update32(Blas &B, float2 *w, const float2 *W, long ldw, int k, lo
 #undef CU
         default: return hipErrorInvalidValue;
     }
-    hipLaunchKernelGGL(k_finish, 1, BS, 0, s, B.partial, blas_blocks(n), 1, B.result);
-    return hipGetLastError();
+    return finish_one(B, n, 1, s);
 }
 
 // w *= inv_b; then result[0] = <w, r>, after which r -= c w with c = that dot
@@ -1207,8 +1459,7 @@ __global__ __launch_bounds__(BS) void k_scale_dot32(float2 *w, double inv_b, con
 hipError_t scale_dot32(Blas &B, float2 *w, double inv_b, const float2 *r, long n, hipStream_t s)
 {
     hipLaunchKernelGGL(k_scale_dot32, blas_blocks(n), BS, 0, s, w, inv_b, r, n, B.partial);
-    hipLaunchKernelGGL(k_finish, 1, BS, 0, s, B.partial, blas_blocks(n), 1, B.result);
-    return hipGetLastError();
+    return finish_one(B, n, 1, s);
 }
 
 // r -= c w; result[0] = (|r|^2, 0)
@@ -1229,8 +1480,7 @@ __global__ __launch_bounds__(BS) void k_axpy32(float2 *r, double2 c, const float
 hipError_t axpy32(Blas &B, float2 *r, double2 c, const float2 *w, long n, hipStream_t s)
 {
     hipLaunchKernelGGL(k_axpy32, blas_blocks(n), BS, 0, s, r, c, w, n, B.partial);
-    hipLaunchKernelGGL(k_finish, 1, BS, 0, s, B.partial, blas_blocks(n), 1, B.result);
-    return hipGetLastError();
+    return finish_one(B, n, 1, s);
 }
 
 // x += scale * sum_j coef[j] Z_j (FP64 x, FP32 Z)
