@@ -234,12 +234,19 @@ struct m3 {
     cx<double> e[9];
 };
 
-__device__ __forceinline__ m3 m3_load(const Geo &g, const double2 *U, const int x[4], int mu)
+// the links of site x begin here in U
+__device__ __forceinline__ long links_at(const Geo &g, const int x[4])
 {
-    long J = encode(g, x);
-    int d = (int)(J / g.Vd), loc = (int)(J - (long)d * g.Vd);
+    const long J = encode(g, x);
+    const int d = (int)(J / g.Vd);
+    return (long)d * 36 * g.Vd + (J - (long)d * g.Vd);
+}
+
+__device__ __forceinline__ m3 m3_load(const Geo &g, const double2 *U, long site, int mu)
+{
     m3 r;
-    for (int e = 0; e < 9; e++) r.e[e] = ld<double, double>(U, (((long)d * 4 + mu) * 9 + e) * g.Vd + loc);
+#pragma unroll
+    for (int e = 0; e < 9; e++) r.e[e] = ld<double, double>(U, site + (long)(mu * 9 + e) * g.Vd);
     return r;
 }
 
@@ -247,9 +254,12 @@ __device__ __forceinline__ m3 m3_load(const Geo &g, const double2 *U, const int 
 __device__ __forceinline__ m3 m3_mul(const m3 &a, bool da, const m3 &b, bool db)
 {
     m3 r;
+#pragma unroll
     for (int i = 0; i < 3; i++)
+#pragma unroll
         for (int j = 0; j < 3; j++) {
             cx<double> s = czero<double>();
+#pragma unroll
             for (int k = 0; k < 3; k++) {
                 cx<double> av = da ? cx<double>{a.e[k * 3 + i].r, -a.e[k * 3 + i].i} : a.e[i * 3 + k];
                 cx<double> bv = db ? cx<double>{b.e[j * 3 + k].r, -b.e[j * 3 + k].i} : b.e[k * 3 + j];
@@ -262,50 +272,59 @@ __device__ __forceinline__ m3 m3_mul(const m3 &a, bool da, const m3 &b, bool db)
 
 __device__ __forceinline__ void shift(const Geo &g, const int x[4], int mu, int step, int y[4])
 {
-    for (int m = 0; m < 4; m++) y[m] = x[m];
-    y[mu] += step;
-    if (y[mu] >= g.L[mu]) y[mu] -= g.L[mu];
-    if (y[mu] < 0) y[mu] += g.L[mu];
+#pragma unroll
+    for (int m = 0; m < 4; m++) {   // (mu is uniform in a wave, the arrays stay in registers)
+        y[m] = m == mu ? x[m] + step : x[m];
+        if (y[m] >= g.L[m]) y[m] -= g.L[m];
+        if (y[m] < 0) y[m] += g.L[m];
+    }
 }
 
-// F_munu = (Q - Q^dag) / 8, Q = sum of the four leaves at x oriented mu -> nu
-__device__ m3 field_strength(const Geo &g, const double2 *U, const int x[4], int mu, int nu)
+// A link (site, direction) that enters a leaf as itself or as its adjoint.
+struct LeafLink {
+    long site;
+    int mu;
+    bool dag;
+};
+// Product of four links.  U is made to depend on what has been formed, so that
+// no more than two links' matrices are in registers ahead of their product.
+__device__ __forceinline__ m3 leaf(const Geo &g, const double2 *&U, LeafLink a, LeafLink b, LeafLink c, LeafLink d)
 {
-    int xpm[4], xmm[4], xpn[4], xmn[4], a[4], b[4], c[4];
-    shift(g, x, mu, +1, xpm);
-    shift(g, x, mu, -1, xmm);
-    shift(g, x, nu, +1, xpn);
-    shift(g, x, nu, -1, xmn);
-    shift(g, xpn, mu, -1, a);   // x + nu - mu
-    shift(g, xmm, nu, -1, b);   // x - mu - nu
-    shift(g, xmn, mu, +1, c);   // x - nu + mu
-    m3 Q, t;
-    // leaf 1: U_mu(x) U_nu(x+mu) U_mu(x+nu)^+ U_nu(x)^+
-    t = m3_mul(m3_load(g, U, x, mu), false, m3_load(g, U, xpm, nu), false);
-    t = m3_mul(t, false, m3_load(g, U, xpn, mu), true);
-    Q = m3_mul(t, false, m3_load(g, U, x, nu), true);
-    // leaf 2: U_nu(x) U_mu(x+nu-mu)^+ U_nu(x-mu)^+ U_mu(x-mu)
-    t = m3_mul(m3_load(g, U, x, nu), false, m3_load(g, U, a, mu), true);
-    t = m3_mul(t, false, m3_load(g, U, xmm, nu), true);
-    t = m3_mul(t, false, m3_load(g, U, xmm, mu), false);
-    for (int e = 0; e < 9; e++) Q.e[e] = Q.e[e] + t.e[e];
-    // leaf 3: U_mu(x-mu)^+ U_nu(x-mu-nu)^+ U_mu(x-mu-nu) U_nu(x-nu)
-    t = m3_mul(m3_load(g, U, xmm, mu), true, m3_load(g, U, b, nu), true);
-    t = m3_mul(t, false, m3_load(g, U, b, mu), false);
-    t = m3_mul(t, false, m3_load(g, U, xmn, nu), false);
-    for (int e = 0; e < 9; e++) Q.e[e] = Q.e[e] + t.e[e];
-    // leaf 4: U_nu(x-nu)^+ U_mu(x-nu) U_nu(x-nu+mu) U_mu(x)^+
-    t = m3_mul(m3_load(g, U, xmn, nu), true, m3_load(g, U, xmn, mu), false);
-    t = m3_mul(t, false, m3_load(g, U, c, nu), false);
-    t = m3_mul(t, false, m3_load(g, U, x, mu), true);
-    for (int e = 0; e < 9; e++) Q.e[e] = Q.e[e] + t.e[e];
-    m3 F;
-    for (int i = 0; i < 3; i++)
-        for (int j = 0; j < 3; j++) {
-            cx<double> q = Q.e[i * 3 + j], qd = {Q.e[j * 3 + i].r, -Q.e[j * 3 + i].i};
-            F.e[i * 3 + j] = scal(0.125, q - qd);
-        }
-    return F;
+    m3 t = m3_mul(m3_load(g, U, a.site, a.mu), a.dag, m3_load(g, U, b.site, b.mu), b.dag);
+    asm volatile("" : "+s"(U) : "v"(t.e[0].r), "v"(t.e[4].r), "v"(t.e[8].i));
+    t = m3_mul(t, false, m3_load(g, U, c.site, c.mu), c.dag);
+    t = m3_mul(t, false, m3_load(g, U, d.site, d.mu), d.dag);
+    asm volatile("" : "+s"(U) : "v"(t.e[0].r), "v"(t.e[4].r), "v"(t.e[8].i));
+    return t;
+}
+
+// Q_munu = sum of the four leaves at x oriented mu -> nu
+__device__ __forceinline__ m3 clover_leaves(const Geo &g, const double2 *U, const int x[4], int mu, int nu)
+{
+    auto at = [&](int m, int step_m, int n, int step_n) {   // links of x + step_m m + step_n n
+        int y[4], z[4];
+        shift(g, x, m, step_m, y);
+        shift(g, y, n, step_n, z);
+        return links_at(g, z);
+    };
+    const long o = links_at(g, x), xpm = at(mu, +1, nu, 0), xmm = at(mu, -1, nu, 0), xpn = at(mu, 0, nu, +1),
+               xmn = at(mu, 0, nu, -1), a = at(mu, -1, nu, +1), b = at(mu, -1, nu, -1), c = at(mu, +1, nu, -1);
+    // U_mu(x) U_nu(x+mu) U_mu(x+nu)^+ U_nu(x)^+
+    m3 Q = leaf(g, U, {o, mu, false}, {xpm, nu, false}, {xpn, mu, true}, {o, nu, true}), t;
+    auto add = [&] {
+#pragma unroll
+        for (int e = 0; e < 9; e++) Q.e[e] = Q.e[e] + t.e[e];
+    };
+    // U_nu(x) U_mu(x+nu-mu)^+ U_nu(x-mu)^+ U_mu(x-mu)
+    t = leaf(g, U, {o, nu, false}, {a, mu, true}, {xmm, nu, true}, {xmm, mu, false});
+    add();
+    // U_mu(x-mu)^+ U_nu(x-mu-nu)^+ U_mu(x-mu-nu) U_nu(x-nu)
+    t = leaf(g, U, {xmm, mu, true}, {b, nu, true}, {b, mu, false}, {xmn, nu, false});
+    add();
+    // U_nu(x-nu)^+ U_mu(x-nu) U_nu(x-nu+mu) U_mu(x)^+
+    t = leaf(g, U, {xmn, nu, true}, {xmn, mu, false}, {c, nu, false}, {o, mu, true});
+    add();
+    return Q;
 }
 
 // In the chiral basis sigma_jk = -eps_jkl diag(s_l, s_l) (j,k spatial) and
@@ -313,103 +332,151 @@ __device__ m3 field_strength(const Geo &g, const double2 *U, const int x[4], int
 // s_l, each chiral block of D_cl is [[E3, E1 - i E2], [E1 + i E2, -E3]] with
 //   upper: E1 = -(i c/2)(F_yz + F_xt), E2 = (i c/2)(F_xz - F_yt), E3 = -(i c/2)(F_xy + F_zt)
 //   lower: E1 = -(i c/2)(F_yz - F_xt), E2 = (i c/2)(F_xz + F_yt), E3 = -(i c/2)(F_xy - F_zt)
-__global__ void k_clover_build(Geo g, const double2 *U, double kappa, double csw, double2 *C)
+//
+// A workgroup takes 64 consecutive sites: wave p forms F_munu = (Q - Q^dag) / 8
+// of plane p for all of them in registers and leaves it in LDS; then wave w
+// forms and stores entries 6w .. 6w + 5 of the 36 packed pairs.  With all six F of
+// a site in one thread the matrices went to scratch (7.7 kB a thread): 16^3x32
+// 0.78 ms, 32^3x64 11.1 ms; now 0.18 and 2.96 ms.  Bound by the links' way through the
+// caches: each is read some hundred times.
+constexpr int CLOVER_SITES = 64;
+__global__ __launch_bounds__(6 * CLOVER_SITES) void k_clover_build(Geo g, const double2 *U, double kappa, double csw, double2 *C)
 {
-    long I = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (I >= g.V) return;
+    __shared__ cx<double> F[6][9][CLOVER_SITES];   // planes xy, xz, xt, yz, yt, zt
+    const int lane = threadIdx.x % CLOVER_SITES, w = __builtin_amdgcn_readfirstlane((int)threadIdx.x / CLOVER_SITES);
+    const long I = (long)blockIdx.x * CLOVER_SITES + lane;   // V is a multiple of 64
     int x[4], d, loc;
     decode(g, I, x, d, loc);
-    m3 Fxy = field_strength(g, U, x, 0, 1), Fxz = field_strength(g, U, x, 0, 2), Fxt = field_strength(g, U, x, 0, 3);
-    m3 Fyz = field_strength(g, U, x, 1, 2), Fyt = field_strength(g, U, x, 1, 3), Fzt = field_strength(g, U, x, 2, 3);
-    const double diag = 1.0 / (2.0 * kappa);
-    for (int blk = 0; blk < 2; blk++) {
-        const double sg = blk == 0 ? 1.0 : -1.0;
-        cx<double> M[6][6];
+    {
+        const m3 Q = clover_leaves(g, U, x, w < 3 ? 0 : w < 5 ? 1 : 2, w < 3 ? w + 1 : w < 5 ? w - 1 : 3);
+#pragma unroll
         for (int i = 0; i < 3; i++)
-            for (int j = 0; j < 3; j++) {
-                int e = i * 3 + j;
-                // -(i c/2) X = (c/2) (X.i, -X.r)
-                cx<double> s1 = Fyz.e[e] + scal(sg, Fxt.e[e]);
-                cx<double> s2 = Fxz.e[e] - scal(sg, Fyt.e[e]);
-                cx<double> s3 = Fxy.e[e] + scal(sg, Fzt.e[e]);
-                cx<double> E1 = scal(0.5 * csw, cx<double>{s1.i, -s1.r});
-                cx<double> E2 = scal(0.5 * csw, cx<double>{-s2.i, s2.r});
-                cx<double> E3 = scal(0.5 * csw, cx<double>{s3.i, -s3.r});
-                M[i][j] = E3;
-                M[3 + i][3 + j] = neg(E3);
-                M[i][3 + j] = E1 - times_i(E2);
-                M[3 + i][j] = E1 + times_i(E2);
-            }
-        for (int i = 0; i < 6; i++) M[i][i].r += diag;
-        long base = ((long)d * 36 + blk * 18) * g.Vd + loc;
-        for (int q = 0; q < 3; q++) C[base + q * g.Vd] = make_double2(M[2 * q][2 * q].r, M[2 * q + 1][2 * q + 1].r);
-        for (int i = 1; i < 6; i++)
-            for (int j = 0; j < i; j++) C[base + (3 + tri_index(i, j)) * g.Vd] = make_double2(M[i][j].r, M[i][j].i);
+#pragma unroll
+            for (int j = 0; j < 3; j++)
+                F[w][i * 3 + j][lane] = scal(0.125, Q.e[i * 3 + j] - cx<double>{Q.e[j * 3 + i].r, -Q.e[j * 3 + i].i});
+    }
+    __syncthreads();
+    // entry (I, J), I >= J, of block blk: colour e, spins I / 3 and J / 3
+    auto entry = [&](int blk, int row, int col) {
+        const double sg = blk == 0 ? 1.0 : -1.0;
+        const int e = row % 3 * 3 + col % 3;
+        // -(i c/2) X = (c/2) (X.i, -X.r)
+        if (row / 3 == col / 3) {
+            const cx<double> s3 = F[0][e][lane] + scal(sg, F[5][e][lane]);
+            const cx<double> E3 = scal(0.5 * csw, cx<double>{s3.i, -s3.r});
+            return row < 3 ? E3 : neg(E3);
+        }
+        const cx<double> s1 = F[3][e][lane] + scal(sg, F[2][e][lane]), s2 = F[1][e][lane] - scal(sg, F[4][e][lane]);
+        const cx<double> E1 = scal(0.5 * csw, cx<double>{s1.i, -s1.r}), E2 = scal(0.5 * csw, cx<double>{-s2.i, s2.r});
+        return E1 + times_i(E2);
+    };
+    const double diag = 1.0 / (2.0 * kappa);
+    const long base = (long)d * 36 * g.Vd + loc;
+    for (int k = 0; k < 6; k++) {
+        const int n = 6 * w + k, blk = n / 18, q = n % 18;
+        double2 v;
+        if (q < 3) {
+            v = make_double2(entry(blk, 2 * q, 2 * q).r + diag, entry(blk, 2 * q + 1, 2 * q + 1).r + diag);
+        } else {
+            int row = 1;
+            while (tri_index(row + 1, 0) <= q - 3) row++;
+            const cx<double> m = entry(blk, row, q - 3 - tri_index(row, 0));
+            v = make_double2(m.r, m.i);
+        }
+        C[base + (long)n * g.Vd] = v;
     }
 }
 
 hipError_t clover_build(const Geo &g, const double2 *U64, double kappa, double csw, double2 *C64, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_clover_build, nblocks(g.V, 128), 128, 0, s, g, U64, kappa, csw, C64);
+    if (g.V % CLOVER_SITES) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_clover_build, (unsigned)(g.V / CLOVER_SITES), 6 * CLOVER_SITES, 0, s, g, U64, kappa, csw, C64);
     return hipGetLastError();
 }
 
-// one thread per (site, chiral block): copy on even sites, Gauss-Jordan
-// inverse with partial pivoting on odd sites
-__global__ void k_clover_schur(Geo g, const double2 *C, double2 *Cs, int *bad)
+// one thread per (site, chiral block): copy on even sites, inverse on odd sites
+// by Gauss-Jordan elimination in place with partial pivoting.  Every index is
+// known at compile time (rows are exchanged by selection), so the matrix stays in
+// registers; with 6 x 12 augmented rows in scratch 16^3x32 took 0.70 ms, 32^3x64
+// 11.0 ms; now 0.039 and 0.48 ms, bound by memory (1152 bytes a site).
+__global__ __launch_bounds__(128) void k_clover_schur(Geo g, const double2 *C, double2 *Cs, int *bad)
 {
-    long t = (long)blockIdx.x * blockDim.x + threadIdx.x;
+    const long t = (long)blockIdx.x * blockDim.x + threadIdx.x;
     if (t >= 2 * g.V) return;
-    long I = t >> 1;
-    int blk = (int)(t & 1);
-    int d = (int)(I / g.Vd), loc = (int)(I - (long)d * g.Vd);
-    long base = ((long)d * 36 + blk * 18) * g.Vd + loc;
+    const int blk = t >= g.V;
+    const long I = t - blk * g.V;
+    const int d = (int)(I / g.Vd), loc = (int)(I - (long)d * g.Vd);
+    const long base = ((long)d * 36 + blk * 18) * g.Vd + loc;
+    double2 in[18];
+#pragma unroll
+    for (int q = 0; q < 18; q++) in[q] = C[base + q * g.Vd];
     if (loc < g.Vh) {
-        for (int q = 0; q < 18; q++) Cs[base + q * g.Vd] = C[base + q * g.Vd];
+#pragma unroll
+        for (int q = 0; q < 18; q++) Cs[base + q * g.Vd] = in[q];
         return;
     }
-    cx<double> M[6][12];
-    for (int i = 0; i < 6; i++)
-        for (int j = 0; j < 12; j++) M[i][j] = czero<double>();
+    cx<double> M[6][6];
+#pragma unroll
     for (int q = 0; q < 3; q++) {
-        double2 v = C[base + q * g.Vd];
-        M[2 * q][2 * q].r = v.x;
-        M[2 * q + 1][2 * q + 1].r = v.y;
+        M[2 * q][2 * q] = {in[q].x, 0};
+        M[2 * q + 1][2 * q + 1] = {in[q].y, 0};
     }
+#pragma unroll
     for (int i = 1; i < 6; i++)
+#pragma unroll
         for (int j = 0; j < i; j++) {
-            double2 v = C[base + (3 + tri_index(i, j)) * g.Vd];
+            const double2 v = in[3 + tri_index(i, j)];
             M[i][j] = {v.x, v.y};
             M[j][i] = {v.x, -v.y};
         }
-    for (int i = 0; i < 6; i++) M[i][6 + i].r = 1.0;
+    int piv[6];   // the row exchanged with row c
+#pragma unroll
     for (int c = 0; c < 6; c++) {
         int p = c;
         double best = M[c][c].r * M[c][c].r + M[c][c].i * M[c][c].i;
+#pragma unroll
         for (int r = c + 1; r < 6; r++) {
-            double v = M[r][c].r * M[r][c].r + M[r][c].i * M[r][c].i;
+            const double v = M[r][c].r * M[r][c].r + M[r][c].i * M[r][c].i;
             if (v > best) { best = v; p = r; }
         }
         if (!(best > 0)) { atomicOr(bad, 1); return; }
-        if (p != c)
-            for (int j = 0; j < 12; j++) { cx<double> tmp = M[c][j]; M[c][j] = M[p][j]; M[p][j] = tmp; }
-        cx<double> piv = M[c][c];
-        double inv = 1.0 / best;
-        cx<double> ip = {piv.r * inv, -piv.i * inv};
-        for (int j = 0; j < 12; j++) M[c][j] = M[c][j] * ip;
+        piv[c] = p;
+#pragma unroll
+        for (int r = c + 1; r < 6; r++) {
+            if (p != r) continue;
+#pragma unroll
+            for (int j = 0; j < 6; j++) { const cx<double> tmp = M[c][j]; M[c][j] = M[r][j]; M[r][j] = tmp; }
+        }
+        const double inv = 1.0 / best;
+        const cx<double> ip = {M[c][c].r * inv, -M[c][c].i * inv};
+#pragma unroll
+        for (int j = 0; j < 6; j++) M[c][j] = j == c ? ip : M[c][j] * ip;
+#pragma unroll
         for (int r = 0; r < 6; r++) {
             if (r == c) continue;
-            cx<double> f = M[r][c];
-            for (int j = 0; j < 12; j++) M[r][j] = M[r][j] - f * M[c][j];
+            const cx<double> f = M[r][c];
+#pragma unroll
+            for (int j = 0; j < 6; j++) M[r][j] = j == c ? neg(f * ip) : M[r][j] - f * M[c][j];
         }
     }
-    for (int q = 0; q < 3; q++) Cs[base + q * g.Vd] = make_double2(M[2 * q][6 + 2 * q].r, M[2 * q + 1][6 + 2 * q + 1].r);
-    for (int i = 1; i < 6; i++)
-        for (int j = 0; j < i; j++) {
-            // Hermitian inverse: average the two triangles to remove rounding asymmetry
-            cx<double> a = M[i][6 + j], b = M[j][6 + i];
-            Cs[base + (3 + tri_index(i, j)) * g.Vd] = make_double2(0.5 * (a.r + b.r), 0.5 * (a.i - b.i));
+    // (P A)^-1 = A^-1 P^-1: the row exchanges, last first, on the columns
+#pragma unroll
+    for (int c = 5; c >= 0; c--)
+#pragma unroll
+        for (int r = c + 1; r < 6; r++) {
+            if (piv[c] != r) continue;
+#pragma unroll
+            for (int i = 0; i < 6; i++) { const cx<double> tmp = M[i][c]; M[i][c] = M[i][r]; M[i][r] = tmp; }
         }
+#pragma unroll
+    for (int q = 0; q < 3; q++) Cs[base + q * g.Vd] = make_double2(M[2 * q][2 * q].r, M[2 * q + 1][2 * q + 1].r);
+#pragma unroll
+    for (int i = 1; i < 6; i++)
+#pragma unroll
+        for (int j = 0; j < i; j++)
+            // Hermitian inverse: average the two triangles to remove rounding asymmetry
+            Cs[base + (3 + tri_index(i, j)) * g.Vd] =
+                make_double2(0.5 * (M[i][j].r + M[j][i].r), 0.5 * (M[i][j].i - M[j][i].i));
 }
 
 hipError_t clover_schur(const Geo &g, const double2 *C64, double2 *Cs64, int *bad, hipStream_t s)
