@@ -71,124 +71,68 @@ template <int BX, int BY, int BZ, int BT> struct Shape {
 
 // ---- block reductions over all VD threads (deterministic order) -----------
 
-// Sum over the 64 lanes of a wave, returned to every lane (all lanes active):
-// DPP permutes within each 16-lane row (lane ^ 1, lane ^ 2, then the mirrored
-// halves of 8 and of 16 lanes) leave every lane with its row's sum; the four
-// row sums are read out and added.
-__device__ __forceinline__ float wave_sum(float v)
+template <int CTRL> __device__ __forceinline__ float dpp(float v)
 {
-    v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0xB1, 0xF, 0xF, false));   // quad_perm 1,0,3,2
-    v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x4E, 0xF, 0xF, false));   // quad_perm 2,3,0,1
-    v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x141, 0xF, 0xF, false));  // row_half_mirror
-    v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x140, 0xF, 0xF, false));  // row_mirror
-    const float r0 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 0));
-    const float r1 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 16));
-    const float r2 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 32));
-    const float r3 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 48));
-    return (r0 + r1) + (r2 + r3);
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, false));
 }
-__device__ __forceinline__ double wave_sum(double v)
+template <int CTRL> __device__ __forceinline__ double dpp(double v)
 {
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
+    return __hiloint2double(__builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xF, 0xF, false),
+                            __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xF, 0xF, false));
+}
+__device__ __forceinline__ float lane_value(float v, int l)
+{
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l));
+}
+__device__ __forceinline__ double lane_value(double v, int l)
+{
+    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), l), __builtin_amdgcn_readlane(__double2loint(v), l));
+}
+// Sum (MAX: maximum) over groups of SEG consecutive lanes (4, 8, 16 or 64), in
+// every lane of the group (all lanes active): DPP permutes within each 16-lane
+// row (lane ^ 1, lane ^ 2, then the mirrored halves of 8 and of 16 lanes) leave
+// every lane with its row's result; the four row results are read out and
+// combined.  A permute is an operand of the addition; a shuffle through LDS
+// waits a hundred cycles and more at each step.  With the 16-bit epilogue's two
+// maxima taken together, a launch on 8^4 went from 28.6 to 27.6 us (FP16, 4^4
+// domains), from 26.8 to 25.4 (2^4), in FP64 from 31.4 to 30.0.
+template <int SEG, bool MAX, typename T> __device__ __forceinline__ T lanes_reduce(T v)
+{
+    static_assert(SEG == 4 || SEG == 8 || SEG == 16 || SEG == 64, "lanes of a group");
+    auto op = [](T a, T b) { return MAX ? fmax(a, b) : a + b; };
+    v = op(v, dpp<0xB1>(v));                           // quad_perm 1,0,3,2
+    v = op(v, dpp<0x4E>(v));                           // quad_perm 2,3,0,1
+    if constexpr (SEG >= 8) v = op(v, dpp<0x141>(v));   // row_half_mirror
+    if constexpr (SEG >= 16) v = op(v, dpp<0x140>(v));  // row_mirror
+    if constexpr (SEG == 64)
+        v = op(op(lane_value(v, 0), lane_value(v, 16)), op(lane_value(v, 32), lane_value(v, 48)));
     return v;
 }
 
-template <int VD, typename T, int N> __device__ __forceinline__ void block_sum(T (&v)[N], T *red)
+// Sums (MAX: maxima) over the sites of each domain of the workgroup, NW waves;
+// every thread joins.  NDW > 1: VH consecutive lanes of a wave belong to one
+// domain, sub the calling thread's; NDW == 1: all waves to one.  No closing
+// barrier: a call site has its own part of red or barriers pass before its next use.
+template <int VH, int NDW, int NW, bool MAX, typename T, int N>
+__device__ __forceinline__ void domain_reduce(T (&v)[N], T *red, int sub)
 {
-    if constexpr (VD >= 64) {
-        constexpr int NW = VD / 64;
+    constexpr int SEG = NDW > 1 ? VH : 64;
+    const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
 #pragma unroll
-        for (int q = 0; q < N; q++) v[q] = wave_sum(v[q]);
-        int w = threadIdx.x >> 6;
-        if ((threadIdx.x & 63) == 0)
+    for (int k = 0; k < N; k++) v[k] = lanes_reduce<SEG, MAX>(v[k]);
+    if (lane % SEG == 0)
 #pragma unroll
-            for (int q = 0; q < N; q++) red[q * NW + w] = v[q];
-        __syncthreads();
+        for (int k = 0; k < N; k++) red[(k * NW + w) * NDW + (NDW > 1 ? lane / SEG : 0)] = v[k];
+    __syncthreads();
 #pragma unroll
-        for (int q = 0; q < N; q++) {
-            T s = 0;
-            for (int k = 0; k < NW; k++) s += red[q * NW + k];
-            v[q] = s;
+    for (int k = 0; k < N; k++) {
+        T s = red[k * NW * NDW + sub];
+#pragma unroll
+        for (int j = 1; j < NW; j++) {
+            const T x = red[(k * NW + j) * NDW + sub];
+            s = MAX ? fmax(s, x) : s + x;
         }
-        __syncthreads();
-    } else {
-#pragma unroll
-        for (int q = 0; q < N; q++) red[q * VD + threadIdx.x] = v[q];
-        __syncthreads();
-        for (int o = VD / 2; o > 0; o >>= 1) {
-            if ((int)threadIdx.x < o)
-#pragma unroll
-                for (int q = 0; q < N; q++) red[q * VD + threadIdx.x] += red[q * VD + threadIdx.x + o];
-            __syncthreads();
-        }
-#pragma unroll
-        for (int q = 0; q < N; q++) v[q] = red[q * VD];
-        __syncthreads();
-    }
-}
-
-template <int VD, typename T> __device__ __forceinline__ T block_max(T v, T *red)
-{
-    if constexpr (VD >= 64) {
-        constexpr int NW = VD / 64;
-        for (int o = 32; o > 0; o >>= 1) v = fmax(v, __shfl_xor(v, o));
-        if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
-        __syncthreads();
-        T m = red[0];
-        for (int k = 1; k < NW; k++) m = fmax(m, red[k]);
-        __syncthreads();
-        return m;
-    } else {
-        red[threadIdx.x] = v;
-        __syncthreads();
-        for (int o = VD / 2; o > 0; o >>= 1) {
-            if ((int)threadIdx.x < o) red[threadIdx.x] = fmax(red[threadIdx.x], red[threadIdx.x + o]);
-            __syncthreads();
-        }
-        T m = red[0];
-        __syncthreads();
-        return m;
-    }
-}
-
-// Reductions over the sites of each domain when NDW domains share a
-// workgroup: wave 0 holds the even sites and wave 1 the odd sites of all NDW
-// domains (NDW * VD / 2 = 64), VD / 2 consecutive lanes per domain.
-template <int VD, int NDW, typename T, int N> __device__ __forceinline__ void slot_sum(T (&v)[N], T *red)
-{
-    if constexpr (NDW == 1) {
-        block_sum<VD, T, N>(v, red);
-    } else {
-        constexpr int VH = VD / 2;
-        static_assert(NDW * VH == 64, "one wave per parity");
-#pragma unroll
-        for (int q = 0; q < N; q++)
-            for (int o = VH / 2; o > 0; o >>= 1) v[q] += __shfl_xor(v[q], o);
-        const int par = threadIdx.x >> 6, sub = (threadIdx.x & 63) / VH;
-        if ((threadIdx.x % VH) == 0)
-#pragma unroll
-            for (int q = 0; q < N; q++) red[(q * 2 + par) * NDW + sub] = v[q];
-        __syncthreads();
-#pragma unroll
-        for (int q = 0; q < N; q++) v[q] = red[(q * 2) * NDW + sub] + red[(q * 2 + 1) * NDW + sub];
-        __syncthreads();
-    }
-}
-
-template <int VD, int NDW, typename T> __device__ __forceinline__ T slot_max(T v, T *red)
-{
-    if constexpr (NDW == 1) {
-        return block_max<VD, T>(v, red);
-    } else {
-        constexpr int VH = VD / 2;
-        static_assert(NDW * VH == 64, "one wave per parity");
-        for (int o = VH / 2; o > 0; o >>= 1) v = fmax(v, __shfl_xor(v, o));
-        const int par = threadIdx.x >> 6, sub = (threadIdx.x & 63) / VH;
-        if ((threadIdx.x % VH) == 0) red[par * NDW + sub] = v;
-        __syncthreads();
-        const T m = fmax(red[sub], red[NDW + sub]);
-        __syncthreads();
-        return m;
+        v[k] = s;
     }
 }
 
@@ -711,7 +655,6 @@ __device__ __forceinline__ void lds_block_solve(const SapArgs &a, const int d, c
     using T = float;
     constexpr int VD = Sh::VD, VH = Sh::VH, NLC = 6;
     constexpr int NT = NDW > 1 ? NDW * VD : Sh::NT;   // threads of the workgroup
-    constexpr int RV = NDW > 1 ? VD : NT;             // reduction width argument
     static_assert(NDW == 1 || NDW * VH == 64, "packed domains: one wave per parity");
     __shared__ c2_t she_all[NDW][6 * VH];     // even sites: r
     __shared__ c2_t sho_all[NDW][6 * VH];     // odd sites: C_o^-1 D_oe r; x in the reconstruction
@@ -719,7 +662,9 @@ __device__ __forceinline__ void lds_block_solve(const SapArgs &a, const int d, c
     // FP32 clover blocks leave no registers for A through the MR steps: it waits in LDS
     constexpr bool A_LDS = sizeof(v2<G>) == 8;
     __shared__ c2_t sa_all[A_LDS ? NDW * 6 * VD : 1];
-    __shared__ T red[NDW > 1 ? 6 * NDW : NT >= 64 ? 3 * (NT / 64) : 3 * NT];
+    constexpr int NW = NT / 64;
+    static_assert(NT % 64 == 0, "whole waves");
+    __shared__ T red[2][3 * NW * NDW];
 
     const int par = (int)threadIdx.x / (NDW * VH);
     const int idx = (int)threadIdx.x - par * (NDW * VH);
@@ -861,7 +806,7 @@ __device__ __forceinline__ void lds_block_solve(const SapArgs &a, const int d, c
                 dots[2] = fmad(P[k].i, P[k].i, fmad(P[k].r, P[k].r, dots[2]));
             }
         }
-        slot_sum<RV, NDW, T, 3>(dots, red);
+        domain_reduce<VH, NDW, NW, false>(dots, red[0], sub);
         if (par == 0) {
             cx<T> alpha = dots[2] > T(0) ? cx<T>{dots[0] / dots[2], dots[1] / dots[2]} : czero<T>();
             if (A_LDS) ld_c2<VD>(va, A);
@@ -910,25 +855,30 @@ __device__ __forceinline__ void lds_block_solve(const SapArgs &a, const int d, c
             for (int j = 0; j < 6; j++) psi[j * VD] = ps[j];
         }
     }
-    if (f.res_out) {
+    T mx[2] = {T(1), T(1)};
+    if constexpr (SCALED) {
+        if (!f.res_out && !f.faces_out) return;
         cx<T> rr[12];
 #pragma unroll
         for (int k = 0; k < 12; k++) rr[k] = czero<T>();
         if (par == 0) ld_c2<VH>(ve, rr);
-        T sc = T(1);
-        if constexpr (SCALED) {
-            sc = pow2_ceil(slot_max<RV, NDW, T>(maxabs12(rr), red));
-            if (loc == 0) global_ptr(a.res_scale)[d] = (float)sc;
+        mx[0] = maxabs12(rr);
+        mx[1] = maxabs12(A);
+        domain_reduce<VH, NDW, NW, true>(mx, red[1], sub);
+        mx[0] = pow2_ceil(mx[0]);
+        mx[1] = T(8) * pow2_ceil(mx[1]);
+        if (f.res_out) {
+            if (loc == 0) global_ptr(a.res_scale)[d] = (float)mx[0];
+            if (par == 0) st_res<VH, SS>(a.res, rbase, T(1) / mx[0], rr);
         }
-        if (par == 0) st_res<VH, SS>(a.res, rbase, T(1) / sc, rr);
+    } else if (f.res_out && par == 0) {
+        cx<T> rr[12];
+        ld_c2<VH>(ve, rr);
+        st_res<VH, SS>(a.res, rbase, T(1), rr);
     }
     if (f.faces_out) {
-        T sc = T(1);
-        if constexpr (SCALED) {
-            sc = T(8) * pow2_ceil(slot_max<RV, NDW, T>(maxabs12(A), red));
-            if (loc == 0) global_ptr(a.face_scale)[d] = (float)sc;
-        }
-        T inv = T(1) / sc;
+        if (SCALED && loc == 0) global_ptr(a.face_scale)[d] = (float)mx[1];
+        const T inv = T(1) / mx[1];
         if (live) {
             face_write<Sh, 0, T, SS>(a, d, l, A, inv, U[0]);
             face_write<Sh, 1, T, SS>(a, d, l, A, inv, U[1]);
@@ -1102,41 +1052,6 @@ __device__ __forceinline__ void split_hops(const typename SpEntry<T>::type *v, t
     }
 }
 
-// Sums (or, MAX, maxima) over the threads of each domain; every thread joins.
-// Waves hold VH consecutive lanes of one domain each (NDW > 1) or one domain's
-// sites; NWD waves (all of the workgroup's) contribute.  No closing barrier:
-// each call site has its own part of red.
-template <int VH, int NDW, int NW, bool MAX, typename T, int N>
-__device__ __forceinline__ void split_reduce(T (&v)[N], T *red, int sub)
-{
-    const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    constexpr int SEG = NDW > 1 ? VH : 64;
-#pragma unroll
-    for (int k = 0; k < N; k++) {
-        if constexpr (!MAX && NDW == 1) {
-            v[k] = wave_sum(v[k]);
-        } else {
-#pragma unroll
-            for (int o = SEG / 2; o > 0; o >>= 1) {
-                const T x = __shfl_xor(v[k], o);
-                v[k] = MAX ? fmax(v[k], x) : v[k] + x;
-            }
-        }
-        if (lane % SEG == 0) red[(k * NW + w) * NDW + (NDW > 1 ? lane / SEG : 0)] = v[k];
-    }
-    __syncthreads();
-#pragma unroll
-    for (int k = 0; k < N; k++) {
-        T s = red[k * NW * NDW + sub];
-#pragma unroll
-        for (int j = 1; j < NW; j++) {
-            const T x = red[(k * NW + j) * NDW + sub];
-            s = MAX ? fmax(s, x) : s + x;
-        }
-        v[k] = s;
-    }
-}
-
 template <class Sh, int NDW> struct SplitShape {
     static constexpr int GP = (NDW * Sh::VH + 63) / 64 * 64;   // threads of one (parity, q)
     static constexpr int NT = 4 * GP;
@@ -1158,7 +1073,7 @@ __device__ __forceinline__ void split_block_solve(const SapArgs &a, const int d,
     constexpr bool CL_LDS = sizeof(G) == 8;
     __shared__ e_t se_all[NDW][FE], so_all[NDW][FE], sx_all[NDW][2 * FE], sE_all[NDW][FE];
     __shared__ v2<G> scl_all[CL_LDS ? 4 * 18 * GP : 1];
-    __shared__ T red[3][3 * NW * NDW];
+    __shared__ T red[2][3 * NW * NDW];
 
     const int grp = __builtin_amdgcn_readfirstlane((int)threadIdx.x / GP);   // whole waves
     const int par = grp >> 1, q = grp & 1, idx = (int)threadIdx.x - grp * GP;
@@ -1300,7 +1215,7 @@ __device__ __forceinline__ void split_block_solve(const SapArgs &a, const int d,
                 dots[2] = fmad(P[k].i, P[k].i, fmad(P[k].r, P[k].r, dots[2]));
             }
         }
-        split_reduce<VH, NDW, NW, false>(dots, red[0], sub);
+        domain_reduce<VH, NDW, NW, false>(dots, red[0], sub);
         if (par == 0) {
             const cx<T> alpha = dots[2] > T(0) ? cx<T>{dots[0] / dots[2], dots[1] / dots[2]} : czero<T>();
 #pragma unroll
@@ -1364,7 +1279,7 @@ __device__ __forceinline__ void split_block_solve(const SapArgs &a, const int d,
         }
         if (!live) mx[1] = 0;
         T m[2] = {mx[0], mx[1]};
-        split_reduce<VH, NDW, NW, true>(m, red[1], sub);
+        domain_reduce<VH, NDW, NW, true>(m, red[1], sub);
         mx[0] = pow2_ceil(m[0]);
         mx[1] = T(8) * pow2_ceil(m[1]);
     } else {
@@ -1417,7 +1332,7 @@ __device__ __forceinline__ void f64_block_solve(const SapArgs &a, const int d, c
     __shared__ cx<T> she[12][VH];   // even sites: MR residual r
     __shared__ cx<T> sho[12][VH];   // odd sites: C_o^-1 D_oe r
     __shared__ cx<T> shx[12][VH];   // even sites: MR solution x
-    __shared__ T red[VD >= 64 ? 3 * (VD / 64) : 3 * VD];
+    __shared__ T red[3 * (VD / 64)];
 
     const int loc = threadIdx.x;
     const int par = loc >= VH;
@@ -1515,7 +1430,7 @@ __device__ __forceinline__ void f64_block_solve(const SapArgs &a, const int d, c
                 dots[2] = fmad(P[k].i, P[k].i, fmad(P[k].r, P[k].r, dots[2]));
             }
         }
-        block_sum<VD, T, 3>(dots, red);
+        domain_reduce<VH, 1, VD / 64, false>(dots, red, 0);
         if (par == 0) {
             const cx<T> alpha = dots[2] > T(0) ? cx<T>{dots[0] / dots[2], dots[1] / dots[2]} : czero<T>();
 #pragma unroll
@@ -1686,14 +1601,14 @@ template <class Sh, int PROD> constexpr int tile_lstr() { return PROD == PROD_VA
 typedef __bf16 bf16x4_t __attribute__((ext_vector_type(4)));
 
 // Sum over the lanes of a wave with equal lane % RT, returned to all of them.
-template <int RT> __device__ __forceinline__ float rhs_wave_sum(float v)
+template <int RT, bool MAX> __device__ __forceinline__ float rhs_wave_reduce(float v)
 {
-    if constexpr (RT == 2)
-        v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x4E, 0xF, 0xF, false));   // quad_perm 2,3,0,1
-    v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x124, 0xF, 0xF, false));   // row_ror:4
-    v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x128, 0xF, 0xF, false));   // row_ror:8
-    v += __shfl_xor(v, 16);
-    v += __shfl_xor(v, 32);
+    auto op = [](float a, float b) { return MAX ? fmax(a, b) : a + b; };
+    if constexpr (RT == 2) v = op(v, dpp<0x4E>(v));   // quad_perm 2,3,0,1
+    v = op(v, dpp<0x124>(v));                          // row_ror:4
+    v = op(v, dpp<0x128>(v));                          // row_ror:8
+    v = op(v, __shfl_xor(v, 16));
+    v = op(v, __shfl_xor(v, 32));
     return v;
 }
 
@@ -1702,7 +1617,7 @@ template <int RT> __device__ __forceinline__ float rhs_wave_sum(float v)
 template <int RT, int NW> __device__ __forceinline__ void rhs_sum(float (&v)[3], f32x4_t *red)
 {
 #pragma unroll
-    for (int q = 0; q < 3; q++) v[q] = rhs_wave_sum<RT>(v[q]);
+    for (int q = 0; q < 3; q++) v[q] = rhs_wave_reduce<RT, false>(v[q]);
     const int w = threadIdx.x >> 6, r = threadIdx.x % RT;
     if ((threadIdx.x & 63) < RT) red[w * RT + r] = f32x4_t{v[0], v[1], v[2], 0.f};
     __syncthreads();
@@ -1719,11 +1634,8 @@ template <int RT, int NW> __device__ __forceinline__ void rhs_sum(float (&v)[3],
 // closing barrier: the caller (the epilogue) gives it its own part of red.
 template <int RT, int NW> __device__ __forceinline__ void rhs_max2(float &a, float &b, f32x4_t *red)
 {
-#pragma unroll
-    for (int o = RT; o < 64; o <<= 1) {
-        a = fmax(a, __shfl_xor(a, o));
-        b = fmax(b, __shfl_xor(b, o));
-    }
+    a = rhs_wave_reduce<RT, true>(a);
+    b = rhs_wave_reduce<RT, true>(b);
     const int w = threadIdx.x >> 6, r = threadIdx.x % RT;
     if ((threadIdx.x & 63) < RT) red[w * RT + r] = f32x4_t{a, b, 0.f, 0.f};
     __syncthreads();
