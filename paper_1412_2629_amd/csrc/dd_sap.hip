@@ -1583,7 +1583,7 @@ __global__ __launch_bounds__((SplitShape<Sh, NDW>::NT), (SplitShape<Sh, NDW>::te
 // workgroups share a CU, and while one moves its domain's data (some 10 bytes a
 // cycle is what one CU gets from beyond its L1) the other one computes.  The
 // FP16 launch of one colour for 12 right-hand sides on 32^3x64 (4096 domains of
-// 4^4) takes 3.11 ms this way.  With tiles of four (157 KB, one workgroup a CU,
+// 4^4) takes 3.13 ms this way.  With tiles of four (157 KB, one workgroup a CU,
 // separate arrays for r and C_o^-1 D_oe r) it took 4.73 ms with 8-byte LDS reads,
 // mixed-precision multiply-adds and each site's lanes moving its boundary terms
 // and accumulator, and 3.89 ms with 16-byte reads, FP32 multiply-adds and whole
