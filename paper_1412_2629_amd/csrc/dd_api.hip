@@ -607,57 +607,69 @@ int apply_A64_list(const std::vector<Sys> &sys, const std::vector<int> &list, In
     return DDQCD_OK;
 }
 
-// Phase timings of a solve: each phase is bracketed by two events on the
-// launch stream; the elapsed times are read once at the end (no extra
-// synchronisation between phases).
+// Phase timings of a solve: stamps of the device's clock in the lead context's
+// pinned area, written by the stream at the phases' ends and read when the host
+// has waited for the stream anyway.  (A pair of events around each phase held
+// the stream up by some 12 us: 230 of 2530 us of a five-step solve on 8x4^3.)
+enum { CLOCK_SLOTS = 64 };
 struct Clock {
     struct Span {
-        hipEvent_t a, b;
+        int a, b;
         double *acc;
     };
     std::vector<Span> spans;
+    unsigned long long *const t;
     hipStream_t s;
-    explicit Clock(hipStream_t s_) : s(s_) {}
+    int n = 0, open = 0;
+    double ms_per_tick = 1e-5;
+    Clock(ddqcd_t lead, hipStream_t s_)
+        : t((unsigned long long *)(lead->res_host + 32L * lead->res_cap)), s(s_)
+    {
+        int dev = 0, khz = 0;
+        if (hipGetDevice(&dev) == hipSuccess &&
+            hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, dev) == hipSuccess && khz > 0)
+            ms_per_tick = 1.0 / khz;
+    }
+    int mark()
+    {
+        const int i = slot();
+        (void)stamp(t + i, s);
+        return i;
+    }
+    int slot()   // a stamp that a kernel of the phase writes
+    {
+        if (n == CLOCK_SLOTS) finish();
+        return n < CLOCK_SLOTS ? n++ : CLOCK_SLOTS - 1;
+    }
+    void add(int a, int b, double *acc) { spans.push_back({a, b, acc}); }
+    // the stream has been waited for
     void collect()
     {
-        if (spans.empty()) return;
-        (void)hipEventSynchronize(spans.back().b);
-        for (Span &p : spans) {
-            float ms = 0;
-            if (hipEventElapsedTime(&ms, p.a, p.b) == hipSuccess) *p.acc += ms;
-        }
-        release();
-    }
-    void release()
-    {
-        for (Span &p : spans) {
-            (void)hipEventDestroy(p.a);
-            (void)hipEventDestroy(p.b);
-        }
+        for (const Span &p : spans) *p.acc += (double)(long long)(t[p.b] - t[p.a]) * ms_per_tick;
         spans.clear();
+        if (open == 0) n = 0;
     }
-    ~Clock() { release(); }
+    void finish()
+    {
+        (void)hipStreamSynchronize(s);
+        collect();
+    }
 };
 
+// follows: nothing was launched since the span added last ended
 struct Timer {
     Clock &clk;
-    Clock::Span sp{nullptr, nullptr, nullptr};
-    Timer(Clock &c, double *acc) : clk(c)
+    double *acc;
+    int a;
+    Timer(Clock &c, double *acc_, bool follows = false) : clk(c), acc(acc_)
     {
-        if (hipEventCreate(&sp.a) != hipSuccess) return;
-        if (hipEventCreate(&sp.b) != hipSuccess) {
-            (void)hipEventDestroy(sp.a);
-            sp.a = nullptr;
-            return;
-        }
-        sp.acc = acc;
-        (void)hipEventRecord(sp.a, clk.s);
+        a = follows && !c.spans.empty() ? c.spans.back().b : c.mark();
+        clk.open++;
     }
     ~Timer()
     {
-        if (!sp.acc) return;
-        (void)hipEventRecord(sp.b, clk.s);
-        clk.spans.push_back(sp);
+        clk.open--;
+        clk.add(a, clk.mark(), acc);
     }
 };
 
@@ -693,7 +705,8 @@ struct ResultArea {
             const int cap = std::max(lead->res_cap, ns);
             if (lead->res_host) (void)hipHostFree(lead->res_host);
             lead->res_host = nullptr;
-            HIPCHK(lead, hipHostMalloc((void **)&lead->res_host, sizeof(double2) * 32 * cap, hipHostMallocDefault));
+            HIPCHK(lead, hipHostMalloc((void **)&lead->res_host, sizeof(double2) * 32 * cap + 8 * CLOCK_SLOTS,
+                                       hipHostMallocDefault));   // and the clock stamps
             lead->res_cap = cap;
         }
         for (int i = 0; i < ns; i++) sys[i].sl->blas.result = lead->res_host + 32L * i;
@@ -732,11 +745,11 @@ int fgcr(const std::vector<Sys> &sys, const std::vector<int> &guess, std::vector
     const int max_cycles = lead->max_cycles;
     const double tol = lead->tol;
     double tsap = 0, tA = 0, tgs = 0, tother = 0;
-    Clock clk(s);
     std::vector<FgcrState> st(ns);
     int e;
     ResultArea area(sys);
     if ((e = area.bind())) return e;
+    Clock clk(lead, s);
     for (int i = 0; i < ns; i++) {
         st[i].a.assign((size_t)m * m, 0);
         st[i].cc.assign(m, 0);
@@ -822,28 +835,26 @@ int fgcr(const std::vector<Sys> &sys, const std::vector<int> &guess, std::vector
                 if (st[i].in_cycle) act.push_back(i);
             if (act.empty()) break;
             // z_k = M r
-            {
-                Timer t(clk, &tsap);
-                std::vector<const double2 *> eta(ns);
-                std::vector<double2 *> out(ns);
-                std::vector<int> on(ns, 0);
-                for (int i = 0; i < ns; i++) {
-                    eta[i] = sys[i].sl->r;
-                    out[i] = Zk(i, k);
-                }
-                for (int i : act) on[i] = 1;
-                if ((e = run_sap(sys, eta, out, on, s))) return e;
+            const int t0 = clk.mark();
+            std::vector<const double2 *> eta(ns);
+            std::vector<double2 *> out(ns);
+            std::vector<int> on(ns, 0);
+            for (int i = 0; i < ns; i++) {
+                eta[i] = sys[i].sl->r;
+                out[i] = Zk(i, k);
             }
+            for (int i : act) on[i] = 1;
+            if ((e = run_sap(sys, eta, out, on, s))) return e;
             // w_k = A z_k
+            const int t1 = clk.mark();
+            if ((e = apply_A64_list(
+                     sys, act, [&](int i) { return (const double2 *)Zk(i, k); }, [&](int i) { return Wk(i, k); }, s)))
+                return e;
+            const int t2 = clk.mark(), t3 = clk.slot();
+            clk.add(t0, t1, &tsap);
+            clk.add(t1, t2, &tA);
+            clk.add(t2, t3, &tgs);
             {
-                Timer t(clk, &tA);
-                if ((e = apply_A64_list(
-                         sys, act, [&](int i) { return (const double2 *)Zk(i, k); }, [&](int i) { return Wk(i, k); },
-                         s)))
-                    return e;
-            }
-            {
-                Timer t(clk, &tgs);
                 // classical Gram-Schmidt against the earlier w-hat, repeated
                 // once for a system whose new vector lost more than half its norm.
                 // The columns of W are kept unnormalised, W_j = b_j w-hat_j:
@@ -856,7 +867,8 @@ int fgcr(const std::vector<Sys> &sys, const std::vector<int> &guess, std::vector
                     // which only the repeat test reads: not for the first vector
                     const int nd = pass == 0 && k > 0 ? k + 1 : k;
                     const bool may_repeat = pass == 0 && k > 0;
-                    HIPCHK(lead, fgcr_step(ops(todo, [&](int i) { return Wk(i, k); }), k, nd, may_repeat, s));
+                    HIPCHK(lead, fgcr_step(ops(todo, [&](int i) { return Wk(i, k); }), k, nd, may_repeat,
+                                           clk.t + t3, s));
                     if ((e = fetch_all(sys, st, todo, s))) return e;
                     std::vector<int> again;
                     for (int i : todo) {
@@ -877,6 +889,7 @@ int fgcr(const std::vector<Sys> &sys, const std::vector<int> &guess, std::vector
                     todo = again;
                 }
             }
+            clk.collect();
             for (int i : act) {
                 FgcrState &f = st[i];
                 f.steps++;
@@ -887,31 +900,29 @@ int fgcr(const std::vector<Sys> &sys, const std::vector<int> &guess, std::vector
             }
         }
         // x += sum_k alpha_k z_k, then the true residual r = b - A x
-        {
-            Timer t(clk, &tother);
-            for (int i : cur) {
-                FgcrState &f = st[i];
-                for (int k = f.kend - 1; k >= 0; k--) {
-                    C sum = f.cc[k];
-                    for (int j = k + 1; j < f.kend; j++) sum -= f.a[(size_t)k * m + j] * f.alpha[j];
-                    f.alpha[k] = sum / f.bb[k];
-                }
-                HIPCHK(sys[i].c, axpy_multi(sys[i].sl->x, sys[i].sl->Z, pairs(f.alpha), f.kend, nc(i), s));
-                std::fill(f.a.begin(), f.a.end(), C(0));
+        const int t0 = clk.mark();
+        for (int i : cur) {
+            FgcrState &f = st[i];
+            for (int k = f.kend - 1; k >= 0; k--) {
+                C sum = f.cc[k];
+                for (int j = k + 1; j < f.kend; j++) sum -= f.a[(size_t)k * m + j] * f.alpha[j];
+                f.alpha[k] = sum / f.bb[k];
             }
+            HIPCHK(sys[i].c, axpy_multi(sys[i].sl->x, sys[i].sl->Z, pairs(f.alpha), f.kend, nc(i), s));
+            std::fill(f.a.begin(), f.a.end(), C(0));
         }
-        {
-            Timer t(clk, &tA);
-            if ((e = apply_A64_list(
-                     sys, cur, [&](int i) { return (const double2 *)sys[i].sl->x; },
-                     [&](int i) { return sys[i].sl->r; }, s)))
-                return e;
-        }
-        {
-            Timer t(clk, &tother);
-            HIPCHK(lead, residual(ops(cur, b_of), s));
-            if ((e = fetch_all(sys, st, cur, s))) return e;
-        }
+        const int t1 = clk.mark();
+        if ((e = apply_A64_list(
+                 sys, cur, [&](int i) { return (const double2 *)sys[i].sl->x; }, [&](int i) { return sys[i].sl->r; }, s)))
+            return e;
+        const int t2 = clk.mark();
+        HIPCHK(lead, residual(ops(cur, b_of), s));
+        const int t3 = clk.mark();
+        clk.add(t0, t1, &tother);
+        clk.add(t1, t2, &tA);
+        clk.add(t2, t3, &tother);
+        if ((e = fetch_all(sys, st, cur, s))) return e;
+        clk.collect();
         for (int i : cur) {
             FgcrState &f = st[i];
             f.cycles++;
@@ -923,7 +934,7 @@ int fgcr(const std::vector<Sys> &sys, const std::vector<int> &guess, std::vector
             }
         }
     }
-    clk.collect();
+    clk.finish();
     int status = DDQCD_OK;
     for (int i = 0; i < ns; i++) {
         ddqcd_info &inf = info[i];
@@ -1132,11 +1143,11 @@ int fgmres_dr(const Sys &y, bool guess, ddqcd_info &info, hipStream_t s)
     auto Vc = [&](int j) { return Vb + (long)j * n; };
     auto Zc = [&](int j) { return Zb + (long)j * n; };
     double tsap = 0, tA = 0, tgs = 0, tother = 0;
-    Clock clk(s);
     double2 h[32];
     const std::vector<Sys> self{y};
     ResultArea area(self);
     if ((e = area.bind())) return e;
+    Clock clk(c, s);
     auto put = [&](const std::vector<C> &v, double2 *dst) -> int {
         HIPCHK(c, hipMemcpyAsync(dst, v.data(), sizeof(double2) * v.size(), hipMemcpyHostToDevice, s));
         return DDQCD_OK;
@@ -1179,12 +1190,12 @@ int fgmres_dr(const Sys &y, bool guess, ddqcd_info &info, hipStream_t s)
                 if ((e = run_sap({y}, {Vc(j)}, {Zc(j)}, {1}, s))) return e;
             }
             {
-                Timer t(clk, &tA);
+                Timer t(clk, &tA, true);
                 if ((e = apply_A64(c, Zc(j), Vc(j + 1), s))) return e;
             }
             double wn2;
             {
-                Timer t(clk, &tgs);
+                Timer t(clk, &tgs, true);
                 double2 *w = Vc(j + 1);
                 double before;
                 std::vector<C> hsum(j + 1, 0.0);
@@ -1233,7 +1244,7 @@ int fgmres_dr(const Sys &y, bool guess, ddqcd_info &info, hipStream_t s)
             HIPCHK(c, axpy_multi(sl.x, Zb, pairs(yv), jend, n, s));
         }
         {
-            Timer t(clk, &tA);
+            Timer t(clk, &tA, true);
             if ((e = apply_A64(c, sl.x, sl.r, s))) return e;
         }
         HIPCHK(c, residual(sl.blas, sl.b, sl.r, n, s));
@@ -1305,7 +1316,7 @@ int fgmres_dr(const Sys &y, bool guess, ddqcd_info &info, hipStream_t s)
         }
         j0 = k;
     }
-    clk.collect();
+    clk.finish();
     info.converged = status == DDQCD_OK;
     info.iters = steps;
     info.restarts = cycles;
@@ -1341,11 +1352,11 @@ int fgcr_mixed(const Sys &y, bool guess, ddqcd_info &info, hipStream_t s)
     // and r32 in W (each FP64 column holds two FP32 ones)
     float2 *Z32 = (float2 *)sl.Z, *W32 = (float2 *)sl.W, *r32 = W32 + (long)m * n;
     double tsap = 0, tA = 0, tgs = 0, tother = 0;
-    Clock clk(s);
     double2 h[32];
     const std::vector<Sys> self{y};
     ResultArea area(self);
     if ((e = area.bind())) return e;
+    Clock clk(c, s);
     auto put = [&](const std::vector<C> &v) -> int {
         HIPCHK(c, hipMemcpyAsync(sl.blas.coef, v.data(), sizeof(double2) * v.size(), hipMemcpyHostToDevice, s));
         return DDQCD_OK;
@@ -1368,7 +1379,7 @@ int fgcr_mixed(const Sys &y, bool guess, ddqcd_info &info, hipStream_t s)
     double rel = 0;
     for (;;) {
         {
-            Timer t(clk, &tA);
+            Timer t(clk, &tA, true);
             if ((e = apply_A64(c, sl.x, sl.r, s))) return e;
         }
         HIPCHK(c, residual(sl.blas, sl.b, sl.r, n, s));
@@ -1393,10 +1404,10 @@ int fgcr_mixed(const Sys &y, bool guess, ddqcd_info &info, hipStream_t s)
                 if ((e = run_sap({y}, {(const double2 *)r32}, {(double2 *)zk}, {1}, s, true))) return e;
             }
             {
-                Timer t(clk, &tA);
+                Timer t(clk, &tA, true);
                 HIPCHK(c, apply_A(c->g, zk, wk, U32, C32, P32, s));
             }
-            Timer t(clk, &tgs);
+            Timer t(clk, &tgs, true);
             double before = 0, wn2 = 0;
             if (k > 0) {
                 HIPCHK(c, multidot32(sl.blas, W32, n, k + 1, wk, n, s));   // column k is w itself
@@ -1445,7 +1456,7 @@ int fgcr_mixed(const Sys &y, bool guess, ddqcd_info &info, hipStream_t s)
             HIPCHK(c, axpy_mixed(sl.blas, sl.x, Z32, n, kend, rn, n, s));
         }
     }
-    clk.collect();
+    clk.finish();
     info.converged = status == DDQCD_OK;
     info.iters = steps;
     info.restarts = outer;

@@ -149,7 +149,9 @@ hipError_t cgs_update(Blas &B, double2 *w, const double2 *W, int k, double2 *r, 
 // = <w, r>; then r -= <w, r> / |w|^2 w, result[STEP_R] = (|r|^2, 0), left out where
 // may_repeat and |w|^2 is not more than a quarter of what it was, or w vanished.
 enum { STEP_DOTS = 0, STEP_W = 16, STEP_R = 18 };
-hipError_t fgcr_step(const std::vector<BlasOp> &ops, int k, int nd, bool may_repeat, hipStream_t s);
+// end: takes the device's clock afterwards.
+hipError_t fgcr_step(const std::vector<BlasOp> &ops, int k, int nd, bool may_repeat, unsigned long long *end, hipStream_t s);
+hipError_t stamp(unsigned long long *t, hipStream_t s);   // *t (pinned host memory) = the device's clock
 // x += sum_j coef[j] Z_j (coef on the host, 1 <= k <= 16)
 hipError_t axpy_multi(double2 *x, const double2 *Z, const double2 *coef, int k, long n, hipStream_t s);
 // r = b - r; result[0] = (|r|^2, 0); in a list, b is the operand w

@@ -1006,7 +1006,17 @@ template <int FIN> __device__ void finish_scalars(const BlasOp &o, const double2
     }
 }
 
-template <int FIN> __global__ __launch_bounds__(BS) void k_finish(BlasList L, int m, int k, bool may_repeat, int at)
+// the device's clock (wall_clock64, of a fixed rate) into pinned host memory
+__global__ void k_stamp(unsigned long long *t) { *t = wall_clock64(); }
+
+hipError_t stamp(unsigned long long *t, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_stamp, 1, 1, 0, s, t);
+    return hipGetLastError();
+}
+
+template <int FIN>
+__global__ __launch_bounds__(BS) void k_finish(BlasList L, int m, int k, bool may_repeat, int at, unsigned long long *end)
 {
     __shared__ double2 red[BS], sum[BLAS_MAXK];
     const BlasOp o = L.op[blockIdx.y];
@@ -1029,12 +1039,16 @@ template <int FIN> __global__ __launch_bounds__(BS) void k_finish(BlasList L, in
         if (threadIdx.x == 0) sum[j] = o.result[at + j] = red[0];
         __syncthreads();
     }
-    if (threadIdx.x == 0) finish_scalars<FIN>(o, sum, m, k, may_repeat, at);
+    if (threadIdx.x == 0) {
+        finish_scalars<FIN>(o, sum, m, k, may_repeat, at);
+        if (end && blockIdx.y == 0) *end = wall_clock64();
+    }
 }
 
-template <int FIN> static void launch_finish(const BlasList &L, int ns, int m, int at, hipStream_t s, int k = 0, bool may_repeat = false)
+template <int FIN> static void launch_finish(const BlasList &L, int ns, int m, int at, hipStream_t s, int k = 0, bool may_repeat = false,
+                                            unsigned long long *end = nullptr)
 {
-    hipLaunchKernelGGL(k_finish<FIN>, dim3(1, ns), BS, 0, s, L, m, k, may_repeat, at);
+    hipLaunchKernelGGL(k_finish<FIN>, dim3(1, ns), BS, 0, s, L, m, k, may_repeat, at, end);
 }
 
 // ---- several systems in one launch: blockIdx.y is the system -----------------
@@ -1199,7 +1213,7 @@ __global__ __launch_bounds__(BS) void k_residual_update(BlasList L)
 // the device and read by the host together.  With a copy and a wait after each
 // reduction and a launch per system, five steps on 8x4^3 took 180 us more (2810
 // us, now 2630) and those of 12 systems on 16^3x32 1.7 ms more (42.6, now 40.9).
-hipError_t fgcr_step(const std::vector<BlasOp> &ops, int k, int nd, bool may_repeat, hipStream_t s)
+hipError_t fgcr_step(const std::vector<BlasOp> &ops, int k, int nd, bool may_repeat, unsigned long long *end, hipStream_t s)
 {
     if (k < 0 || k > BLAS_MAXK || nd < k || nd > BLAS_MAXK) return hipErrorInvalidValue;
     return for_lists(ops, [&](const BlasList &L, int ns, dim3 grid) {
@@ -1210,7 +1224,7 @@ hipError_t fgcr_step(const std::vector<BlasOp> &ops, int k, int nd, bool may_rep
         (void)launch_cgs_update(L, grid, k, s);
         launch_finish<FIN_CGS>(L, ns, 2, STEP_W, s, k, may_repeat);
         hipLaunchKernelGGL(k_residual_update, grid, BS, 0, s, L);
-        launch_finish<FIN_STORE>(L, ns, 1, STEP_R, s);
+        launch_finish<FIN_STORE>(L, ns, 1, STEP_R, s, 0, false, end);
     });
 }
 
