@@ -39,8 +39,8 @@ CPU_BUDGET_S = 30.0          # bound on the oracle's host time
 # the figure is reported as null until it is measured again.
 # Keyed by (workload, domain shape, product form).
 KERNEL_SOURCES = ("paper_1412_2629_amd/csrc/dd_sap.hip", "paper_1412_2629_amd/csrc/dd_device.h")
-MEASURED_TRAFFIC = {("C4", (4, 4, 4, 4), "tile"): {"bytes_per_launch": 5.1026e9, "sources": "b43375ccdb70b66a"},
-                    ("C3", (8, 4, 4, 4), "lane"): {"bytes_per_launch": 602.75e6, "sources": "b43375ccdb70b66a"}}
+MEASURED_TRAFFIC = {("C4", (4, 4, 4, 4), "tile"): {"bytes_per_launch": 5.8354e9, "sources": "9aec07267e86aee7"},
+                    ("C3", (8, 4, 4, 4), "lane"): {"bytes_per_launch": 633.00e6, "sources": "9aec07267e86aee7"}}
 
 
 def log(*a):
@@ -184,8 +184,8 @@ def main():
     ap.add_argument("--domain", default=None,
                     help="override the workload's domain shape, e.g. 4,4,4,4 (single-lattice workloads)")
     ap.add_argument("--product", default="auto", choices=["auto", "lane", "tile", "mfma_f32", "mfma_bf16"],
-                    help="block-solve product form: one right-hand side per workgroup, or tiles of four with the "
-                         "link products on VALU, FP32 MFMA or BF16-input MFMA (4^4 domains, FP16 storage); auto: "
+                    help="block-solve product form: one right-hand side per workgroup, or tiles with the link products "
+                         "on VALU (two right-hand sides), FP32 MFMA or BF16-input MFMA (four) (4^4 domains, FP16 storage); auto: "
                          "tuned with the domain shape by ddqcd_tune_sap")
     ap.add_argument("--outer", default="fgcr",
                     help="outer solver: fgcr, or fgmres_dr:M:K (flexible GMRES with deflated restarts, basis M, "

@@ -1211,7 +1211,7 @@ __global__ __launch_bounds__(BS) void k_residual_update(BlasList L)
 // One pass of the Gram-Schmidt step of every system and, unless it has to be
 // repeated, the residual's update: three reductions whose results are used on
 // the device and read by the host together.  With a copy and a wait after each
-// reduction and a launch per system, five steps on 8x4^3 took 180 us more (2810
+// reduction and a launch per system, five steps on 4^4 took 180 us more (2810
 // us, now 2630) and those of 12 systems on 16^3x32 1.7 ms more (42.6, now 40.9).
 hipError_t fgcr_step(const std::vector<BlasOp> &ops, int k, int nd, bool may_repeat, unsigned long long *end, hipStream_t s)
 {
