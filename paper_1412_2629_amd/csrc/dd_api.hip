@@ -707,7 +707,7 @@ struct ResultArea {
             if (lead->res_host) (void)hipHostFree(lead->res_host);
             lead->res_host = nullptr;
             HIPCHK(lead, hipHostMalloc((void **)&lead->res_host, sizeof(double2) * 32 * cap + 8 * CLOCK_SLOTS,
-                                       hipHostMallocDefault));   // and the clock stamps
+                                       hipHostMallocCoherent));   // and the clock stamps
             lead->res_cap = cap;
         }
         for (int i = 0; i < ns; i++) sys[i].sl->blas.result = lead->res_host + 32L * i;
