@@ -24,6 +24,7 @@
 #include <vector>
 
 #include "../../include/ddqcd.h"
+#include "dd_clock.h"
 #include "dd_internal.h"
 
 using namespace dd;
@@ -607,72 +608,30 @@ int apply_A64_list(const std::vector<Sys> &sys, const std::vector<int> &list, In
     return DDQCD_OK;
 }
 
-// Phase timings of a solve: stamps of the device's clock in the lead context's
-// pinned area, written by the stream at the phases' ends and read when the host
-// has waited for the stream anyway.  (A pair of events around each phase held
-// the stream up by some 12 us: a five-step solve in FP64 on 4^4 took 2530 us, 2430
-// now and 2300 without any timing.)
-enum { CLOCK_SLOTS = 64 };
-struct Clock {
-    struct Span {
-        int a, b;
-        double *acc;
-    };
-    std::vector<Span> spans;
-    unsigned long long *const t;
+// The clock of a solve's phase timings; its slots lie behind the lead context's
+// result area.  (A pair of events around each phase held the stream up by some
+// 12 us: a five-step solve in FP64 on 4^4 took 2530 us, 2430 with stamps and 2300
+// without any timing.)
+struct StreamClock {
     hipStream_t s;
-    int n = 0, open = 0;
-    double ms_per_tick = 1e-5;
-    Clock(ddqcd_t lead, hipStream_t s_)
-        : t((unsigned long long *)(lead->res_host + 32L * lead->res_cap)), s(s_)
+    double tick_ms = 1e-5;
+    explicit StreamClock(hipStream_t s_) : s(s_)
     {
         int dev = 0, khz = 0;
         if (hipGetDevice(&dev) == hipSuccess &&
             hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, dev) == hipSuccess && khz > 0)
-            ms_per_tick = 1.0 / khz;
+            tick_ms = 1.0 / khz;
     }
-    int mark()
-    {
-        const int i = slot();
-        (void)stamp(t + i, s);
-        return i;
-    }
-    int slot()   // a stamp that a kernel of the phase writes
-    {
-        if (n == CLOCK_SLOTS) finish();
-        return n < CLOCK_SLOTS ? n++ : CLOCK_SLOTS - 1;
-    }
-    void add(int a, int b, double *acc) { spans.push_back({a, b, acc}); }
-    // the stream has been waited for
-    void collect()
-    {
-        for (const Span &p : spans) *p.acc += (double)(long long)(t[p.b] - t[p.a]) * ms_per_tick;
-        spans.clear();
-        if (open == 0) n = 0;
-    }
-    void finish()
-    {
-        (void)hipStreamSynchronize(s);
-        collect();
-    }
+    void stamp(unsigned long long *t) { (void)dd::stamp(t, s); }
+    void wait() { (void)hipStreamSynchronize(s); }
+    double ms_per_tick() const { return tick_ms; }
 };
-
-// follows: nothing was launched since the span added last ended
-struct Timer {
-    Clock &clk;
-    double *acc;
-    int a;
-    Timer(Clock &c, double *acc_, bool follows = false) : clk(c), acc(acc_)
-    {
-        a = follows && !c.spans.empty() ? c.spans.back().b : c.mark();
-        clk.open++;
-    }
-    ~Timer()
-    {
-        clk.open--;
-        clk.add(a, clk.mark(), acc);
-    }
-};
+typedef dd::Clock<StreamClock> Clock;
+typedef dd::Timer<StreamClock> Timer;
+Clock solve_clock(ddqcd_t lead, hipStream_t s)
+{
+    return Clock(StreamClock(s), (unsigned long long *)(lead->res_host + 32L * lead->res_cap));
+}
 
 using C = std::complex<double>;
 
@@ -750,7 +709,7 @@ int fgcr(const std::vector<Sys> &sys, const std::vector<int> &guess, std::vector
     int e;
     ResultArea area(sys);
     if ((e = area.bind())) return e;
-    Clock clk(lead, s);
+    Clock clk = solve_clock(lead, s);
     for (int i = 0; i < ns; i++) {
         st[i].a.assign((size_t)m * m, 0);
         st[i].cc.assign(m, 0);
@@ -836,7 +795,7 @@ int fgcr(const std::vector<Sys> &sys, const std::vector<int> &guess, std::vector
                 if (st[i].in_cycle) act.push_back(i);
             if (act.empty()) break;
             // z_k = M r
-            const int t0 = clk.mark();
+            const long t0 = clk.mark();
             std::vector<const double2 *> eta(ns);
             std::vector<double2 *> out(ns);
             std::vector<int> on(ns, 0);
@@ -847,11 +806,11 @@ int fgcr(const std::vector<Sys> &sys, const std::vector<int> &guess, std::vector
             for (int i : act) on[i] = 1;
             if ((e = run_sap(sys, eta, out, on, s))) return e;
             // w_k = A z_k
-            const int t1 = clk.mark();
+            const long t1 = clk.mark();
             if ((e = apply_A64_list(
                      sys, act, [&](int i) { return (const double2 *)Zk(i, k); }, [&](int i) { return Wk(i, k); }, s)))
                 return e;
-            const int t2 = clk.mark(), t3 = clk.slot();
+            const long t2 = clk.mark(), t3 = clk.slot();
             clk.add(t0, t1, &tsap);
             clk.add(t1, t2, &tA);
             clk.add(t2, t3, &tgs);
@@ -869,7 +828,7 @@ int fgcr(const std::vector<Sys> &sys, const std::vector<int> &guess, std::vector
                     const int nd = pass == 0 && k > 0 ? k + 1 : k;
                     const bool may_repeat = pass == 0 && k > 0;
                     HIPCHK(lead, fgcr_step(ops(todo, [&](int i) { return Wk(i, k); }), k, nd, may_repeat,
-                                           clk.t + t3, s));
+                                           clk.at(t3), s));
                     if ((e = fetch_all(sys, st, todo, s))) return e;
                     std::vector<int> again;
                     for (int i : todo) {
@@ -901,7 +860,7 @@ int fgcr(const std::vector<Sys> &sys, const std::vector<int> &guess, std::vector
             }
         }
         // x += sum_k alpha_k z_k, then the true residual r = b - A x
-        const int t0 = clk.mark();
+        const long t0 = clk.mark();
         for (int i : cur) {
             FgcrState &f = st[i];
             for (int k = f.kend - 1; k >= 0; k--) {
@@ -912,13 +871,13 @@ int fgcr(const std::vector<Sys> &sys, const std::vector<int> &guess, std::vector
             HIPCHK(sys[i].c, axpy_multi(sys[i].sl->x, sys[i].sl->Z, pairs(f.alpha), f.kend, nc(i), s));
             std::fill(f.a.begin(), f.a.end(), C(0));
         }
-        const int t1 = clk.mark();
+        const long t1 = clk.mark();
         if ((e = apply_A64_list(
                  sys, cur, [&](int i) { return (const double2 *)sys[i].sl->x; }, [&](int i) { return sys[i].sl->r; }, s)))
             return e;
-        const int t2 = clk.mark();
+        const long t2 = clk.mark();
         HIPCHK(lead, residual(ops(cur, b_of), s));
-        const int t3 = clk.mark();
+        const long t3 = clk.mark();
         clk.add(t0, t1, &tother);
         clk.add(t1, t2, &tA);
         clk.add(t2, t3, &tother);
@@ -1148,7 +1107,7 @@ int fgmres_dr(const Sys &y, bool guess, ddqcd_info &info, hipStream_t s)
     const std::vector<Sys> self{y};
     ResultArea area(self);
     if ((e = area.bind())) return e;
-    Clock clk(c, s);
+    Clock clk = solve_clock(c, s);
     auto put = [&](const std::vector<C> &v, double2 *dst) -> int {
         HIPCHK(c, hipMemcpyAsync(dst, v.data(), sizeof(double2) * v.size(), hipMemcpyHostToDevice, s));
         return DDQCD_OK;
@@ -1357,7 +1316,7 @@ int fgcr_mixed(const Sys &y, bool guess, ddqcd_info &info, hipStream_t s)
     const std::vector<Sys> self{y};
     ResultArea area(self);
     if ((e = area.bind())) return e;
-    Clock clk(c, s);
+    Clock clk = solve_clock(c, s);
     auto put = [&](const std::vector<C> &v) -> int {
         HIPCHK(c, hipMemcpyAsync(sl.blas.coef, v.data(), sizeof(double2) * v.size(), hipMemcpyHostToDevice, s));
         return DDQCD_OK;
