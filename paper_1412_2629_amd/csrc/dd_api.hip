@@ -1429,6 +1429,16 @@ int fgcr_mixed(const Sys &y, bool guess, ddqcd_info &info, hipStream_t s)
     return status;
 }
 
+// The status of a solve that ended with an error, once the stream has been waited
+// for: an error can be found while later work is queued (BiCGstab's next
+// direction, the stamp that ends a phase), which would run on beside whatever the
+// caller does next with the context's vectors on another stream.
+int ended(int status, hipStream_t s)
+{
+    if (status != DDQCD_OK && status != DDQCD_ERR_NOT_CONVERGED) (void)hipStreamSynchronize(s);
+    return status;
+}
+
 // shared body of ddqcd_solve and ddqcd_solve_batch
 int solve_systems(const std::vector<Sys> &sys, double *const *x, const double *const *b, int x_is_guess,
                   ddqcd_info *info, hipStream_t s)
@@ -1446,13 +1456,13 @@ int solve_systems(const std::vector<Sys> &sys, double *const *x, const double *c
         for (size_t i = 0; i < sys.size(); i++) {
             const int si = sys[0].c->outer == DDQCD_OUTER_FGMRES_DR ? fgmres_dr(sys[i], x_is_guess != 0, inf[i], s)
                                                                      : fgcr_mixed(sys[i], x_is_guess != 0, inf[i], s);
-            if (si != DDQCD_OK && si != DDQCD_ERR_NOT_CONVERGED) return si;
+            if (si != DDQCD_OK && si != DDQCD_ERR_NOT_CONVERGED) return ended(si, s);
             if (si != DDQCD_OK) st = si;
         }
     } else {
         st = fgcr(sys, std::vector<int>(sys.size(), x_is_guess != 0), inf, s);
     }
-    if (st != DDQCD_OK && st != DDQCD_ERR_NOT_CONVERGED) return st;
+    if (st != DDQCD_OK && st != DDQCD_ERR_NOT_CONVERGED) return ended(st, s);
     for (size_t i = 0; i < sys.size(); i++) HIPCHK(sys[i].c, export_spinor(sys[i].c->g, sys[i].sl->x, P64, x[i], s));
     HIPCHK(sys[0].c, hipStreamSynchronize(s));
     const double ms = std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t0).count();
@@ -2087,7 +2097,7 @@ int ddqcd_solve_bicgstab(ddqcd_t c, double *x, const double *b, int x_is_guess, 
     if (x_is_guess) HIPCHK(c, import_spinor(c->g, x, sl.x, P64, s));
     ddqcd_info inf{};
     const int st = bicgstab(Sys{c, &sl}, x_is_guess != 0, max_iter, inf, s);
-    if (st != DDQCD_OK && st != DDQCD_ERR_NOT_CONVERGED) return st;
+    if (st != DDQCD_OK && st != DDQCD_ERR_NOT_CONVERGED) return ended(st, s);
     HIPCHK(c, export_spinor(c->g, sl.x, P64, x, s));
     HIPCHK(c, hipStreamSynchronize(s));
     inf.t_total_ms = std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t0).count();
