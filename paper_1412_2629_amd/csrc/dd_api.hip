@@ -356,7 +356,7 @@ int build_plan_once(const std::vector<Sys> &sys, const std::string &key, Plan *&
     std::vector<std::vector<int>> members;
     for (size_t i = 0; i < sys.size(); i++) {
         const std::array<int, 3> k{sap_shape_id(sys[i].c->g.b), sys[i].c->sap_prec,
-                                   sap_kernel_form(sys[i].c->g, sys[i].c->sap_prec, sys[i].c->product)};
+                                   sap_lattice_form(sys[i].c->g, sys[i].c->sap_prec, sys[i].c->product)};
         size_t gi = std::find(gk.begin(), gk.end(), k) - gk.begin();
         if (gi == gk.size()) {
             gk.push_back(k);
@@ -2013,7 +2013,7 @@ int ddqcd_sap_noalloc(ddqcd_t c, double *out, const double *in, void *stream)
     HIPCHK(c, import_spinor(g, in, eta, P64, s));
     HIPCHK(c, sap_put_args(a, d_args, s));
     const int shape = sap_shape_id(g.b), prec = c->sap_prec, half_nd = g.nd / 2;
-    const int form = sap_kernel_form(g, prec, c->product);
+    const int form = sap_lattice_form(g, prec, c->product);
     HIPCHK(c, sap_schedule_items(g, sap_rhs_per_workgroup(form) > 1 ? 1 << 24 : 0, items, s));
     for (int cyc = 0; cyc < c->n_cycles; cyc++) {
         Visit v{};

@@ -5,10 +5,9 @@
 #include <vector>
 
 #include "dd_device.h"
+#include "dd_form.h"
 
 namespace dd {
-
-enum { P64 = 0, P32 = 1, P16 = 2, PB16 = 3 };   // FP64, FP32, FP16, BF16 storage
 
 // Canonical FP64 spinor [V][12] complex <-> internal layout in precision prec.
 hipError_t import_spinor(const Geo &g, const double *canon, void *internal, int prec, hipStream_t s);
@@ -85,18 +84,9 @@ bool sap_shape_supported(const int b[4]);
 bool sap_prec_supported(const int b[4], int prec);
 long sap_face_sites(const int b[4]);
 int sap_shape_id(const int b[4]);
-// How a block-solve workgroup forms the SU(3) products of its hops:
-// PRODUCT_LANE, one right-hand side per workgroup and one site per thread
-// (VALU); the TILE forms take a tile of right-hand sides of one lattice per
-// workgroup (4^4 domains, FP16 or BF16 storage) with the product on the VALU
-// (two right-hand sides), on FP32 MFMA, or on BF16-input MFMA with FP32
-// accumulation (four).
-// PRODUCT_LANE_SPLIT, two threads per site, is not selected by the caller:
-// sap_kernel_form names it for PRODUCT_LANE where it is the better kernel.
-enum { PRODUCT_LANE = 0, PRODUCT_TILE_VALU = 1, PRODUCT_TILE_MFMA_F32 = 2, PRODUCT_TILE_MFMA_BF16 = 3, PRODUCT_LANE_SPLIT = 4 };
-// The kernel form that solves this lattice's blocks, given the caller's product;
-// the functions below take it as their product.
-int sap_kernel_form(const Geo &g, int prec, int product);
+// The kernel form (dd_form.h) that solves this lattice's blocks, given the
+// caller's product; the functions below take it as their product.
+int sap_lattice_form(const Geo &g, int prec, int product);
 bool sap_product_supported(const int b[4], int prec, int product);
 // Right-hand sides one workgroup takes (1, or 2 or 4 for the tile forms): the items
 // of a tile launch are (first system | systems in the tile << 24, domain).

@@ -31,9 +31,6 @@ namespace dd {
 template <int BX, int BY, int BZ, int BT> struct Shape {
     static constexpr int VD = BX * BY * BZ * BT;
     static constexpr int VH = VD / 2;
-    // threads of a one-domain block-solve workgroup: whole waves (idle padding
-    // threads beyond VD) for domains of 64 sites or more
-    static constexpr int NT = VD >= 64 ? (VD + 63) / 64 * 64 : VD;
     static constexpr int B[4] = {BX, BY, BZ, BT};
     static constexpr int FS[4] = {VD / BX, VD / BY, VD / BZ, VD / BT};
     static constexpr int FTOT = 2 * (VD / BX + VD / BY + VD / BZ + VD / BT);
@@ -654,7 +651,7 @@ __device__ __forceinline__ void lds_block_solve(const SapArgs &a, const int d, c
 {
     using T = float;
     constexpr int VD = Sh::VD, VH = Sh::VH, NLC = 6;
-    constexpr int NT = NDW > 1 ? NDW * VD : Sh::NT;   // threads of the workgroup
+    constexpr int NT = NDW * VD;              // threads of the workgroup
     static_assert(NDW == 1 || NDW * VH == 64, "packed domains: one wave per parity");
     __shared__ c2_t she_all[NDW][6 * VH];     // even sites: r
     __shared__ c2_t sho_all[NDW][6 * VH];     // odd sites: C_o^-1 D_oe r; x in the reconstruction
@@ -671,9 +668,6 @@ __device__ __forceinline__ void lds_block_solve(const SapArgs &a, const int d, c
     const int sub = idx / VH;   // this thread's domain within the workgroup
     const int hi = idx - sub * VH;
     const int loc = par * VH + hi;
-    // padding threads (threadIdx >= VD, only when VD is not a multiple of 64)
-    // take part in barriers and reductions with zeros and touch no memory
-    const bool live = NDW > 1 || NT == VD || (int)threadIdx.x < VD;
     // this half index
     c2_t *const ve = she_all[sub] + hi, *const vo = sho_all[sub] + hi, *const vx = shx_all[sub] + hi;
     int l[4];
@@ -698,11 +692,8 @@ __device__ __forceinline__ void lds_block_solve(const SapArgs &a, const int d, c
     v2<G> lt[4][NLC], cl[36];
     const long lb = (long)d * 4 * NLC * VD + loc;
 #pragma unroll
-    for (int q = 0; q < 4 * NLC; q++) lt[q / NLC][q % NLC] = live ? glinks[lb + (long)q * VD] : v2<G>{};
-    if (!live) {
-#pragma unroll
-        for (int k = 0; k < 12; k++) A[k] = czero<T>();
-    } else if (f.first) {
+    for (int q = 0; q < 4 * NLC; q++) lt[q / NLC][q % NLC] = glinks[lb + (long)q * VD];
+    if (f.first) {
         if (a.io32) {
 #pragma unroll
             for (int k = 0; k < 12; k++) A[k] = ld<T, float>(global_ptr((const float2 *)a.eta), sbase + (long)k * VD);
@@ -719,7 +710,7 @@ __device__ __forceinline__ void lds_block_solve(const SapArgs &a, const int d, c
     cx<T> hf[4][6];
     T wf[4] = {0, 0, 0, 0};
     int sf[4] = {0, 0, 0, 0};
-    if (f.faces_in && live) {
+    if (f.faces_in) {
         face_fetch<Sh, 0, T, SS, SCALED>(a, D, l, hf[0], wf[0], sf[0]);
         face_fetch<Sh, 1, T, SS, SCALED>(a, D, l, hf[1], wf[1], sf[1]);
         face_fetch<Sh, 2, T, SS, SCALED>(a, D, l, hf[2], wf[2], sf[2]);
@@ -727,7 +718,7 @@ __device__ __forceinline__ void lds_block_solve(const SapArgs &a, const int d, c
     }
     const long cbase = (long)d * 36 * VD + loc;
 #pragma unroll
-    for (int q = 0; q < 36; q++) cl[q] = live ? cs[cbase + (long)q * VD] : v2<G>{};
+    for (int q = 0; q < 36; q++) cl[q] = cs[cbase + (long)q * VD];
     RegLink<G> U[4];
 #pragma unroll
     for (int mu = 0; mu < 4; mu++) U[mu].put(lt[mu]);
@@ -736,7 +727,7 @@ __device__ __forceinline__ void lds_block_solve(const SapArgs &a, const int d, c
         if constexpr (sizeof(v2<G>) == 4) clover_wide([&](int q) { return widen<G>(cl[q]); }, in, out);
         else clover_wide([&](int q) { return cx<T>{(T)cl[q].x, (T)cl[q].y}; }, in, out);
     };
-    if (f.faces_in && live) {
+    if (f.faces_in) {
         face_apply<Sh, 0, T>(U[0], hf[0], wf[0], sf[0], A);
         face_apply<Sh, 1, T>(U[1], hf[1], wf[1], sf[1], A);
         face_apply<Sh, 2, T>(U[2], hf[2], wf[2], sf[2], A);
@@ -762,7 +753,7 @@ __device__ __forceinline__ void lds_block_solve(const SapArgs &a, const int d, c
         st_c2<VH>(ve, P);
     }
     c2_t *const va = sa_all + (A_LDS ? sub * 6 * VD + loc : 0);
-    if (A_LDS && live) st_c2<VD>(va, A);
+    if (A_LDS) st_c2<VD>(va, A);
     // C has arrived: without this, a path around the MR loop on which it has
     // not makes the later waits for its registers wait for younger loads
 #pragma unroll
@@ -826,9 +817,9 @@ __device__ __forceinline__ void lds_block_solve(const SapArgs &a, const int d, c
     c2_t ps[6];
 #pragma unroll
     for (int j = 0; j < 6; j++) ps[j] = c2_t{0.f, 0.f, 0.f, 0.f};
-    if (A_LDS && live) ld_c2<VD>(va, A);
+    if (A_LDS) ld_c2<VD>(va, A);
     if (par == 0) st_c2<VH>(vo, A);
-    if (live && !f.first)
+    if (!f.first)
 #pragma unroll
         for (int j = 0; j < 6; j++) ps[j] = psi[j * VD];
     __syncthreads();
@@ -840,20 +831,18 @@ __device__ __forceinline__ void lds_block_solve(const SapArgs &a, const int d, c
     }
 
     // ---- epilogue
-    if (live) {
 #pragma unroll
-        for (int j = 0; j < 6; j++) ps[j] += c2_t{A[2 * j].r, A[2 * j].i, A[2 * j + 1].r, A[2 * j + 1].i};
-        if (f.last) {
+    for (int j = 0; j < 6; j++) ps[j] += c2_t{A[2 * j].r, A[2 * j].i, A[2 * j + 1].r, A[2 * j + 1].i};
+    if (f.last) {
 #pragma unroll
-            for (int k = 0; k < 12; k++) {
-                const cx<T> c = {ps[k / 2][2 * (k & 1)], ps[k / 2][2 * (k & 1) + 1]};
-                if (a.io32) st<T, float>(global_ptr((float2 *)a.out), sbase + (long)k * VD, c);
-                else st<T, double>(global_ptr(a.out), sbase + (long)k * VD, c);
-            }
-        } else {
-#pragma unroll
-            for (int j = 0; j < 6; j++) psi[j * VD] = ps[j];
+        for (int k = 0; k < 12; k++) {
+            const cx<T> c = {ps[k / 2][2 * (k & 1)], ps[k / 2][2 * (k & 1) + 1]};
+            if (a.io32) st<T, float>(global_ptr((float2 *)a.out), sbase + (long)k * VD, c);
+            else st<T, double>(global_ptr(a.out), sbase + (long)k * VD, c);
         }
+    } else {
+#pragma unroll
+        for (int j = 0; j < 6; j++) psi[j * VD] = ps[j];
     }
     T mx[2] = {T(1), T(1)};
     if constexpr (SCALED) {
@@ -879,12 +868,10 @@ __device__ __forceinline__ void lds_block_solve(const SapArgs &a, const int d, c
     if (f.faces_out) {
         if (SCALED && loc == 0) global_ptr(a.face_scale)[d] = (float)mx[1];
         const T inv = T(1) / mx[1];
-        if (live) {
-            face_write<Sh, 0, T, SS>(a, d, l, A, inv, U[0]);
-            face_write<Sh, 1, T, SS>(a, d, l, A, inv, U[1]);
-            face_write<Sh, 2, T, SS>(a, d, l, A, inv, U[2]);
-            face_write<Sh, 3, T, SS>(a, d, l, A, inv, U[3]);
-        }
+        face_write<Sh, 0, T, SS>(a, d, l, A, inv, U[0]);
+        face_write<Sh, 1, T, SS>(a, d, l, A, inv, U[1]);
+        face_write<Sh, 2, T, SS>(a, d, l, A, inv, U[2]);
+        face_write<Sh, 3, T, SS>(a, d, l, A, inv, U[3]);
     }
 }
 
@@ -1511,7 +1498,7 @@ __device__ __forceinline__ void bind_faces(SapArgs &a, const Visit &v)
 // With NDW > 1, items come in runs of NDW domains of one system (the plan
 // never splits or pads a run), and workgroup i takes run i.
 template <class Sh, int NDW, typename SS, typename G, bool SCALED>
-__global__ __launch_bounds__(NDW > 1 ? Sh::VD * NDW : Sh::NT, 2) void k_sap_lds(const SapArgs *args, const int2 *items,
+__global__ __launch_bounds__(Sh::VD * NDW, 2) void k_sap_lds(const SapArgs *args, const int2 *items,
                                                                              Visit v)
 {
     const int2 it = items[(long)blockIdx.x * NDW];
@@ -2309,19 +2296,21 @@ static hipError_t launch_batch(const SapArgs *args, const int2 *items, int nitem
         return hipErrorInvalidValue;
     }
     if (prec == P64) {
-        // whole waves only: no FP64 kernel for padded workgroups
+        // whole waves only
         if constexpr (Sh::VD >= 64 && Sh::VD % 64 == 0)
             return launch_bounded(k_sap_f64<Sh>, nitems, Sh::VD, s, args, items, v);
         else
             return hipErrorInvalidValue;
-    } else {
-        constexpr int NT = NDW > 1 ? Sh::VD * NDW : Sh::NT;
+    } else if constexpr (Sh::VD * NDW % 64 == 0) {
+        constexpr int NT = Sh::VD * NDW;
         if (prec == P32)
             return launch_bounded(k_sap_lds<Sh, NDW, float, float, false>, nitems / NDW, NT, s, args, items, v);
         else if (prec == P16)
             return launch_bounded(k_sap_lds<Sh, NDW, half_t, half_t, true>, nitems / NDW, NT, s, args, items, v);
         else
             return launch_bounded(k_sap_lds<Sh, NDW, bf16_t, bf16_t, false>, nitems / NDW, NT, s, args, items, v);
+    } else {
+        return hipErrorInvalidValue;   // two threads per site (dd_form.h)
     }
 }
 
@@ -2342,20 +2331,9 @@ bool sap_product_supported(const int b[4], int prec, int product)
     return sap_shape_id(b) == 1 && (prec == P16 || prec == PB16);
 }
 
-// Two threads per site where one thread per site would leave the device idle:
-// a colour of at most SPLIT_MAX workgroups (one per CU).  The rule looks at the
-// lattice, not at the launch, so that a system is solved with the same bits
-// alone and in a batch.  At 256 workgroups of 4^4 domains two threads per site
-// take 33.7 us and one takes 40.5; beyond, a second round of workgroups begins,
-// while with one thread per site two workgroups share a CU in 344 us for 4096
-// (21.5 us per 256).  512-site domains have two waves per SIMD as they are.
-constexpr int SPLIT_MAX = 256;
-int sap_kernel_form(const Geo &g, int prec, int product)
+int sap_lattice_form(const Geo &g, int prec, int product)
 {
-    if (product != PRODUCT_LANE) return product;
-    if (prec == P64) return g.Vd == 16 ? PRODUCT_LANE_SPLIT : product;
-    const int shape = sap_shape_id(g.b);
-    return g.Vd < 512 && g.nd / 2 / sap_domains_per_workgroup(shape, prec, product) <= SPLIT_MAX ? PRODUCT_LANE_SPLIT : product;
+    return sap_kernel_form(g.Vd, prec, product, g.nd / 2 / sap_domains_per_workgroup(sap_shape_id(g.b), prec, product));
 }
 
 int sap_shape_id(const int b[4])
