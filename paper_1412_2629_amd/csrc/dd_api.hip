@@ -343,6 +343,9 @@ int build_plan(const std::vector<Sys> &sys, Plan *&out)
     return e;
 }
 
+// a system's domains in one launch: those of a colour, or all
+long launch_domains(ddqcd_t c) { return c->schwarz == DDQCD_SCHWARZ_ADDITIVE ? c->g.nd : c->g.nd / 2; }
+
 int build_plan_once(const std::vector<Sys> &sys, const std::string &key, Plan *&out)
 {
     ddqcd_t lead = sys[0].c;
@@ -369,8 +372,10 @@ int build_plan_once(const std::vector<Sys> &sys, const std::string &key, Plan *&
         Plan::Group &G = plan->groups.back();
         G.shape = gk[gi][0];
         G.prec = gk[gi][1];
-        G.product = gk[gi][2];
-        const int ndw = sap_domains_per_workgroup(G.shape, G.prec, G.product);
+        const int ndw = sap_domains_per_workgroup(G.shape, G.prec, gk[gi][2]);
+        long workgroups = 0;   // of a launch, where a workgroup takes one system
+        for (int si : members[gi]) workgroups += launch_domains(sys[si].c) / ndw;
+        G.product = sap_launch_form(sys[members[gi][0]].c->g.Vd, gk[gi][2], workgroups);
         const int rt = sap_rhs_per_workgroup(G.product);
         // tiles: up to rt systems of one context with consecutive system
         // numbers (one system each for the one-right-hand-side kernels)
@@ -2013,7 +2018,8 @@ int ddqcd_sap_noalloc(ddqcd_t c, double *out, const double *in, void *stream)
     HIPCHK(c, import_spinor(g, in, eta, P64, s));
     HIPCHK(c, sap_put_args(a, d_args, s));
     const int shape = sap_shape_id(g.b), prec = c->sap_prec, half_nd = g.nd / 2;
-    const int form = sap_lattice_form(g, prec, c->product);
+    const int lattice_form = sap_lattice_form(g, prec, c->product);
+    const int form = sap_launch_form(g.Vd, lattice_form, launch_domains(c) / sap_domains_per_workgroup(shape, prec, lattice_form));
     HIPCHK(c, sap_schedule_items(g, sap_rhs_per_workgroup(form) > 1 ? 1 << 24 : 0, items, s));
     for (int cyc = 0; cyc < c->n_cycles; cyc++) {
         Visit v{};

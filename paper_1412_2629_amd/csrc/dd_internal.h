@@ -84,8 +84,8 @@ bool sap_shape_supported(const int b[4]);
 bool sap_prec_supported(const int b[4], int prec);
 long sap_face_sites(const int b[4]);
 int sap_shape_id(const int b[4]);
-// The kernel form (dd_form.h) that solves this lattice's blocks, given the
-// caller's product; the functions below take it as their product.
+// The form (dd_form.h) of this lattice's block solves, given the caller's product;
+// the functions below take it, or the launch's form, as their product.
 int sap_lattice_form(const Geo &g, int prec, int product);
 bool sap_product_supported(const int b[4], int prec, int product);
 // Right-hand sides one workgroup takes (1, or 2 or 4 for the tile forms): the items

@@ -558,10 +558,12 @@ template <class Sh, int MU> __device__ __forceinline__ void lane_pull(const c2_t
 // parity's spinors in LDS at this half index, own: this thread's own spinor
 // (threads of the other parity), X: the half-spinors handed over.  Every thread
 // of the workgroup calls this (it holds a barrier, after which v is free); X is
-// free after the next one.
-template <class Sh, typename Link>
-__device__ __forceinline__ void lane_hops(const c2_t *v, const cx<float> own[12], c2_t *X, int po, int par, const int l[4],
-                                          const Link (&U)[4], cx<float> acc[12])
+// free after the next one.  HALVES: the forward hops are summed as split_hops
+// does, by pairs of directions; the first pair's sum waits in the site's own entry
+// of park, which is free after the barrier.
+template <class Sh, bool HALVES, typename Link>
+__device__ __forceinline__ void lane_hops(const c2_t *v, const cx<float> own[12], c2_t *X, c2_t *park, int po, int par,
+                                          const int l[4], const Link (&U)[4], cx<float> acc[12])
 {
     const int ox = l[0] & 1;
 #pragma unroll
@@ -569,8 +571,20 @@ __device__ __forceinline__ void lane_hops(const c2_t *v, const cx<float> own[12]
     if (par == po) {
         lane_fwd<Sh, 0>(v, l, ox, U[0], acc);
         lane_fwd<Sh, 1>(v, l, ox, U[1], acc);
+        if constexpr (HALVES) {
+            st_c2<Sh::VH>(park, acc);
+            asm volatile("" ::: "memory");   // read back below, not kept in registers
+#pragma unroll
+            for (int k = 0; k < 12; k++) acc[k] = czero<float>();
+        }
         lane_fwd<Sh, 2>(v, l, ox, U[2], acc);
         lane_fwd<Sh, 3>(v, l, ox, U[3], acc);
+        if constexpr (HALVES) {
+            cx<float> early[12];
+            ld_c2<Sh::VH>(park, early);
+#pragma unroll
+            for (int k = 0; k < 12; k++) acc[k] = early[k] + acc[k];
+        }
     } else if (par == 1 - po) {
         lane_push<Sh, 0>(own, l, U[0], X);
         lane_push<Sh, 1>(own, l, U[1], X);
@@ -643,10 +657,39 @@ __device__ __forceinline__ void face_write(const SapArgs &a, int d, const int l[
     for (int k = 0; k < 6; k++) st<T, SS>(face, fb + (long)k * Sh::FS[MU] + fi, scal(inv_sc, h[k]));
 }
 
+// The sums over a domain's sites (one domain a workgroup, its even sites in the
+// first half of the NW waves) of the two halves v[0 .. 2] and v[3 .. 5] of three
+// values, in the order in which domain_reduce sums them where each half has waves
+// of its own.  No closing barrier (see domain_reduce).
+template <int NW, typename T> __device__ __forceinline__ void halves_sum(T (&v)[6], T (&out)[3], T *red)
+{
+    const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+#pragma unroll
+    for (int k = 0; k < 6; k++) v[k] = lanes_reduce<64, false>(v[k]);
+    if (lane == 0)
+#pragma unroll
+        for (int k = 0; k < 6; k++) red[k * NW + w] = v[k];
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < 3; k++) {
+        T s = red[k * NW];
+#pragma unroll
+        for (int j = 1; j < NW / 2; j++) s += red[k * NW + j];
+#pragma unroll
+        for (int j = 0; j < NW / 2; j++) s += red[(3 + k) * NW + j];
+        out[k] = s;
+    }
+}
+
 // SS: storage of the block residual and the boundary terms; G: of links (two
 // rows) and clover.  The accumulator ([d][6][VD] 16-byte entries, FP32) and the
 // block residual are laid out for 16-byte accesses.
-template <class Sh, int NDW, typename SS, typename G, bool SCALED>
+// HALVES: every sum in the order of split_block_solve, with the bits that it gives,
+// for launches of many systems of small lattices (dd_form.h).  4^4 domains on 16^3x32,
+// 3072 workgroups: 358 us a launch in FP32 and 330 in FP16, 9 to 14 % above the
+// kernel's own order, for the first pair's hops going through LDS and twice the
+// wave sums; with the pair in registers FP32 spilled 172 bytes and took 466 us.
+template <class Sh, int NDW, typename SS, typename G, bool SCALED, bool HALVES>
 __device__ __forceinline__ void lds_block_solve(const SapArgs &a, const int d, const Visit f)
 {
     using T = float;
@@ -656,12 +699,17 @@ __device__ __forceinline__ void lds_block_solve(const SapArgs &a, const int d, c
     __shared__ c2_t she_all[NDW][6 * VH];     // even sites: r
     __shared__ c2_t sho_all[NDW][6 * VH];     // odd sites: C_o^-1 D_oe r; x in the reconstruction
     __shared__ c2_t shx_all[NDW][4 * 3 * VH]; // half-spinors handed to x + mu
-    // FP32 clover blocks leave no registers for A through the MR steps: it waits in LDS
-    constexpr bool A_LDS = sizeof(v2<G>) == 8;
-    __shared__ c2_t sa_all[A_LDS ? NDW * 6 * VD : 1];
+    // FP32 clover blocks leave no registers for A through the MR steps, nor do sums by
+    // halves: it waits in LDS (with them, where two workgroups are to share a CU, only
+    // the even sites' A; the odd ones' in memory)
+    constexpr bool A_LDS = sizeof(v2<G>) == 8 || HALVES;
+    constexpr int NA = HALVES ? VH : VD;
+    __shared__ c2_t sa_all[A_LDS ? NDW * 6 * NA : 1];
+    __shared__ c2_t park_all[HALVES ? 6 * VH : 1];
     constexpr int NW = NT / 64;
     static_assert(NT % 64 == 0, "whole waves");
-    __shared__ T red[2][3 * NW * NDW];
+    static_assert(!HALVES || (NDW == 1 && VH % 64 == 0), "halves: one domain a workgroup, whole waves of each parity");
+    __shared__ T red[2][(HALVES ? 6 : 3) * NW * NDW];
 
     const int par = (int)threadIdx.x / (NDW * VH);
     const int idx = (int)threadIdx.x - par * (NDW * VH);
@@ -670,6 +718,7 @@ __device__ __forceinline__ void lds_block_solve(const SapArgs &a, const int d, c
     const int loc = par * VH + hi;
     // this half index
     c2_t *const ve = she_all[sub] + hi, *const vo = sho_all[sub] + hi, *const vx = shx_all[sub] + hi;
+    c2_t *const vp = park_all + (HALVES ? hi : 0);
     int l[4];
     Sh::coords(loc, l);
     int D[4];
@@ -728,10 +777,22 @@ __device__ __forceinline__ void lds_block_solve(const SapArgs &a, const int d, c
         else clover_wide([&](int q) { return cx<T>{(T)cl[q].x, (T)cl[q].y}; }, in, out);
     };
     if (f.faces_in) {
-        face_apply<Sh, 0, T>(U[0], hf[0], wf[0], sf[0], A);
-        face_apply<Sh, 1, T>(U[1], hf[1], wf[1], sf[1], A);
-        face_apply<Sh, 2, T>(U[2], hf[2], wf[2], sf[2], A);
-        face_apply<Sh, 3, T>(U[3], hf[3], wf[3], sf[3], A);
+        if constexpr (HALVES) {
+            cx<T> early[12], late[12];
+#pragma unroll
+            for (int k = 0; k < 12; k++) early[k] = late[k] = czero<T>();
+            face_apply<Sh, 0, T>(U[0], hf[0], wf[0], sf[0], early);
+            face_apply<Sh, 1, T>(U[1], hf[1], wf[1], sf[1], early);
+            face_apply<Sh, 2, T>(U[2], hf[2], wf[2], sf[2], late);
+            face_apply<Sh, 3, T>(U[3], hf[3], wf[3], sf[3], late);
+#pragma unroll
+            for (int k = 0; k < 12; k++) A[k] = A[k] + (early[k] + late[k]);
+        } else {
+            face_apply<Sh, 0, T>(U[0], hf[0], wf[0], sf[0], A);
+            face_apply<Sh, 1, T>(U[1], hf[1], wf[1], sf[1], A);
+            face_apply<Sh, 2, T>(U[2], hf[2], wf[2], sf[2], A);
+            face_apply<Sh, 3, T>(U[3], hf[3], wf[3], sf[3], A);
+        }
     }
 
     // ---- even-odd preparation: r = rho_e - D_eo C_o^-1 rho_o, x = 0
@@ -743,7 +804,7 @@ __device__ __forceinline__ void lds_block_solve(const SapArgs &a, const int d, c
     // the even-site MR residual r lives in its own slot of she for the whole
     // solve (fewer live registers); x stays in the registers of A
     cx<T> t[12];
-    lane_hops<Sh>(vo, P, vx, 0, par, l, U, t);
+    lane_hops<Sh, HALVES>(vo, P, vx, vp, 0, par, l, U, t);
     if (par == 0) {
 #pragma unroll
         for (int k = 0; k < 12; k++) {
@@ -752,8 +813,14 @@ __device__ __forceinline__ void lds_block_solve(const SapArgs &a, const int d, c
         }
         st_c2<VH>(ve, P);
     }
-    c2_t *const va = sa_all + (A_LDS ? sub * 6 * VD + loc : 0);
-    if (A_LDS) st_c2<VD>(va, A);
+    c2_t *const va = sa_all + (A_LDS ? sub * 6 * NA + (HALVES ? hi : loc) : 0);
+    v2<T> *const rho_g = global_ptr((v2<T> *)a.rho_tmp) + (long)d * 12 * VH + hi;
+    if (HALVES && par == 1) {
+#pragma unroll
+        for (int k = 0; k < 12; k++) st<T, T>(rho_g, (long)k * VH, A[k]);
+    } else if (A_LDS) {
+        st_c2<NA>(va, A);
+    }
     // C has arrived: without this, a path around the MR loop on which it has
     // not makes the later waits for its registers wait for younger loads
 #pragma unroll
@@ -774,7 +841,7 @@ __device__ __forceinline__ void lds_block_solve(const SapArgs &a, const int d, c
         }
         __syncthreads();
         if (par == 0) ld_c2<VH>(ve, P);
-        lane_hops<Sh>(ve, P, vx, 1, par, l, U, t);       // -2 D_oe r
+        lane_hops<Sh, HALVES>(ve, P, vx, vp, 1, par, l, U, t);       // -2 D_oe r
         if (par == 1) {
             clover(t, P);                                // -2 C_o^-1 D_oe r
             st_c2<VH>(vo, P);
@@ -784,29 +851,31 @@ __device__ __forceinline__ void lds_block_solve(const SapArgs &a, const int d, c
             clover(t, P);
         }
         __syncthreads();
-        T dots[3] = {0, 0, 0};
-        lane_hops<Sh>(vo, P, vx, 0, par, l, U, t);
+        T dots[3] = {0, 0, 0}, half[6] = {0, 0, 0, 0, 0, 0};
+        lane_hops<Sh, HALVES>(vo, P, vx, vp, 0, par, l, U, t);
         cx<T> rr[12];
         if (par == 0) {
             ld_c2<VH>(ve, rr);
 #pragma unroll
             for (int k = 0; k < 12; k++) {
                 P[k] = P[k] + scal(T(-0.25), t[k]);      // p = C_e r - D_eo C_o^-1 D_oe r
-                dots[0] = fmad(P[k].i, rr[k].i, fmad(P[k].r, rr[k].r, dots[0]));
-                dots[1] = fmad(-P[k].i, rr[k].r, fmad(P[k].r, rr[k].i, dots[1]));
-                dots[2] = fmad(P[k].i, P[k].i, fmad(P[k].r, P[k].r, dots[2]));
+                T *const s = HALVES ? half + k / 6 * 3 : dots;
+                s[0] = fmad(P[k].i, rr[k].i, fmad(P[k].r, rr[k].r, s[0]));
+                s[1] = fmad(-P[k].i, rr[k].r, fmad(P[k].r, rr[k].i, s[1]));
+                s[2] = fmad(P[k].i, P[k].i, fmad(P[k].r, P[k].r, s[2]));
             }
         }
-        domain_reduce<VH, NDW, NW, false>(dots, red[0], sub);
+        if constexpr (HALVES) halves_sum<NW>(half, dots, red[0]);
+        else domain_reduce<VH, NDW, NW, false>(dots, red[0], sub);
         if (par == 0) {
             cx<T> alpha = dots[2] > T(0) ? cx<T>{dots[0] / dots[2], dots[1] / dots[2]} : czero<T>();
-            if (A_LDS) ld_c2<VD>(va, A);
+            if (A_LDS) ld_c2<NA>(va, A);
 #pragma unroll
             for (int k = 0; k < 12; k++) {
                 A[k] = cmac(A[k], alpha, rr[k]);
                 P[k] = cmac(rr[k], neg(alpha), P[k]);
             }
-            if (A_LDS) st_c2<VD>(va, A);
+            if (A_LDS) st_c2<NA>(va, A);
             st_c2<VH>(ve, P);
         }
     }
@@ -817,13 +886,18 @@ __device__ __forceinline__ void lds_block_solve(const SapArgs &a, const int d, c
     c2_t ps[6];
 #pragma unroll
     for (int j = 0; j < 6; j++) ps[j] = c2_t{0.f, 0.f, 0.f, 0.f};
-    if (A_LDS) ld_c2<VD>(va, A);
+    if (HALVES && par == 1) {
+#pragma unroll
+        for (int k = 0; k < 12; k++) A[k] = ld<T, T>(rho_g, (long)k * VH);
+    } else if (A_LDS) {
+        ld_c2<NA>(va, A);
+    }
     if (par == 0) st_c2<VH>(vo, A);
     if (!f.first)
 #pragma unroll
         for (int j = 0; j < 6; j++) ps[j] = psi[j * VD];
     __syncthreads();
-    lane_hops<Sh>(vo, A, vx, 1, par, l, U, t);
+    lane_hops<Sh, HALVES>(vo, A, vx, vp, 1, par, l, U, t);
     if (par == 1) {
 #pragma unroll
         for (int k = 0; k < 12; k++) t[k] = A[k] + scal(T(0.5), t[k]);
@@ -1497,7 +1571,7 @@ __device__ __forceinline__ void bind_faces(SapArgs &a, const Visit &v)
 
 // With NDW > 1, items come in runs of NDW domains of one system (the plan
 // never splits or pads a run), and workgroup i takes run i.
-template <class Sh, int NDW, typename SS, typename G, bool SCALED>
+template <class Sh, int NDW, typename SS, typename G, bool SCALED, bool HALVES>
 __global__ __launch_bounds__(Sh::VD * NDW, 2) void k_sap_lds(const SapArgs *args, const int2 *items,
                                                                              Visit v)
 {
@@ -1508,7 +1582,7 @@ __global__ __launch_bounds__(Sh::VD * NDW, 2) void k_sap_lds(const SapArgs *args
     bind_faces(a, v);
     int d = it.y;
     if constexpr (NDW > 1) d = items[(long)blockIdx.x * NDW + ((int)threadIdx.x & 63) / Sh::VH].y;
-    lds_block_solve<Sh, NDW, SS, G, SCALED>(a, d, v);
+    lds_block_solve<Sh, NDW, SS, G, SCALED, HALVES>(a, d, v);
 }
 
 template <class Sh>
@@ -2241,11 +2315,24 @@ static hipError_t launch_bounded(void (*kernel)(P...), unsigned grid, unsigned b
     return hipGetLastError();
 }
 
+// one thread per site, FP32 arithmetic
+template <class Sh, int NDW, bool HALVES>
+static hipError_t launch_lds(const SapArgs *args, const int2 *items, int nitems, int prec, Visit v, hipStream_t s)
+{
+    constexpr int NT = Sh::VD * NDW;
+    if (prec == P32)
+        return launch_bounded(k_sap_lds<Sh, NDW, float, float, false, HALVES>, nitems / NDW, NT, s, args, items, v);
+    else if (prec == P16)
+        return launch_bounded(k_sap_lds<Sh, NDW, half_t, half_t, true, HALVES>, nitems / NDW, NT, s, args, items, v);
+    else
+        return launch_bounded(k_sap_lds<Sh, NDW, bf16_t, bf16_t, false, HALVES>, nitems / NDW, NT, s, args, items, v);
+}
+
 template <class Sh>
 static hipError_t launch_batch(const SapArgs *args, const int2 *items, int nitems, int prec, int product, Visit v,
                                hipStream_t s)
 {
-    if (product != PRODUCT_LANE && product != PRODUCT_LANE_SPLIT) {
+    if (product >= PRODUCT_TILE_VALU && product <= PRODUCT_TILE_MFMA_BF16) {
         // a tile of right-hand sides per workgroup: 4^4 domains, FP16 storage
         if constexpr (std::is_same<Sh, Shape<4, 4, 4, 4>>::value) {
             constexpr int NT = Sh::VH * RT_MFMA, NTV = Sh::VH * RT_VALU;
@@ -2280,6 +2367,11 @@ static hipError_t launch_batch(const SapArgs *args, const int2 *items, int nitem
     }
     constexpr int NDW = Sh::VD < 64 ? 128 / Sh::VD : 1;
     if (nitems % NDW) return hipErrorInvalidValue;
+    if (product == PRODUCT_LANE_HALVES) {
+        if constexpr (Sh::VD == 256)
+            if (prec != P64) return launch_lds<Sh, NDW, true>(args, items, nitems, prec, v, s);
+        return hipErrorInvalidValue;
+    }
     if (product == PRODUCT_LANE_SPLIT) {
         if constexpr (Sh::VD < 512) {
             constexpr int NT = SplitShape<Sh, NDW>::NT;
@@ -2302,13 +2394,7 @@ static hipError_t launch_batch(const SapArgs *args, const int2 *items, int nitem
         else
             return hipErrorInvalidValue;
     } else if constexpr (Sh::VD * NDW % 64 == 0) {
-        constexpr int NT = Sh::VD * NDW;
-        if (prec == P32)
-            return launch_bounded(k_sap_lds<Sh, NDW, float, float, false>, nitems / NDW, NT, s, args, items, v);
-        else if (prec == P16)
-            return launch_bounded(k_sap_lds<Sh, NDW, half_t, half_t, true>, nitems / NDW, NT, s, args, items, v);
-        else
-            return launch_bounded(k_sap_lds<Sh, NDW, bf16_t, bf16_t, false>, nitems / NDW, NT, s, args, items, v);
+        return launch_lds<Sh, NDW, false>(args, items, nitems, prec, v, s);
     } else {
         return hipErrorInvalidValue;   // two threads per site (dd_form.h)
     }
@@ -2321,7 +2407,12 @@ int sap_domains_per_workgroup(int shape, int prec, int product)
 
 int sap_rhs_per_workgroup(int product)
 {
-    return product == PRODUCT_LANE || product == PRODUCT_LANE_SPLIT ? 1 : product == PRODUCT_TILE_VALU ? RT_VALU : RT_MFMA;
+    switch (product) {
+        case PRODUCT_TILE_VALU: return RT_VALU;
+        case PRODUCT_TILE_MFMA_F32:
+        case PRODUCT_TILE_MFMA_BF16: return RT_MFMA;
+        default: return 1;
+    }
 }
 
 bool sap_product_supported(const int b[4], int prec, int product)

@@ -6,13 +6,17 @@ import pytest
 
 CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_1412_2629_amd", "csrc")
 P64, P32, P16, PB16 = range(4)
-LANE, TILE_VALU, MFMA_F32, MFMA_BF16, SPLIT = range(5)
+LANE, TILE_VALU, MFMA_F32, MFMA_BF16, SPLIT, HALVES = range(6)
 
 MAIN = r"""
 #include <cstdio>
 #include <cstdlib>
 #include "dd_form.h"
-int main(int, char **v) { printf("%d\n", dd::sap_kernel_form(atoi(v[1]), atoi(v[2]), atoi(v[3]), atol(v[4]))); }
+int main(int, char **v)
+{
+    const int form = dd::sap_kernel_form(atoi(v[1]), atoi(v[2]), atoi(v[3]), atol(v[4]));
+    printf("%d\n", v[5] ? dd::sap_launch_form(atoi(v[1]), form, atol(v[5])) : form);
+}
 """
 
 
@@ -38,3 +42,20 @@ def test_forms_that_hold_at_every_size(form, workgroups):
         assert form(sites, P64, LANE, workgroups) == LANE     # the only one of larger domains
     for product in (TILE_VALU, MFMA_F32, MFMA_BF16):
         assert form(256, P16, product, workgroups) == product
+
+
+@pytest.mark.parametrize("prec", [P32, P16, PB16])
+def test_a_full_launch_of_small_lattices_has_one_thread_per_site(form, prec):
+    # lattices of 8, 128 and 256 workgroups a colour: two threads per site until the launch holds more than 256
+    for lattice in (8, 128, 256):
+        assert form(256, prec, LANE, lattice, lattice) == SPLIT
+        assert form(256, prec, LANE, lattice, 256) == SPLIT
+        for launch in (257, 264, 3072):
+            assert form(256, prec, LANE, lattice, launch) == HALVES
+    # a larger lattice keeps its own order of sums, other domains their kernel
+    assert form(256, prec, LANE, 257, 257) == LANE
+    assert form(512, prec, LANE, 8, 3072) == LANE
+    assert form(288, prec, LANE, 8, 3072) == SPLIT
+    assert form(16, prec, LANE, 8, 3072) == SPLIT
+    assert form(256, P64, LANE, 8, 3072) == LANE
+    assert form(256, P16, TILE_VALU, 8, 3072) == TILE_VALU
