@@ -507,10 +507,13 @@ __device__ __forceinline__ void a_load(const Geo &g, const v2<std::conditional_t
     }
 }
 
-// The right-hand sides of a launch.
-struct RhsFields {
-    const void *in[A_MAX_RHS];
-    void *out[A_MAX_RHS];
+// The right-hand sides of a launch in storage S.  16-bit operands come one at a time,
+// and their list is known to hold one when the kernel is compiled (with a list of 16
+// a call took half a microsecond longer: FP16 on 8^4 29.7 us, now 29.1).
+template <typename S> struct RhsFields {
+    enum { MAX = sizeof(S) == 2 ? 1 : A_MAX_RHS };
+    const void *in[MAX];
+    void *out[MAX];
     int n;
 };
 // Block and right-hand side of this workgroup.  Workgroup w runs on XCD w mod 8.
@@ -519,9 +522,9 @@ struct RhsFields {
 // XCD's L2 by its neighbours (a plain order spreads neighbouring blocks over
 // all eight L2s).  The right-hand sides of a block follow one another there, so
 // its links and clover blocks come from memory once for all of them.
-__device__ __forceinline__ void rhs_block(int n, unsigned &blk, unsigned &rhs)
+template <typename S> __device__ __forceinline__ void rhs_block(const RhsFields<S> &io, unsigned &blk, unsigned &rhs)
 {
-    const unsigned nr = (unsigned)n, nbk = gridDim.x / nr, w = blockIdx.x;
+    const unsigned nr = RhsFields<S>::MAX == 1 ? 1 : (unsigned)io.n, nbk = gridDim.x / nr, w = blockIdx.x;
     if (nbk % 8 == 0) {
         const unsigned q = w / 8;
         rhs = q % nr;
@@ -571,12 +574,12 @@ __device__ __forceinline__ void a_hop(const Geo &g, const int x[4], int d, int l
 
 // One thread per site; CANON: in the canonical FP64 fields of the interface.
 template <typename T, typename SI, typename SO, typename G, int NLC, bool CANON>
-__global__ __launch_bounds__(256) void k_apply_A(Geo g, RhsFields io, const v2<G> *links, const v2<G> *clov)
+__global__ __launch_bounds__(256) void k_apply_A(Geo g, RhsFields<SI> io, const v2<G> *links, const v2<G> *clov)
 {
     typedef std::conditional_t<CANON, double, SI> FI;
     typedef std::conditional_t<CANON, double, SO> FO;
     unsigned blk, rhs;
-    rhs_block(io.n, blk, rhs);
+    rhs_block(io, blk, rhs);
     long I = (long)blk * blockDim.x + threadIdx.x;
     if (I >= g.V) return;
     const v2<FI> *in = global_ptr((const v2<FI> *)io.in[rhs]);
@@ -720,7 +723,7 @@ __device__ __forceinline__ void a_dom_dir(const Geo &g, const int x[4], int d, i
 }
 
 template <int NT, typename T, typename SI, typename SO, typename G, int NLC, bool CANON>
-__global__ __launch_bounds__(NT, 2) void k_apply_A_dom(Geo g, RhsFields io, const v2<G> *links, const v2<G> *clov)
+__global__ __launch_bounds__(NT, 2) void k_apply_A_dom(Geo g, RhsFields<SI> io, const v2<G> *links, const v2<G> *clov)
 {
     typedef std::conditional_t<CANON, double, SI> FI;
     typedef std::conditional_t<CANON, double, SO> FO;
@@ -728,7 +731,7 @@ __global__ __launch_bounds__(NT, 2) void k_apply_A_dom(Geo g, RhsFields io, cons
     __shared__ cx<T> ex[6][NT];                // backward terms pushed to x + mu
     __shared__ int2 site_of[CANON ? NT : 1];   // lexicographic sites: (canonical index, place in the workgroup)
     unsigned blk, rhs;
-    rhs_block(io.n, blk, rhs);
+    rhs_block(io, blk, rhs);
     const int t = threadIdx.x;
     const long I = (long)blk * NT + t;         // V is a multiple of NT: every thread has a site
     const v2<FI> *in = global_ptr((const v2<FI> *)io.in[rhs]);
@@ -801,26 +804,34 @@ __global__ __launch_bounds__(NT, 2) void k_apply_A_dom(Geo g, RhsFields io, cons
 }
 
 template <bool DOM, int NT, typename T, typename S, int NLC, bool CANON>
-static void launch_A(const Geo &g, const RhsFields &io, const void *links, const void *clov, hipStream_t s)
+static void launch_A(const Geo &g, const void *const *in, void *const *out, int n, const void *links, const void *clov,
+                     hipStream_t s)
 {
+    RhsFields<S> io{};
+    io.n = n;
+    for (int q = 0; q < n; q++) {
+        io.in[q] = in[q];
+        io.out[q] = out[q];
+    }
     if constexpr (DOM)
-        hipLaunchKernelGGL((k_apply_A_dom<NT, T, S, S, S, NLC, CANON>), (unsigned)(g.V / NT) * io.n, NT, 0, s, g, io,
+        hipLaunchKernelGGL((k_apply_A_dom<NT, T, S, S, S, NLC, CANON>), (unsigned)(g.V / NT) * n, NT, 0, s, g, io,
                            (const v2<S> *)links, (const v2<S> *)clov);
     else
-        hipLaunchKernelGGL((k_apply_A<T, S, S, S, NLC, CANON>), nblocks(g.V, NT) * io.n, NT, 0, s, g, io,
+        hipLaunchKernelGGL((k_apply_A<T, S, S, S, NLC, CANON>), nblocks(g.V, NT) * n, NT, 0, s, g, io,
                            (const v2<S> *)links, (const v2<S> *)clov);
 }
 
+// at most 16 right-hand sides (16-bit storage: one)
 template <bool DOM, int NT>
-static void launch_apply_A(const Geo &g, const RhsFields &io, const void *links, const void *clov, int prec, bool canon,
-                           hipStream_t s)
+static void launch_apply_A(const Geo &g, const void *const *in, void *const *out, int n, const void *links,
+                           const void *clov, int prec, bool canon, hipStream_t s)
 {
-    if (canon && prec == P64) launch_A<DOM, NT, double, double, 9, true>(g, io, links, clov, s);
-    else if (canon) launch_A<DOM, NT, float, float, 6, true>(g, io, links, clov, s);
-    else if (prec == P64) launch_A<DOM, NT, double, double, 9, false>(g, io, links, clov, s);
-    else if (prec == P32) launch_A<DOM, NT, float, float, 6, false>(g, io, links, clov, s);
-    else if (prec == P16) launch_A<DOM, NT, float, half_t, 6, false>(g, io, links, clov, s);
-    else launch_A<DOM, NT, float, bf16_t, 6, false>(g, io, links, clov, s);
+    if (canon && prec == P64) launch_A<DOM, NT, double, double, 9, true>(g, in, out, n, links, clov, s);
+    else if (canon) launch_A<DOM, NT, float, float, 6, true>(g, in, out, n, links, clov, s);
+    else if (prec == P64) launch_A<DOM, NT, double, double, 9, false>(g, in, out, n, links, clov, s);
+    else if (prec == P32) launch_A<DOM, NT, float, float, 6, false>(g, in, out, n, links, clov, s);
+    else if (prec == P16) launch_A<DOM, NT, float, half_t, 6, false>(g, in, out, n, links, clov, s);
+    else launch_A<DOM, NT, float, bf16_t, 6, false>(g, in, out, n, links, clov, s);
 }
 
 // whole domains per workgroup where the domain size divides the workgroup's
@@ -847,17 +858,13 @@ static hipError_t apply_A_rhs(const Geo &g, const void *const *in, void *const *
                               const void *clov, int prec, bool canon, hipStream_t s)
 {
     const int nt = dom_sites(g, prec);
-    for (int k = 0; k < n; k += A_MAX_RHS) {
-        RhsFields io{};
-        io.n = n - k < A_MAX_RHS ? n - k : A_MAX_RHS;
-        for (int q = 0; q < io.n; q++) {
-            io.in[q] = in[k + q];
-            io.out[q] = out[k + q];
-        }
-        const bool few = g.V / 256 * io.n <= 256 && prec != P16;
-        if (!nt || few) launch_apply_A<false, 256>(g, io, links, clov, prec, canon, s);
-        else if (nt == 256) launch_apply_A<true, 256>(g, io, links, clov, prec, canon, s);
-        else launch_apply_A<true, 512>(g, io, links, clov, prec, canon, s);
+    const int most = prec == P64 || prec == P32 ? (int)A_MAX_RHS : 1;
+    for (int k = 0; k < n; k += most) {
+        const int take = n - k < most ? n - k : most;
+        const bool few = g.V / 256 * take <= 256 && prec != P16;
+        if (!nt || few) launch_apply_A<false, 256>(g, in + k, out + k, take, links, clov, prec, canon, s);
+        else if (nt == 256) launch_apply_A<true, 256>(g, in + k, out + k, take, links, clov, prec, canon, s);
+        else launch_apply_A<true, 512>(g, in + k, out + k, take, links, clov, prec, canon, s);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
