@@ -57,11 +57,6 @@ struct Visit {
 // Arguments of the block solves of one system (one lattice, one right-hand side).
 struct SapArgs {
     Geo g;
-    int first;          // first visit of these domains: residual is eta
-    int faces_in;       // add the boundary terms of the previous half-sweep
-    int last;           // last visit: write psi (+ delta) to out
-    int faces_out;      // write this sweep's boundary terms
-    int res_out;        // store the block residual
     int n_mr;
     const double2 *eta; // FP64 input of the preconditioner
     double2 *out;       // FP64 output
