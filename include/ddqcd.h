@@ -80,7 +80,7 @@ typedef struct {
     int restarts;         /* FGCR cycles */
     double rel_residual;  /* true residual |b - A x| / |b|, recomputed in FP64 at exit */
     double t_total_ms;    /* wall time of the call */
-    double t_sap_ms;      /* preconditioner M (stream time, events) */
+    double t_sap_ms;      /* preconditioner M (stream time, by the device's clock) */
     double t_A_ms;        /* operator A */
     double t_gs_ms;       /* Gram-Schmidt */
     double t_other_ms;    /* remaining linear algebra */
@@ -104,7 +104,8 @@ int ddqcd_destroy(ddqcd_t ctx);
 /* How the block solves form the SU(3) link x half-spinor products of their
  * hops (the hop structure of Sec. II-B: project, multiply by the link,
  * reconstruct).  DDQCD_PRODUCT_LANE: one right-hand side per workgroup, one
- * site per thread, products on the vector ALUs.  The tile forms solve one
+ * site per thread (two threads per site on small lattices and 6x6x2x4 domains),
+ * products on the vector ALUs.  The tile forms solve one
  * domain for a tile of right-hand sides of a lattice per workgroup (two for
  * DDQCD_PRODUCT_TILE_VALU, four for the others; the link is staged once for
  * the tile): DDQCD_PRODUCT_TILE_VALU with the products on the vector ALUs, DDQCD_PRODUCT_MFMA_F32 on FP32 matrix instructions

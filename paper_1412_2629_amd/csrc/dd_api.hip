@@ -664,7 +664,7 @@ struct ResultArea {
     {
         const int ns = (int)sys.size();
         if (lead->res_cap < ns && lead->ws)
-            return fail(lead, DDQCD_ERR_NOMEM, "more systems than the workspace's reduction area holds (" +
+            return fail(lead, DDQCD_ERR_NOMEM, "more systems than a context with this workspace leads (" +
                                                    std::to_string(lead->res_cap) + ")");
         if (!lead->res_host || lead->res_cap < ns) {
             const int cap = std::max(lead->res_cap, ns);
@@ -1824,7 +1824,7 @@ int ddqcd_set_workspace(ddqcd_t c, void *dev_ptr, size_t bytes)
     c->ws_plan = c->ws + (bytes - c->ws_plan_bytes) / 256 * 256;
     c->ws_plan_bytes = bytes - (size_t)(c->ws_plan - c->ws);
     c->ws_nrhs = nrhs;
-    // systems of the solves this context leads
+    // the most systems of a solve that this context leads (include/ddqcd.h)
     c->res_cap = std::max(nrhs, 64);
     return DDQCD_OK;
 }

@@ -643,11 +643,10 @@ __global__ __launch_bounds__(256) void k_apply_A(Geo g, RhsFields<SI> io, const 
 // conversions are needed.
 //
 // Bound by memory.  FP64 on 32^3x64 with 4^4 domains, per right-hand side: in
-// canonical fields 802 us alone, 616 us when three share a launch (their
+// canonical fields 786 us alone, 552 us when three share a launch (their
 // workgroups follow one another on one XCD, and the links and clover blocks
 // come from its L2: 960 + 192 bytes a site instead of 1536); a layout conversion
-// each way and one launch per right-hand side took 1065 us, two right-hand
-// sides in the lanes of one workgroup 728 us in canonical fields.
+// each way and one launch per right-hand side take 1059 us.
 
 // Spinors in LDS: [12][NT + 1]; the odd stride keeps the twelve components of
 // one site, which consecutive lanes move to and from canonical memory, in
@@ -849,9 +848,9 @@ static int dom_sites(const Geo &g, int prec)
 // Whole domains per workgroup, or one thread per site: the latter for domains
 // without such a kernel (288 sites), and where the launch has at most one
 // workgroup per CU, which then lasts as long as one workgroup: without LDS and
-// barriers it waits for memory less often (8^4 in canonical fields: FP64 18.7
-// against 21.3 us, FP32 15.9 against 20.9; 16^3x32 with three right-hand sides,
-// 1536 workgroups: FP64 162 against 116 us for all).  Not in FP16, where the two
+// barriers it waits for memory less often (8^4 in canonical fields: FP64 16.9
+// against 18.2 us, FP32 14.4 against 17.8; 16^3x32 with three right-hand sides,
+// 1536 workgroups: FP64 155 against 102 us for all).  Not in FP16, where the two
 // kernels' third link rows are not contracted alike and the bits would depend
 // on the number of right-hand sides.
 static hipError_t apply_A_rhs(const Geo &g, const void *const *in, void *const *out, int n, const void *links,
@@ -871,9 +870,11 @@ static hipError_t apply_A_rhs(const Geo &g, const void *const *in, void *const *
     return hipSuccess;
 }
 
-// FP64 and FP32 only: with 16-bit storage the neighbours' FP64 spinors cost more
-// than the conversions save (BF16 on 32^3x64: 551 against 521 us); the field
-// under 4 GiB (32-bit byte offsets)
+// FP64 and FP32 only: with 16-bit storage the neighbours' FP64 spinors cost as much
+// as the conversions or more (one right-hand side on 32^3x64 with 4^4 domains: FP16
+// 666 us against 478 with the conversions, BF16 459 against 471; on 24x12x12x24 with
+// 6x6x2x4: 54 against 37 and 41 against 35); the field under 4 GiB (32-bit byte
+// offsets)
 bool apply_A_canonical_fits(const Geo &g, int prec)
 {
     return (prec == P64 || prec == P32) && (size_t)g.V * 12 * 16 < ((size_t)1 << 32);

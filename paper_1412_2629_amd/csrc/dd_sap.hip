@@ -502,8 +502,8 @@ template <class Sh, int MU, int SIGN> __device__ __forceinline__ int hop_step(in
 // spinor in LDS for the site x + mu.  So both parities' threads work in every
 // phase, links need neither LDS nor a conversion at each use, and the LDS
 // traffic is that of reading eight neighbour spinors.
-// One launch (a colour) with 8x4^3 domains: 45.7 us in FP32 on 16^3x32 (half the
-// CUs have one), 385 us with FP16 storage on 32^3x64.  With a pair of threads
+// One launch (a colour) with 8x4^3 domains: 45.3 us in FP32 on 16^3x32 (half the
+// CUs have one), 377 us with FP16 storage on 32^3x64.  With a pair of threads
 // reading all eight neighbours and the links from LDS it took 47.8 and 422 us,
 // and 56.4 and 520 us with 8-byte LDS reads, mixed-precision multiply-adds and
 // generic loads.  What is left is mostly the issue of FP32 instructions: 8 of 10
@@ -685,10 +685,11 @@ template <int NW, typename T> __device__ __forceinline__ void halves_sum(T (&v)[
 // rows) and clover.  The accumulator ([d][6][VD] 16-byte entries, FP32) and the
 // block residual are laid out for 16-byte accesses.
 // HALVES: every sum in the order of split_block_solve, with the bits that it gives,
-// for launches of many systems of small lattices (dd_form.h).  4^4 domains on 16^3x32,
-// 3072 workgroups: 358 us a launch in FP32 and 330 in FP16, 9 to 14 % above the
-// kernel's own order, for the first pair's hops going through LDS and twice the
-// wave sums; with the pair in registers FP32 spilled 172 bytes and took 466 us.
+// for launches of many systems of small lattices (dd_form.h).  4^4 domains on 16^3x32
+// with 12 right-hand sides, 3072 workgroups: 324 us a launch in FP32 and 282 in FP16,
+// 14 and 8 % above the kernel's own order, for the first pair's hops going through
+// LDS and twice the wave sums; with the pair in registers FP32 spilled 172 bytes and
+// took 1.3 times as long.
 template <class Sh, int NDW, typename SS, typename G, bool SCALED, bool HALVES>
 __device__ __forceinline__ void lds_block_solve(const SapArgs &a, const int d, const Visit f)
 {
@@ -954,7 +955,7 @@ __device__ __forceinline__ void lds_block_solve(const SapArgs &a, const int d, c
 //
 // The schedule of lds_block_solve for lattices whose colour does not fill the
 // device with one thread per site (a launch then lasts as long as one block
-// solve), and for FP64 on 2^4 domains.  Thread (parity, q, half index) holds the
+// solve), for 6x6x2x4 domains and for FP64 on 2^4 domains (dd_form.h).  Thread (parity, q, half index) holds the
 // site's links of directions 2q and 2q + 1 and its clover block q (the spinor's
 // components 6q .. 6q + 5, on which C is block diagonal), and owns that half of
 // x, r, rho and delta: it takes the forward or backward hops of its directions,
@@ -1644,7 +1645,7 @@ __global__ __launch_bounds__((SplitShape<Sh, NDW>::NT), (SplitShape<Sh, NDW>::te
 // workgroups share a CU, and while one moves its domain's data (some 10 bytes a
 // cycle is what one CU gets from beyond its L1) the other one computes.  The
 // FP16 launch of one colour for 12 right-hand sides on 32^3x64 (4096 domains of
-// 4^4) takes 3.13 ms this way.  With tiles of four (157 KB, one workgroup a CU,
+// 4^4) takes 3.15 ms this way.  With tiles of four (157 KB, one workgroup a CU,
 // separate arrays for r and C_o^-1 D_oe r) it took 4.73 ms with 8-byte LDS reads,
 // mixed-precision multiply-adds and each site's lanes moving its boundary terms
 // and accumulator, and 3.89 ms with 16-byte reads, FP32 multiply-adds and whole
@@ -2447,7 +2448,7 @@ void sap_shape_extents(int shape, int b[4])
 
 bool sap_shape_supported(const int b[4]) { return sap_shape_id(b) >= 0; }
 
-// FP64 block solves need 16 sites or whole waves (no padded FP64 workgroups)
+// FP64 block solves need 16 sites or whole waves of one thread per site
 bool sap_prec_supported(const int b[4], int prec)
 {
     const int id = sap_shape_id(b);
